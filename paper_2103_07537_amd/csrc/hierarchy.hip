@@ -79,6 +79,9 @@ struct BlockLevel {
     // smoothed transfers: P rows of this level, P^T rows of the next level (sliced by the next level)
     SellPart pro, res;
     int pro_split = 1, res_split = 1;          // waves per slice in the transfer kernels
+    // P's slices: 64 consecutive rows in colour order (its rows are independent)
+    DevBuf<int32_t> pro_row0, pro_nrow;
+    int pro_slices = 0;
     // P^T's slices: the next level's rows in natural (aggregate) order, 64 per slice; the
     // restriction writes slice row r to the next level's colour-order row iperm[r]
     DevBuf<int32_t> res_row0, res_nrow;
@@ -87,14 +90,18 @@ struct BlockLevel {
     bool res_rows = false;
     RowPart rres;
     int res_group = 4;                         // lanes per coarse row in the tentative restriction
-    int row_split = 1;                         // row form smoother: wavefronts per row (1, or 4 with 4 x 4 blocks)
-    // coarse levels with long rows: the smoother and residual run on the row form
-    bool rows = false;
+    // lanes per row: 1, the sliced form (one lane per row, 64 rows per slice), or 4 .. 64, the
+    // grouped form (64 / group rows per slice), whose diagonal blocks and nodal inverses are
+    // plain d x d blocks in colour order and whose slices are listed in launch order
+    int group = 1;
+    DevBuf<int32_t> cstart;                    // grouped form: first row of each slice's colour
+    DevBuf<SweepRec> recs;
+    std::vector<int> colour_rec;               // per colour: first launch position (+ end)
+    std::vector<int32_t> h_order, h_cstart;    // slice of each launch position (-1: none); cstart on the host
+    DevBuf<double> gdiag64, gdinv64;
+    DevBuf<float> gdiag32, gdinv32;
     // within-colour row order sorted by length in windows (coarse levels with mixed row lengths)
     bool sell_sorted = false;
-    RowPart raff, rafg;
-    DevBuf<double> rdinv64;
-    DevBuf<float> rdinv32;
     // transfer to the next level (colour orders of both levels)
     DevBuf<int32_t> agg_p, mem_ptr, mem_idx;
     DevBuf<double> q64;
@@ -104,9 +111,17 @@ struct BlockLevel {
     SliceView slices() const { return {row0.p, nrow.p}; }
 };
 
+// t2, tickets: grouped levels only -- the two undamped buffers t and t2 take
+// turns (see k_sweep; both all "unwritten" between V-cycles), and so do the two
+// ticket counters (both zero between V-cycles).  busy: a V-cycle is being
+// enqueued on the level; still set when the next one begins only if an error cut
+// the enqueueing short, and then the buffers and counters are set up anew.
 template <class T>
 struct Vecs {
-    DevBuf<T> b, x, xs, t, r;
+    DevBuf<T> b, x, xs, t, t2, r;
+    DevBuf<uint32_t> tickets;
+    bool busy = false;
+    int turn_t = 0, turn_ticket = 0;
 };
 
 struct Level {
@@ -452,26 +467,53 @@ constexpr int SELL_SIGMA = 1024;
 
 // Fraction of a sliced layout's slots that hold a stored block, for rows in
 // the given order cut into slices of 64 (per colour).
-static double slice_fill(const std::vector<int32_t>& order, const std::vector<int>& colour_row, const int32_t* rp) {
+static double slice_fill(const std::vector<int32_t>& order, const std::vector<int>& colour_row, const int32_t* rp,
+                         int group) {
     int64_t blocks = 0, slots = 0;
     for (size_t c = 0; c + 1 < colour_row.size(); ++c)
-        for (int r = colour_row[c]; r < colour_row[c + 1]; r += WAVE) {
+        for (int r = colour_row[c]; r < colour_row[c + 1]; r += WAVE / group) {
             int w = 0;
-            for (int q = r; q < std::min(r + WAVE, colour_row[c + 1]); ++q) {
+            for (int q = r; q < std::min(r + WAVE / group, colour_row[c + 1]); ++q) {
                 const int len = rp[order[q] + 1] - rp[order[q]];
                 blocks += len;
-                w = std::max(w, len);
+                w = std::max(w, (len + group - 1) / group);
             }
             slots += (int64_t)w * WAVE;
         }
     return slots ? (double)blocks / (double)slots : 1.0;
 }
 
+// The launch order of a grouped block row: every colour's slices, padded to a
+// multiple of SWEEP_WAVES positions (-1: nothing to do).  Workgroups take their
+// tickets about in turn over the 8 XCDs, so every eighth ticket of a colour gets
+// neighbouring slices: an XCD's gathers then stay in one region of the colour.
+static void launch_order(BlockLevel& B) {
+    B.h_order.clear();
+    B.h_cstart.assign((size_t)std::max(B.n_slices, 1), 0);
+    B.colour_rec.assign(B.n_colours + 1, 0);
+    for (int c = 0; c < B.n_colours; ++c) {
+        const int first = (int)B.h_order.size();
+        B.colour_rec[c] = first;
+        const int b = B.colour_slice[c], e = B.colour_slice[c + 1];
+        std::fill(B.h_cstart.begin() + b, B.h_cstart.begin() + e, B.colour_row[c]);
+        const int wgs = (int)ceil_div(e - b, SWEEP_WAVES);
+        B.h_order.resize((size_t)first + (size_t)wgs * SWEEP_WAVES, -1);
+        int sl = b;
+        for (int x = 0; x < 8; ++x)
+            for (int k = x; k < wgs; k += 8)
+                for (int u = 0; u < SWEEP_WAVES && sl < e; ++u)
+                    B.h_order[(size_t)first + (size_t)k * SWEEP_WAVES + u] = sl++;
+    }
+    B.colour_rec[B.n_colours] = (int)B.h_order.size();
+}
+
 // rp: row pointers of the block row's diagonal block (row lengths), or NULL
-// for the natural order within each colour.
-static void order_and_slice(BlockLevel& B, int n, int ncol, const int32_t* rp = nullptr) {
+// for the natural order within each colour.  group: lanes per row.
+static void order_and_slice(BlockLevel& B, int n, int ncol, const int32_t* rp = nullptr, int group = 1) {
     B.n = n;
     B.n_colours = ncol;
+    B.group = group;
+    const int rows = WAVE / group;
     std::vector<int> cnt(ncol + 1, 0);
     for (int i = 0; i < n; ++i) cnt[B.colour[i] + 1]++;
     B.colour_row.assign(ncol + 1, 0);
@@ -481,7 +523,7 @@ static void order_and_slice(BlockLevel& B, int n, int ncol, const int32_t* rp = 
     std::vector<int> cur(B.colour_row.begin(), B.colour_row.end() - 1);
     for (int i = 0; i < n; ++i) B.perm[cur[B.colour[i]]++] = i;
     B.sell_sorted = false;
-    if (rp && slice_fill(B.perm, B.colour_row, rp) < 0.9) {
+    if (rp && slice_fill(B.perm, B.colour_row, rp, group) < 0.9) {
         B.sell_sorted = true;
         auto len = [rp](int32_t i) { return rp[i + 1] - rp[i]; };
         for (int c = 0; c < ncol; ++c)
@@ -497,21 +539,59 @@ static void order_and_slice(BlockLevel& B, int n, int ncol, const int32_t* rp = 
     B.colour_slice.assign(ncol + 1, 0);
     for (int c = 0; c < ncol; ++c) {
         B.colour_slice[c] = (int)B.h_row0.size();
-        for (int r = B.colour_row[c]; r < B.colour_row[c + 1]; r += WAVE) {
+        for (int r = B.colour_row[c]; r < B.colour_row[c + 1]; r += rows) {
             B.h_row0.push_back(r);
-            B.h_nrow.push_back(std::min(WAVE, B.colour_row[c + 1] - r));
+            B.h_nrow.push_back(std::min(rows, B.colour_row[c + 1] - r));
         }
     }
     B.colour_slice[ncol] = (int)B.h_row0.size();
     B.n_slices = (int)B.h_row0.size();
+    if (group > 1) launch_order(B);
 }
 
 enum class PartKind { Off = 0, Cpl = 1, Diag = 2, Dinv = 3 };
 
-// coarse levels with at most this many rows per colour (on average) take the row form
-// (measured crossover of the two layouts' colour passes on 4 x 4 FP64 blocks: 2.8K rows
-// 6.9 us in the row form against 12.5 us sliced, 11K rows 15.6 against 13.6 us)
-constexpr int ROWS_PER_COLOUR_MAX = 8192;
+// Lanes per row of a block row (see BlockLevel::group) of n rows and `blocks`
+// blocks in A_ff, on a level whose larger block row has n_level rows.
+//
+// Which levels: all coarse ones, and finest levels of up to GROUP_FINEST_MAX
+// nodes, whose colour passes are short launches.  Measured per FP64 V-cycle,
+// all sweeps of a level, one launch per colour (sliced, or one wavefront per
+// row) against this form: 583 nodes in 10 colours 210 -> 67 us, 13,945 in 9
+// colours 222 -> 85 us, 188,588 in 9 colours 602 -> 453 us, 976 in 5 colours
+// (3 x 3 blocks) 85 -> 33 us; a finest level of 65,536 nodes (two colours)
+// 61 -> 54 us, but one of 151,951 nodes 87 -> 150 us: there a colour pass
+// already runs at the bandwidth its loads get, and the sliced form moves fewer
+// lanes.
+//
+// How many lanes: the first power of two that covers an average row's
+// off-diagonal blocks, so that most rows are at most two slots, one round of
+// loads (10 colours of 583 rows, 13 off-diagonal blocks on average: 26 us a
+// sweep with 8 lanes, 17 us with 16 or 32); but no more than fill the chip a
+// few times over, as fewer lanes waste less on short rows (188,588 rows: 4 lanes
+// 453 us, 8 lanes 495 us, 16 lanes 597 us per cycle; 65,536 rows of 4 blocks: 4 lanes
+// 54 us, 8 lanes 76 us).
+constexpr int GROUP_FINEST_MAX = 65536;
+constexpr int64_t GROUP_WAVES_MAX = 16384;
+static int choose_group(const mbamg_params& p, int lvl, int n_level, int n, int64_t blocks) {
+    if (p.smoother == 1) return 1;   // the full-node kernel reads the sliced parts
+    bool grouped = lvl > 0 || n_level <= GROUP_FINEST_MAX;
+    // MBAMG_ROWS_FORM (tests): "rows" forces the grouped form on every coarse level, anything
+    // else the sliced one on every level; MBAMG_SLICE_SPLIT the sliced one on the finest level
+    if (const char* fo = form_override("MBAMG_ROWS_FORM")) grouped = lvl > 0 && std::strcmp(fo, "rows") == 0;
+    if (lvl == 0 && form_override("MBAMG_SLICE_SPLIT")) grouped = false;
+    if (!grouped) return 1;
+    const double len = n ? (double)blocks / n : 1.0;
+    int g = 4;
+    while (g < 64 && len - 1.0 > g) g *= 2;
+    while (g > 4 && (int64_t)n * g > GROUP_WAVES_MAX * WAVE) g /= 2;
+    if (const char* fo = form_override("MBAMG_SWEEP_GROUP")) {   // tests: 4, 8, 16, 32 or 64 lanes per row
+        g = std::atoi(fo);
+        MB_CHECK(g == 4 || g == 8 || g == 16 || g == 32 || g == 64, MBAMG_E_INVALID,
+                 "MBAMG_SWEEP_GROUP must be 4, 8, 16, 32 or 64");
+    }
+    return g;
+}
 
 // Waves per slice (1..16) for a launch over `slices` slices of `width` slots
 // on average: wide slices are shared by more waves until the launch has
@@ -560,9 +640,9 @@ static std::vector<int32_t> slab_order(const std::vector<int>& colour_slice) {
 // next levels of at most this many rows take the restriction in row form
 constexpr int RES_ROWS_MAX = 16384;
 
-// Slices of 64 consecutive rows of an n-row matrix in natural order (identity
-// row order), for parts whose rows need not follow a colour order.
-static void natural_slicing(BlockLevel& B, int n, hipStream_t s) {
+// Slices of 64 consecutive rows of an n-row matrix in the given row order
+// (NULL: the natural order), for parts whose rows need not be cut by colour.
+static void natural_slicing(BlockLevel& B, int n, hipStream_t s, const std::vector<int32_t>* perm = nullptr) {
     B.n = n;
     B.n_slices = (int)ceil_div(n, WAVE);
     B.h_row0.resize(B.n_slices);
@@ -571,8 +651,12 @@ static void natural_slicing(BlockLevel& B, int n, hipStream_t s) {
         B.h_row0[sl] = sl * WAVE;
         B.h_nrow[sl] = std::min(WAVE, n - sl * WAVE);
     }
-    B.perm.resize(n);
-    for (int i = 0; i < n; ++i) B.perm[i] = i;
+    if (perm) {
+        B.perm = *perm;
+    } else {
+        B.perm.resize(n);
+        for (int i = 0; i < n; ++i) B.perm[i] = i;
+    }
     B.row0.upload(B.h_row0, s);
     B.nrow.upload(B.h_nrow, s);
     B.d_perm.upload(B.perm, s);
@@ -591,12 +675,12 @@ static void build_part(SellPart& P, PartKind kind, const BlockLevel& B, const Se
     const int32_t* rp = A ? A->rp.p : nullptr;
     const int32_t* ci = A ? A->ci.p : nullptr;
     DevBuf<int32_t> coff32;
-    part_layout(B.n, ns, k, B.d_perm.p, rp, ci, B.row0.p, B.nrow.p, P.width, coff32, P.n_slots, s);
+    part_layout(B.n, ns, k, B.group, B.d_perm.p, rp, ci, B.row0.p, B.nrow.p, P.width, coff32, P.n_slots, s);
     const int64_t nsl = std::max<int64_t>(P.n_slots, 1);
     P.col.alloc(nsl * WAVE);
     DevBuf<int64_t> src(nsl * WAVE);
     DevBuf<int32_t> sblk(nsl);
-    part_fill_index(ns, k, B.row0.p, B.nrow.p, P.width.p, coff32.p, B.d_perm.p, rp, ci, col_iperm, P.n_slots, P.col.p,
+    part_fill_index(ns, k, B.group, B.n, B.row0.p, B.nrow.p, k == (int)PartKind::Off ? B.cstart.p : nullptr, P.width.p, coff32.p, B.d_perm.p, rp, ci, col_iperm, P.n_slots, P.col.p,
                     src.p, sblk.p, s);
     P.coff.alloc(std::max(ns, 1));
     i32_to_i64(ns, coff32.p, P.coff.p, s);
@@ -611,6 +695,10 @@ static void build_part(SellPart& P, PartKind kind, const BlockLevel& B, const Se
         P.v32.alloc(std::max<int64_t>(P.n_groups, 1) * WAVE);
         cast_to_f32(P.v64.p, P.v32.p, P.n_groups * WAVE, s);
     }
+    if (B.group > 1) {   // the byte model of a grouped level counts by rows
+        MB_HIP(hipStreamSynchronize(s));   // the temporaries are released on return
+        return;
+    }
     // host copies for the byte model, with one synchronisation (which also keeps the
     // temporaries alive until the kernels have finished)
     std::vector<int32_t> c32;
@@ -623,14 +711,40 @@ static void build_part(SellPart& P, PartKind kind, const BlockLevel& B, const Se
     P.h_coff.assign(c32.begin(), c32.end());
 }
 
+// the undamped buffers all "unwritten", the tickets zero (fill kernels: this may be captured)
 template <class T>
-static void alloc_vecs(Vecs<T>& v, int64_t n) {
+static void reset_sweeps(Vecs<T>& v, hipStream_t s) {
+    fill_words(reinterpret_cast<uint32_t*>(v.t.p), (int64_t)(v.t.bytes() / 4), 0xFFFFFFFFu, s);
+    fill_words(reinterpret_cast<uint32_t*>(v.t2.p), (int64_t)(v.t2.bytes() / 4), 0xFFFFFFFFu, s);
+    fill_words(v.tickets.p, 2, 0u, s);
+    v.turn_t = v.turn_ticket = 0;
+    v.busy = false;
+}
+
+template <class T>
+static void alloc_vecs(Vecs<T>& v, int64_t n, bool grouped, hipStream_t s) {
     int64_t m = std::max<int64_t>(n, 1);
     v.b.alloc(m);
     v.x.alloc(m);
     v.xs.alloc(m);
     v.t.alloc(m);
     v.r.alloc(m);
+    if (grouped) {
+        v.t2.alloc(m);
+        v.tickets.alloc(2);
+        reset_sweeps(v, s);
+    }
+}
+
+// The launch records of a grouped block row, once its parts are built.
+static void build_recs(BlockLevel& B, hipStream_t s) {
+    MB_CHECK(B.off.n_slots < INT_MAX && B.cpl.n_slots < INT_MAX, MBAMG_E_INVALID, "too many slots in a grouped part");
+    DevBuf<int32_t> order;
+    order.upload(B.h_order, s);
+    B.recs.alloc(std::max<size_t>(B.h_order.size(), 1));
+    sweep_recs((int)B.h_order.size(), order.p, B.row0.p, B.nrow.p, B.cstart.p, B.off.width.p, B.off.coff.p,
+               B.cpl.width.p, B.cpl.coff.p, B.recs.p, s);
+    MB_HIP(hipStreamSynchronize(s));   // order is released on return
 }
 
 // ----------------------------------------------------------------------------
@@ -681,7 +795,7 @@ static void choose_weights(mbamg_hierarchy* h, Level& cur, const Aggregates& G, 
 // (host work on the diagonal blocks' patterns).  `ready` marks the point on
 // the setup stream after which the level's blocks are complete; the patterns
 // are copied on a stream of the calling thread.
-static void colour_level(Level& Lv, hipEvent_t ready, int device) {
+static void colour_level(Level& Lv, int lvl, const mbamg_params& p, hipEvent_t ready, int device) {
     MB_HIP(hipSetDevice(device));   // the calling thread may be a fresh one
     const bool verbose = std::getenv("MBAMG_VERBOSE") != nullptr;
     using clock = std::chrono::steady_clock;
@@ -742,6 +856,10 @@ static void colour_level(Level& Lv, hipEvent_t ready, int device) {
             B.perm = B0.perm;
             B.iperm = B0.iperm;
             B.sell_sorted = B0.sell_sorted;
+            B.group = B0.group;
+            B.colour_rec = B0.colour_rec;
+            B.h_order = B0.h_order;
+            B.h_cstart = B0.h_cstart;
             B.h_row0 = B0.h_row0;
             B.h_nrow = B0.h_nrow;
             B.colour_slice = B0.colour_slice;
@@ -754,7 +872,8 @@ static void colour_level(Level& Lv, hipEvent_t ready, int device) {
             const bool asym = f == 1 && transpose_pattern(nf, rp[f], ci[f], trp, tci);
             int ncol = asym ? greedy_colour(nf, rp[f], ci[f], B.colour, trp.data(), tci.data())
                             : greedy_colour(nf, rp[f], ci[f], B.colour);
-            order_and_slice(B, nf, ncol, rp[f]);
+            // one form for the whole level (its size: the larger block's)
+            order_and_slice(B, nf, ncol, rp[f], choose_group(p, lvl, std::max(Lv.n, Lv.n1), nf, rp[f][nf]));
         }
     }
 }
@@ -797,6 +916,13 @@ static void clone_smoother(BlockLevel& d, const BlockLevel& b, hipStream_t s) {
     d.perm = b.perm;
     d.iperm = b.iperm;
     d.sell_sorted = b.sell_sorted;
+    d.group = b.group;
+    d.colour_rec = b.colour_rec;
+    clone_buf(d.recs, b.recs, s);
+    clone_buf(d.gdiag64, b.gdiag64, s);
+    clone_buf(d.gdinv64, b.gdinv64, s);
+    clone_buf(d.gdiag32, b.gdiag32, s);
+    clone_buf(d.gdinv32, b.gdinv32, s);
     d.colour = b.colour;
     d.h_row0 = b.h_row0;
     d.h_nrow = b.h_nrow;
@@ -900,7 +1026,9 @@ static void setup_impl(mbamg_hierarchy* h, const mbamg_bsr* Ab, hipStream_t s, D
             colour_events.push_back(ev);
             MB_HIP(hipEventRecord(ev, s));
             Level* lp = &cur;
-            colour_jobs[lvl] = std::async(std::launch::async, [lp, ev, device] { colour_level(*lp, ev, device); });
+            const mbamg_params* pp = &h->p;
+            colour_jobs[lvl] = std::async(std::launch::async,
+                                          [lp, lvl, pp, ev, device] { colour_level(*lp, lvl, *pp, ev, device); });
         }
         Aggregates& G = cur.G;
         if (donor_level) {
@@ -943,7 +1071,9 @@ static void setup_impl(mbamg_hierarchy* h, const mbamg_bsr* Ab, hipStream_t s, D
             colour_events.push_back(ev);
             MB_HIP(hipEventRecord(ev, s));
             Level* lp = &cur;
-            colour_jobs[lvl] = std::async(std::launch::async, [lp, ev, device] { colour_level(*lp, ev, device); });
+            const mbamg_params* pp = &h->p;
+            colour_jobs[lvl] = std::async(std::launch::async,
+                                          [lp, lvl, pp, ev, device] { colour_level(*lp, lvl, *pp, ev, device); });
         }
         const int nc = G.n_agg;
         DevBuf<double> q[2], Bc[2];
@@ -1081,8 +1211,8 @@ static void setup_impl(mbamg_hierarchy* h, const mbamg_bsr* Ab, hipStream_t s, D
             }
             c.apply_parts = true;
         }
-        alloc_vecs(c.v64, c.ndof());
-        if (want32) alloc_vecs(c.v32, c.ndof());
+        alloc_vecs(c.v64, c.ndof(), false, s);
+        if (want32) alloc_vecs(c.v32, c.ndof(), false, s);
     }
 
     // smoother format on every other level, in two passes: first each level's own smoother
@@ -1110,7 +1240,7 @@ static void setup_impl(mbamg_hierarchy* h, const mbamg_bsr* Ab, hipStream_t s, D
                 MB_HIP(hipEventCreateWithFlags(&ev, hipEventDisableTiming));
                 colour_events.push_back(ev);
                 MB_HIP(hipEventRecord(ev, s));
-                colour_level(Lv, ev, device);
+                colour_level(Lv, l, p, ev, device);
             }
             clk.mark("colouring joined", l);
         }
@@ -1120,22 +1250,8 @@ static void setup_impl(mbamg_hierarchy* h, const mbamg_bsr* Ab, hipStream_t s, D
             B.nrow.upload(B.h_nrow, s);
             B.d_perm.upload(B.perm, s);
             B.d_iperm.upload(B.iperm, s);
+            if (B.group > 1) B.cstart.upload(B.h_cstart, s);
         }
-        // coarse levels with few rows per colour take the row form: every colour pass is a short,
-        // latency-bound launch, and one wavefront per row (four on rows of 4 x 4 blocks) shortens
-        // its chain of dependent loads (the 128^3 workload's third level, 7461 nodes in 11
-        // colours: 10.8 -> 7.3 us per pass; 2735 nodes in 28 colours with smoothed transfers:
-        // 15 -> 6.7 us; the 64^3 workload's second level, 23,915 nodes in 9 colours: 819 -> 665 us
-        // per FP64 V-cycle).  Larger levels keep the sliced layout, whose rows are sorted by
-        // length within each colour when their lengths differ (the 128^3 workload's second
-        // level, 188,588 nodes: 9 colours 0.80 against 1.10 ms per FP64 V-cycle in the row form;
-        // 18 colours with smoothed transfers 1.36 against 1.56 ms).  The row form's sliced parts
-        // are not built.
-        const int max_colours = std::max(Lv.blk[0].n_colours, Lv.blk[1].n_colours);
-        bool rows_level = l > 0 && (int64_t)std::max(Lv.n, Lv.n1) <= (int64_t)ROWS_PER_COLOUR_MAX * max_colours;
-        // MBAMG_ROWS_FORM (tests): "rows" forces the row form on every coarse level, anything else the sliced one
-        if (const char* fo = form_override("MBAMG_ROWS_FORM")) rows_level = l > 0 && std::strcmp(fo, "rows") == 0;
-        if (p.smoother == 1) rows_level = false;   // the full-node kernel reads the sliced parts
         for (int f = 0; f < 2 && !shared; ++f) {
             const int g = 1 - f;
             BlockLevel& B = Lv.blk[f];
@@ -1145,41 +1261,27 @@ static void setup_impl(mbamg_hierarchy* h, const mbamg_bsr* Ab, hipStream_t s, D
             if (f == 0) clk.mark("colouring", l);
             build_dinv(Lv.A[f][f], dinv.p, s);
             clk.mark("dinv", l);
-            B.rows = rows_level;
-            if (B.rows) {
-                // the per-colour counts the sliced parts would have recorded (byte model)
-                const std::vector<int64_t> cs7 =
-                    row_colour_stats(nf, B.d_perm.p, Lv.A[f][f], Lv.A[f][g], dinv.p, B.colour_row, s);
-                B.cstats.assign(B.n_colours, ColourStats{});
-                for (int c = 0; c < B.n_colours; ++c) {
-                    ColourStats& cs = B.cstats[c];
-                    const int64_t* v = &cs7[(size_t)c * 7];
-                    cs.off_nz = v[0];
-                    cs.off_bl = v[1];
-                    cs.cpl_nz = v[2];
-                    cs.cpl_bl = v[3];
-                    cs.dinv_nz = v[4];
-                    B.all_nz += v[0] + v[2] + v[5];
-                    B.all_bl += v[1] + v[3] + v[6];
-                }
+            if (B.group > 1) {
                 B.split = 1;
-                // few rows per colour (small, latency-bound launches): a workgroup's four
-                // wavefronts share each row, for shorter chains of dependent passes (measured
-                // 12 % faster on a 98-rows-per-colour level, 60 % slower on 10K rows per colour)
-                B.row_split = (df == 4 && nf <= 1024 * std::max(1, B.n_colours)) ? 4 : 1;
-                if (const char* fo = form_override("MBAMG_ROW_SPLIT")) B.row_split = df == 4 ? std::atoi(fo) : 1;
-                build_rows(B.raff, nf, B.d_perm.p, Lv.A[f][f], B.d_iperm.p, want32, s);
-                build_rows(B.rafg, nf, B.d_perm.p, Lv.A[f][g], Lv.blk[g].d_iperm.p, want32, s);
-                B.rdinv64.alloc((size_t)nf * df * df);
-                gather_blocks(nf, df * df, B.d_perm.p, dinv.p, B.rdinv64.p, s);
+                build_part(B.off, PartKind::Off, B, &Lv.A[f][f], B.d_iperm.p, Lv.A[f][f].val.p, df, df, want32, s);
+                build_part(B.cpl, PartKind::Cpl, B, &Lv.A[f][g], Lv.blk[g].d_iperm.p, Lv.A[f][g].val.p, df, dg,
+                           want32, s);
+                build_recs(B, s);
+                const int64_t nd = (int64_t)nf * df * df;
+                B.gdinv64.alloc(nd);
+                gather_blocks(nf, df * df, B.d_perm.p, dinv.p, B.gdinv64.p, s);
+                B.gdiag64.alloc(nd);
+                gather_diag(nf, B.d_perm.p, Lv.A[f][f], B.gdiag64.p, s);
                 if (want32) {
-                    B.rdinv32.alloc((size_t)nf * df * df);
-                    cast_to_f32(B.rdinv64.p, B.rdinv32.p, (int64_t)nf * df * df, s);
+                    B.gdinv32.alloc(nd);
+                    cast_to_f32(B.gdinv64.p, B.gdinv32.p, nd, s);
+                    B.gdiag32.alloc(nd);
+                    cast_to_f32(B.gdiag64.p, B.gdiag32.p, nd, s);
                 }
                 MB_HIP(hipStreamSynchronize(s));   // dinv is released at the end of this iteration
                 if (clk.on)
-                    std::fprintf(stderr, "[mbamg setup] level %d block %d: %d nodes, %d colours, row form\n", l, f,
-                                 nf, B.n_colours);
+                    std::fprintf(stderr, "[mbamg setup] level %d block %d: %d nodes, %d colours, %d lanes per row\n",
+                                 l, f, nf, B.n_colours, B.group);
                 continue;
             }
             build_part(B.off, PartKind::Off, B, &Lv.A[f][f], B.d_iperm.p, Lv.A[f][f].val.p, df, df, want32, s);
@@ -1220,7 +1322,7 @@ static void setup_impl(mbamg_hierarchy* h, const mbamg_bsr* Ab, hipStream_t s, D
         // the residual is one launch over both blocks' slices, not one colour: its split is
         // chosen for the whole level, up to about 32K waves (MBAMG_SLICE_SPLIT forces both)
         Lv.resid_split = std::max(Lv.blk[0].split, Lv.blk[1].split);
-        if (l > 0 && !Lv.blk[0].rows && !Lv.blk[1].rows && !form_override("MBAMG_SLICE_SPLIT")) {
+        if (l > 0 && Lv.blk[0].group == 1 && !form_override("MBAMG_SLICE_SPLIT")) {
             int64_t slots = 0, slices = 0;
             for (int f = 0; f < 2; ++f) {
                 const BlockLevel& B = Lv.blk[f];
@@ -1233,7 +1335,7 @@ static void setup_impl(mbamg_hierarchy* h, const mbamg_bsr* Ab, hipStream_t s, D
         // each XCD takes (contiguous launch ranges) cover one slab of the domain in all colours
         // and their neighbour gathers stay in its L2 (in colour order an XCD's range spans a
         // whole colour, i.e. the whole domain)
-        if (l > 0 && !Lv.blk[0].rows && !Lv.blk[1].rows)
+        if (l > 0 && Lv.blk[0].group == 1)
             for (int f = 0; f < 2; ++f) Lv.resid_order[f].upload(slab_order(Lv.blk[f].colour_slice), s);
         clk.mark("sliced parts", l);
         if (p.smoother == 1) {
@@ -1264,7 +1366,13 @@ static void setup_impl(mbamg_hierarchy* h, const mbamg_bsr* Ab, hipStream_t s, D
         for (int f = 0; f < 2 && Lv.smoothed; ++f) {
             BlockLevel& B = Lv.blk[f];
             BlockLevel& C = Nx.blk[f];
-            build_part(B.pro, PartKind::Cpl, B, &Lv.P[f], C.d_iperm.p, Lv.P[f].val.p, B.d, B.d, want32, s);
+            // P sliced by 64 rows in colour order, whatever the level's own slices
+            BlockLevel col;
+            natural_slicing(col, Lv.nodes(f), s, &B.perm);
+            build_part(B.pro, PartKind::Cpl, col, &Lv.P[f], C.d_iperm.p, Lv.P[f].val.p, B.d, B.d, want32, s);
+            B.pro_row0 = std::move(col.row0);
+            B.pro_nrow = std::move(col.nrow);
+            B.pro_slices = col.n_slices;
             // P^T sliced over the next level's rows in natural order: neighbouring aggregates,
             // whose rows gather the same fine rows, share slices and stay on one XCD (in the
             // colour order a slice mixes aggregates from all over the domain: 4x the
@@ -1281,7 +1389,7 @@ static void setup_impl(mbamg_hierarchy* h, const mbamg_bsr* Ab, hipStream_t s, D
             B.res_rows = Nx.nodes(f) <= RES_ROWS_MAX;
             if (const char* fo = form_override("MBAMG_XFER_FORM")) B.res_rows = std::strcmp(fo, "rows") == 0;
             if (B.res_rows) build_rows(B.rres, Nx.nodes(f), nat.d_perm.p, Lv.PT[f], B.d_iperm.p, want32, s);
-            B.pro_split = transfer_split(B.pro, B.n_slices);
+            B.pro_split = transfer_split(B.pro, B.pro_slices);
             B.res_split = transfer_split(B.res, B.res_slices);
         }
         for (int f = 0; f < 2 && Lv.damped; ++f) {
@@ -1313,8 +1421,8 @@ static void setup_impl(mbamg_hierarchy* h, const mbamg_bsr* Ab, hipStream_t s, D
                 cast_to_f32(B.qm64.p, B.qm32.p, (int64_t)nf * B.d, s);
             }
         }
-        alloc_vecs(Lv.v64, Lv.ndof());
-        if (want32) alloc_vecs(Lv.v32, Lv.ndof());
+        alloc_vecs(Lv.v64, Lv.ndof(), Lv.blk[0].group > 1, s);
+        if (want32) alloc_vecs(Lv.v32, Lv.ndof(), Lv.blk[0].group > 1, s);
         MB_HIP(hipStreamSynchronize(s));
     }
 
@@ -1360,6 +1468,33 @@ static void setup_impl(mbamg_hierarchy* h, const mbamg_bsr* Ab, hipStream_t s, D
 // ----------------------------------------------------------------------------
 // byte model (algorithmic bytes of the finest level's kernels)
 // ----------------------------------------------------------------------------
+// The counts of a grouped level's block rows (what sliced parts record as they are
+// built), from its blocks when the byte model is first asked for: only measurements
+// read them.
+static void count_grouped_levels(mbamg_hierarchy* h) {
+    for (auto& lp : h->L) {
+        Level& Lv = *lp;
+        for (int f = 0; f < 2; ++f) {
+            BlockLevel& B = Lv.blk[f];
+            if (Lv.coarsest || B.group == 1 || !B.cstats.empty()) continue;
+            const std::vector<int64_t> cs7 = row_colour_stats(Lv.nodes(f), B.d_perm.p, Lv.A[f][f], Lv.A[f][1 - f],
+                                                              B.gdinv64.p, B.colour_row, nullptr);
+            B.cstats.assign(B.n_colours, ColourStats{});
+            for (int c = 0; c < B.n_colours; ++c) {
+                ColourStats& cs = B.cstats[c];
+                const int64_t* v = &cs7[(size_t)c * 7];
+                cs.off_nz = v[0];
+                cs.off_bl = v[1];
+                cs.cpl_nz = v[2];
+                cs.cpl_bl = v[3];
+                cs.dinv_nz = v[4];
+                B.all_nz += v[0] + v[2] + v[5];
+                B.all_bl += v[1] + v[3] + v[6];
+            }
+        }
+    }
+}
+
 static double gs_bytes(const BlockLevel& B, int c, bool zero_x, bool skip_off, bool cpl, int s, int dg) {
     const ColourStats& cs = B.cstats[c];
     const int64_t rows = B.colour_row[c + 1] - B.colour_row[c];
@@ -1467,11 +1602,30 @@ RowView<double> rview<double>(const RowPart& R) { return {R.rp.p, R.col.p, R.v64
 template <>
 RowView<float> rview<float>(const RowPart& R) { return {R.rp.p, R.col.p, R.v32.p}; }
 template <class T>
-static const T* rdinv(const BlockLevel& B);
+static const T* gdinv(const BlockLevel& B);
 template <>
-const double* rdinv<double>(const BlockLevel& B) { return B.rdinv64.p; }
+const double* gdinv<double>(const BlockLevel& B) { return B.gdinv64.p; }
 template <>
-const float* rdinv<float>(const BlockLevel& B) { return B.rdinv32.p; }
+const float* gdinv<float>(const BlockLevel& B) { return B.gdinv32.p; }
+
+template <class T>
+static const T* gdiag(const BlockLevel& B);
+template <>
+const double* gdiag<double>(const BlockLevel& B) { return B.gdiag64.p; }
+template <>
+const float* gdiag<float>(const BlockLevel& B) { return B.gdiag32.p; }
+
+template <class T>
+static GroupView<T> gview(const SellPart& P) {
+    const SellView<T> v = P.view<T>();
+    return {v.voff, v.mask, v.col, v.val};
+}
+
+static int log2_of(int g) {
+    int l = 0;
+    while ((1 << l) < g) ++l;
+    return l;
+}
 
 template <class T>
 static const T* qptr(const BlockLevel& B);
@@ -1537,6 +1691,52 @@ static void smooth_fc(mbamg_hierarchy* h, int l, bool zero, const T* b, const T*
         }
 }
 
+// The same for a block row in grouped form.  The first inner sweep is one launch
+// over all colours; a further one continues from t in place, where a row waits
+// for nothing, so its colours are launched one by one -- as they all are while
+// single launches are timed.
+template <class T>
+static void sweep_block(mbamg_hierarchy* h, int l, int f, bool zero, const T* b, const T* x, T* xn, const T* xg,
+                        hipStream_t s) {
+    Level& Lv = *h->L[l];
+    BlockLevel& B = Lv.blk[f];
+    Vecs<T>& V = vecs<T>(Lv);
+    const int64_t off = f == 0 ? 0 : (int64_t)Lv.n * Lv.d[0];
+    const bool timed = h->time_launches();
+    T* const t[2] = {V.t.p + off, V.t2.p + off};
+    SweepArgs<T> a{};
+    a.rec = B.recs.p;
+    a.lg = log2_of(B.group);
+    a.off = gview<T>(B.off);
+    a.cpl = gview<T>(B.cpl);
+    a.dinv = gdinv<T>(B);
+    a.b = b;
+    a.x = x;
+    a.t = t[V.turn_t];
+    a.xn = xn;
+    a.xg = xg;
+    a.omega = (T)h->p.omega;
+    a.w_row = Lv.damped ? wrow<T>(B) : nullptr;
+    for (int k = 0; k < h->p.inner_sweeps; ++k) {
+        const int step = (timed || k > 0) ? 1 : std::max(1, B.n_colours);
+        a.inplace = k > 0;
+        a.t_reset = k == 0 ? t[1 - V.turn_t] : nullptr;
+        for (int c = 0; c < B.n_colours; c += step) {
+            a.begin = B.colour_rec[c];
+            a.count = B.colour_rec[c + step] - a.begin;
+            a.ticket = V.tickets.p + V.turn_ticket;
+            a.ticket_next = V.tickets.p + (1 - V.turn_ticket);
+            const bool skip = zero && k == 0 && c == 0;
+            const double bytes = timed ? gs_bytes(B, c, zero, skip, xg != nullptr, (int)sizeof(T), Lv.d[1 - f]) : 0.0;
+            TimerScope ts(h, s, timed, launch_kind(l, (!zero && xg) ? 0 : 3), bytes);
+            if (a.count == 0) continue;
+            launch_sweep<T>(B.d, zero, xg != nullptr, a, s);
+            V.turn_ticket = 1 - V.turn_ticket;
+        }
+    }
+    if (f == 1) V.turn_t = 1 - V.turn_t;   // both blocks' parts of t are written
+}
+
 template <class T>
 static void smooth_block(mbamg_hierarchy* h, int l, int f, bool zero, const T* b, const T* x, T* xn, const T* xg,
                          hipStream_t s) {
@@ -1547,29 +1747,8 @@ static void smooth_block(mbamg_hierarchy* h, int l, int f, bool zero, const T* b
     T* tbuf = vecs<T>(Lv).t.p + off;
     const bool has_cpl = xg != nullptr;
     const bool timed = h->time_launches();
-    if (B.rows) {
-        for (int k = 0; k < h->p.inner_sweeps; ++k)
-            for (int c = 0; c < B.n_colours; ++c) {
-                const bool skip = zero && k == 0 && c == 0;
-                double bytes = timed ? gs_bytes(B, c, zero, skip, has_cpl, (int)sizeof(T), Lv.d[g]) : 0.0;
-                TimerScope ts(h, s, timed, launch_kind(l, (!zero && has_cpl) ? 0 : 3), bytes);
-                GsRowArgs<T> a{};
-                a.r_begin = B.colour_row[c];
-                a.r_count = B.colour_row[c + 1] - B.colour_row[c];
-                a.aff = rview<T>(B.raff);
-                a.afg = rview<T>(B.rafg);
-                a.dinv = rdinv<T>(B);
-                a.b = b;
-                a.x = x;
-                a.t = tbuf;
-                a.xn = xn;
-                a.xg = xg;
-                a.cstart = k == 0 ? B.colour_row[c] : INT_MAX;
-                a.omega = (T)h->p.omega;
-                a.w_row = Lv.damped ? wrow<T>(B) : nullptr;
-                a.skip_off = (zero && k == 0 && c == 0) ? 1 : 0;
-                launch_gs_rows<T>(B.d, B.row_split, zero, has_cpl, a, s);
-            }
+    if (B.group > 1) {
+        sweep_block<T>(h, l, f, zero, b, x, xn, xg, s);
         return;
     }
     for (int k = 0; k < h->p.inner_sweeps; ++k) {
@@ -1619,17 +1798,21 @@ static void resid(mbamg_hierarchy* h, int l, const T* b, const T* x, T* r, hipSt
     const bool timed = h->time_launches() && kind >= 0 && (l == 0 || kind == 1);
     double bytes = timed ? resid_bytes(Lv, (int)sizeof(T), b != nullptr) : 0.0;
     TimerScope ts(h, s, timed, launch_kind(l, kind), bytes);
-    if (Lv.blk[0].rows && Lv.blk[1].rows) {
-        ResidRowArgs<T> ra{};
+    if (Lv.blk[0].group > 1) {
+        ResidGroupArgs<T> ga{};
         for (int f = 0; f < 2; ++f) {
-            ra.n[f] = Lv.nodes(f);
-            ra.aff[f] = rview<T>(Lv.blk[f].raff);
-            ra.afg[f] = rview<T>(Lv.blk[f].rafg);
-            ra.b[f] = a.b[f];
-            ra.x[f] = a.x[f];
-            ra.r[f] = a.r[f];
+            const BlockLevel& B = Lv.blk[f];
+            ga.rec[f] = B.recs.p;
+            ga.count[f] = B.colour_rec.back();
+            ga.lg[f] = log2_of(B.group);
+            ga.off[f] = gview<T>(B.off);
+            ga.cpl[f] = gview<T>(B.cpl);
+            ga.diag[f] = gdiag<T>(B);
+            ga.b[f] = a.b[f];
+            ga.x[f] = a.x[f];
+            ga.r[f] = a.r[f];
         }
-        launch_resid_rows<T>(Lv.d[0], ra, s);
+        launch_resid_group<T>(Lv.d[0], ga, s);
         return;
     }
     launch_resid<T>(Lv.d[0], Lv.resid_split, a, s);
@@ -1650,6 +1833,10 @@ static void vcycle_level(mbamg_hierarchy* h, int l, const T* b, T* out, hipStrea
     std::optional<TimerScope> seg;
     seg.emplace(h, s, tl, TK_LEVEL + 2 * l, seg_down);
     Vecs<T>& V = vecs<T>(Lv);
+    if (Lv.blk[0].group > 1) {
+        if (V.busy) reset_sweeps(V, s);
+        V.busy = true;
+    }
     const int64_t n0 = (int64_t)Lv.n * Lv.d[0];
     const int writes = 2 * h->p.bgs_sweeps;
     // ping-pong so that the last write lands in out
@@ -1730,8 +1917,8 @@ static void vcycle_level(mbamg_hierarchy* h, int l, const T* b, T* out, hipStrea
     if (Lv.smoothed) {
         XferArgs<T> a{};
         for (int f = 0; f < 2; ++f) {
-            a.s_count[f] = Lv.blk[f].n_slices;
-            a.sl[f] = Lv.blk[f].slices();
+            a.s_count[f] = Lv.blk[f].pro_slices;
+            a.sl[f] = {Lv.blk[f].pro_row0.p, Lv.blk[f].pro_nrow.p};
             a.A[f] = Lv.blk[f].pro.view<T>();
             a.x[f] = C.x.p + (f ? nc0 : 0);
             a.y[f] = buf[cur] + (f ? n0 : 0);
@@ -1759,6 +1946,10 @@ static void vcycle_level(mbamg_hierarchy* h, int l, const T* b, T* out, hipStrea
     }
     for (int k = 0; k < h->p.bgs_sweeps; ++k) sweep(false);
     MB_CHECK(buf[cur] == out, MBAMG_E_STATE, "internal: V-cycle result not in the output buffer");
+    // every launch of the way down has its counterpart on the way up, so both turns are back
+    // where they began and the cycle can be captured and replayed
+    MB_CHECK(V.turn_t == 0 && V.turn_ticket == 0, MBAMG_E_STATE, "internal: sweep buffers out of turn");
+    V.busy = false;
 }
 
 
@@ -2665,6 +2856,7 @@ mbamg_status mbamg_timing_enable(mbamg_hierarchy* h, int32_t enable) {
         }
         h->timed.clear();
         MB_CHECK(enable >= 0 && enable <= 3, MBAMG_E_INVALID, "timing mode must be 0..3");
+        if (enable) count_grouped_levels(h);
         h->timing = enable;
         return MBAMG_OK;
     });
@@ -2695,6 +2887,7 @@ mbamg_status mbamg_vcycle_bytes(const mbamg_hierarchy* h, double* bytes) {
     return guarded([&]() -> mbamg_status {
         MB_CHECK(h && bytes, MBAMG_E_INVALID, "NULL argument");
         MB_CHECK(h->nb == 2, MBAMG_E_STATE, "the byte model covers two-block hierarchies");
+        count_grouped_levels(const_cast<mbamg_hierarchy*>(h));
         double tot = 0.0;
         for (int l = 0; l < (int)h->L.size(); ++l) {
             double down = 0.0, up = 0.0;
@@ -2711,6 +2904,7 @@ mbamg_status mbamg_level_vcycle_bytes(const mbamg_hierarchy* h, int32_t level, d
         MB_CHECK(h && down && up, MBAMG_E_INVALID, "NULL argument");
         MB_CHECK(h->nb == 2, MBAMG_E_STATE, "the byte model covers two-block hierarchies");
         MB_CHECK(level >= 0 && level < (int)h->L.size(), MBAMG_E_INVALID, "bad argument");
+        count_grouped_levels(const_cast<mbamg_hierarchy*>(h));
         level_vcycle_bytes(h, level, *down, *up);
         return MBAMG_OK;
     });

@@ -35,6 +35,8 @@ Aggregates build_aggregates(const Strength& S, uint64_t seed, int level, hipStre
 void fill_ones(double* a, int64_t n, hipStream_t s);
 // a[0..n) = v with a kernel (no memset node, so the call may sit in a captured graph)
 void fill_value(double* a, int64_t n, double v, hipStream_t s);
+// n 32-bit words = v, with a kernel
+void fill_words(uint32_t* a, int64_t n, uint32_t v, hipStream_t s);
 void build_tentative(const Aggregates& G, int d, const double* B, double* q, double* Bc, hipStream_t s);
 // the tentative prolongator as a block matrix: row i holds diag(q_i) in column agg(i)
 SetupBsr tentative_bsr(const Aggregates& G, int d, const double* q, hipStream_t s);
@@ -80,9 +82,11 @@ void build_rows(RowPart& R, int n, const int32_t* perm, const SetupBsr& A, const
                 hipStream_t s);
 // dst[p] = src[perm[p]] for blocks of bs values
 void gather_blocks(int n, int bs, const int32_t* perm, const double* src, double* dst, hipStream_t s);
+// dst[p] = the diagonal block of row perm[p] of A
+void gather_diag(int n, const int32_t* perm, const SetupBsr& A, double* dst, hipStream_t s);
 // For each colour c (rows colour_row[c] .. colour_row[c+1] in colour order,
 // node perm[p]): 7 sums -- nonzero entries and blocks of A_ff's off-diagonal
-// blocks, of A_fg, nonzero entries of D^-1 (natural order), nonzero entries
+// blocks, of A_fg, nonzero entries of D^-1 (dinv, colour order), nonzero entries
 // and blocks of A_ff's diagonal block.
 std::vector<int64_t> row_colour_stats(int n, const int32_t* perm, const SetupBsr& Aff, const SetupBsr& Afg,
                                       const double* dinv, const std::vector<int>& colour_row, hipStream_t s);
@@ -96,14 +100,18 @@ void check_bsr_device(int n_rows, int n_cols, int64_t nnzb, const int32_t* rp, c
 // Test-only choice between equivalent kernel forms: the value of environment
 // variable `var`, or null when it is unset or empty.
 const char* form_override(const char* var);
-// device construction of the sliced smoother format (see hierarchy.hip)
-void part_layout(int n, int ns, int kind, const int32_t* perm, const int32_t* rp, const int32_t* ci,
+// device construction of the sliced and grouped smoother formats (see hierarchy.hip), G lanes per row
+void part_layout(int n, int ns, int kind, int G, const int32_t* perm, const int32_t* rp, const int32_t* ci,
                  const int32_t* row0, const int32_t* nrow, DevBuf<int32_t>& width, DevBuf<int32_t>& coff32,
                  int64_t& n_slots, hipStream_t s);
-void part_fill_index(int ns, int kind, const int32_t* row0, const int32_t* nrow, const int32_t* width,
-                     const int32_t* coff32, const int32_t* perm, const int32_t* rp, const int32_t* ci,
-                     const int32_t* col_iperm, int64_t n_slots, int32_t* col, int64_t* src, int32_t* slot_blocks,
-                     hipStream_t s);
+void part_fill_index(int ns, int kind, int G, int n_cols, const int32_t* row0, const int32_t* nrow,
+                     const int32_t* cstart, const int32_t* width, const int32_t* coff32, const int32_t* perm,
+                     const int32_t* rp, const int32_t* ci, const int32_t* col_iperm, int64_t n_slots, int32_t* col,
+                     int64_t* src, int32_t* slot_blocks, hipStream_t s);
+struct SweepRec;
+void sweep_recs(int n, const int32_t* order, const int32_t* row0, const int32_t* nrow, const int32_t* cstart,
+                const int32_t* ow, const int64_t* oc, const int32_t* cw, const int64_t* cc, SweepRec* out,
+                hipStream_t s);
 int64_t slot_offsets(int64_t n_slots, const uint32_t* mask, DevBuf<int64_t>& voff, hipStream_t s);
 void i32_to_i64(int64_t n, const int32_t* a, int64_t* b, hipStream_t s);
 void transfer_maps(int n, int nc, const int32_t* perm, const int32_t* iperm, const int32_t* agg,

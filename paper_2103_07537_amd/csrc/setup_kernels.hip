@@ -8,6 +8,7 @@
 // evaluation in the same order.  That keeps the aggregates of coarse levels
 // (which compare those numbers) reproducible.
 #include "setup_kernels.h"
+#include "solve_kernels.h"
 
 #include <utility>
 #include <cstdlib>
@@ -1424,28 +1425,41 @@ __global__ void k_part_rowlen(int n, int kind, const int32_t* perm, const int32_
     rowlen[p] = c;
 }
 
-__global__ void k_part_width(int ns, int kind, const int32_t* row0, const int32_t* nrow, const int32_t* rowlen,
-                             int32_t* width) {
+// G lanes per row: a slice's slot holds G blocks of each of its rows
+__global__ void k_part_width(int ns, int kind, int G, const int32_t* row0, const int32_t* nrow,
+                             const int32_t* rowlen, int32_t* width) {
     int sl = blockIdx.x * blockDim.x + threadIdx.x;
     if (sl >= ns) return;
     int w = 0;
     for (int l = 0; l < nrow[sl]; ++l) w = max(w, rowlen[row0[sl] + l]);
-    width[sl] = (kind >= 2) ? 1 : w;
+    width[sl] = (kind >= 2) ? 1 : (w + G - 1) / G;
+}
+
+// blocks per slot: the slots of a slice belong to its wavefront alone; a lane
+// holds blocks in its first `placed` slots
+__device__ inline void count_slot_blocks(int placed, int w, int64_t base, int lane, int32_t* slot_blocks) {
+    for (int kk = 0; kk < w; ++kk) {
+        const int c = (int)__popcll(__ballot(kk < placed));
+        if (lane == 0) slot_blocks[base + kk] = c;
+    }
 }
 
 // one thread per (slice, lane): column (in the column block's colour order) and
-// source index of each slot, -1 for padding
-__global__ void k_part_fill_index(int ns, int kind, const int32_t* row0, const int32_t* nrow, const int32_t* width,
-                                  const int32_t* coff, const int32_t* perm, const int32_t* rp, const int32_t* ci,
-                                  const int32_t* col_iperm, int32_t* col, int64_t* src, int32_t* slot_blocks) {
+// source index of each slot, -1 for padding; with G lanes per row, block k of a
+// row goes to lane k % G of its slot k / G
+__global__ void k_part_fill_index(int ns, int kind, int G, const int32_t* row0, const int32_t* nrow,
+                                  const int32_t* width, const int32_t* coff, const int32_t* perm, const int32_t* rp,
+                                  const int32_t* ci, const int32_t* col_iperm, int32_t* col, int64_t* src,
+                                  int32_t* slot_blocks) {
     int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (t >= (int64_t)ns * WAVE) return;
     int sl = (int)(t / WAVE), lane = (int)(t % WAVE);
     int w = width[sl];
     int64_t base = coff[sl];
-    int k = 0;
-    if (lane < nrow[sl]) {
-        int p = row0[sl] + lane;
+    int k = 0, seen = 0;
+    const int r = lane / G, mine = lane % G;
+    if (r < nrow[sl]) {
+        int p = row0[sl] + r;
         int node = perm[p];
         if (kind == 3) {
             col[base * WAVE + lane] = p;
@@ -1455,6 +1469,7 @@ __global__ void k_part_fill_index(int ns, int kind, const int32_t* row0, const i
             for (int q = rp[node]; q < rp[node + 1] && k < w; ++q) {
                 int j = ci[q];
                 if (!part_selects(kind, node, j)) continue;
+                if (seen++ % G != mine) continue;
                 col[(base + k) * WAVE + lane] = col_iperm[j];
                 src[(base + k) * WAVE + lane] = q;
                 ++k;
@@ -1466,11 +1481,67 @@ __global__ void k_part_fill_index(int ns, int kind, const int32_t* row0, const i
         col[(base + k) * WAVE + lane] = -1;
         src[(base + k) * WAVE + lane] = -1;
     }
-    // blocks per slot: the slots of a slice belong to its wavefront alone
-    for (int kk = 0; kk < w; ++kk) {
-        const int c = (int)__popcll(__ballot(kk < placed));
-        if (lane == 0) slot_blocks[base + kk] = c;
+    count_slot_blocks(placed, w, base, lane, slot_blocks);
+}
+
+// The same for the off-diagonal blocks of a grouped block row, one wavefront per
+// slice, a row's blocks in the order of the sweep's waits: the columns of its own
+// and later colours first, then the earlier colours' ascending (cstart[slice]:
+// first row of the slice's colour).  A block's place is its rank among the row's
+// keys, which are held in LDS (rows too long for their share of it read them from
+// memory again).
+constexpr int ORDER_KEYS = 1024;   // per wavefront, shared by its 64 / G rows
+__global__ __launch_bounds__(256) void k_group_fill_index(int ns, int G, int n_cols, const int32_t* row0,
+                                                          const int32_t* nrow, const int32_t* cstart,
+                                                          const int32_t* width, const int32_t* coff,
+                                                          const int32_t* perm, const int32_t* rp, const int32_t* ci,
+                                                          const int32_t* col_iperm, int32_t* col, int64_t* src,
+                                                          int32_t* slot_blocks) {
+    __shared__ int32_t keys_all[256 / WAVE][ORDER_KEYS];
+    const int sl = (int)((blockIdx.x * (int64_t)blockDim.x + threadIdx.x) / WAVE);
+    if (sl >= ns) return;   // whole wavefronts; no barrier follows
+    const int lane = threadIdx.x % WAVE;
+    const int r = lane / G, mine = lane % G, cap = ORDER_KEYS / (WAVE / G);
+    int32_t* keys = keys_all[threadIdx.x / WAVE] + r * cap;
+    const int w = width[sl];
+    const int64_t base = coff[sl];
+    const bool row_ok = r < nrow[sl];
+    const int node = row_ok ? perm[row0[sl] + r] : 0;
+    const int b = row_ok ? rp[node] : 0, len = row_ok ? rp[node + 1] - b : 0;
+    const int cs = cstart[sl];
+    // own and later colours sort before the earlier ones; the diagonal block sorts last
+    auto key_of = [&](int q) {
+        const int j = ci[b + q];
+        if (j == node) return INT_MAX;
+        const int jp = col_iperm[j];
+        return jp < cs ? jp : jp - n_cols;
+    };
+    const bool in_lds = len <= cap;
+    if (in_lds)
+        for (int q = mine; q < len; q += G) keys[q] = key_of(q);
+    __builtin_amdgcn_wave_barrier();   // one wavefront: its LDS accesses stay in order
+    int placed = 0;
+    bool diag = false;
+    for (int q = 0; q < w; ++q) {
+        col[(base + q) * WAVE + lane] = -1;
+        src[(base + q) * WAVE + lane] = -1;
     }
+    for (int q = mine; q < len; q += G) {
+        const int k = in_lds ? keys[q] : key_of(q);
+        if (k == INT_MAX) continue;
+        int rank = 0;
+        for (int q2 = 0; q2 < len; ++q2) rank += (in_lds ? keys[q2] : key_of(q2)) < k;
+        const int64_t at = (base + rank / G) * WAVE + r * G + rank % G;
+        col[at] = k < 0 ? k + n_cols : k;
+        src[at] = b + q;
+    }
+    for (int q = mine; q < len; q += G) diag = diag || (in_lds ? keys[q] : key_of(q)) == INT_MAX;
+    // off-diagonal blocks of the row: one fewer where one of its G lanes met the diagonal
+    const uint64_t ball = __ballot(diag);
+    const uint64_t group = G == WAVE ? ~0ull : ((1ull << G) - 1ull) << (r * G);
+    const int total = len - ((ball & group) != 0 ? 1 : 0);
+    placed = total / G + (mine < total % G ? 1 : 0);
+    count_slot_blocks(placed, w, base, lane, slot_blocks);
 }
 
 __global__ void k_popcount(int64_t n, const uint32_t* mask, int32_t* cnt) {
@@ -1844,6 +1915,17 @@ void build_tentative(const Aggregates& G, int d, const double* B, double* q, dou
 
 void fill_ones(double* a, int64_t n, hipStream_t s) { fill_value(a, n, 1.0, s); }
 
+__global__ void k_fill_words(uint32_t* a, int64_t n, uint32_t v) {
+    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x)
+        a[i] = v;
+}
+
+void fill_words(uint32_t* a, int64_t n, uint32_t v, hipStream_t s) {
+    if (n <= 0) return;
+    k_fill_words<<<(unsigned)std::min<int64_t>(4096, ceil_div(n, 256)), 256, 0, s>>>(a, n, v);
+    MB_LAUNCH_CHECK();
+}
+
 void fill_value(double* a, int64_t n, double v, hipStream_t s) {
     if (n <= 0) return;
     k_fill_f64<<<grid_for(n), 256, 0, s>>>(a, n, v);
@@ -2143,7 +2225,7 @@ __global__ __launch_bounds__(256) void k_row_stats(int n, const int32_t* __restr
         }
     }
     for (int u0 = 0; u0 < fbs; u0 += WAVE)
-        dinv_nz += (int)__popcll(__ballot(u0 + lane < fbs && dinv[(int64_t)node * fbs + u0 + lane] != 0.0));
+        dinv_nz += (int)__popcll(__ballot(u0 + lane < fbs && dinv[(int64_t)p * fbs + u0 + lane] != 0.0));
     if (lane != 0) return;
     int32_t* o = out + (int64_t)p * 7;
     o[0] = off_nz;
@@ -2170,6 +2252,28 @@ std::vector<int64_t> row_colour_stats(int n, const int32_t* perm, const SetupBsr
         for (int p = colour_row[c]; p < colour_row[c + 1]; ++p)
             for (int k = 0; k < 7; ++k) sums[(size_t)c * 7 + k] += h[(size_t)p * 7 + k];
     return sums;
+}
+
+// dst[p] = the diagonal block of row perm[p] of A (zero where the row has none)
+__global__ void k_gather_diag(int n, int bs, const int32_t* perm, const int32_t* rp, const int32_t* ci,
+                              const double* val, double* dst) {
+    const int p = blockIdx.x * blockDim.x + threadIdx.x;
+    if (p >= n) return;
+    const int node = perm[p];
+    int lo = rp[node], hi = rp[node + 1];
+    while (lo < hi) {   // columns are sorted within a row
+        const int mid = (lo + hi) >> 1;
+        if (ci[mid] < node) lo = mid + 1;
+        else hi = mid;
+    }
+    const bool found = lo < rp[node + 1] && ci[lo] == node;
+    for (int e = 0; e < bs; ++e) dst[(int64_t)p * bs + e] = found ? val[(int64_t)lo * bs + e] : 0.0;
+}
+
+void gather_diag(int n, const int32_t* perm, const SetupBsr& A, double* dst, hipStream_t s) {
+    if (n == 0) return;
+    k_gather_diag<<<grid_for(n), 256, 0, s>>>(n, A.br * A.bc, perm, A.rp.p, A.ci.p, A.val.p, dst);
+    MB_LAUNCH_CHECK();
 }
 
 void gather_blocks(int n, int bs, const int32_t* perm, const double* src, double* dst, hipStream_t s) {
@@ -2399,25 +2503,58 @@ void spgemm_multi(const SetupBsr* const* A, const SetupBsr* const* B, int K, Set
     MB_HIP(hipStreamSynchronize(s));   // crow is released on return
 }
 
-void part_layout(int n, int ns, int kind, const int32_t* perm, const int32_t* rp, const int32_t* ci,
+void part_layout(int n, int ns, int kind, int G, const int32_t* perm, const int32_t* rp, const int32_t* ci,
                  const int32_t* row0, const int32_t* nrow, DevBuf<int32_t>& width, DevBuf<int32_t>& coff32,
                  int64_t& n_slots, hipStream_t s) {
     DevBuf<int32_t> rowlen(std::max(n, 1));
     k_part_rowlen<<<grid_for(n), 256, 0, s>>>(n, kind, perm, rp, ci, rowlen.p);
     width.alloc(std::max(ns, 1));
-    k_part_width<<<grid_for(ns), 256, 0, s>>>(ns, kind, row0, nrow, rowlen.p, width.p);
+    k_part_width<<<grid_for(ns), 256, 0, s>>>(ns, kind, G, row0, nrow, rowlen.p, width.p);
     MB_LAUNCH_CHECK();
     coff32.alloc(ns + 1);
     n_slots = scan_exclusive(width.p, ns, coff32.p, s);
 }
 
-void part_fill_index(int ns, int kind, const int32_t* row0, const int32_t* nrow, const int32_t* width,
-                     const int32_t* coff32, const int32_t* perm, const int32_t* rp, const int32_t* ci,
-                     const int32_t* col_iperm, int64_t n_slots, int32_t* col, int64_t* src, int32_t* slot_blocks,
-                     hipStream_t s) {
+void part_fill_index(int ns, int kind, int G, int n_cols, const int32_t* row0, const int32_t* nrow,
+                     const int32_t* cstart, const int32_t* width, const int32_t* coff32, const int32_t* perm,
+                     const int32_t* rp, const int32_t* ci, const int32_t* col_iperm, int64_t n_slots, int32_t* col,
+                     int64_t* src, int32_t* slot_blocks, hipStream_t s) {
     MB_HIP(hipMemsetAsync(slot_blocks, 0, sizeof(int32_t) * std::max<int64_t>(n_slots, 1), s));
-    k_part_fill_index<<<grid_for((int64_t)ns * WAVE), 256, 0, s>>>(ns, kind, row0, nrow, width, coff32, perm, rp, ci,
-                                                                   col_iperm, col, src, slot_blocks);
+    const unsigned grid = grid_for((int64_t)ns * WAVE);
+    if (cstart)
+        k_group_fill_index<<<grid, 256, 0, s>>>(ns, G, n_cols, row0, nrow, cstart, width, coff32, perm, rp, ci,
+                                                col_iperm, col, src, slot_blocks);
+    else
+        k_part_fill_index<<<grid, 256, 0, s>>>(ns, kind, G, row0, nrow, width, coff32, perm, rp, ci, col_iperm, col,
+                                               src, slot_blocks);
+    MB_LAUNCH_CHECK();
+}
+
+// launch records of a grouped block row (see SweepRec): position i runs slice order[i] (-1: nothing)
+__global__ void k_sweep_recs(int n, const int32_t* order, const int32_t* row0, const int32_t* nrow,
+                             const int32_t* cstart, const int32_t* ow, const int64_t* oc, const int32_t* cw,
+                             const int64_t* cc, SweepRec* out) {
+    const int i = blockIdx.x * blockDim.x + threadIdx.x;
+    if (i >= n) return;
+    SweepRec r{};
+    const int sl = order[i];
+    if (sl >= 0) {
+        r.row0 = row0[sl];
+        r.nrow = nrow[sl];
+        r.cstart = cstart[sl];
+        r.off_w = ow[sl];
+        r.off_c = (int32_t)oc[sl];
+        r.cpl_w = cw[sl];
+        r.cpl_c = (int32_t)cc[sl];
+    }
+    out[i] = r;
+}
+
+void sweep_recs(int n, const int32_t* order, const int32_t* row0, const int32_t* nrow, const int32_t* cstart,
+                const int32_t* ow, const int64_t* oc, const int32_t* cw, const int64_t* cc, SweepRec* out,
+                hipStream_t s) {
+    if (n <= 0) return;
+    k_sweep_recs<<<grid_for(n), 256, 0, s>>>(n, order, row0, nrow, cstart, ow, oc, cw, cc, out);
     MB_LAUNCH_CHECK();
 }
 

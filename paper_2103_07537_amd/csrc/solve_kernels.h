@@ -66,10 +66,8 @@ struct GsFcArgs {
     int skip_off;                  // nothing processed yet and zero start: the sums vanish
 };
 
-// A block row of a coarse level in row form: rows in colour order, each row's
-// blocks contiguous (row-major br x bc) with columns in the column block's
-// colour order.  Used where rows are long (dense coarse stencils): one
-// wavefront per row, its lanes over the row's blocks.
+// A block row in row form: each row's blocks contiguous (row-major br x bc)
+// with columns in the column block's colour order.
 template <class T>
 struct RowView {
     const int32_t* rp;         // rows + 1
@@ -77,30 +75,58 @@ struct RowView {
     const T* val;
 };
 
+// One slice of a grouped block row as the sweep and the grouped residual read
+// it: its rows, the first row of its colour, and its slots in the two parts.
+struct SweepRec {
+    int32_t row0, nrow;        // nrow == 0: a launch position with nothing to do
+    int32_t cstart;            // first row of the slice's colour
+    int32_t off_w, off_c;      // A_ff without its diagonal: slots, first slot
+    int32_t cpl_w, cpl_c;      // A_fg: the same
+    int32_t pad;
+};
+
+// Slots of a grouped part (see k_sweep): like SellView, but a slice has 64 / G
+// rows and G consecutive lanes hold G blocks of one row.
 template <class T>
-struct GsRowArgs {
-    int r_begin, r_count;      // rows of this colour
-    RowView<T> aff, afg;       // A_ff with its diagonal block (skipped here), A_fg
+struct GroupView {
+    const int64_t* voff;       // per slot
+    const uint32_t* mask;
+    const int32_t* col;
+    const T* val;
+};
+
+// One Gauss-Seidel sub-solve of a block row in grouped form, over the launch
+// positions [begin, begin + count) of its record list (whole colours, ascending).
+template <class T>
+struct SweepArgs {
+    const SweepRec* rec;
+    int begin, count;
+    int lg;                    // log2 of the lanes per row
+    GroupView<T> off, cpl;
     const T* dinv;             // d x d per row, colour order
     const T* b;
-    const T* x;
-    T* t;
-    T* xn;
-    const T* xg;
-    int cstart;
+    const T* x;                // current iterate (unused when starting from zero)
+    T* t;                      // undamped iterate x + e: written, and awaited for earlier colours
+    T* t_reset;                // the other undamped buffer: this launch's rows are set to "not yet written" (NULL: no)
+    T* xn;                     // damped result x + omega e
+    const T* xg;               // iterate of the other block for the coupling term
+    int inplace;               // a further inner sweep: every neighbour's value comes from t
     T omega;
-    const T* w_row;
-    int skip_off;
+    const T* w_row;            // per-row damping (NULL: use omega)
+    uint32_t* ticket;          // zero at launch
+    uint32_t* ticket_next;     // set to zero for the next launch
 };
 
 template <class T>
-struct ResidRowArgs {
-    int n[2];
-    RowView<T> aff[2], afg[2];
+struct ResidGroupArgs {
+    const SweepRec* rec[2];
+    int count[2];
+    int lg[2];
+    GroupView<T> off[2], cpl[2];
+    const T* diag[2];          // d x d per row, colour order
     const T* b[2];             // NULL for a plain operator apply
     const T* x[2];
     T* r[2];
-    const int32_t* order[2];   // slice of each launch position (NULL: the position itself)
 };
 
 template <class T>
@@ -163,11 +189,12 @@ template <class T>
 void launch_resid(int d, int P, const ResidArgs<T>& a, hipStream_t s);
 template <class T>
 void launch_gs_fc(int d, int P, bool zero_x, const GsFcArgs<T>& a, hipStream_t s);
+// positions of a record list are taken this many at a time: every colour's are padded to a multiple
+constexpr int SWEEP_WAVES = 8;
 template <class T>
-// rp: wavefronts per row (1, or 4 with 4 x 4 blocks for long rows)
-void launch_gs_rows(int d, int rp, bool zero_x, bool has_cpl, const GsRowArgs<T>& a, hipStream_t s);
+void launch_sweep(int d, bool zero_x, bool has_cpl, const SweepArgs<T>& a, hipStream_t s);
 template <class T>
-void launch_resid_rows(int d, const ResidRowArgs<T>& a, hipStream_t s);
+void launch_resid_group(int d, const ResidGroupArgs<T>& a, hipStream_t s);
 // y += sign * A x for one block in row form, any block shape up to 4 x 4 (one thread per row)
 template <class T>
 void launch_rows_acc(int n, int br, int bc, const RowView<T>& A, const T* x, T* y, T sign, hipStream_t s);

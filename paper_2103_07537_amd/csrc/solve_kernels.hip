@@ -10,6 +10,7 @@
 
 #include <algorithm>
 #include <climits>
+#include <cmath>
 #include <utility>
 
 namespace mbamg {
@@ -379,8 +380,309 @@ __global__ __launch_bounds__(waves_per_block<P>() * WAVE) void k_gs_fc(GsFcArgs<
 }
 
 // ---------------------------------------------------------------------------
-// Row-form kernels for coarse levels: one wavefront per row, lanes over the
-// row's blocks, partial sums combined across the wavefront.
+// Grouped form (coarse levels and small finest levels): G = 4 .. 64 lanes per
+// block row, 64 / G rows per wavefront; a slot holds the next G blocks of every
+// row of the slice, its values stored as in the sliced form (one 64-lane group
+// per nonzero entry), so a row of L blocks is ceil(L / G) slots deep.
+// ---------------------------------------------------------------------------
+
+// "not yet written" in an undamped buffer: all bits set, a NaN that no store
+// below ever writes
+__device__ __forceinline__ bool unwritten(double v) { return __double_as_longlong(v) == -1ll; }
+__device__ __forceinline__ bool unwritten(float v) { return __float_as_uint(v) == 0xFFFFFFFFu; }
+template <class T>
+__device__ __forceinline__ T unwritten_value() {
+    if constexpr (sizeof(T) == 8) return __longlong_as_double(-1ll);
+    else return __uint_as_float(0xFFFFFFFFu);
+}
+
+// A row's D values as other workgroups of the running launch may be writing
+// them: relaxed loads at device scope (past the L1, coherent across the XCDs),
+// 8 bytes at a time where rows are 8-byte aligned.  Each value is its own
+// signal, so no order between different addresses is needed.
+template <class T, int D>
+__device__ __forceinline__ void load_shared_vec(const T* p, T (&v)[D]) {
+    if constexpr (sizeof(T) == 4 && D % 2 == 0) {
+#pragma unroll
+        for (int c = 0; c < D; c += 2) {
+            const unsigned long long u = __hip_atomic_load(reinterpret_cast<const unsigned long long*>(p + c),
+                                                           __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            v[c] = __uint_as_float((unsigned)u);
+            v[c + 1] = __uint_as_float((unsigned)(u >> 32));
+        }
+    } else {
+#pragma unroll
+        for (int c = 0; c < D; ++c) v[c] = __hip_atomic_load(p + c, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+}
+template <class T, int D>
+__device__ __forceinline__ bool any_unwritten(const T (&v)[D]) {
+    bool m = false;
+#pragma unroll
+    for (int c = 0; c < D; ++c) m = m || unwritten(v[c]);
+    return m;
+}
+
+// data that no running launch writes, at an address all lanes share: a scalar load
+template <class U>
+__device__ __forceinline__ U uniform_load(const U* p) {
+    typedef const U __attribute__((address_space(4))) * ConstPtr;
+    return *(ConstPtr)(uintptr_t)p;
+}
+
+// A wait ends after this many rounds even if the value never comes (each round
+// is a device-scope load of half a microsecond or more): the launch then
+// finishes with NaN results instead of hanging.
+constexpr int SWEEP_MAX_ROUNDS = 1 << 20;
+
+// acc -= sum over the slice's slots of one part.  MODE 0: x_j from xa.  MODE 1:
+// columns below cstart from ta (awaited), others from xa.  MODE 2: columns below
+// cstart from ta (awaited), others contribute 0.
+template <class T, int D, int MODE>
+__device__ __forceinline__ void group_sub(const GroupView<T>& A, int w, int cb, int lane, const T* __restrict__ xa,
+                                          const T* ta, int cstart, T (&acc)[D]) {
+    constexpr int CH = 2;
+    for (int t0 = 0; t0 < w; t0 += CH) {
+        int j[CH];
+        uint32_t m[CH];
+        int64_t vg[CH];
+#pragma unroll
+        for (int u = 0; u < CH; ++u) {
+            const bool live = t0 + u < w;
+            const int64_t sl = (int64_t)cb + t0 + u;
+            m[u] = live ? uniform_load(A.mask + sl) : 0u;
+            vg[u] = live ? uniform_load(A.voff + sl) : 0;
+            j[u] = live ? A.col[sl * WAVE + lane] : -1;
+        }
+        T v[CH][D * D], xj[CH][D];
+#pragma unroll
+        for (int u = 0; u < CH; ++u) load_masked<T, D * D>(A.val + vg[u] * WAVE + lane, m[u], v[u]);
+        // every load of the chunk is issued before the first value is looked at
+        bool await[CH];
+#pragma unroll
+        for (int u = 0; u < CH; ++u) {
+#pragma unroll
+            for (int c = 0; c < D; ++c) xj[u][c] = T(0);
+            await[u] = MODE != 0 && j[u] >= 0 && j[u] < cstart;
+            if (await[u]) load_shared_vec<T, D>(ta + (int64_t)j[u] * D, xj[u]);
+            else if (MODE != 2 && j[u] >= 0) load_vec<T, D>(xa + (int64_t)j[u] * D, xj[u]);
+        }
+        if (MODE != 0) {
+            for (int round = 0; round < SWEEP_MAX_ROUNDS; ++round) {
+                bool more = false;
+#pragma unroll
+                for (int u = 0; u < CH; ++u) {
+                    await[u] = await[u] && any_unwritten<T, D>(xj[u]);
+                    more = more || await[u];
+                }
+                if (!__any(more)) break;
+#pragma unroll
+                for (int u = 0; u < CH; ++u)
+                    if (await[u]) load_shared_vec<T, D>(ta + (int64_t)j[u] * D, xj[u]);
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < CH; ++u)
+#pragma unroll
+            for (int r = 0; r < D; ++r)
+#pragma unroll
+                for (int c = 0; c < D; ++c) acc[r] -= v[u][r * D + c] * xj[u][c];
+    }
+}
+
+__device__ __forceinline__ SweepRec load_rec(const SweepRec* p) {
+    typedef int v8i __attribute__((ext_vector_type(8)));
+    static_assert(sizeof(SweepRec) == sizeof(v8i), "one 32-byte record");
+    return __builtin_bit_cast(SweepRec, uniform_load(reinterpret_cast<const v8i*>(p)));
+}
+
+template <int CTRL>
+__device__ __forceinline__ float dpp_get(float v) {
+    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xF, 0xF, true));
+}
+template <int CTRL>
+__device__ __forceinline__ double dpp_get(double v) {
+    const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), CTRL, 0xF, 0xF, true);
+    const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), CTRL, 0xF, 0xF, true);
+    return __hiloint2double(hi, lo);
+}
+
+// the sum over each aligned group of 2^lg lanes (4 .. 64), in every lane of the
+// group, per component; lg is the same for the whole wavefront
+template <class T, int D>
+__device__ __forceinline__ void group_all_sum(T (&acc)[D], int lg) {
+#pragma unroll
+    for (int r = 0; r < D; ++r) {
+        acc[r] += dpp_get<0xB1>(acc[r]);    // quad_perm [1,0,3,2]
+        acc[r] += dpp_get<0x4E>(acc[r]);    // quad_perm [2,3,0,1]
+    }
+    if (lg >= 3)
+#pragma unroll
+        for (int r = 0; r < D; ++r) acc[r] += dpp_get<0x141>(acc[r]);   // row_half_mirror
+    if (lg >= 4)
+#pragma unroll
+        for (int r = 0; r < D; ++r) acc[r] += dpp_get<0x140>(acc[r]);   // row_mirror
+    if (lg >= 5)
+#pragma unroll
+        for (int r = 0; r < D; ++r) acc[r] += __shfl_xor(acc[r], 16, WAVE);
+    if (lg >= 6)
+#pragma unroll
+        for (int r = 0; r < D; ++r) acc[r] += __shfl_xor(acc[r], 32, WAVE);
+}
+
+// All colours of one block's Gauss-Seidel sub-solve in one launch (the
+// arithmetic of k_gs).  A colour pass on a coarse level is a few microseconds
+// of launch and dependent loads whatever its size, and one such pass per colour
+// was most of a small system's cycle.  Here the rows wait for their own
+// neighbours instead: a row of colour c reads t_j of its neighbours of earlier
+// colours with device-scope loads and repeats them until the values are there
+// ("unwritten" before).  The hop from one workgroup's store to another's load
+// is 0.5 us, against 4.0 - 5.0 us per launched colour pass.
+//
+// Every wait ends: a workgroup takes its positions of the record list by an
+// atomic ticket, the list is ordered by colour, and a position waits only for
+// positions of earlier colours, whose tickets were taken before by workgroups
+// that are already running.  The tickets are one counter (11 ns each), so a
+// workgroup takes SWEEP_WAVES slices per ticket.
+//
+// The two undamped buffers of a level take turns: a launch writes t and sets its
+// rows of the other buffer to "unwritten" for the next launch.
+template <class T, int D, bool ZX, bool CPL>
+__global__ __launch_bounds__(SWEEP_WAVES * WAVE) void k_sweep(SweepArgs<T> a) {
+    __shared__ int tick;
+    if (threadIdx.x == 0) {
+        const uint32_t k = __hip_atomic_fetch_add(a.ticket, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (k == 0) *a.ticket_next = 0u;
+        tick = (int)k;
+    }
+    __syncthreads();
+    const int pos = __builtin_amdgcn_readfirstlane(tick) * SWEEP_WAVES + wave_id();
+    if (pos >= a.count) return;   // whole wavefronts; no barrier follows
+    const SweepRec rec = load_rec(a.rec + a.begin + pos);
+    if (rec.nrow == 0) return;
+    const int lane = threadIdx.x & (WAVE - 1);
+    const int q = lane & ((1 << a.lg) - 1), rr = lane >> a.lg;
+    const bool act = rr < rec.nrow && q < D;   // lane q of a row's group finishes component q
+    const int row = rec.row0 + (rr < rec.nrow ? rr : 0);
+    const int64_t at = (int64_t)row * D + (q < D ? q : 0);
+    // the row's own data: fetched before the sums, whose latency it overlaps
+    T bb[D], dv[D], xo = T(0);
+    load_vec<T, D>(a.b + (int64_t)row * D, bb);
+    load_vec<T, D>(a.dinv + at * D, dv);
+    if (!ZX) xo = a.x[at];
+    const T wgt = a.w_row ? a.w_row[row] : a.omega;
+    T acc[D];
+#pragma unroll
+    for (int r = 0; r < D; ++r) acc[r] = T(0);
+    if (CPL) group_sub<T, D, 0>(a.cpl, rec.cpl_w, rec.cpl_c, lane, a.xg, nullptr, 0, acc);
+    const int cstart = a.inplace ? INT_MAX : rec.cstart;
+    if (ZX) {
+        if (cstart > 0) group_sub<T, D, 2>(a.off, rec.off_w, rec.off_c, lane, nullptr, a.t, cstart, acc);
+    } else {
+        group_sub<T, D, 1>(a.off, rec.off_w, rec.off_c, lane, a.x, a.t, cstart, acc);
+    }
+    group_all_sum<T, D>(acc, a.lg);
+    if (!act) return;
+    T tn = T(0);
+#pragma unroll
+    for (int c = 0; c < D; ++c) tn += dv[c] * (bb[c] + acc[c]);
+    const T xn = ZX ? wgt * tn : xo + wgt * (tn - xo);
+    a.xn[at] = xn;
+    if (a.t_reset) a.t_reset[at] = unwritten_value<T>();
+    if (unwritten(tn)) tn = T(NAN);
+    __hip_atomic_store(a.t + at, tn, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// r = b - A x (or w = A x when b is NULL) in grouped form, block 0's record
+// list, then block 1's
+template <class T, int D>
+__global__ __launch_bounds__(256) void k_resid_group(ResidGroupArgs<T> a, int padded_blocks) {
+    int pos = xcd_block(padded_blocks) * WPB + wave_id();
+    int f = 0;
+    if (pos >= a.count[0]) {
+        pos -= a.count[0];
+        f = 1;
+        if (pos >= a.count[1]) return;   // whole wavefront
+    }
+    const SweepRec rec = load_rec(a.rec[f] + pos);
+    if (rec.nrow == 0) return;
+    const int lane = threadIdx.x & (WAVE - 1), lg = a.lg[f];
+    const int q = lane & ((1 << lg) - 1), rr = lane >> lg;
+    const bool act = rr < rec.nrow && q < D;
+    const int row = rec.row0 + (rr < rec.nrow ? rr : 0);
+    const int64_t at = (int64_t)row * D + (q < D ? q : 0);
+    T dg[D], xr[D], bq = T(0);
+    load_vec<T, D>(a.diag[f] + at * D, dg);
+    load_vec<T, D>(a.x[f] + (int64_t)row * D, xr);
+    if (a.b[f]) bq = a.b[f][at];
+    T acc[D];
+#pragma unroll
+    for (int r = 0; r < D; ++r) acc[r] = T(0);
+    group_sub<T, D, 0>(a.off[f], rec.off_w, rec.off_c, lane, a.x[f], nullptr, 0, acc);
+    group_sub<T, D, 0>(a.cpl[f], rec.cpl_w, rec.cpl_c, lane, a.x[1 - f], nullptr, 0, acc);
+    group_all_sum<T, D>(acc, lg);
+    if (!act) return;
+    T own = T(0);
+#pragma unroll
+    for (int c = 0; c < D; ++c) own += dg[c] * xr[c];
+    T sum = T(0);
+#pragma unroll
+    for (int c = 0; c < D; ++c) sum = c == q ? acc[c] : sum;
+    const T ax = own - sum;
+    a.r[f][at] = a.b[f] ? bq - ax : ax;
+}
+
+template <class T, int D>
+static void sweep_dispatch(bool zx, bool cpl, const SweepArgs<T>& a, hipStream_t s) {
+    const unsigned grid = (unsigned)ceil_div(a.count, SWEEP_WAVES);
+    constexpr int TPB = SWEEP_WAVES * WAVE;
+    if (zx) {
+        if (cpl) k_sweep<T, D, true, true><<<grid, TPB, 0, s>>>(a);
+        else k_sweep<T, D, true, false><<<grid, TPB, 0, s>>>(a);
+    } else {
+        if (cpl) k_sweep<T, D, false, true><<<grid, TPB, 0, s>>>(a);
+        else k_sweep<T, D, false, false><<<grid, TPB, 0, s>>>(a);
+    }
+}
+
+template <class T>
+void launch_sweep(int d, bool zero_x, bool has_cpl, const SweepArgs<T>& a, hipStream_t s) {
+    if (a.count <= 0) return;
+    MB_CHECK(a.lg >= 2 && a.lg <= 6, MBAMG_E_INVALID, "4 to 64 lanes per row");
+    switch (d) {
+        case 1: sweep_dispatch<T, 1>(zero_x, has_cpl, a, s); break;
+        case 2: sweep_dispatch<T, 2>(zero_x, has_cpl, a, s); break;
+        case 3: sweep_dispatch<T, 3>(zero_x, has_cpl, a, s); break;
+        case 4: sweep_dispatch<T, 4>(zero_x, has_cpl, a, s); break;
+        default: throw Error(MBAMG_E_INVALID, "dofs per node must be 1..4");
+    }
+    MB_LAUNCH_CHECK();
+}
+template void launch_sweep<double>(int, bool, bool, const SweepArgs<double>&, hipStream_t);
+template void launch_sweep<float>(int, bool, bool, const SweepArgs<float>&, hipStream_t);
+
+template <class T>
+void launch_resid_group(int d, const ResidGroupArgs<T>& a, hipStream_t s) {
+    const int total = a.count[0] + a.count[1];
+    if (total <= 0) return;
+    MB_CHECK(a.lg[0] >= 2 && a.lg[0] <= 6 && a.lg[1] >= 2 && a.lg[1] <= 6, MBAMG_E_INVALID, "4 to 64 lanes per row");
+    const unsigned grid = xcd_grid(total, 1);
+    const int pb = (int)grid;
+    switch (d) {
+        case 1: k_resid_group<T, 1><<<grid, 256, 0, s>>>(a, pb); break;
+        case 2: k_resid_group<T, 2><<<grid, 256, 0, s>>>(a, pb); break;
+        case 3: k_resid_group<T, 3><<<grid, 256, 0, s>>>(a, pb); break;
+        case 4: k_resid_group<T, 4><<<grid, 256, 0, s>>>(a, pb); break;
+        default: throw Error(MBAMG_E_INVALID, "dofs per node must be 1..4");
+    }
+    MB_LAUNCH_CHECK();
+}
+template void launch_resid_group<double>(int, const ResidGroupArgs<double>&, hipStream_t);
+template void launch_resid_group<float>(int, const ResidGroupArgs<float>&, hipStream_t);
+
+// ---------------------------------------------------------------------------
+// Row form (transfers to small levels): one wavefront per row, its lanes over
+// the row's blocks, partial sums combined across the wavefront.
 // ---------------------------------------------------------------------------
 // a dense block of N values, with 16-byte loads where the size allows (blocks
 // are stored back to back, so a block of 4 or 16 entries is 16-byte aligned)
@@ -404,26 +706,18 @@ __device__ __forceinline__ void load_block(const T* __restrict__ p, T (&v)[N]) {
     }
 }
 
-template <class T, int D, int DG, int MODE, bool SKIP_DIAG>
-__device__ __forceinline__ void row_sub(const RowView<T>& A, int row, int lane, const T* __restrict__ xa,
-                                        const T* __restrict__ xb, int cstart, T (&acc)[D]) {
+template <class T, int D>
+__device__ __forceinline__ void row_sub(const RowView<T>& A, int row, int lane, const T* __restrict__ x, T (&acc)[D]) {
     const int e = A.rp[row + 1];
     for (int p = A.rp[row] + lane; p < e; p += WAVE) {
-        const int j = A.col[p];
-        if (SKIP_DIAG && j == row) continue;
-        const T* src;
-        if (MODE == 0) src = xa;
-        else if (MODE == 1) src = j < cstart ? xa : xb;
-        else src = j < cstart ? xa : nullptr;
-        if (!src) continue;
-        T xj[DG];
-        load_vec<T, DG>(src + (int64_t)j * DG, xj);
-        T blk[D * DG];
-        load_block<T, D * DG>(A.val + (int64_t)p * D * DG, blk);
+        T xj[D];
+        load_vec<T, D>(x + (int64_t)A.col[p] * D, xj);
+        T blk[D * D];
+        load_block<T, D * D>(A.val + (int64_t)p * D * D, blk);
 #pragma unroll
         for (int r = 0; r < D; ++r)
 #pragma unroll
-            for (int c = 0; c < DG; ++c) acc[r] -= blk[r * DG + c] * xj[c];
+            for (int c = 0; c < D; ++c) acc[r] -= blk[r * D + c] * xj[c];
     }
 }
 
@@ -432,10 +726,9 @@ __device__ __forceinline__ void row_sub(const RowView<T>& A, int row, int lane, 
 // half of a double one), so one load instruction covers 1 KiB with no gaps.
 // Every lane keeps one block-row position (the row's first block starts a
 // piece group), so its partial sum belongs to one component r.
-// With RP wavefronts on one row, wavefront `part` takes every RP-th pass.
-template <class T, int D, int MODE, bool SKIP_DIAG, int RP = 1>
-__device__ __forceinline__ void row_sub_c(const RowView<T>& A, int row, int lane, const T* __restrict__ xa,
-                                          const T* __restrict__ xb, int cstart, T (&acc)[D], int wpart = 0) {
+template <class T, int D>
+__device__ __forceinline__ void row_sub_c(const RowView<T>& A, int row, int lane, const T* __restrict__ x,
+                                          T (&acc)[D]) {
     constexpr int V = 16 / (int)sizeof(T);   // values per piece
     static_assert(D % V == 0, "block rows split into 16-byte pieces");
     constexpr int LR = D / V;                // pieces per block row
@@ -446,21 +739,16 @@ __device__ __forceinline__ void row_sub_c(const RowView<T>& A, int row, int lane
     const int r = part / LR, c0 = (part % LR) * V;
     const int64_t u0 = (int64_t)A.rp[row] * LB, u1 = (int64_t)A.rp[row + 1] * LB;
     T sum = T(0);
-    for (int64_t ub = u0 + (int64_t)wpart * WAVE; ub < u1; ub += UNROLL * RP * WAVE) {
+    for (int64_t ub = u0; ub < u1; ub += UNROLL * WAVE) {
         T av[UNROLL][V], xv[UNROLL][V];
         bool ok[UNROLL];
 #pragma unroll
         for (int h = 0; h < UNROLL; ++h) {
-            const int64_t u = ub + (int64_t)h * RP * WAVE + lane;
+            const int64_t u = ub + (int64_t)h * WAVE + lane;
             ok[h] = u < u1;
             const int64_t uc = ok[h] ? u : u0 + part;   // in range: the row's first block
-            const int j = A.col[uc / LB];
-            if (SKIP_DIAG && j == row) ok[h] = false;
-            const T* src = xa;
-            if (MODE == 1 && j >= cstart) src = xb;
-            if (MODE == 2 && j >= cstart) ok[h] = false;
             load_vec<T, V>(A.val + uc * V, av[h]);
-            load_vec<T, V>(src + (int64_t)j * D + c0, xv[h]);
+            load_vec<T, V>(x + (int64_t)A.col[uc / LB] * D + c0, xv[h]);
         }
 #pragma unroll
         for (int h = 0; h < UNROLL; ++h) {
@@ -481,125 +769,6 @@ __device__ __forceinline__ void wave_sum_vec(T (&acc)[D]) {
     for (int r = 0; r < D; ++r) acc[r] = group_sum<64>(acc[r]);
 }
 
-// Sum of the RP wavefronts' partial sums of one row (each valid in its lane
-// WAVE - 1), in wavefront order, left in wavefront 0's lane WAVE - 1.
-template <class T, int D, int RP>
-__device__ __forceinline__ void combine_row_parts(T (&acc)[D], int wpart, int lane) {
-    if constexpr (RP > 1) {
-        __shared__ T red[RP][D];
-        if (lane == WAVE - 1)
-#pragma unroll
-            for (int r = 0; r < D; ++r) red[wpart][r] = acc[r];
-        __syncthreads();
-        if (wpart == 0 && lane == WAVE - 1) {
-#pragma unroll
-            for (int r = 0; r < D; ++r) {
-                T v = red[0][r];
-#pragma unroll
-                for (int q = 1; q < RP; ++q) v += red[q][r];
-                acc[r] = v;
-            }
-        }
-    }
-}
-
-// One colour of the block row's Gauss-Seidel sub-solve (the arithmetic of k_gs).
-// RP = 1: one wavefront per row; RP = 4: the four wavefronts of a workgroup
-// share one long row (4 x 4 blocks only).
-template <class T, int D, bool ZX, bool CPL, int RP>
-__global__ __launch_bounds__(256) void k_gs_rows(GsRowArgs<T> a) {
-    static_assert(RP == 1 || (RP == WPB && D == 4), "rows shared by the workgroup's wavefronts: 4 x 4 blocks");
-    const int lane = threadIdx.x & (WAVE - 1);
-    const int wpart = RP > 1 ? wave_id() : 0;
-    const int w = RP > 1 ? (int)blockIdx.x : (int)blockIdx.x * WPB + wave_id();
-    if (w >= a.r_count) return;   // whole wavefronts (the whole workgroup when RP > 1)
-    const int row = a.r_begin + w;
-    // the row's own data first: its latency overlaps the row sums'
-    T bb[D], dv[D * D], xo[D];
-    if (wpart == 0) {
-        load_vec<T, D>(a.b + (int64_t)row * D, bb);
-        load_block<T, D * D>(a.dinv + (int64_t)row * D * D, dv);
-        if (!ZX) load_vec<T, D>(a.x + (int64_t)row * D, xo);
-    }
-    const T wgt = a.w_row ? a.w_row[row] : a.omega;
-    T acc[D];
-#pragma unroll
-    for (int r = 0; r < D; ++r) acc[r] = T(0);
-    if constexpr (D == 4) {
-        if (!a.skip_off) {
-            if (ZX) row_sub_c<T, D, 2, true, RP>(a.aff, row, lane, a.t, nullptr, a.cstart, acc, wpart);
-            else row_sub_c<T, D, 1, true, RP>(a.aff, row, lane, a.t, a.x, a.cstart, acc, wpart);
-        }
-        if (CPL) row_sub_c<T, D, 0, false, RP>(a.afg, row, lane, a.xg, nullptr, 0, acc, wpart);
-    } else {
-        if (!a.skip_off) {
-            if (ZX) row_sub<T, D, D, 2, true>(a.aff, row, lane, a.t, nullptr, a.cstart, acc);
-            else row_sub<T, D, D, 1, true>(a.aff, row, lane, a.t, a.x, a.cstart, acc);
-        }
-        if (CPL) row_sub<T, D, D, 0, false>(a.afg, row, lane, a.xg, nullptr, 0, acc);
-    }
-    wave_sum_vec<T, D>(acc);
-    combine_row_parts<T, D, RP>(acc, wpart, lane);
-    if (wpart != 0 || lane != WAVE - 1) return;
-#pragma unroll
-    for (int r = 0; r < D; ++r) acc[r] += bb[r];
-    T tn[D];
-#pragma unroll
-    for (int r = 0; r < D; ++r) {
-        T sum = T(0);
-#pragma unroll
-        for (int c = 0; c < D; ++c) sum += dv[r * D + c] * acc[c];
-        tn[r] = sum;
-    }
-    T xn[D];
-    if (ZX) {
-#pragma unroll
-        for (int r = 0; r < D; ++r) xn[r] = wgt * tn[r];
-    } else {
-#pragma unroll
-        for (int r = 0; r < D; ++r) xn[r] = xo[r] + wgt * (tn[r] - xo[r]);
-    }
-    store_vec<T, D>(a.t + (int64_t)row * D, tn);
-    store_vec<T, D>(a.xn + (int64_t)row * D, xn);
-}
-
-// r = b - A x (or w = A x when b is NULL), rows of block 0 then block 1
-template <class T, int D>
-__global__ __launch_bounds__(256) void k_resid_rows(ResidRowArgs<T> a) {
-    const int lane = threadIdx.x & (WAVE - 1);
-    int row = blockIdx.x * WPB + wave_id();
-    int f = 0;
-    if (row >= a.n[0]) {
-        row -= a.n[0];
-        f = 1;
-        if (row >= a.n[1]) return;   // whole wavefront
-    }
-    const int g = 1 - f;
-    T bb[D];   // fetched first: its latency overlaps the row sums'
-    if (a.b[f]) load_vec<T, D>(a.b[f] + (int64_t)row * D, bb);
-    T acc[D];
-#pragma unroll
-    for (int r = 0; r < D; ++r) acc[r] = T(0);
-    if constexpr (D == 4) {
-        row_sub_c<T, D, 0, false>(a.aff[f], row, lane, a.x[f], nullptr, 0, acc);
-        row_sub_c<T, D, 0, false>(a.afg[f], row, lane, a.x[g], nullptr, 0, acc);
-    } else {
-        row_sub<T, D, D, 0, false>(a.aff[f], row, lane, a.x[f], nullptr, 0, acc);
-        row_sub<T, D, D, 0, false>(a.afg[f], row, lane, a.x[g], nullptr, 0, acc);
-    }
-    wave_sum_vec<T, D>(acc);
-    if (lane != WAVE - 1) return;
-    T out[D];
-    if (a.b[f]) {
-#pragma unroll
-        for (int r = 0; r < D; ++r) out[r] = bb[r] + acc[r];
-    } else {
-#pragma unroll
-        for (int r = 0; r < D; ++r) out[r] = -acc[r];
-    }
-    store_vec<T, D>(a.r[f] + (int64_t)row * D, out);
-}
-
 // y = A x (or y += A x when accumulating) for a transfer in row form: one
 // wavefront per row, the row's blocks read as in the row-form smoother.
 template <class T, int D>
@@ -615,8 +784,8 @@ __global__ __launch_bounds__(256) void k_xfer_rows(XferRowArgs<T> a) {
     T acc[D];
 #pragma unroll
     for (int r = 0; r < D; ++r) acc[r] = T(0);
-    if constexpr (D == 4) row_sub_c<T, D, 0, false>(a.A[f], row, lane, a.x[f], nullptr, 0, acc);
-    else row_sub<T, D, D, 0, false>(a.A[f], row, lane, a.x[f], nullptr, 0, acc);
+    if constexpr (D == 4) row_sub_c<T, D>(a.A[f], row, lane, a.x[f], acc);
+    else row_sub<T, D>(a.A[f], row, lane, a.x[f], acc);
     wave_sum_vec<T, D>(acc);
     if (lane != WAVE - 1) return;
     const int orow = a.out_row[f] ? a.out_row[f][row] : row;
@@ -925,54 +1094,6 @@ void launch_gs_fc(int d, int P, bool zero_x, const GsFcArgs<T>& a, hipStream_t s
     }
     MB_LAUNCH_CHECK();
 }
-
-template <class T, int D, int RP>
-static void gs_rows_dispatch(bool zx, bool cpl, const GsRowArgs<T>& a, hipStream_t s) {
-    const unsigned grid = (unsigned)ceil_div(a.r_count, WPB / RP);
-    if (zx) {
-        if (cpl) k_gs_rows<T, D, true, true, RP><<<grid, 256, 0, s>>>(a);
-        else k_gs_rows<T, D, true, false, RP><<<grid, 256, 0, s>>>(a);
-    } else {
-        if (cpl) k_gs_rows<T, D, false, true, RP><<<grid, 256, 0, s>>>(a);
-        else k_gs_rows<T, D, false, false, RP><<<grid, 256, 0, s>>>(a);
-    }
-}
-
-template <class T>
-void launch_gs_rows(int d, int rp, bool zero_x, bool has_cpl, const GsRowArgs<T>& a, hipStream_t s) {
-    if (a.r_count <= 0) return;
-    MB_CHECK(rp == 1 || (rp == WPB && d == 4), MBAMG_E_INVALID, "row split must be 1, or 4 with 4 x 4 blocks");
-    switch (d) {
-        case 1: gs_rows_dispatch<T, 1, 1>(zero_x, has_cpl, a, s); break;
-        case 2: gs_rows_dispatch<T, 2, 1>(zero_x, has_cpl, a, s); break;
-        case 3: gs_rows_dispatch<T, 3, 1>(zero_x, has_cpl, a, s); break;
-        case 4:
-            if (rp == WPB) gs_rows_dispatch<T, 4, WPB>(zero_x, has_cpl, a, s);
-            else gs_rows_dispatch<T, 4, 1>(zero_x, has_cpl, a, s);
-            break;
-        default: throw Error(MBAMG_E_INVALID, "dofs per node must be 1..4");
-    }
-    MB_LAUNCH_CHECK();
-}
-template void launch_gs_rows<double>(int, int, bool, bool, const GsRowArgs<double>&, hipStream_t);
-template void launch_gs_rows<float>(int, int, bool, bool, const GsRowArgs<float>&, hipStream_t);
-
-template <class T>
-void launch_resid_rows(int d, const ResidRowArgs<T>& a, hipStream_t s) {
-    const int total = a.n[0] + a.n[1];
-    if (total <= 0) return;
-    const unsigned grid = (unsigned)ceil_div(total, WPB);
-    switch (d) {
-        case 1: k_resid_rows<T, 1><<<grid, 256, 0, s>>>(a); break;
-        case 2: k_resid_rows<T, 2><<<grid, 256, 0, s>>>(a); break;
-        case 3: k_resid_rows<T, 3><<<grid, 256, 0, s>>>(a); break;
-        case 4: k_resid_rows<T, 4><<<grid, 256, 0, s>>>(a); break;
-        default: throw Error(MBAMG_E_INVALID, "dofs per node must be 1..4");
-    }
-    MB_LAUNCH_CHECK();
-}
-template void launch_resid_rows<double>(int, const ResidRowArgs<double>&, hipStream_t);
-template void launch_resid_rows<float>(int, const ResidRowArgs<float>&, hipStream_t);
 
 template <class T, int D>
 static void resid_dispatch(int P, const ResidArgs<T>& a, hipStream_t s) {
