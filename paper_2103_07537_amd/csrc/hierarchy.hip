@@ -158,12 +158,10 @@ struct Level {
 
 // Systems of more than two blocks (eq. block-prec-form), co-located fields:
 // the aggregates of A_00 are cloned to every block, and Algorithm 1 runs over
-// the blocks in order with each block's couplings folded into its right-hand
-// side.  Every block keeps its own colour order and sliced smoother parts
-// (A_ff without its diagonal, nodal inverses); every block A_fg is also held
-// in row form (rows in block f's colour order, columns in block g's) for the
-// couplings, the residual and the operator.
-constexpr int MAXB = 4;
+// the blocks in order.  Every block row keeps its own colour order and the grouped form (lanes per
+// row >= 4) on every level: A_ff without its diagonal, the diagonal blocks, the
+// nodal inverses and every coupling block A_fg on block f's slices.
+constexpr int MAXB = SWEEP_MAX_BLOCKS;
 struct GLevel {
     int n = 0, nb = 0;
     int d[MAXB] = {0, 0, 0, 0};
@@ -172,8 +170,8 @@ struct GLevel {
     SetupBsr A[MAXB][MAXB];
     Aggregates G;
     BlockLevel blk[MAXB];
-    RowPart R[MAXB][MAXB];
-    DevBuf<double> b, x, xs, t, r, rhs;
+    SellPart C[MAXB][MAXB];                    // A_fg, g != f
+    Vecs<double> v;
     void set_blocks(int nodes, int nblocks, const int* dofs) {
         n = nodes;
         nb = nblocks;
@@ -573,14 +571,7 @@ enum class PartKind { Off = 0, Cpl = 1, Diag = 2, Dinv = 3 };
 // 54 us, 8 lanes 76 us).
 constexpr int GROUP_FINEST_MAX = 65536;
 constexpr int64_t GROUP_WAVES_MAX = 16384;
-static int choose_group(const mbamg_params& p, int lvl, int n_level, int n, int64_t blocks) {
-    if (p.smoother == 1) return 1;   // the full-node kernel reads the sliced parts
-    bool grouped = lvl > 0 || n_level <= GROUP_FINEST_MAX;
-    // MBAMG_ROWS_FORM (tests): "rows" forces the grouped form on every coarse level, anything
-    // else the sliced one on every level; MBAMG_SLICE_SPLIT the sliced one on the finest level
-    if (const char* fo = form_override("MBAMG_ROWS_FORM")) grouped = lvl > 0 && std::strcmp(fo, "rows") == 0;
-    if (lvl == 0 && form_override("MBAMG_SLICE_SPLIT")) grouped = false;
-    if (!grouped) return 1;
+static int group_lanes(int n, int64_t blocks) {
     const double len = n ? (double)blocks / n : 1.0;
     int g = 4;
     while (g < 64 && len - 1.0 > g) g *= 2;
@@ -591,6 +582,16 @@ static int choose_group(const mbamg_params& p, int lvl, int n_level, int n, int6
                  "MBAMG_SWEEP_GROUP must be 4, 8, 16, 32 or 64");
     }
     return g;
+}
+
+static int choose_group(const mbamg_params& p, int lvl, int n_level, int n, int64_t blocks) {
+    if (p.smoother == 1) return 1;   // the full-node kernel reads the sliced parts
+    bool grouped = lvl > 0 || n_level <= GROUP_FINEST_MAX;
+    // MBAMG_ROWS_FORM (tests): "rows" forces the grouped form on every coarse level, anything
+    // else the sliced one on every level; MBAMG_SLICE_SPLIT the sliced one on the finest level
+    if (const char* fo = form_override("MBAMG_ROWS_FORM")) grouped = lvl > 0 && std::strcmp(fo, "rows") == 0;
+    if (lvl == 0 && form_override("MBAMG_SLICE_SPLIT")) grouped = false;
+    return grouped ? group_lanes(n, blocks) : 1;
 }
 
 // Waves per slice (1..16) for a launch over `slices` slices of `width` slots
@@ -739,11 +740,12 @@ static void alloc_vecs(Vecs<T>& v, int64_t n, bool grouped, hipStream_t s) {
 // The launch records of a grouped block row, once its parts are built.
 static void build_recs(BlockLevel& B, hipStream_t s) {
     MB_CHECK(B.off.n_slots < INT_MAX && B.cpl.n_slots < INT_MAX, MBAMG_E_INVALID, "too many slots in a grouped part");
+
     DevBuf<int32_t> order;
     order.upload(B.h_order, s);
     B.recs.alloc(std::max<size_t>(B.h_order.size(), 1));
     sweep_recs((int)B.h_order.size(), order.p, B.row0.p, B.nrow.p, B.cstart.p, B.off.width.p, B.off.coff.p,
-               B.cpl.width.p, B.cpl.coff.p, B.recs.p, s);
+               B.cpl.width.p, B.cpl.coff.p, B.recs.p, s);   // (cpl NULL: a block among more than two)
     MB_HIP(hipStreamSynchronize(s));   // order is released on return
 }
 
@@ -2053,7 +2055,8 @@ static void gen_setup_impl(mbamg_hierarchy* h, const mbamg_bsr* Ab, hipStream_t 
             B.d = Lv.d[f];
             if (Lv.coarsest) {
                 B.colour.assign(Lv.n, 0);
-                order_and_slice(B, Lv.n, 1);
+                // (a one-level hierarchy's operator and couplings read the grouped parts too)
+                order_and_slice(B, Lv.n, 1, nullptr, group_lanes(Lv.n, Lv.A[f][f].nnzb));
             } else {
                 const std::vector<int32_t> rp = Lv.A[f][f].rp.download(s, (size_t)Lv.n + 1);
                 const std::vector<int32_t> ci = Lv.A[f][f].ci.download(s, (size_t)Lv.A[f][f].nnzb);
@@ -2061,37 +2064,38 @@ static void gen_setup_impl(mbamg_hierarchy* h, const mbamg_bsr* Ab, hipStream_t 
                 const bool asym = transpose_pattern(Lv.n, rp.data(), ci.data(), trp, tci);
                 const int ncol = asym ? greedy_colour(Lv.n, rp.data(), ci.data(), B.colour, trp.data(), tci.data())
                                       : greedy_colour(Lv.n, rp.data(), ci.data(), B.colour);
-                order_and_slice(B, Lv.n, ncol, rp.data());
+                order_and_slice(B, Lv.n, ncol, rp.data(), group_lanes(Lv.n, Lv.A[f][f].nnzb));
             }
             B.row0.upload(B.h_row0, s);
             B.nrow.upload(B.h_nrow, s);
             B.d_perm.upload(B.perm, s);
             B.d_iperm.upload(B.iperm, s);
         }
-        for (int f = 0; f < nb; ++f)
+        // the coarsest level's vectors serve the dense solve; its operator is only applied when it
+        // is the only level
+        const bool parts = !Lv.coarsest || h->GL.size() == 1;
+        for (int f = 0; f < nb && parts; ++f) {
+            BlockLevel& B = Lv.blk[f];
+            const int df = Lv.d[f];
+            B.cstart.upload(B.h_cstart, s);
+            build_part(B.off, PartKind::Off, B, &Lv.A[f][f], B.d_iperm.p, Lv.A[f][f].val.p, df, df, false, s);
             for (int g = 0; g < nb; ++g)
-                build_rows(Lv.R[f][g], Lv.n, Lv.blk[f].d_perm.p, Lv.A[f][g], Lv.blk[g].d_iperm.p, false, s);
-        if (!Lv.coarsest) {
-            for (int f = 0; f < nb; ++f) {
-                BlockLevel& B = Lv.blk[f];
-                const int df = Lv.d[f];
-                DevBuf<double> dinv((size_t)Lv.n * df * df);
+                if (g != f && Lv.A[f][g].nnzb > 0)
+                    build_part(Lv.C[f][g], PartKind::Cpl, B, &Lv.A[f][g], Lv.blk[g].d_iperm.p, Lv.A[f][g].val.p, df,
+                               Lv.d[g], false, s);
+            build_recs(B, s);
+            const int64_t nd = (int64_t)Lv.n * df * df;
+            DevBuf<double> dinv((size_t)nd);
+            B.gdiag64.alloc(nd);
+            gather_diag(Lv.n, B.d_perm.p, Lv.A[f][f], B.gdiag64.p, s);
+            if (!Lv.coarsest) {
                 build_dinv(Lv.A[f][f], dinv.p, s);
-                build_part(B.off, PartKind::Off, B, &Lv.A[f][f], B.d_iperm.p, Lv.A[f][f].val.p, df, df, false, s);
-                build_part(B.dinv, PartKind::Dinv, B, nullptr, nullptr, dinv.p, df, df, false, s);
-                int64_t slots = 0;
-                for (int sl = 0; sl < B.n_slices; ++sl) slots += B.off.h_width[sl];
-                const double avg_width = B.n_slices ? (double)slots / B.n_slices : 0.0;
-                B.split = slot_split((double)B.n_slices / std::max(1, B.n_colours), avg_width);
+                B.gdinv64.alloc(nd);
+                gather_blocks(Lv.n, df * df, B.d_perm.p, dinv.p, B.gdinv64.p, s);
             }
+            MB_HIP(hipStreamSynchronize(s));   // dinv is released here
         }
-        const int64_t nd = std::max<int64_t>(Lv.ndof(), 1);
-        Lv.b.alloc(nd);
-        Lv.x.alloc(nd);
-        Lv.xs.alloc(nd);
-        Lv.t.alloc(nd);
-        Lv.r.alloc(nd);
-        Lv.rhs.alloc(nd);
+        alloc_vecs(Lv.v, std::max<int64_t>(Lv.ndof(), 1), !Lv.coarsest, s);
         MB_HIP(hipStreamSynchronize(s));
     }
     // transfers between each level's and the next level's colour orders
@@ -2139,26 +2143,44 @@ static void gen_setup_impl(mbamg_hierarchy* h, const mbamg_bsr* Ab, hipStream_t 
     h->info.t_setup_ms = h->t_setup_ms;
 }
 
-static RowView<double> grview(const RowPart& R) { return {R.rp.p, R.col.p, R.v64.p}; }
-
-// y_f = b_f - sum over blocks g of A_fg x_g (b NULL: y = sum A_fg x_g); xs[g] NULL skips block g
-static void gen_block_rows(const GLevel& Lv, int f, const double* b, const double* const* xs, double* y, bool skip_f,
-                           hipStream_t s) {
-    const int64_t len = (int64_t)Lv.n * Lv.d[f];
-    if (b) MB_HIP(hipMemcpyAsync(y, b, sizeof(double) * len, hipMemcpyDeviceToDevice, s));
-    else fill_value(y, len, 0.0, s);
-    for (int g = 0; g < Lv.nb; ++g) {
-        if ((skip_f && g == f) || !xs[g] || Lv.R[f][g].nnzb == 0) continue;
-        launch_rows_acc<double>(Lv.n, Lv.d[f], Lv.d[g], grview(Lv.R[f][g]), xs[g], y, b ? -1.0 : 1.0, s);
-    }
+static GroupPart group_part(const SellPart& P, const double* x) {
+    return {gview<double>(P), P.width.p, P.coff.p, x, P.bc};
 }
 
 // w = A x (b NULL) or r = b - A x on level l (colour order, all blocks)
 static void gen_resid(mbamg_hierarchy* h, int l, const double* b, const double* x, double* r, hipStream_t s) {
     GLevel& Lv = *h->GL[l];
-    const double* xs[MAXB];
-    for (int g = 0; g < Lv.nb; ++g) xs[g] = x + Lv.off[g];
-    for (int f = 0; f < Lv.nb; ++f) gen_block_rows(Lv, f, b ? b + Lv.off[f] : nullptr, xs, r + Lv.off[f], false, s);
+    ResidNArgs a{};
+    a.nb = Lv.nb;
+    for (int f = 0; f < Lv.nb; ++f) {
+        const BlockLevel& B = Lv.blk[f];
+        a.count[f] = B.colour_rec.back();
+        a.rec[f] = B.recs.p;
+        a.lg[f] = log2_of(B.group);
+        a.d[f] = Lv.d[f];
+        a.off[f] = gview<double>(B.off);
+        a.diag[f] = B.gdiag64.p;
+        for (int g = 0; g < Lv.nb; ++g)
+            if (g != f && Lv.A[f][g].nnzb > 0) a.cpl[f][a.n_cpl[f]++] = group_part(Lv.C[f][g], x + Lv.off[g]);
+        a.b[f] = b ? b + Lv.off[f] : nullptr;
+        a.x[f] = x + Lv.off[f];
+        a.r[f] = r + Lv.off[f];
+    }
+    launch_resid_n(a, s);
+}
+
+// Two blocks with the same dofs per node share a transfer launch: fn(f, g), g < 0
+// for a block on its own.
+template <class Fn>
+static void pair_blocks(const GLevel& Lv, Fn&& fn) {
+    bool done[MAXB] = {};
+    for (int f = 0; f < Lv.nb; ++f) {
+        if (done[f]) continue;
+        int g = f + 1;
+        while (g < Lv.nb && (done[g] || Lv.d[g] != Lv.d[f])) ++g;
+        if (g < Lv.nb) done[g] = true;
+        fn(f, g < Lv.nb ? g : -1);
+    }
 }
 
 // One V-cycle on level l from a zero guess (the MGV figure of Sec. 3) with
@@ -2169,71 +2191,91 @@ static void gen_vcycle_level(mbamg_hierarchy* h, int l, const double* b, double*
         launch_coarse<double>(h->coarse_n, h->coarse_inv.p, b, out, s);
         return;
     }
+    Vecs<double>& V = Lv.v;
+    if (V.busy) reset_sweeps(V, s);
+    V.busy = true;
     const int nb = Lv.nb;
     const int writes = 2 * h->p.bgs_sweeps;
     double* buf[2];
-    buf[0] = (writes % 2 == 0) ? Lv.xs.p : out;
-    buf[1] = (writes % 2 == 0) ? out : Lv.xs.p;
+    buf[0] = (writes % 2 == 0) ? V.xs.p : out;
+    buf[1] = (writes % 2 == 0) ? out : V.xs.p;
     int cur = -1;
     auto sweep = [&](bool zero) {
         const int nx = cur < 0 ? 0 : 1 - cur;
         const double* X = cur < 0 ? nullptr : buf[cur];
         double* XN = buf[nx];
         for (int f = 0; f < nb; ++f) {
-            // the couplings of block f with the blocks before it (already relaxed in this sweep)
-            // and after it (the incoming iterate) go into its right-hand side
-            const double* xs[MAXB];
-            for (int g = 0; g < nb; ++g) xs[g] = g < f ? XN + Lv.off[g] : (X ? X + Lv.off[g] : nullptr);
-            double* rhs = Lv.rhs.p + Lv.off[f];
-            gen_block_rows(Lv, f, b + Lv.off[f], xs, rhs, true, s);
             BlockLevel& B = Lv.blk[f];
-            for (int k = 0; k < h->p.inner_sweeps; ++k)
-                for (int c = 0; c < B.n_colours; ++c) {
-                    GsArgs<double> a{};
-                    a.s_begin = B.colour_slice[c];
-                    a.s_count = B.colour_slice[c + 1] - B.colour_slice[c];
-                    a.sl = B.slices();
-                    a.off = B.off.view<double>();
-                    a.dinv = B.dinv.view<double>();
-                    a.b = rhs;
-                    a.x = X ? X + Lv.off[f] : nullptr;
-                    a.t = Lv.t.p + Lv.off[f];
-                    a.xn = XN + Lv.off[f];
-                    a.xg = nullptr;
-                    a.cstart = k == 0 ? B.colour_row[c] : INT_MAX;
-                    a.omega = h->p.omega;
-                    a.w_row = nullptr;
-                    a.skip_off = (zero && k == 0 && c == 0) ? 1 : 0;
-                    launch_gs<double>(B.d, B.split, zero, false, a, s);
+            double* const t[2] = {V.t.p + Lv.off[f], V.t2.p + Lv.off[f]};
+            SweepNArgs a{};
+            // the couplings with the blocks before f (already relaxed in this sweep) and after it
+            // (the incoming iterate)
+            for (int g = 0; g < nb; ++g) {
+                const double* xg = g < f ? XN + Lv.off[g] : (X ? X + Lv.off[g] : nullptr);
+                if (g != f && xg && Lv.A[f][g].nnzb > 0) a.cpl[a.n_cpl++] = group_part(Lv.C[f][g], xg);
+            }
+            a.s.rec = B.recs.p;
+            a.s.lg = log2_of(B.group);
+            a.s.off = gview<double>(B.off);
+            a.s.dinv = B.gdinv64.p;
+            a.s.b = b + Lv.off[f];
+            a.s.x = X ? X + Lv.off[f] : nullptr;
+            a.s.t = t[V.turn_t];
+            a.s.xn = XN + Lv.off[f];
+            a.s.omega = h->p.omega;
+            for (int k = 0; k < h->p.inner_sweeps; ++k) {
+                const int step = k > 0 ? 1 : std::max(1, B.n_colours);
+                a.s.inplace = k > 0;
+                a.s.t_reset = k == 0 ? t[1 - V.turn_t] : nullptr;
+                for (int c = 0; c < B.n_colours; c += step) {
+                    a.s.begin = B.colour_rec[c];
+                    a.s.count = B.colour_rec[c + step] - a.s.begin;
+                    a.s.ticket = V.tickets.p + V.turn_ticket;
+                    a.s.ticket_next = V.tickets.p + (1 - V.turn_ticket);
+                    if (a.s.count == 0) continue;
+                    launch_sweep_n(B.d, zero, a, s);
+                    V.turn_ticket = 1 - V.turn_ticket;
                 }
+            }
         }
+        V.turn_t = 1 - V.turn_t;
         cur = nx;
     };
     for (int k = 0; k < h->p.bgs_sweeps; ++k) sweep(k == 0);
-    gen_resid(h, l, b, buf[cur], Lv.r.p, s);
+    gen_resid(h, l, b, buf[cur], V.r.p, s);
     GLevel& Nx = *h->GL[l + 1];
-    for (int f = 0; f < nb; ++f) {   // restriction, one block at a time (its own block size)
+    pair_blocks(Lv, [&](int f0, int f1) {   // restriction
         TransferArgs<double> a{};
-        a.n_rows[0] = Nx.n;
-        a.map[0] = Lv.blk[f].mem_ptr.p;
-        a.idx[0] = Lv.blk[f].mem_idx.p;
-        a.q[0] = Lv.blk[f].qm64.p;
-        a.in[0] = Lv.r.p + Lv.off[f];
-        a.out[0] = Nx.b.p + Nx.off[f];
-        launch_restrict<double>(Lv.d[f], a, Lv.blk[f].res_group, s);
-    }
-    gen_vcycle_level(h, l + 1, Nx.b.p, Nx.x.p, s);
-    for (int f = 0; f < nb; ++f) {   // prolongation
+        for (int k = 0; k < 2; ++k) {
+            const int f = k == 0 ? f0 : f1;
+            if (f < 0) continue;
+            a.n_rows[k] = Nx.n;
+            a.map[k] = Lv.blk[f].mem_ptr.p;
+            a.idx[k] = Lv.blk[f].mem_idx.p;
+            a.q[k] = Lv.blk[f].qm64.p;
+            a.in[k] = V.r.p + Lv.off[f];
+            a.out[k] = Nx.v.b.p + Nx.off[f];
+        }
+        launch_restrict<double>(Lv.d[f0], a, Lv.blk[f0].res_group, s);
+    });
+    gen_vcycle_level(h, l + 1, Nx.v.b.p, Nx.v.x.p, s);
+    pair_blocks(Lv, [&](int f0, int f1) {   // prolongation
         TransferArgs<double> a{};
-        a.n_rows[0] = Lv.n;
-        a.map[0] = Lv.blk[f].agg_p.p;
-        a.q[0] = Lv.blk[f].q64.p;
-        a.in[0] = Nx.x.p + Nx.off[f];
-        a.out[0] = buf[cur] + Lv.off[f];
-        launch_prolong<double>(Lv.d[f], a, s);
-    }
+        for (int k = 0; k < 2; ++k) {
+            const int f = k == 0 ? f0 : f1;
+            if (f < 0) continue;
+            a.n_rows[k] = Lv.n;
+            a.map[k] = Lv.blk[f].agg_p.p;
+            a.q[k] = Lv.blk[f].q64.p;
+            a.in[k] = Nx.v.x.p + Nx.off[f];
+            a.out[k] = buf[cur] + Lv.off[f];
+        }
+        launch_prolong<double>(Lv.d[f0], a, s);
+    });
     for (int k = 0; k < h->p.bgs_sweeps; ++k) sweep(false);
     MB_CHECK(buf[cur] == out, MBAMG_E_STATE, "internal: V-cycle result not in the output buffer");
+    MB_CHECK(V.turn_t == 0 && V.turn_ticket == 0, MBAMG_E_STATE, "internal: sweep buffers out of turn");
+    V.busy = false;
 }
 
 // z = M^-1 v for FP64 colour-order vectors of the finest level (either form).

@@ -2544,8 +2544,9 @@ __global__ void k_sweep_recs(int n, const int32_t* order, const int32_t* row0, c
         r.cstart = cstart[sl];
         r.off_w = ow[sl];
         r.off_c = (int32_t)oc[sl];
-        r.cpl_w = cw[sl];
-        r.cpl_c = (int32_t)cc[sl];
+        r.cpl_w = cw ? cw[sl] : 0;
+        r.cpl_c = cc ? (int32_t)cc[sl] : 0;
+        r.slice = sl;
     }
     out[i] = r;
 }

@@ -81,8 +81,8 @@ struct SweepRec {
     int32_t row0, nrow;        // nrow == 0: a launch position with nothing to do
     int32_t cstart;            // first row of the slice's colour
     int32_t off_w, off_c;      // A_ff without its diagonal: slots, first slot
-    int32_t cpl_w, cpl_c;      // A_fg: the same
-    int32_t pad;
+    int32_t cpl_w, cpl_c;      // A_fg: the same (two-block systems)
+    int32_t slice;
 };
 
 // Slots of a grouped part (see k_sweep): like SellView, but a slice has 64 / G
@@ -115,6 +115,36 @@ struct SweepArgs {
     const T* w_row;            // per-row damping (NULL: use omega)
     uint32_t* ticket;          // zero at launch
     uint32_t* ticket_next;     // set to zero for the next launch
+};
+
+// More than two blocks: one coupling block A_fg (any shape up to 4 x 4) in
+// grouped form on block f's slices, and the vector it multiplies.
+constexpr int SWEEP_MAX_BLOCKS = 4;
+struct GroupPart {
+    GroupView<double> a;
+    const int32_t* width;      // per slice
+    const int64_t* coff;       // per slice
+    const double* x;
+    int bc;
+};
+struct SweepNArgs {
+    SweepArgs<double> s;       // s.cpl and s.xg unused
+    int n_cpl;
+    GroupPart cpl[SWEEP_MAX_BLOCKS - 1];
+};
+// r_f = b_f - sum_g A_fg x_g (b NULL: w_f = sum_g A_fg x_g) for every block f
+struct ResidNArgs {
+    int nb;
+    int count[SWEEP_MAX_BLOCKS];           // launch positions of block f
+    const SweepRec* rec[SWEEP_MAX_BLOCKS];
+    int lg[SWEEP_MAX_BLOCKS], d[SWEEP_MAX_BLOCKS];
+    GroupView<double> off[SWEEP_MAX_BLOCKS];
+    const double* diag[SWEEP_MAX_BLOCKS];
+    int n_cpl[SWEEP_MAX_BLOCKS];
+    GroupPart cpl[SWEEP_MAX_BLOCKS][SWEEP_MAX_BLOCKS - 1];
+    const double* b[SWEEP_MAX_BLOCKS];
+    const double* x[SWEEP_MAX_BLOCKS];
+    double* r[SWEEP_MAX_BLOCKS];
 };
 
 template <class T>
@@ -195,9 +225,8 @@ template <class T>
 void launch_sweep(int d, bool zero_x, bool has_cpl, const SweepArgs<T>& a, hipStream_t s);
 template <class T>
 void launch_resid_group(int d, const ResidGroupArgs<T>& a, hipStream_t s);
-// y += sign * A x for one block in row form, any block shape up to 4 x 4 (one thread per row)
-template <class T>
-void launch_rows_acc(int n, int br, int bc, const RowView<T>& A, const T* x, T* y, T sign, hipStream_t s);
+void launch_sweep_n(int d, bool zero_x, const SweepNArgs& a, hipStream_t s);
+void launch_resid_n(const ResidNArgs& a, hipStream_t s);
 
 template <class T>
 // G: lanes per coarse row (4, 8, 16 or 64)

@@ -547,8 +547,9 @@ __device__ __forceinline__ void group_all_sum(T (&acc)[D], int lg) {
 //
 // The two undamped buffers of a level take turns: a launch writes t and sets its
 // rows of the other buffer to "unwritten" for the next launch.
-template <class T, int D, bool ZX, bool CPL>
-__global__ __launch_bounds__(SWEEP_WAVES * WAVE) void k_sweep(SweepArgs<T> a) {
+// This wavefront's position of the launch (all of a workgroup call it).
+template <class T>
+__device__ __forceinline__ int sweep_position(const SweepArgs<T>& a) {
     __shared__ int tick;
     if (threadIdx.x == 0) {
         const uint32_t k = __hip_atomic_fetch_add(a.ticket, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -556,11 +557,12 @@ __global__ __launch_bounds__(SWEEP_WAVES * WAVE) void k_sweep(SweepArgs<T> a) {
         tick = (int)k;
     }
     __syncthreads();
-    const int pos = __builtin_amdgcn_readfirstlane(tick) * SWEEP_WAVES + wave_id();
-    if (pos >= a.count) return;   // whole wavefronts; no barrier follows
-    const SweepRec rec = load_rec(a.rec + a.begin + pos);
-    if (rec.nrow == 0) return;
-    const int lane = threadIdx.x & (WAVE - 1);
+    return __builtin_amdgcn_readfirstlane(tick) * SWEEP_WAVES + wave_id();
+}
+
+// One slice of a sweep; couplings(acc) subtracts the coupling terms.
+template <class T, int D, bool ZX, class Cpl>
+__device__ __forceinline__ void sweep_slice(const SweepArgs<T>& a, const SweepRec& rec, int lane, Cpl&& couplings) {
     const int q = lane & ((1 << a.lg) - 1), rr = lane >> a.lg;
     const bool act = rr < rec.nrow && q < D;   // lane q of a row's group finishes component q
     const int row = rec.row0 + (rr < rec.nrow ? rr : 0);
@@ -574,7 +576,7 @@ __global__ __launch_bounds__(SWEEP_WAVES * WAVE) void k_sweep(SweepArgs<T> a) {
     T acc[D];
 #pragma unroll
     for (int r = 0; r < D; ++r) acc[r] = T(0);
-    if (CPL) group_sub<T, D, 0>(a.cpl, rec.cpl_w, rec.cpl_c, lane, a.xg, nullptr, 0, acc);
+    couplings(acc);
     const int cstart = a.inplace ? INT_MAX : rec.cstart;
     if (ZX) {
         if (cstart > 0) group_sub<T, D, 2>(a.off, rec.off_w, rec.off_c, lane, nullptr, a.t, cstart, acc);
@@ -591,6 +593,119 @@ __global__ __launch_bounds__(SWEEP_WAVES * WAVE) void k_sweep(SweepArgs<T> a) {
     if (a.t_reset) a.t_reset[at] = unwritten_value<T>();
     if (unwritten(tn)) tn = T(NAN);
     __hip_atomic_store(a.t + at, tn, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+template <class T, int D, bool ZX, bool CPL>
+__global__ __launch_bounds__(SWEEP_WAVES * WAVE) void k_sweep(SweepArgs<T> a) {
+    const int pos = sweep_position(a);
+    if (pos >= a.count) return;   // whole wavefronts; no barrier follows
+    const SweepRec rec = load_rec(a.rec + a.begin + pos);
+    if (rec.nrow == 0) return;
+    const int lane = threadIdx.x & (WAVE - 1);
+    sweep_slice<T, D, ZX>(a, rec, lane, [&](T (&acc)[D]) {
+        if (CPL) group_sub<T, D, 0>(a.cpl, rec.cpl_w, rec.cpl_c, lane, a.xg, nullptr, 0, acc);
+    });
+}
+
+// acc -= one slice's A_fg x_g with BR x BC blocks
+template <int BR, int BC>
+__device__ __forceinline__ void group_sub_rect(const GroupPart& P, int slice, int lane, double (&acc)[BR]) {
+    constexpr int CH = 2;
+    const int w = uniform_load(P.width + slice);
+    const int64_t cb = uniform_load(P.coff + slice);
+    for (int t0 = 0; t0 < w; t0 += CH) {
+        double v[CH][BR * BC], xj[CH][BC];
+#pragma unroll
+        for (int u = 0; u < CH; ++u) {
+            const bool live = t0 + u < w;
+            const int64_t sl = cb + t0 + u;
+            const uint32_t m = live ? uniform_load(P.a.mask + sl) : 0u;
+            const int64_t vg = live ? uniform_load(P.a.voff + sl) : 0;
+            const int j = live ? P.a.col[sl * WAVE + lane] : -1;
+            load_masked<double, BR * BC>(P.a.val + vg * WAVE + lane, m, v[u]);
+#pragma unroll
+            for (int c = 0; c < BC; ++c) xj[u][c] = 0.0;
+            if (j >= 0) load_vec<double, BC>(P.x + (int64_t)j * BC, xj[u]);
+        }
+#pragma unroll
+        for (int u = 0; u < CH; ++u)
+#pragma unroll
+            for (int r = 0; r < BR; ++r)
+#pragma unroll
+                for (int c = 0; c < BC; ++c) acc[r] -= v[u][r * BC + c] * xj[u][c];
+    }
+}
+
+template <int D>
+__device__ __forceinline__ void group_sub_parts(const GroupPart* parts, int n, int slice, int lane, double (&acc)[D]) {
+    for (int k = 0; k < n; ++k) {
+        const GroupPart& P = parts[k];
+        switch (P.bc) {
+            case 1: group_sub_rect<D, 1>(P, slice, lane, acc); break;
+            case 2: group_sub_rect<D, 2>(P, slice, lane, acc); break;
+            case 3: group_sub_rect<D, 3>(P, slice, lane, acc); break;
+            default: group_sub_rect<D, 4>(P, slice, lane, acc); break;
+        }
+    }
+}
+
+// The sweep of one block among more than two: its couplings with every other
+// block are summed with the row instead of being folded into a right-hand side
+// beforehand (a launch per coupling, one thread per row: 33 us each on the 40^3
+// system of 4 blocks, 1266 of 2080 us per V-cycle; that cycle takes 468 us now).
+template <int D, bool ZX>
+__global__ __launch_bounds__(SWEEP_WAVES * WAVE) void k_sweep_n(SweepNArgs a) {
+    const int pos = sweep_position(a.s);
+    if (pos >= a.s.count) return;   // whole wavefronts; no barrier follows
+    const SweepRec rec = load_rec(a.s.rec + a.s.begin + pos);
+    if (rec.nrow == 0) return;
+    const int lane = threadIdx.x & (WAVE - 1);
+    sweep_slice<double, D, ZX>(a.s, rec, lane,
+                               [&](double (&acc)[D]) { group_sub_parts<D>(a.cpl, a.n_cpl, rec.slice, lane, acc); });
+}
+
+template <int D>
+__device__ __forceinline__ void resid_slice_n(const ResidNArgs& a, int f, const SweepRec& rec, int lane) {
+    const int lg = a.lg[f];
+    const int q = lane & ((1 << lg) - 1), rr = lane >> lg;
+    const bool act = rr < rec.nrow && q < D;
+    const int row = rec.row0 + (rr < rec.nrow ? rr : 0);
+    const int64_t at = (int64_t)row * D + (q < D ? q : 0);
+    double dg[D], xr[D], bq = 0.0;
+    load_vec<double, D>(a.diag[f] + at * D, dg);
+    load_vec<double, D>(a.x[f] + (int64_t)row * D, xr);
+    if (a.b[f]) bq = a.b[f][at];
+    double acc[D];
+#pragma unroll
+    for (int r = 0; r < D; ++r) acc[r] = 0.0;
+    group_sub<double, D, 0>(a.off[f], rec.off_w, rec.off_c, lane, a.x[f], nullptr, 0, acc);
+    group_sub_parts<D>(a.cpl[f], a.n_cpl[f], rec.slice, lane, acc);
+    group_all_sum<double, D>(acc, lg);
+    if (!act) return;
+    double own = 0.0, sum = 0.0;
+#pragma unroll
+    for (int c = 0; c < D; ++c) {
+        own += dg[c] * xr[c];
+        sum = c == q ? acc[c] : sum;
+    }
+    const double ax = own - sum;
+    a.r[f][at] = a.b[f] ? bq - ax : ax;
+}
+
+__global__ __launch_bounds__(256) void k_resid_n(ResidNArgs a, int padded_blocks) {
+    int pos = xcd_block(padded_blocks) * WPB + wave_id();
+    int f = 0;
+    while (f < a.nb && pos >= a.count[f]) pos -= a.count[f++];
+    if (f >= a.nb) return;   // whole wavefront
+    const SweepRec rec = load_rec(a.rec[f] + pos);
+    if (rec.nrow == 0) return;
+    const int lane = threadIdx.x & (WAVE - 1);
+    switch (a.d[f]) {
+        case 1: resid_slice_n<1>(a, f, rec, lane); break;
+        case 2: resid_slice_n<2>(a, f, rec, lane); break;
+        case 3: resid_slice_n<3>(a, f, rec, lane); break;
+        default: resid_slice_n<4>(a, f, rec, lane); break;
+    }
 }
 
 // r = b - A x (or w = A x when b is NULL) in grouped form, block 0's record
@@ -660,6 +775,46 @@ void launch_sweep(int d, bool zero_x, bool has_cpl, const SweepArgs<T>& a, hipSt
 }
 template void launch_sweep<double>(int, bool, bool, const SweepArgs<double>&, hipStream_t);
 template void launch_sweep<float>(int, bool, bool, const SweepArgs<float>&, hipStream_t);
+
+template <int D>
+static void sweep_n_dispatch(bool zx, const SweepNArgs& a, hipStream_t s) {
+    const unsigned grid = (unsigned)ceil_div(a.s.count, SWEEP_WAVES);
+    constexpr int TPB = SWEEP_WAVES * WAVE;
+    if (zx) k_sweep_n<D, true><<<grid, TPB, 0, s>>>(a);
+    else k_sweep_n<D, false><<<grid, TPB, 0, s>>>(a);
+}
+
+void launch_sweep_n(int d, bool zero_x, const SweepNArgs& a, hipStream_t s) {
+    if (a.s.count <= 0) return;
+    MB_CHECK(a.s.lg >= 2 && a.s.lg <= 6, MBAMG_E_INVALID, "4 to 64 lanes per row");
+    MB_CHECK(a.n_cpl >= 0 && a.n_cpl < SWEEP_MAX_BLOCKS, MBAMG_E_INVALID, "at most 4 blocks");
+    for (int k = 0; k < a.n_cpl; ++k)
+        MB_CHECK(a.cpl[k].bc >= 1 && a.cpl[k].bc <= 4, MBAMG_E_INVALID, "row blocks of at most 4 x 4");
+    switch (d) {
+        case 1: sweep_n_dispatch<1>(zero_x, a, s); break;
+        case 2: sweep_n_dispatch<2>(zero_x, a, s); break;
+        case 3: sweep_n_dispatch<3>(zero_x, a, s); break;
+        case 4: sweep_n_dispatch<4>(zero_x, a, s); break;
+        default: throw Error(MBAMG_E_INVALID, "dofs per node must be 1..4");
+    }
+    MB_LAUNCH_CHECK();
+}
+
+void launch_resid_n(const ResidNArgs& a, hipStream_t s) {
+    MB_CHECK(a.nb >= 1 && a.nb <= SWEEP_MAX_BLOCKS, MBAMG_E_INVALID, "at most 4 blocks");
+    int total = 0;
+    for (int f = 0; f < a.nb; ++f) {
+        total += a.count[f];
+        MB_CHECK(a.lg[f] >= 2 && a.lg[f] <= 6 && a.d[f] >= 1 && a.d[f] <= 4, MBAMG_E_INVALID,
+                 "4 to 64 lanes per row, 1..4 dofs per node");
+        for (int k = 0; k < a.n_cpl[f]; ++k)
+            MB_CHECK(a.cpl[f][k].bc >= 1 && a.cpl[f][k].bc <= 4, MBAMG_E_INVALID, "row blocks of at most 4 x 4");
+    }
+    if (total <= 0) return;
+    const unsigned grid = xcd_grid(total, 1);
+    k_resid_n<<<grid, 256, 0, s>>>(a, (int)grid);
+    MB_LAUNCH_CHECK();
+}
 
 template <class T>
 void launch_resid_group(int d, const ResidGroupArgs<T>& a, hipStream_t s) {
@@ -818,39 +973,6 @@ void launch_xfer_rows(int d, const XferRowArgs<T>& a, hipStream_t s) {
 }
 template void launch_xfer_rows<double>(int, const XferRowArgs<double>&, hipStream_t);
 template void launch_xfer_rows<float>(int, const XferRowArgs<float>&, hipStream_t);
-
-// y += sign * A x for one block A_fg of any block shape (br, bc <= 4) in row
-// form (rows in block f's colour order, columns in block g's): one thread per
-// row, the row's blocks in their stored order.  Used where a system has more
-// than two blocks, whose couplings are folded into the right-hand sides.
-template <class T>
-__global__ __launch_bounds__(256) void k_rows_acc(int n, int br, int bc, const int32_t* __restrict__ rp,
-                                                  const int32_t* __restrict__ col, const T* __restrict__ val,
-                                                  const T* __restrict__ x, T* __restrict__ y, T sign) {
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n) return;
-    T acc[4] = {T(0), T(0), T(0), T(0)};
-    const int bs = br * bc;
-    for (int p = rp[i]; p < rp[i + 1]; ++p) {
-        const int64_t j = col[p];
-        const T* v = val + (int64_t)p * bs;
-        T xj[4];
-        for (int c = 0; c < bc; ++c) xj[c] = x[j * bc + c];
-        for (int r = 0; r < br; ++r)
-            for (int c = 0; c < bc; ++c) acc[r] += v[r * bc + c] * xj[c];
-    }
-    for (int r = 0; r < br; ++r) y[(int64_t)i * br + r] += sign * acc[r];
-}
-
-template <class T>
-void launch_rows_acc(int n, int br, int bc, const RowView<T>& A, const T* x, T* y, T sign, hipStream_t s) {
-    if (n <= 0) return;
-    MB_CHECK(br >= 1 && br <= 4 && bc >= 1 && bc <= 4, MBAMG_E_INVALID, "row blocks of at most 4 x 4");
-    k_rows_acc<T><<<(unsigned)ceil_div(n, 256), 256, 0, s>>>(n, br, bc, A.rp, A.col, A.val, x, y, sign);
-    MB_LAUNCH_CHECK();
-}
-template void launch_rows_acc<double>(int, int, int, const RowView<double>&, const double*, double*, double,
-                                      hipStream_t);
 
 // r = b - A x (or w = A x when b is NULL) for both block rows in one launch.
 template <class T, int D, int P>

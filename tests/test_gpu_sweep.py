@@ -106,3 +106,29 @@ def test_a_nan_in_the_input_ends_the_cycle():
         hg.vcycle(torch_dev(r), z)
         assert torch.isfinite(z).all()
         hg.close()
+
+
+# more than two blocks: the couplings (3 x 1, 1 x 3, 3 x 3, 1 x 1 blocks) are summed with the sweep
+@pytest.mark.parametrize("split", ["3d-split4", "2d-split3"])
+@pytest.mark.parametrize("group", [4, 16, 64])
+@pytest.mark.parametrize("sweeps", [(1, 1), (2, 2)])
+def test_more_than_two_blocks_with_every_group_size(split, group, sweeps, monkeypatch):
+    from oracle import amg, nblock
+    from paper_2103_07537_amd import mbamg
+    from paper_2103_07537_amd.inputs import split_fields
+    t = split_fields(make_system(11, 3, 0.6, seed=5, kappa="lognormal")) if split == "3d-split4" else \
+        split_fields(make_system(25, 2, 0.5, seed=4), split_second=False)
+    kw = dict(max_coarse=60, bgs_sweeps=sweeps[0], inner_sweeps=sweeps[1])
+    ho = nblock.setup(t.blocks, t.dofs, amg.Params(**kw))
+    monkeypatch.setenv("MBAMG_SWEEP_GROUP", str(group))
+    hg = mbamg.Hierarchy(t.blocks, t.dofs, t.n_vec, **kw)
+    assert hg.num_levels() == len(ho.levels) >= 3
+    z, w = torch_dev(np.zeros(t.n_dofs)), torch_dev(np.zeros(t.n_dofs))
+    for seed in (1, 2):
+        r = np.random.default_rng(seed).standard_normal(t.n_dofs)
+        hg.vcycle(torch_dev(r), z)
+        assert_close(z.cpu().numpy(), nblock.vcycle(ho, r), 1e-12)
+    hg.apply(torch_dev(r), w)
+    ref = t.to_scipy() @ r
+    assert np.max(np.abs(w.cpu().numpy() - ref)) <= 1e-13 * np.max(np.abs(ref))
+    hg.close()
