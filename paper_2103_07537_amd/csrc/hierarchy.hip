@@ -135,6 +135,7 @@ struct Level {
     Aggregates G1;                             // block 1's own aggregates (separate aggregation)
     bool separate = false;
     BlockLevel blk[2];
+    int shape = SHAPE_FULL;                    // of all four blocks (see solve_kernels.h)
     int resid_split = 1;                       // waves per slice in the residual (one launch, both blocks)
     DevBuf<int32_t> resid_order[2];            // the residual's slice order per block (empty: identity)
     // smoothed prolongators (natural order) and the weights that built them
@@ -594,6 +595,23 @@ static int choose_group(const mbamg_params& p, int lvl, int n_level, int n, int6
     return grouped ? group_lanes(n, blocks) : 1;
 }
 
+// The shape a level's blocks are stored in, from what block_shape_flags found in
+// them (d x d blocks): the fewest entries that determine every block, whenever the
+// blocks allow it.  A sliced finest level of the 3D system then reads 24 + 4 and
+// 8 + 4 bytes per neighbour (FP64 values and column) instead of 48 + 4 and 24 + 4;
+// 128^3 nodes, FP64: post-smoother colour pass 158 -> 107 us, residual 552 -> 344 us,
+// level 1's sweeps 454 -> 398 us per cycle, its residual 194 -> 141 us.
+static int level_shape(const mbamg_params& p, int d, int bad) {
+    if (d == 1 || p.smoother == 1 || (bad & 1)) return SHAPE_FULL;
+    // more waves per slice than the shaped kernels are built for (forced by a test)
+    if (const char* fo = form_override("MBAMG_SLICE_SPLIT"))
+        if (std::atoi(fo) > SHAPE_MAX_SPLIT) return SHAPE_FULL;
+    // MBAMG_BLOCK_SHAPE = 0 | 1 (tests): the most that is used of what the blocks allow
+    int most = SHAPE_SYMMETRIC;
+    if (const char* fo = form_override("MBAMG_BLOCK_SHAPE")) most = std::atoi(fo);
+    return std::min(most, (bad & 2) ? SHAPE_SCALED : SHAPE_SYMMETRIC);
+}
+
 // Waves per slice (1..16) for a launch over `slices` slices of `width` slots
 // on average: wide slices are shared by more waves until the launch has
 // about 2048 waves, keeping at least 4 slots per wave.
@@ -666,9 +684,9 @@ static void natural_slicing(BlockLevel& B, int n, hipStream_t s, const std::vect
 // Pack one part of block row f into masked slices on the device.  A: the
 // natural-order source block (unused for Dinv); val: its values, or the dense
 // per-node inverse array for Dinv; col_iperm: natural column node -> colour
-// order of the column block.
+// order of the column block; shape: which entries of the (square) blocks are kept.
 static void build_part(SellPart& P, PartKind kind, const BlockLevel& B, const SetupBsr* A, const int32_t* col_iperm,
-                       const double* val, int br, int bc, bool want32, hipStream_t s) {
+                       const double* val, int br, int bc, bool want32, hipStream_t s, int shape = SHAPE_FULL) {
     P.br = br;
     P.bc = bc;
     const int ns = B.n_slices;
@@ -688,10 +706,10 @@ static void build_part(SellPart& P, PartKind kind, const BlockLevel& B, const Se
     P.mask.alloc(nsl);
     DevBuf<uint32_t> slot_nz(nsl);
     MB_HIP(hipMemsetAsync(slot_nz.p, 0, sizeof(uint32_t) * nsl, s));
-    sell_masks(P.n_slots, br * bc, src.p, val, P.mask.p, slot_nz.p, s);
+    sell_masks(P.n_slots, br * bc, shape, br, src.p, val, P.mask.p, slot_nz.p, s);
     P.n_groups = slot_offsets(P.n_slots, P.mask.p, P.voff, s);
     P.v64.alloc(std::max<int64_t>(P.n_groups, 1) * WAVE);
-    sell_fill(P.n_slots, br * bc, src.p, val, P.mask.p, P.voff.p, P.v64.p, s);
+    sell_fill(P.n_slots, br * bc, shape, br, src.p, val, P.mask.p, P.voff.p, P.v64.p, s);
     if (want32) {
         P.v32.alloc(std::max<int64_t>(P.n_groups, 1) * WAVE);
         cast_to_f32(P.v64.p, P.v32.p, P.n_groups * WAVE, s);
@@ -1009,6 +1027,9 @@ static void setup_impl(mbamg_hierarchy* h, const mbamg_bsr* Ab, hipStream_t s, D
         Bn[f].alloc((size_t)nb);
         fill_ones(Bn[f].p, nb, s);
     }
+    // per level: what rules out the shapes with fewer stored entries
+    DevBuf<int32_t> shape_flags((size_t)p.max_levels);
+    MB_HIP(hipMemsetAsync(shape_flags.p, 0, sizeof(int32_t) * p.max_levels, s));
     int lvl = 0;
     while (true) {
         Level& cur = *h->L.back();
@@ -1077,6 +1098,9 @@ static void setup_impl(mbamg_hierarchy* h, const mbamg_bsr* Ab, hipStream_t s, D
             colour_jobs[lvl] = std::async(std::launch::async,
                                           [lp, lvl, pp, ev, device] { colour_level(*lp, lvl, *pp, ev, device); });
         }
+        if (d0 > 1 && p.smoother == 0)
+            for (int f = 0; f < 2; ++f)
+                for (int g = 0; g < 2; ++g) block_shape_flags(cur.A[f][g], shape_flags.p + lvl, s);
         const int nc = G.n_agg;
         DevBuf<double> q[2], Bc[2];
         for (int f = 0; f < 2; ++f) {     // block 1 reuses block 0's aggregates unless aggregated separately
@@ -1217,6 +1241,15 @@ static void setup_impl(mbamg_hierarchy* h, const mbamg_bsr* Ab, hipStream_t s, D
         if (want32) alloc_vecs(c.v32, c.ndof(), false, s);
     }
 
+    // the shapes of the levels' blocks, read back at once
+    {
+        const int nl = (int)h->L.size();
+        std::vector<int32_t> bad(nl);
+        MB_HIP(hipMemcpyAsync(bad.data(), shape_flags.p, sizeof(int32_t) * nl, hipMemcpyDeviceToHost, s));
+        MB_HIP(hipStreamSynchronize(s));
+        for (int l = 0; l + 1 < nl; ++l) h->L[l]->shape = level_shape(p, d0, bad[l]);
+    }
+
     // smoother format on every other level, in two passes: first each level's own smoother
     // blocks (its colouring, order and parts), then the transfers, which need the next
     // level's order.  A build that lends its level 0 does that level first and publishes
@@ -1265,9 +1298,10 @@ static void setup_impl(mbamg_hierarchy* h, const mbamg_bsr* Ab, hipStream_t s, D
             clk.mark("dinv", l);
             if (B.group > 1) {
                 B.split = 1;
-                build_part(B.off, PartKind::Off, B, &Lv.A[f][f], B.d_iperm.p, Lv.A[f][f].val.p, df, df, want32, s);
+                build_part(B.off, PartKind::Off, B, &Lv.A[f][f], B.d_iperm.p, Lv.A[f][f].val.p, df, df, want32, s,
+                       Lv.shape);
                 build_part(B.cpl, PartKind::Cpl, B, &Lv.A[f][g], Lv.blk[g].d_iperm.p, Lv.A[f][g].val.p, df, dg,
-                           want32, s);
+                           want32, s, Lv.shape);
                 build_recs(B, s);
                 const int64_t nd = (int64_t)nf * df * df;
                 B.gdinv64.alloc(nd);
@@ -1282,14 +1316,18 @@ static void setup_impl(mbamg_hierarchy* h, const mbamg_bsr* Ab, hipStream_t s, D
                 }
                 MB_HIP(hipStreamSynchronize(s));   // dinv is released at the end of this iteration
                 if (clk.on)
-                    std::fprintf(stderr, "[mbamg setup] level %d block %d: %d nodes, %d colours, %d lanes per row\n",
-                                 l, f, nf, B.n_colours, B.group);
+                    std::fprintf(stderr, "[mbamg setup] level %d block %d: %d nodes, %d colours, %d lanes per row, "
+                                 "fill %.2f + %.2f, shape %d\n", l, f, nf, B.n_colours, B.group,
+                                 (double)(Lv.A[f][f].nnzb - nf) / std::max<double>(1, (double)B.off.n_slots * WAVE),
+                                 (double)Lv.A[f][g].nnzb / std::max<double>(1, (double)B.cpl.n_slots * WAVE), Lv.shape);
                 continue;
             }
-            build_part(B.off, PartKind::Off, B, &Lv.A[f][f], B.d_iperm.p, Lv.A[f][f].val.p, df, df, want32, s);
-            build_part(B.diag, PartKind::Diag, B, &Lv.A[f][f], B.d_iperm.p, Lv.A[f][f].val.p, df, df, want32, s);
+            build_part(B.off, PartKind::Off, B, &Lv.A[f][f], B.d_iperm.p, Lv.A[f][f].val.p, df, df, want32, s,
+                       Lv.shape);
+            build_part(B.diag, PartKind::Diag, B, &Lv.A[f][f], B.d_iperm.p, Lv.A[f][f].val.p, df, df, want32, s,
+                       Lv.shape);
             build_part(B.cpl, PartKind::Cpl, B, &Lv.A[f][g], Lv.blk[g].d_iperm.p, Lv.A[f][g].val.p, df, dg, want32,
-                       s);
+                       s, Lv.shape);
             build_part(B.dinv, PartKind::Dinv, B, nullptr, nullptr, dinv.p, df, df, want32, s);
             B.cstats.assign(B.n_colours, ColourStats{});
             int64_t slots = 0;
@@ -1309,6 +1347,7 @@ static void setup_impl(mbamg_hierarchy* h, const mbamg_bsr* Ab, hipStream_t s, D
             const double avg_width = B.n_slices ? (double)slots / B.n_slices : 0.0;
             const double per_colour = (double)B.n_slices / std::max(1, B.n_colours);
             B.split = slot_split(per_colour, avg_width);
+            if (Lv.shape != SHAPE_FULL) B.split = std::min(B.split, SHAPE_MAX_SPLIT);
             // MBAMG_SLICE_SPLIT = 1 | 2 | 4 | 8 | 16 forces the waves per slice on every sliced
             // level, for tests: the split changes the order of each row's partial sums
             if (const char* fo = form_override("MBAMG_SLICE_SPLIT")) {
@@ -1332,6 +1371,7 @@ static void setup_impl(mbamg_hierarchy* h, const mbamg_bsr* Ab, hipStream_t s, D
                 slices += B.n_slices;
             }
             Lv.resid_split = slot_split((double)slices, slices ? (double)slots / (double)slices : 0.0, 32768);
+            if (Lv.shape != SHAPE_FULL) Lv.resid_split = std::min(Lv.resid_split, SHAPE_MAX_SPLIT);
         }
         // the residual's launch order: the same eighth of every colour together, so the blocks
         // each XCD takes (contiguous launch ranges) cover one slab of the domain in all colours
@@ -1623,6 +1663,11 @@ static GroupView<T> gview(const SellPart& P) {
     return {v.voff, v.mask, v.col, v.val};
 }
 
+// at most half as many workgroups per colour as compute units (see sweep_lds)
+static bool few_per_colour(const BlockLevel& B) {
+    return B.colour_rec.back() <= 128 * SWEEP_WAVES * std::max(1, B.n_colours);
+}
+
 static int log2_of(int g) {
     int l = 0;
     while ((1 << l) < g) ++l;
@@ -1707,6 +1752,8 @@ static void sweep_block(mbamg_hierarchy* h, int l, int f, bool zero, const T* b,
     const bool timed = h->time_launches();
     T* const t[2] = {V.t.p + off, V.t2.p + off};
     SweepArgs<T> a{};
+    a.shape = Lv.shape;
+    a.spread = few_per_colour(B);
     a.rec = B.recs.p;
     a.lg = log2_of(B.group);
     a.off = gview<T>(B.off);
@@ -1756,6 +1803,7 @@ static void smooth_block(mbamg_hierarchy* h, int l, int f, bool zero, const T* b
     for (int k = 0; k < h->p.inner_sweeps; ++k) {
         for (int c = 0; c < B.n_colours; ++c) {
             GsArgs<T> a{};
+            a.shape = Lv.shape;
             a.s_begin = B.colour_slice[c];
             a.s_count = B.colour_slice[c + 1] - B.colour_slice[c];
             a.sl = B.slices();
@@ -1784,6 +1832,7 @@ static void resid(mbamg_hierarchy* h, int l, const T* b, const T* x, T* r, hipSt
     Level& Lv = *h->L[l];
     const int64_t n0 = (int64_t)Lv.n * Lv.d[0];
     ResidArgs<T> a{};
+    a.shape = Lv.shape;
     for (int f = 0; f < 2; ++f) {
         BlockLevel& B = Lv.blk[f];
         const int64_t off = f == 0 ? 0 : n0;
@@ -1802,6 +1851,7 @@ static void resid(mbamg_hierarchy* h, int l, const T* b, const T* x, T* r, hipSt
     TimerScope ts(h, s, timed, launch_kind(l, kind), bytes);
     if (Lv.blk[0].group > 1) {
         ResidGroupArgs<T> ga{};
+        ga.shape = Lv.shape;
         for (int f = 0; f < 2; ++f) {
             const BlockLevel& B = Lv.blk[f];
             ga.rec[f] = B.recs.p;
@@ -2214,6 +2264,7 @@ static void gen_vcycle_level(mbamg_hierarchy* h, int l, const double* b, double*
                 const double* xg = g < f ? XN + Lv.off[g] : (X ? X + Lv.off[g] : nullptr);
                 if (g != f && xg && Lv.A[f][g].nnzb > 0) a.cpl[a.n_cpl++] = group_part(Lv.C[f][g], xg);
             }
+            a.s.spread = few_per_colour(B);
             a.s.rec = B.recs.p;
             a.s.lg = log2_of(B.group);
             a.s.off = gview<double>(B.off);

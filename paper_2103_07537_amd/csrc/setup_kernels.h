@@ -51,9 +51,12 @@ void build_node_inverses(const SetupBsr (&A)[2][2], int n_slices, const int32_t*
                          DevBuf<float>* inv32, hipStream_t s);
 // true when every block of B lies in A's pattern (same rows)
 bool within_pattern(const SetupBsr& A, const SetupBsr& B, hipStream_t s);
-void sell_masks(int64_t n_slots, int bs, const int64_t* src, const double* val, uint32_t* mask, uint32_t* slot_nz,
-                hipStream_t s);
-void sell_fill(int64_t n_slots, int bs, const int64_t* src, const double* val, const uint32_t* mask,
+// flags[0] |= 1 / 2 where A's blocks rule out SHAPE_SCALED / the equality that SHAPE_SYMMETRIC adds
+void block_shape_flags(const SetupBsr& A, int32_t* flags, hipStream_t s);
+// shape: the kept entries of D x D blocks (SHAPE_FULL: all bs of them)
+void sell_masks(int64_t n_slots, int bs, int shape, int D, const int64_t* src, const double* val, uint32_t* mask,
+                uint32_t* slot_nz, hipStream_t s);
+void sell_fill(int64_t n_slots, int bs, int shape, int D, const int64_t* src, const double* val, const uint32_t* mask,
                const int64_t* slot_voff, double* out, hipStream_t s);
 void cast_to_f32(const double* a, float* b, int64_t n, hipStream_t s);
 // smoothed prolongator (vector components), block transpose, generic ordered block product

@@ -27,8 +27,22 @@ struct SellView {
     const T* val;
 };
 
+// What every block of a level's four matrix blocks has in common.  Vector fields
+// whose components are coupled alike (a vector Laplacian, a component-wise
+// coupling) have blocks whose leading (D-1) x (D-1) part is a multiple of the
+// identity; where the last column also equals the last row (a gradient and its
+// divergence, coarsened with equal transfers) it need not be stored twice.
+//   SHAPE_FULL       any block: all D x D entries
+//   SHAPE_SCALED     s I in the leading part: s, the last column, the last row, the last entry
+//   SHAPE_SYMMETRIC  that, last column = last row: s, the last column, the last entry
+// Entries that are zero in a whole slot are left out under every shape.
+constexpr int SHAPE_FULL = 0, SHAPE_SCALED = 1, SHAPE_SYMMETRIC = 2;
+// waves per slice that the sliced kernels are instantiated for, beyond SHAPE_FULL
+constexpr int SHAPE_MAX_SPLIT = 2;
+
 template <class T>
 struct GsArgs {
+    int shape;
     int s_begin, s_count;      // slices of this colour
     SliceView sl;
     SellView<T> off, cpl, dinv;
@@ -99,8 +113,10 @@ struct GroupView {
 // positions [begin, begin + count) of its record list (whole colours, ascending).
 template <class T>
 struct SweepArgs {
+    int shape;
     const SweepRec* rec;
     int begin, count;
+    int spread;                // few workgroups per colour: one per compute unit
     int lg;                    // log2 of the lanes per row
     GroupView<T> off, cpl;
     const T* dinv;             // d x d per row, colour order
@@ -149,6 +165,7 @@ struct ResidNArgs {
 
 template <class T>
 struct ResidGroupArgs {
+    int shape;
     const SweepRec* rec[2];
     int count[2];
     int lg[2];
@@ -161,6 +178,7 @@ struct ResidGroupArgs {
 
 template <class T>
 struct ResidArgs {
+    int shape;
     int s_count[2];
     SliceView sl[2];
     SellView<T> off[2], cpl[2], diag[2];
