@@ -260,9 +260,9 @@ struct DonorLink {
 
 thread_local std::string g_last_error;
 
-// Krylov scalar buffer layout (device and pinned host copies): the dot pass's
-// sums, the update pass's sums, two norms
-constexpr int KB_D1 = 0, KB_D2 = KMAXQ, KB_NU0 = 2 * KMAXQ, KB_NU1 = 2 * KMAXQ + 1, KB_TOTAL = 2 * KMAXQ + 2;
+// Layout of one set of Krylov results (page-locked host memory): the dot pass's
+// sums, the update pass's sums, nu', a squared norm
+constexpr int KB_D1 = 0, KB_D2 = KMAXQ, KB_NU = 2 * KMAXQ, KB_NU2 = 2 * KMAXQ + 1, KB_TOTAL = 2 * KMAXQ + 2;
 
 }  // namespace mbamg
 
@@ -279,11 +279,13 @@ struct mbamg_hierarchy {
     int coarse_n = 0;
     // Krylov workspace
     int64_t n_fine = 0;
-    DevBuf<double> V, Z64, w, xw, bw, ztmp, partial, hbuf, ybuf, coef;
+    DevBuf<double> V, Z64, w, xw, bw, ztmp, partial, ybuf, coef;
+    DevBuf<uint32_t> kcounter;     // blocks of the running Krylov pass that are done
     DevBuf<float> mlp;             // network parameters (5122) followed by feature mean and std (12 + 12)
-    double* hbuf_host = nullptr;   // pinned: Krylov scalars read back each iteration
-    double* coef_host = nullptr;   // pinned: the update pass's coefficients going up
+    double* hbuf_host = nullptr;   // pinned: two sets of Krylov results, written by the device
+    double* coef_host = nullptr;   // pinned: 1/nu of a restart's first candidate going up
     double* y_host = nullptr;
+    hipEvent_t step_done[2] = {nullptr, nullptr};   // the Krylov step whose results a set of hbuf_host holds
     double judge_rho[2] = {0.0, 0.0};   // probe factors of the learned and the fixed hierarchy
     // a learned hierarchy the judge kept holds the fixed-weight one it was judged against: a
     // solve that stalls with the learned preconditioner finishes with it
@@ -310,6 +312,8 @@ struct mbamg_hierarchy {
         if (hbuf_host) (void)hipHostFree(hbuf_host);
         if (coef_host) (void)hipHostFree(coef_host);
         if (y_host) (void)hipHostFree(y_host);
+        for (auto e : step_done)
+            if (e) (void)hipEventDestroy(e);
     }
 };
 
@@ -1491,12 +1495,14 @@ static void setup_impl(mbamg_hierarchy* h, const mbamg_bsr* Ab, hipStream_t s, D
     h->vio.alloc(n);
     h->vio2.alloc(n);
     h->partial.alloc((size_t)KBLOCKS * KMAXQ);
-    h->hbuf.alloc(KB_TOTAL);
+    h->kcounter.alloc(KCOUNTER_WORDS);
+    fill_words(h->kcounter.p, KCOUNTER_WORDS, 0u, s);
     h->ybuf.alloc(KMAXQ);
     h->coef.alloc(KC_TOTAL);
-    MB_HIP(hipHostMalloc((void**)&h->hbuf_host, sizeof(double) * KB_TOTAL, hipHostMallocDefault));
-    MB_HIP(hipHostMalloc((void**)&h->coef_host, sizeof(double) * KC_TOTAL, hipHostMallocDefault));
+    MB_HIP(hipHostMalloc((void**)&h->hbuf_host, sizeof(double) * 2 * KB_TOTAL, hipHostMallocDefault));
+    MB_HIP(hipHostMalloc((void**)&h->coef_host, sizeof(double), hipHostMallocDefault));
     MB_HIP(hipHostMalloc((void**)&h->y_host, sizeof(double) * KMAXQ, hipHostMallocDefault));
+    for (auto& e : h->step_done) MB_HIP(hipEventCreateWithFlags(&e, hipEventDisableTiming));
     MB_HIP(hipStreamSynchronize(s));
     auto t1 = std::chrono::steady_clock::now();
     h->t_setup_ms = std::chrono::duration<double, std::milli>(t1 - t0).count();
@@ -2178,12 +2184,14 @@ static void gen_setup_impl(mbamg_hierarchy* h, const mbamg_bsr* Ab, hipStream_t 
     h->vio.alloc(n);
     h->vio2.alloc(n);
     h->partial.alloc((size_t)KBLOCKS * KMAXQ);
-    h->hbuf.alloc(KB_TOTAL);
+    h->kcounter.alloc(KCOUNTER_WORDS);
+    fill_words(h->kcounter.p, KCOUNTER_WORDS, 0u, s);
     h->ybuf.alloc(KMAXQ);
     h->coef.alloc(KC_TOTAL);
-    MB_HIP(hipHostMalloc((void**)&h->hbuf_host, sizeof(double) * KB_TOTAL, hipHostMallocDefault));
-    MB_HIP(hipHostMalloc((void**)&h->coef_host, sizeof(double) * KC_TOTAL, hipHostMallocDefault));
+    MB_HIP(hipHostMalloc((void**)&h->hbuf_host, sizeof(double) * 2 * KB_TOTAL, hipHostMallocDefault));
+    MB_HIP(hipHostMalloc((void**)&h->coef_host, sizeof(double), hipHostMallocDefault));
     MB_HIP(hipHostMalloc((void**)&h->y_host, sizeof(double) * KMAXQ, hipHostMallocDefault));
+    for (auto& e : h->step_done) MB_HIP(hipEventCreateWithFlags(&e, hipEventDisableTiming));
     MB_HIP(hipStreamSynchronize(s));
     h->t_setup_ms = std::chrono::duration<double, std::milli>(std::chrono::steady_clock::now() - t0).count();
     int64_t nz0 = h->GL[0]->nnzb_total(), nzs = 0;
@@ -2396,16 +2404,16 @@ static void apply_A(mbamg_hierarchy* h, const double* x, double* w, hipStream_t 
 // ----------------------------------------------------------------------------
 // GMRES (right preconditioned) / FGMRES, restarted
 // ----------------------------------------------------------------------------
-// ||v||^2 through the deterministic two-pass reduction (synchronous)
+static KrylovBufs krylov_bufs(mbamg_hierarchy* h, int set = 0) {
+    double* r = h->hbuf_host + (size_t)set * KB_TOTAL;
+    return {h->partial.p, h->kcounter.p, h->coef.p, r + KB_D1, r + KB_D2, r + KB_NU, r + KB_NU2};
+}
+
+// ||v||^2 through the deterministic reduction (synchronous)
 static double norm2_dev(mbamg_hierarchy* h, const double* v, hipStream_t s) {
-    const int nb = krylov_blocks(h->n_fine);
-    double* kb = h->hbuf.p;
-    launch_orth(h->n_fine, 0, nullptr, 0, v, h->partial.p, nb, s);
-    launch_orth_reduce(h->partial.p, nb, 0, nullptr, kb + KB_NU0, nullptr, s);
-    double r = 0.0;
-    MB_HIP(hipMemcpyAsync(&r, kb + KB_NU0, sizeof(double), hipMemcpyDeviceToHost, s));
+    launch_norm2(h->n_fine, v, krylov_bufs(h), s);
     MB_HIP(hipStreamSynchronize(s));
-    return r;
+    return h->hbuf_host[KB_NU2];
 }
 
 // Restarted GMRES (FGMRES when the cycle runs in FP32), right preconditioned.
@@ -2441,6 +2449,15 @@ static double norm2_dev(mbamg_hierarchy* h, const double* v, hipStream_t s) {
 // (MBAMG_REVERT_RHO overrides the threshold, for tests.)
 constexpr double REVERT_STALL = 0.99;
 
+// Systems of up to this many unknowns have the next Krylov step enqueued before the
+// host has read the present one's results (the device has all it needs for it): the
+// stream then never runs dry while the host waits, updates the least-squares problem
+// and launches again, about 20 us per step.  The last step of a solve or restart that
+// ends early is for nothing, so a step must cost little against what all of them gain
+// (24,576 unknowns: 130 -> 113 us per step with the shorter Krylov passes; a step of
+// 2.1M unknowns takes 730 us, of 16.8M 2.8 ms).
+constexpr int64_t AHEAD_MAX = (int64_t)1 << 20;
+
 static double revert_threshold() {
     if (const char* f = form_override("MBAMG_REVERT_RHO")) return std::atof(f);
     return REVERT_STALL;
@@ -2465,12 +2482,9 @@ static mbamg_status solve_impl(mbamg_hierarchy* h, const double* b, double* x, d
     // H: the least-squares matrix (rotated as it grows), Hr: its unrotated columns
     // (the Arnoldi relation), Ac[j][i] = a_{j,i}, nuv[j] = nu_j
     const int ld = m + 1;
+    const bool ahead = n <= AHEAD_MAX && h->timing == 0;
     std::vector<double> H((size_t)ld * m), Hr((size_t)ld * m), cs(m), sn(m), g(ld), y(m), t(m), nuv(ld),
         Ac((size_t)ld * ld);
-    double* hb = h->hbuf_host;
-    double* kb = h->hbuf.p;
-    double* ch = h->coef_host;
-    const int nb = krylov_blocks(n);
     if (bnorm == 0.0) {
         MB_HIP(hipMemsetAsync(h->xw.p, 0, sizeof(double) * n, s));
         rel = 0.0;
@@ -2484,27 +2498,35 @@ static mbamg_status solve_impl(mbamg_hierarchy* h, const double* b, double* x, d
             if (beta <= rtol * bnorm) break;
             if (its >= h->p.max_iters) { st = MBAMG_NOT_CONVERGED; break; }
             nuv[0] = beta;
-            ch[KC_INV_NU] = 1.0 / beta;
-            MB_HIP(hipMemcpyAsync(h->coef.p + KC_INV_NU, ch + KC_INV_NU, sizeof(double), hipMemcpyHostToDevice, s));
+            h->coef_host[0] = 1.0 / beta;
+            MB_HIP(hipMemcpyAsync(h->coef.p + KC_INV_NU, h->coef_host, sizeof(double), hipMemcpyHostToDevice, s));
             std::fill(g.begin(), g.end(), 0.0);
             std::fill(Hr.begin(), Hr.end(), 0.0);
             g[0] = beta;
             int k = 0;
-            for (int j = 0; j < m; ++j) {
+            // step j on the device: everything it reads from earlier steps is there
+            auto enqueue = [&](int j) {
                 double* vj = h->V.p + (size_t)j * n;
                 double* vn = h->V.p + (size_t)(j + 1) * n;
                 double* zj64 = fp32 ? h->ztmp.p : h->Z64.p + (size_t)j * n;
                 float* zj32 = fp32 ? h->Z32.p + (size_t)j * n : nullptr;
+                const KrylovBufs kb = krylov_bufs(h, j & 1);
                 apply_precond(h, vj, zj64, zj32, s);
                 apply_A(h, zj64, h->w.p, s);
                 // dot pass: b = Q^T w and u_j . w; c_j on the device
-                launch_orth(n, j + 1, h->V.p, n, h->w.p, h->partial.p, nb, s);
-                launch_orth_reduce(h->partial.p, nb, j + 1, kb + KB_D1, nullptr, h->coef.p, s);
-                // update pass: Q_j over u_j, u_{j+1} into V_{j+1}, a_{j+1} and |u_{j+1}|^2
-                launch_dcgs_update(n, j, h->V.p, n, h->coef.p, vj, h->w.p, vn, h->partial.p, nb, s);
-                launch_orth_reduce(h->partial.p, nb, j + 1, kb + KB_D2, kb + KB_NU1, nullptr, s);
-                MB_HIP(hipMemcpyAsync(hb, kb, sizeof(double) * KB_TOTAL, hipMemcpyDeviceToHost, s));
-                MB_HIP(hipStreamSynchronize(s));
+                launch_orth(n, j + 1, h->V.p, n, h->w.p, kb, s);
+                // update pass: Q_j over u_j, u_{j+1} into V_{j+1}, a_{j+1} and nu_{j+1}
+                launch_dcgs_update(n, j, h->V.p, n, vj, h->w.p, vn, kb, s);
+                MB_HIP(hipEventRecord(h->step_done[j & 1], s));
+            };
+            int queued = 0;
+            for (int j = 0; j < m; ++j) {
+                // step j + 1 goes out before step j's results are looked at, where that is worth
+                // it (see AHEAD_MAX); it writes only what step j's end would not use
+                const int upto = ahead && j + 1 < m && its + 1 < h->p.max_iters ? j + 1 : j;
+                while (queued <= upto) enqueue(queued++);
+                MB_HIP(hipEventSynchronize(h->step_done[j & 1]));
+                const double* hb = h->hbuf_host + (size_t)(j & 1) * KB_TOTAL;
                 const double* bq = hb + KB_D1;
                 const double* an = hb + KB_D2;
                 const double* aj = &Ac[(size_t)j * ld];
@@ -2518,18 +2540,11 @@ static mbamg_status solve_impl(mbamg_hierarchy* h, const double* b, double* x, d
                     const double proj = l < j ? bq[l] : (bq[j] - ab) / nuj;
                     raw[l] = (proj - c) / nuj + an[l];
                 }
-                double nu2 = hb[KB_NU1];
-                for (int l = 0; l <= j; ++l) nu2 -= an[l] * an[l];
-                // nu2 <= 0: the candidate lies in the basis (breakdown)
-                const double nun = nu2 > 0.0 && std::isfinite(nu2) ? std::sqrt(nu2) : 0.0;
+                // 0: the candidate lies in the basis (breakdown)
+                const double nun = hb[KB_NU];
                 raw[j + 1] = nun;
                 nuv[j + 1] = nun;
                 for (int l = 0; l <= j; ++l) Ac[(size_t)(j + 1) * ld + l] = an[l];
-                if (nun > 0.0 && j + 1 < m) {
-                    for (int l = 0; l <= j; ++l) ch[KC_A + l] = an[l];
-                    ch[KC_INV_NU] = 1.0 / nun;
-                    MB_HIP(hipMemcpyAsync(h->coef.p, ch, sizeof(double) * KC_TOTAL, hipMemcpyHostToDevice, s));
-                }
                 double* col = &H[(size_t)j * ld];
                 for (int l = 0; l <= j + 1; ++l) col[l] = raw[l];
                 for (int i = 0; i < j; ++i) {

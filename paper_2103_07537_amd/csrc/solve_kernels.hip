@@ -825,48 +825,132 @@ template void launch_coarse<double>(int, const double*, const double*, double*, 
 template void launch_coarse<float>(int, const double*, const float*, float*, hipStream_t);
 
 // ---------------------------------------------------------------------------
-// Krylov kernels: fixed grid, per-block partial sums, one-block final sums
+// Krylov kernels: fixed grid, per-block partial sums; the block that finishes
+// last adds them up in a fixed order
 // ---------------------------------------------------------------------------
-__device__ inline double block_sum(double v, double* sh) {
-    const int t = threadIdx.x;
+constexpr int KT = 256, KW = KT / WAVE;   // threads and wavefronts per block
+
+// This block's sums of N per-thread values, left in the first N threads' return
+// values: wavefront sums by DPP moves (no barrier per value), one pass through LDS.
+template <int N>
+__device__ __forceinline__ double block_sums(double (&v)[N], double (*sh)[KMAXQ]) {
+    const int t = threadIdx.x, lane = t & (WAVE - 1), w = t / WAVE;
 #pragma unroll
-    for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, WAVE);
+    for (int q = 0; q < N; ++q) {
+        v[q] = group_sum<WAVE>(v[q]);
+        if (lane == WAVE - 1) sh[w][q] = v[q];
+    }
     __syncthreads();
-    if ((t & 63) == 0) sh[t >> 6] = v;
-    __syncthreads();
-    double r = sh[0] + sh[1] + sh[2] + sh[3];
+    double r = 0.0;
+    if (t < N) {
+        r = sh[0][t];
+#pragma unroll
+        for (int k = 1; k < KW; ++k) r += sh[k][t];
+    }
     return r;
 }
 
-// Dot pass: partial[q][block] = sum V_q . w over this block's elements (q < NQ),
-// partial[NQ][block] = sum w . w.  NQ is the exact count (one instance per
-// count: guarded loads would cost a branch each and registers for the
-// predicates); all loads of one element are issued before any use.
-template <int NQ>
-__global__ __launch_bounds__(256) void k_orth(int64_t n, const double* __restrict__ V, int64_t ldv,
-                                              const double* __restrict__ w, double* __restrict__ partial) {
-    __shared__ double sh[4];
-    double acc[NQ > 0 ? NQ : 1];
+// Publishes this block's N sums (thread q < N holds sum q) and tells whether it is
+// the last block to do so; that block gets the totals in res (all threads, after
+// the return) and leaves the counters at zero for the next launch.  The partials go
+// through device-scope stores and loads: a store has reached the point all compute
+// units see when its wait ends, so the counter's increment follows the block's
+// partials without flushing the cache (a release at device scope writes back the
+// XCD's whole L2, once per block).
+template <int N>
+__device__ __forceinline__ bool last_block_totals(double mine, double* partial, uint32_t* counter, double* res) {
+    __shared__ int last;
+    const int t = threadIdx.x, nb = gridDim.x;
+    if (t < N)
+        __hip_atomic_store(partial + (int64_t)t * KBLOCKS + blockIdx.x, mine, __ATOMIC_RELAXED,
+                           __HIP_MEMORY_SCOPE_AGENT);
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __syncthreads();
+    // increments of one address take 11 ns each (1024 blocks: 12 us at the end of a short
+    // pass), so the blocks count in KCOUNTERS groups, and the groups' last ones in one more
+    if (t == 0) {
+        const int k = blockIdx.x % KCOUNTERS, members = (nb - k + KCOUNTERS - 1) / KCOUNTERS;
+        uint32_t* sub = counter + (1 + k) * KCOUNTER_STRIDE;
+        last = 0;
+        if (__hip_atomic_fetch_add(sub, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == (uint32_t)members - 1u) {
+            __hip_atomic_store(sub, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            const int groups = nb < KCOUNTERS ? nb : KCOUNTERS;
+            last = __hip_atomic_fetch_add(counter, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) ==
+                   (uint32_t)groups - 1u;
+            if (last) __hip_atomic_store(counter, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
+    }
+    __syncthreads();
+    if (!last) return false;
+    // 8 lanes per sum, all sums at once: lane l adds the blocks l, l + 8, ... in turn (16
+    // loads in flight), then the group (a wavefront per sum took the sums one after the other)
+    constexpr int G = 8, U = 16;
+    static_assert(N <= 2 * (KT / G), "two sums per group at most");
+    const int l = t % G;
+    for (int q = t / G; q < N; q += KT / G) {
+        double v = 0.0;
+        for (int b0 = l; b0 < nb; b0 += U * G) {
+            double x[U];
 #pragma unroll
-    for (int q = 0; q < NQ; ++q) acc[q] = 0.0;
-    double nn = 0.0;
-    const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-    for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < n; e += stride) {
-        double v[NQ > 0 ? NQ : 1];
+            for (int u = 0; u < U; ++u)
+                x[u] = b0 + u * G < nb ? __hip_atomic_load(partial + (int64_t)q * KBLOCKS + b0 + u * G,
+                                                           __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)
+                                       : 0.0;
 #pragma unroll
-        for (int q = 0; q < NQ; ++q) v[q] = V[q * ldv + e];
+            for (int u = 0; u < U; ++u) v += x[u];
+        }
+        v = group_sum<G>(v);
+        if (l == G - 1) res[q] = v;
+    }
+    __syncthreads();
+    return true;
+}
+
+// Dot pass: r_q = V_q . w (q < NQ) and, WITH_NORM, r_NQ = w . w.  NQ is the exact
+// count (one instance per count: guarded loads would cost a branch each and
+// registers for the predicates); all loads of one element are issued before any
+// use.  The last block writes kb.d1[q] = r_q (q < NQ), or *kb.nu2 = r_0 for a norm, and
+// the delayed reorthogonalisation's coefficients b_q = r_q (q < NQ - 1) and
+// c_j = (r_{NQ-1} - sum_q a_q r_q) / nu.  At 16.8M unknowns the pass streams 5.9 TB/s
+// (27 vectors 640 us); four wavefronts per unit are all the grid has, and without the
+// attribute the compiler kept some counts' loads back to fit eight (24 - 26, 29 and 30
+// vectors 800 - 880 us).
+template <int NQ, bool NORM>
+__global__ __launch_bounds__(KT) __attribute__((amdgpu_waves_per_eu(4, 4))) void k_orth(int64_t n, const double* __restrict__ V, int64_t ldv,
+                                             const double* __restrict__ w, KrylovBufs kb) {
+    constexpr int N = NORM ? 1 : NQ;
+    __shared__ double sh[KW][KMAXQ];
+    __shared__ double res[KMAXQ];
+    double acc[N];
+#pragma unroll
+    for (int q = 0; q < N; ++q) acc[q] = 0.0;
+    const int64_t stride = (int64_t)gridDim.x * KT;
+    for (int64_t e = (int64_t)blockIdx.x * KT + threadIdx.x; e < n; e += stride) {
         const double u = w[e];
+        if constexpr (NORM) {
+            acc[0] += u * u;
+        } else {
+            double v[N];
 #pragma unroll
-        for (int q = 0; q < NQ; ++q) acc[q] += v[q] * u;
-        nn += u * u;
-    }
+            for (int q = 0; q < N; ++q) v[q] = V[q * ldv + e];
 #pragma unroll
-    for (int q = 0; q < NQ; ++q) {
-        const double r = block_sum(acc[q], sh);
-        if (threadIdx.x == 0) partial[(int64_t)q * KBLOCKS + blockIdx.x] = r;
+            for (int q = 0; q < N; ++q) acc[q] += v[q] * u;
+        }
     }
-    const double r = block_sum(nn, sh);
-    if (threadIdx.x == 0) partial[(int64_t)NQ * KBLOCKS + blockIdx.x] = r;
+    const double mine = block_sums<N>(acc, sh);
+    if (!last_block_totals<N>(mine, kb.partial, kb.counter, res)) return;
+    const int t = threadIdx.x;
+    if constexpr (NORM) {
+        if (t == 0) *kb.nu2 = res[0];
+    } else {
+        if (t < NQ) kb.d1[t] = res[t];
+        if (t < NQ - 1) kb.coef[KC_B + t] = res[t];
+        if (t == 0) {
+            double ab = 0.0;
+            for (int k = 0; k < NQ - 1; ++k) ab += kb.coef[KC_A + k] * res[k];
+            kb.coef[KC_CJ] = (res[NQ - 1] - ab) * kb.coef[KC_INV_NU];
+        }
+    }
 }
 
 // Update pass of classical Gram-Schmidt with delayed reorthogonalisation
@@ -877,30 +961,31 @@ __global__ __launch_bounds__(256) void k_orth(int64_t n, const double* __restric
 // nu = |u - Q a|, and c_j = (u . w - a . b) / nu.  Per element:
 //   q  = (u - sum_k a_k Q_k) / nu            (the reorthogonalised candidate, over u)
 //   un = (w - sum_k b_k Q_k - c_j q) / nu     (the next candidate, projected once)
-// and the dots a' = [Q q]^T un and |un|^2 for the next step:
-// partial[k] = Q_k . un (k < NQ), partial[NQ] = q . un, partial[NQ + 1] = un . un.
-// NQ is the exact count, as in k_orth.
+// and the dots a' = [Q q]^T un and |un|^2 for the next step.  The last block
+// writes them out (d2, nu2), the next candidate's nu' = sqrt(|un|^2 - |a'|^2) (nu;
+// 0 when the candidate lies in the basis) and the next step's coefficients a' and
+// 1/nu', so the next step needs nothing from the host.  NQ is the exact count.
 template <int NQ>
-__global__ __launch_bounds__(256) void k_dcgs_update(int64_t n, const double* __restrict__ V, int64_t ldv,
-                                                     const double* __restrict__ coef, double* u,
-                                                     const double* __restrict__ w, double* __restrict__ out,
-                                                     double* __restrict__ partial) {
-    __shared__ double sh[4];
-    __shared__ double cab[2 * (NQ > 0 ? NQ : 1)];
+__global__ __launch_bounds__(KT) void k_dcgs_update(int64_t n, const double* __restrict__ V, int64_t ldv, double* u,
+                                                    const double* __restrict__ w, double* __restrict__ out,
+                                                    KrylovBufs kb) {
+    constexpr int NV = NQ > 0 ? NQ : 1;
+    __shared__ double sh[KW][KMAXQ];
+    __shared__ double res[KMAXQ];
+    __shared__ double cab[2 * NV];
     if (threadIdx.x < NQ) {
-        cab[threadIdx.x] = coef[KC_A + threadIdx.x];
-        cab[NQ + threadIdx.x] = coef[KC_B + threadIdx.x];
+        cab[threadIdx.x] = kb.coef[KC_A + threadIdx.x];
+        cab[NQ + threadIdx.x] = kb.coef[KC_B + threadIdx.x];
     }
-    const double inv_nu = coef[KC_INV_NU];
-    const double cj = coef[KC_CJ];
+    const double inv_nu = kb.coef[KC_INV_NU];
+    const double cj = kb.coef[KC_CJ];
     __syncthreads();
-    double acc[NQ > 0 ? NQ : 1];
+    double acc[NQ + 2];   // Q_k . un, q . un, un . un
 #pragma unroll
-    for (int k = 0; k < NQ; ++k) acc[k] = 0.0;
-    double accq = 0.0, nn = 0.0;
-    const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-    for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < n; e += stride) {
-        double v[NQ > 0 ? NQ : 1];
+    for (int k = 0; k < NQ + 2; ++k) acc[k] = 0.0;
+    const int64_t stride = (int64_t)gridDim.x * KT;
+    for (int64_t e = (int64_t)blockIdx.x * KT + threadIdx.x; e < n; e += stride) {
+        double v[NV];
 #pragma unroll
         for (int k = 0; k < NQ; ++k) v[k] = V[k * ldv + e];
         double q = u[e];
@@ -916,56 +1001,23 @@ __global__ __launch_bounds__(256) void k_dcgs_update(int64_t n, const double* __
         out[e] = un;
 #pragma unroll
         for (int k = 0; k < NQ; ++k) acc[k] += v[k] * un;
-        accq += q * un;
-        nn += un * un;
+        acc[NQ] += q * un;
+        acc[NQ + 1] += un * un;
     }
-#pragma unroll
-    for (int k = 0; k < NQ; ++k) {
-        const double r = block_sum(acc[k], sh);
-        if (threadIdx.x == 0) partial[(int64_t)k * KBLOCKS + blockIdx.x] = r;
-    }
-    double r = block_sum(accq, sh);
-    if (threadIdx.x == 0) partial[(int64_t)NQ * KBLOCKS + blockIdx.x] = r;
-    r = block_sum(nn, sh);
-    if (threadIdx.x == 0) partial[(int64_t)(NQ + 1) * KBLOCKS + blockIdx.x] = r;
-}
-
-// Final sums in a fixed order, one wavefront per slot: lane l adds the blocks
-// l, l + 64, ... in turn, then a butterfly over the wavefront.  r_q for q = 0..nq:
-// d[q] = r_q (q < nq), *nu = r_nq; with coef, the delayed-reorthogonalisation
-// coefficients b (r_q, q < nq - 1) and c_j (see launch_orth_reduce).
-__global__ __launch_bounds__(1024) void k_orth_reduce(const double* __restrict__ partial, int nb, int nq,
-                                                      double* __restrict__ d, double* __restrict__ nu,
-                                                      double* __restrict__ coef) {
-    __shared__ double res[KMAXQ];
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & (WAVE - 1);
-    for (int q = wave; q <= nq; q += (int)(blockDim.x >> 6)) {
-        // all of a lane's loads issued before the first add (KBLOCKS / WAVE of them)
-        static_assert(KBLOCKS % WAVE == 0, "whole rounds of block partials");
-        double t[KBLOCKS / WAVE];
-#pragma unroll
-        for (int u = 0; u < KBLOCKS / WAVE; ++u) {
-            const int b = lane + u * WAVE;
-            t[u] = b < nb ? partial[(int64_t)q * KBLOCKS + b] : 0.0;
-        }
-        double v = 0.0;
-#pragma unroll
-        for (int u = 0; u < KBLOCKS / WAVE; ++u) v += t[u];
-#pragma unroll
-        for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, WAVE);
-        if (lane == 0) res[q] = v;
-    }
-    __syncthreads();
+    const double mine = block_sums<NQ + 2>(acc, sh);
+    if (!last_block_totals<NQ + 2>(mine, kb.partial, kb.counter, res)) return;
     const int t = threadIdx.x;
-    if (d != nullptr && t < nq) d[t] = res[t];
-    if (nu != nullptr && t == 0) *nu = res[nq];
-    if (coef != nullptr) {
-        if (t < nq - 1) coef[KC_B + t] = res[t];
-        if (t == 0) {
-            double ab = 0.0;
-            for (int k = 0; k < nq - 1; ++k) ab += coef[KC_A + k] * res[k];
-            coef[KC_CJ] = (res[nq - 1] - ab) * coef[KC_INV_NU];
-        }
+    // every block has read its coefficients before it published its sums
+    if (t <= NQ) {
+        kb.d2[t] = res[t];
+        kb.coef[KC_A + t] = res[t];
+    }
+    if (t == 0) {
+        double nu2 = res[NQ + 1];
+        for (int k = 0; k <= NQ; ++k) nu2 -= res[k] * res[k];
+        const double nu = nu2 > 0.0 && nu2 <= 1.7976931348623157e308 ? sqrt(nu2) : 0.0;
+        *kb.nu = nu;
+        kb.coef[KC_INV_NU] = nu > 0.0 ? 1.0 / nu : 0.0;
     }
 }
 
@@ -1026,7 +1078,10 @@ __global__ void k_seeded(int64_t n, uint64_t seed, double* v) {
     }
 }
 
-int krylov_blocks(int64_t n) { return (int)std::max<int64_t>(1, std::min<int64_t>(KBLOCKS, ceil_div(n, 1024))); }
+// one element per thread up to 262,144 unknowns: a small system's pass is a chain of
+// latencies, and fewer, longer blocks only lengthen it (24,576 unknowns, 27 vectors, with
+// the final sums: 24 blocks and a launch for the sums 26 us, 96 blocks 8 us)
+int krylov_blocks(int64_t n) { return (int)std::max<int64_t>(1, std::min<int64_t>(KBLOCKS, ceil_div(n, KT))); }
 
 static unsigned stream_grid(int64_t n) {
     return (unsigned)std::max<int64_t>(1, std::min<int64_t>(4096, ceil_div(n, 256)));
@@ -1043,58 +1098,51 @@ struct OrthArgs {
     const double* V;
     int64_t ldv;
     const double* w;
-    double* partial;
-    int nblocks;
+    const KrylovBufs& kb;
     hipStream_t s;
 };
 template <int Q>
 struct OrthLaunch {
     using Args = OrthArgs;
-    static void run(const OrthArgs& a) { k_orth<Q><<<a.nblocks, 256, 0, a.s>>>(a.n, a.V, a.ldv, a.w, a.partial); }
+    static void run(const OrthArgs& a) {
+        if constexpr (Q > 0) k_orth<Q, false><<<krylov_blocks(a.n), KT, 0, a.s>>>(a.n, a.V, a.ldv, a.w, a.kb);
+    }
 };
 
 struct DcgsArgs {
     int64_t n;
     const double* V;
     int64_t ldv;
-    const double* coef;
     double* u;
     const double* w;
     double* out;
-    double* partial;
-    int nblocks;
+    const KrylovBufs& kb;
     hipStream_t s;
 };
 template <int Q>
 struct DcgsLaunch {
     using Args = DcgsArgs;
     static void run(const DcgsArgs& a) {
-        k_dcgs_update<Q><<<a.nblocks, 256, 0, a.s>>>(a.n, a.V, a.ldv, a.coef, a.u, a.w, a.out, a.partial);
+        k_dcgs_update<Q><<<krylov_blocks(a.n), KT, 0, a.s>>>(a.n, a.V, a.ldv, a.u, a.w, a.out, a.kb);
     }
 };
 
-void launch_orth(int64_t n, int nq, const double* V, int64_t ldv, const double* w, double* partial, int nblocks,
+void launch_norm2(int64_t n, const double* w, const KrylovBufs& kb, hipStream_t s) {
+    k_orth<1, true><<<krylov_blocks(n), KT, 0, s>>>(n, nullptr, 0, w, kb);
+    MB_LAUNCH_CHECK();
+}
+
+void launch_orth(int64_t n, int nq, const double* V, int64_t ldv, const double* w, const KrylovBufs& kb,
                  hipStream_t s) {
-    MB_CHECK(nq >= 0 && nq <= KMAXQ - 1 && nq <= 32 && nblocks >= 1 && nblocks <= KBLOCKS, MBAMG_E_INVALID,
-             "too many Krylov vectors");
-    by_count<OrthLaunch>(nq, std::make_integer_sequence<int, 33>{}, OrthArgs{n, V, ldv, w, partial, nblocks, s});
+    MB_CHECK(nq >= 1 && nq <= KMAXQ - 1 && nq <= 32, MBAMG_E_INVALID, "too many Krylov vectors");
+    by_count<OrthLaunch>(nq, std::make_integer_sequence<int, 33>{}, OrthArgs{n, V, ldv, w, kb, s});
     MB_LAUNCH_CHECK();
 }
 
-void launch_dcgs_update(int64_t n, int nq, const double* V, int64_t ldv, const double* coef, double* u,
-                        const double* w, double* out, double* partial, int nblocks, hipStream_t s) {
-    MB_CHECK(nq >= 0 && nq <= KMAXQ - 2 && nq <= 31 && nblocks >= 1 && nblocks <= KBLOCKS, MBAMG_E_INVALID,
-             "too many Krylov vectors");
-    by_count<DcgsLaunch>(nq, std::make_integer_sequence<int, 32>{},
-                         DcgsArgs{n, V, ldv, coef, u, w, out, partial, nblocks, s});
-    MB_LAUNCH_CHECK();
-}
-
-void launch_orth_reduce(const double* partial, int nblocks, int nq, double* d, double* nu, double* coef,
-                        hipStream_t s) {
-    MB_CHECK(nq >= 0 && nq <= KMAXQ - 1 && nblocks >= 1 && nblocks <= KBLOCKS && (coef == nullptr || nq >= 1),
-             MBAMG_E_INVALID, "invalid Krylov reduction");
-    k_orth_reduce<<<1, 1024, 0, s>>>(partial, nblocks, nq, d, nu, coef);
+void launch_dcgs_update(int64_t n, int nq, const double* V, int64_t ldv, double* u, const double* w, double* out,
+                        const KrylovBufs& kb, hipStream_t s) {
+    MB_CHECK(nq >= 0 && nq <= KMAXQ - 2 && nq <= 31, MBAMG_E_INVALID, "too many Krylov vectors");
+    by_count<DcgsLaunch>(nq, std::make_integer_sequence<int, 32>{}, DcgsArgs{n, V, ldv, u, w, out, kb, s});
     MB_LAUNCH_CHECK();
 }
 
