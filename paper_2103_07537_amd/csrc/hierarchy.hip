@@ -2362,32 +2362,26 @@ static void apply_precond(mbamg_hierarchy* h, const double* v, double* z64, floa
     }
 }
 
-static void to_colour(mbamg_hierarchy* h, const double* src, double* dst, hipStream_t s) {
-    if (h->nb > 2) {
-        const GLevel& L0 = *h->GL[0];
-        for (int f = 0; f < L0.nb; ++f)
-            launch_gather(L0.n, L0.d[f], L0.blk[f].d_perm.p, src + L0.off[f], dst + L0.off[f], s);
-        return;
+static ReorderArgs reorder_args(mbamg_hierarchy* h) {
+    ReorderArgs a{};
+    a.nb = h->nb;
+    for (int f = 0; f < h->nb; ++f) {
+        const BlockLevel& B = h->nb > 2 ? h->GL[0]->blk[f] : h->L[0]->blk[f];
+        MB_CHECK(B.d_iperm.p, MBAMG_E_STATE, "internal: finest-level order missing");
+        a.n[f] = h->nb > 2 ? h->GL[0]->n : h->L[0]->nodes(f);
+        a.d[f] = h->nb > 2 ? h->GL[0]->d[f] : h->L[0]->d[f];
+        a.off[f] = f == 0 ? 0 : a.off[f - 1] + (int64_t)a.n[f - 1] * a.d[f - 1];
+        a.iperm[f] = B.d_iperm.p;
     }
-    Level& L0 = *h->L[0];
-    MB_CHECK(L0.blk[0].d_perm.p && L0.blk[1].d_perm.p, MBAMG_E_STATE, "internal: finest-level order missing");
-    const int64_t n0 = (int64_t)L0.n * L0.d[0];
-    for (int f = 0; f < 2; ++f)
-        launch_gather(L0.nodes(f), L0.d[f], L0.blk[f].d_perm.p, src + (f ? n0 : 0), dst + (f ? n0 : 0), s);
+    return a;
+}
+
+static void to_colour(mbamg_hierarchy* h, const double* src, double* dst, hipStream_t s) {
+    launch_reorder(true, reorder_args(h), src, dst, s);
 }
 
 static void from_colour(mbamg_hierarchy* h, const double* src, double* dst, hipStream_t s) {
-    if (h->nb > 2) {
-        const GLevel& L0 = *h->GL[0];
-        for (int f = 0; f < L0.nb; ++f)
-            launch_scatter(L0.n, L0.d[f], L0.blk[f].d_perm.p, src + L0.off[f], dst + L0.off[f], s);
-        return;
-    }
-    Level& L0 = *h->L[0];
-    MB_CHECK(L0.blk[0].d_perm.p && L0.blk[1].d_perm.p, MBAMG_E_STATE, "internal: finest-level order missing");
-    const int64_t n0 = (int64_t)L0.n * L0.d[0];
-    for (int f = 0; f < 2; ++f)
-        launch_scatter(L0.nodes(f), L0.d[f], L0.blk[f].d_perm.p, src + (f ? n0 : 0), dst + (f ? n0 : 0), s);
+    launch_reorder(false, reorder_args(h), src, dst, s);
 }
 
 // A x on the finest level (colour order), FP64

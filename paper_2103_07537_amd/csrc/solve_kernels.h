@@ -287,7 +287,15 @@ void launch_axpby(int64_t n, double a, const double* x, double b, double* y, hip
 void launch_seeded(int64_t n, uint64_t seed, double* v, hipStream_t s);
 int krylov_blocks(int64_t n);
 void launch_gather(int n_rows, int d, const int32_t* perm, const double* src, double* dst, hipStream_t s);
-void launch_scatter(int n_rows, int d, const int32_t* perm, const double* src, double* dst, hipStream_t s);
+// all blocks of a vector between the interface's (natural) order and the colour order
+struct ReorderArgs {
+    int nb;
+    int n[SWEEP_MAX_BLOCKS], d[SWEEP_MAX_BLOCKS];
+    int64_t off[SWEEP_MAX_BLOCKS];               // first entry of each block
+    const int32_t* iperm[SWEEP_MAX_BLOCKS];      // colour position of every natural row
+    int blocks[SWEEP_MAX_BLOCKS];                // (set by the launcher)
+};
+void launch_reorder(bool to_colour, ReorderArgs a, const double* src, double* dst, hipStream_t s);
 void launch_cast64to32(int64_t n, const double* a, float* b, hipStream_t s);
 void launch_cast32to64(int64_t n, const float* a, double* b, hipStream_t s);
 
