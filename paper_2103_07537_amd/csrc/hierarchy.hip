@@ -1744,52 +1744,88 @@ static void smooth_fc(mbamg_hierarchy* h, int l, bool zero, const T* b, const T*
         }
 }
 
-// The same for a block row in grouped form.  The first inner sweep is one launch
-// over all colours; a further one continues from t in place, where a row waits
-// for nothing, so its colours are launched one by one -- as they all are while
-// single launches are timed.
+// Block rows of at most this many launch positions (slices) share a launch.  It saves
+// a launch and its start, 3 - 5 us, but block 1's coupling sums then wait for block
+// 0's values and compute their damping, which costs more where a slice is not waited
+// for anyway.  Both sub-solves of a sweep, two launches against one: 583 nodes in 10
+// colours (146 slices) 30 -> 28 us, 976 nodes (122 slices, 3 x 3 blocks) 16.0 -> 13.9 us;
+// 375 nodes in 26 colours (375 slices, FP32) 1 % slower over the whole cycle, 9,267 nodes
+// (1,159 slices) 22 -> 24 us, 188,588 nodes (11,787 slices) 228 -> 259 us.  A solve of
+// 24,576 unknowns (levels of 256 and 74 slices) 6.3 -> 5.7 ms.
+constexpr int BOTH_BLOCKS_MAX = 256;
+
+// Algorithm 1 on a level in grouped form, from x (NULL: zero) into xn; b, x and xn
+// hold both blocks.  The first inner sweep of a block is one launch over all colours,
+// on small levels over both blocks.  A further inner sweep continues from t in place,
+// where a row waits for nothing, so its colours are launched one by one -- as they
+// all are while single launches are timed.
 template <class T>
-static void sweep_block(mbamg_hierarchy* h, int l, int f, bool zero, const T* b, const T* x, T* xn, const T* xg,
-                        hipStream_t s) {
+static void sweep_level(mbamg_hierarchy* h, int l, bool zero, const T* b, const T* x, T* xn, hipStream_t s) {
     Level& Lv = *h->L[l];
-    BlockLevel& B = Lv.blk[f];
     Vecs<T>& V = vecs<T>(Lv);
-    const int64_t off = f == 0 ? 0 : (int64_t)Lv.n * Lv.d[0];
+    const int64_t n0 = (int64_t)Lv.n * Lv.d[0];
     const bool timed = h->time_launches();
-    T* const t[2] = {V.t.p + off, V.t2.p + off};
-    SweepArgs<T> a{};
+    const bool together = !timed && h->p.inner_sweeps == 1 && Lv.blk[0].colour_rec.back() <= BOTH_BLOCKS_MAX &&
+                          Lv.blk[1].colour_rec.back() <= BOTH_BLOCKS_MAX;
+    T* const t[2] = {V.t.p, V.t2.p};
+    Sweep2Args<T> a{};
     a.shape = Lv.shape;
-    a.spread = few_per_colour(B);
-    a.rec = B.recs.p;
-    a.lg = log2_of(B.group);
-    a.off = gview<T>(B.off);
-    a.cpl = gview<T>(B.cpl);
-    a.dinv = gdinv<T>(B);
-    a.b = b;
-    a.x = x;
-    a.t = t[V.turn_t];
-    a.xn = xn;
-    a.xg = xg;
-    a.omega = (T)h->p.omega;
-    a.w_row = Lv.damped ? wrow<T>(B) : nullptr;
-    for (int k = 0; k < h->p.inner_sweeps; ++k) {
-        const int step = (timed || k > 0) ? 1 : std::max(1, B.n_colours);
-        a.inplace = k > 0;
-        a.t_reset = k == 0 ? t[1 - V.turn_t] : nullptr;
-        for (int c = 0; c < B.n_colours; c += step) {
-            a.begin = B.colour_rec[c];
-            a.count = B.colour_rec[c + step] - a.begin;
-            a.ticket = V.tickets.p + V.turn_ticket;
-            a.ticket_next = V.tickets.p + (1 - V.turn_ticket);
-            const bool skip = zero && k == 0 && c == 0;
-            const double bytes = timed ? gs_bytes(B, c, zero, skip, xg != nullptr, (int)sizeof(T), Lv.d[1 - f]) : 0.0;
-            TimerScope ts(h, s, timed, launch_kind(l, (!zero && xg) ? 0 : 3), bytes);
-            if (a.count == 0) continue;
-            launch_sweep<T>(B.d, zero, xg != nullptr, a, s);
-            V.turn_ticket = 1 - V.turn_ticket;
+    a.spread = few_per_colour(Lv.blk[0]) && few_per_colour(Lv.blk[1]);
+    for (int f = 0; f < 2; ++f) {
+        const BlockLevel& B = Lv.blk[f];
+        const int64_t off = f == 0 ? 0 : n0, offg = f == 0 ? n0 : 0;
+        SweepArgs<T>& q = a.s[f];
+        q.rec = B.recs.p;
+        q.lg = log2_of(B.group);
+        q.off = gview<T>(B.off);
+        q.dinv = gdinv<T>(B);
+        q.b = b + off;
+        q.x = x ? x + off : nullptr;
+        q.t = t[V.turn_t] + off;
+        q.t_reset = t[1 - V.turn_t] + off;
+        q.xn = xn + off;
+        q.omega = (T)h->p.omega;
+        q.w_row = Lv.damped ? wrow<T>(B) : nullptr;
+        q.count = together ? B.colour_rec.back() : 0;
+        a.cpl[f] = gview<T>(B.cpl);
+        // block 0 takes the incoming x1, block 1 (Algorithm 1) the already updated x0
+        SweepOperand<T>& o = a.xg[f];
+        if (f == 0) o.x = x ? x + offg : nullptr;
+        else if (!together) o.x = xn + offg;
+        else o = {x ? x + offg : nullptr, t[V.turn_t] + offg, Lv.damped ? wrow<T>(Lv.blk[0]) : nullptr,
+                  (T)h->p.omega};
+    }
+    auto launch = [&] {
+        a.ticket = V.tickets.p + V.turn_ticket;
+        a.ticket_next = V.tickets.p + (1 - V.turn_ticket);
+        launch_sweep<T>(Lv.d[0], zero, a, s);
+        V.turn_ticket = 1 - V.turn_ticket;
+    };
+    if (together) launch();
+    const Sweep2Args<T> each = a;
+    for (int f = 0; f < 2 && !together; ++f) {
+        const BlockLevel& B = Lv.blk[f];
+        a.s[0] = each.s[f];
+        a.cpl[0] = each.cpl[f];
+        a.xg[0] = each.xg[f];
+        a.spread = few_per_colour(B);
+        SweepArgs<T>& q = a.s[0];
+        const bool has_cpl = a.xg[0].x != nullptr;
+        for (int k = 0; k < h->p.inner_sweeps; ++k) {
+            const int step = (timed || k > 0) ? 1 : std::max(1, B.n_colours);
+            q.inplace = k > 0;
+            if (k > 0) q.t_reset = nullptr;
+            for (int c = 0; c < B.n_colours; c += step) {
+                q.begin = B.colour_rec[c];
+                q.count = B.colour_rec[c + step] - q.begin;
+                const bool skip = zero && k == 0 && c == 0;
+                const double bytes = timed ? gs_bytes(B, c, zero, skip, has_cpl, (int)sizeof(T), Lv.d[1 - f]) : 0.0;
+                TimerScope ts(h, s, timed, launch_kind(l, (!zero && has_cpl) ? 0 : 3), bytes);
+                if (q.count > 0) launch();
+            }
         }
     }
-    if (f == 1) V.turn_t = 1 - V.turn_t;   // both blocks' parts of t are written
+    V.turn_t = 1 - V.turn_t;
 }
 
 template <class T>
@@ -1802,10 +1838,6 @@ static void smooth_block(mbamg_hierarchy* h, int l, int f, bool zero, const T* b
     T* tbuf = vecs<T>(Lv).t.p + off;
     const bool has_cpl = xg != nullptr;
     const bool timed = h->time_launches();
-    if (B.group > 1) {
-        sweep_block<T>(h, l, f, zero, b, x, xn, xg, s);
-        return;
-    }
     for (int k = 0; k < h->p.inner_sweeps; ++k) {
         for (int c = 0; c < B.n_colours; ++c) {
             GsArgs<T> a{};
@@ -1905,8 +1937,9 @@ static void vcycle_level(mbamg_hierarchy* h, int l, const T* b, T* out, hipStrea
     auto sweep = [&](bool zero) {
         int nx = cur < 0 ? 0 : 1 - cur;
         T* X = cur < 0 ? nullptr : buf[cur];
-        if (Lv.fc) {
-            smooth_fc<T>(h, l, zero, b, X, buf[nx], s);
+        if (Lv.fc || Lv.blk[0].group > 1) {
+            if (Lv.fc) smooth_fc<T>(h, l, zero, b, X, buf[nx], s);
+            else sweep_level<T>(h, l, zero, b, X, buf[nx], s);
             cur = nx;
             return;
         }
@@ -2272,7 +2305,7 @@ static void gen_vcycle_level(mbamg_hierarchy* h, int l, const double* b, double*
                 const double* xg = g < f ? XN + Lv.off[g] : (X ? X + Lv.off[g] : nullptr);
                 if (g != f && xg && Lv.A[f][g].nnzb > 0) a.cpl[a.n_cpl++] = group_part(Lv.C[f][g], xg);
             }
-            a.s.spread = few_per_colour(B);
+            a.spread = few_per_colour(B);
             a.s.rec = B.recs.p;
             a.s.lg = log2_of(B.group);
             a.s.off = gview<double>(B.off);
@@ -2289,8 +2322,8 @@ static void gen_vcycle_level(mbamg_hierarchy* h, int l, const double* b, double*
                 for (int c = 0; c < B.n_colours; c += step) {
                     a.s.begin = B.colour_rec[c];
                     a.s.count = B.colour_rec[c + step] - a.s.begin;
-                    a.s.ticket = V.tickets.p + V.turn_ticket;
-                    a.s.ticket_next = V.tickets.p + (1 - V.turn_ticket);
+                    a.ticket = V.tickets.p + V.turn_ticket;
+                    a.ticket_next = V.tickets.p + (1 - V.turn_ticket);
                     if (a.s.count == 0) continue;
                     launch_sweep_n(B.d, zero, a, s);
                     V.turn_ticket = 1 - V.turn_ticket;

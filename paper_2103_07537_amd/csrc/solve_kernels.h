@@ -109,26 +109,45 @@ struct GroupView {
     const T* val;
 };
 
-// One Gauss-Seidel sub-solve of a block row in grouped form, over the launch
-// positions [begin, begin + count) of its record list (whole colours, ascending).
+// One block row's share of a sweep launch in grouped form: the launch positions
+// [begin, begin + count) of its record list (whole colours, ascending).
 template <class T>
 struct SweepArgs {
-    int shape;
     const SweepRec* rec;
     int begin, count;
-    int spread;                // few workgroups per colour: one per compute unit
     int lg;                    // log2 of the lanes per row
-    GroupView<T> off, cpl;
+    GroupView<T> off;
     const T* dinv;             // d x d per row, colour order
     const T* b;
     const T* x;                // current iterate (unused when starting from zero)
     T* t;                      // undamped iterate x + e: written, and awaited for earlier colours
     T* t_reset;                // the other undamped buffer: this launch's rows are set to "not yet written" (NULL: no)
     T* xn;                     // damped result x + omega e
-    const T* xg;               // iterate of the other block for the coupling term
     int inplace;               // a further inner sweep: every neighbour's value comes from t
     T omega;
     const T* w_row;            // per-row damping (NULL: use omega)
+};
+
+// The vector a coupling block multiplies: x (t NULL), or the damped result of a
+// block relaxed in the same launch, x + omega (t - x) (x NULL: omega t), with t
+// awaited.
+template <class T>
+struct SweepOperand {
+    const T* x;
+    const T* t;
+    const T* w_row;
+    T omega;
+};
+
+// Algorithm 1 over two blocks of one size: block 0's positions, then block 1's; or
+// one block alone, in the first places (the second count is zero then).
+template <class T>
+struct Sweep2Args {
+    int shape;
+    int spread;                // few workgroups per colour: one per compute unit
+    SweepArgs<T> s[2];
+    GroupView<T> cpl[2];
+    SweepOperand<T> xg[2];     // x and t NULL: no coupling term; t: launches of both blocks only
     uint32_t* ticket;          // zero at launch
     uint32_t* ticket_next;     // set to zero for the next launch
 };
@@ -144,9 +163,12 @@ struct GroupPart {
     int bc;
 };
 struct SweepNArgs {
-    SweepArgs<double> s;       // s.cpl and s.xg unused
+    SweepArgs<double> s;
+    int spread;
     int n_cpl;
     GroupPart cpl[SWEEP_MAX_BLOCKS - 1];
+    uint32_t* ticket;
+    uint32_t* ticket_next;
 };
 // r_f = b_f - sum_g A_fg x_g (b NULL: w_f = sum_g A_fg x_g) for every block f
 struct ResidNArgs {
@@ -240,7 +262,7 @@ void launch_gs_fc(int d, int P, bool zero_x, const GsFcArgs<T>& a, hipStream_t s
 // positions of a record list are taken this many at a time: every colour's are padded to a multiple
 constexpr int SWEEP_WAVES = 8;
 template <class T>
-void launch_sweep(int d, bool zero_x, bool has_cpl, const SweepArgs<T>& a, hipStream_t s);
+void launch_sweep(int d, bool zero_x, const Sweep2Args<T>& a, hipStream_t s);
 template <class T>
 void launch_resid_group(int d, const ResidGroupArgs<T>& a, hipStream_t s);
 void launch_sweep_n(int d, bool zero_x, const SweepNArgs& a, hipStream_t s);

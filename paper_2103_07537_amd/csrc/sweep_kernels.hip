@@ -61,12 +61,27 @@ __device__ __forceinline__ U uniform_load(const U* p) {
 // finishes with NaN results instead of hanging.
 constexpr int SWEEP_MAX_ROUNDS = 1 << 20;
 
+// The damped update of one value; written by a sweep and recomputed by the blocks
+// that follow in the same launch.
+template <class T>
+__device__ __forceinline__ T damped(T x, T w, T t) { return x + w * (t - x); }
+
+// x_j of a coupling operand whose block is relaxed in this launch, from the awaited t_j
+template <class T, int D>
+__device__ __forceinline__ void operand_value(const SweepOperand<T>& o, int j, const T (&xo)[D], T (&v)[D]) {
+    const T w = o.w_row ? o.w_row[j] : o.omega;
+#pragma unroll
+    for (int c = 0; c < D; ++c) v[c] = o.x ? damped(xo[c], w, v[c]) : w * v[c];
+}
+
 // acc -= sum over the slice's slots of one part.  MODE 0: x_j from xa.  MODE 1:
 // columns below cstart from ta (awaited), others from xa.  MODE 2: columns below
-// cstart from ta (awaited), others contribute 0.
+// cstart from ta (awaited), others contribute 0.  MODE 3: the coupling operand op,
+// every column awaited.
 template <class T, int D, int MODE, int S>
 __device__ __forceinline__ void group_sub(const GroupView<T>& A, int w, int cb, int lane, const T* __restrict__ xa,
-                                          const T* ta, int cstart, T (&acc)[D]) {
+                                          const T* ta, int cstart, T (&acc)[D],
+                                          const SweepOperand<T>* op = nullptr) {
     constexpr int CH = 2;
     for (int t0 = 0; t0 < w; t0 += CH) {
         int j[CH];
@@ -81,7 +96,7 @@ __device__ __forceinline__ void group_sub(const GroupView<T>& A, int w, int cb, 
             j[u] = live ? A.col[sl * WAVE + lane] : -1;
         }
         constexpr int NE = shape_entries<D, S>();
-        T v[CH][NE], xj[CH][D];
+        T v[CH][NE], xj[CH][D], xo[MODE == 3 ? CH : 1][D];
 #pragma unroll
         for (int u = 0; u < CH; ++u) load_masked<T, NE>(A.val + vg[u] * WAVE + lane, m[u], v[u]);
         // every load of the chunk is issued before the first value is looked at
@@ -90,9 +105,14 @@ __device__ __forceinline__ void group_sub(const GroupView<T>& A, int w, int cb, 
         for (int u = 0; u < CH; ++u) {
 #pragma unroll
             for (int c = 0; c < D; ++c) xj[u][c] = T(0);
-            await[u] = MODE != 0 && j[u] >= 0 && j[u] < cstart;
+            await[u] = MODE != 0 && j[u] >= 0 && (MODE == 3 || j[u] < cstart);
+            if (MODE == 3) {
+#pragma unroll
+                for (int c = 0; c < D; ++c) xo[u][c] = T(0);
+                if (xa && j[u] >= 0) load_vec<T, D>(xa + (int64_t)j[u] * D, xo[u]);
+            }
             if (await[u]) load_shared_vec<T, D>(ta + (int64_t)j[u] * D, xj[u]);
-            else if (MODE != 2 && j[u] >= 0) load_vec<T, D>(xa + (int64_t)j[u] * D, xj[u]);
+            else if (MODE < 2 && j[u] >= 0) load_vec<T, D>(xa + (int64_t)j[u] * D, xj[u]);
         }
         if (MODE != 0) {
             for (int round = 0; round < SWEEP_MAX_ROUNDS; ++round) {
@@ -107,6 +127,11 @@ __device__ __forceinline__ void group_sub(const GroupView<T>& A, int w, int cb, 
                 for (int u = 0; u < CH; ++u)
                     if (await[u]) load_shared_vec<T, D>(ta + (int64_t)j[u] * D, xj[u]);
             }
+        }
+        if (MODE == 3) {
+#pragma unroll
+            for (int u = 0; u < CH; ++u)
+                if (j[u] >= 0) operand_value<T, D>(*op, j[u], xo[u], xj[u]);
         }
 #pragma unroll
         for (int u = 0; u < CH; ++u) block_sub<T, D, S>(v[u], xj[u], acc);
@@ -153,20 +178,24 @@ __device__ __forceinline__ void group_all_sum(T (&acc)[D], int lg) {
         for (int r = 0; r < D; ++r) acc[r] += __shfl_xor(acc[r], 32, WAVE);
 }
 
-// All colours of one block's Gauss-Seidel sub-solve in one launch (the
-// arithmetic of k_gs).  A colour pass on a coarse level is a few microseconds
-// of launch and dependent loads whatever its size, and one such pass per colour
-// was most of a small system's cycle.  Here the rows wait for their own
+// Algorithm 1's Gauss-Seidel sub-solves in one launch, all colours of block 0, then
+// all of block 1 (the arithmetic of k_gs).  A colour pass on a coarse level is a few
+// microseconds of launch and dependent loads whatever its size, and one such pass
+// per colour was most of a small system's cycle.  Here the rows wait for their own
 // neighbours instead: a row of colour c reads t_j of its neighbours of earlier
 // colours with device-scope loads and repeats them until the values are there
-// ("unwritten" before).  The hop from one workgroup's store to another's load
-// is 0.5 us, against 4.0 - 5.0 us per launched colour pass.
+// ("unwritten" before); a row of block 1 does the same for the rows of block 0 it is
+// coupled to and applies their damping itself.  The hop from one workgroup's store
+// to another's load is 0.5 us, against 4.0 - 5.0 us per launched colour pass.
 //
-// Every wait ends: a workgroup takes its positions of the record list by an
-// atomic ticket, the list is ordered by colour, and a position waits only for
-// positions of earlier colours, whose tickets were taken before by workgroups
-// that are already running.  The tickets are one counter (11 ns each), so a
-// workgroup takes SWEEP_WAVES slices per ticket.
+// Every wait ends: a workgroup takes its positions of the record lists by an atomic
+// ticket, the lists are ordered by block and colour, and a position waits only for
+// positions of earlier colours or blocks, whose tickets were taken before by
+// workgroups that are already running.  The tickets are one counter (11 ns each),
+// so a workgroup takes SWEEP_WAVES slices per ticket.
+//
+// A launch takes both blocks on small levels and one on larger ones (see
+// BOTH_BLOCKS_MAX).
 //
 // The two undamped buffers of a level take turns: a launch writes t and sets its
 // rows of the other buffer to "unwritten" for the next launch.
@@ -174,19 +203,18 @@ __device__ __forceinline__ void group_all_sum(T (&acc)[D], int lg) {
 // used: more than half of a compute unit's 160 KiB, so that each unit takes one
 // workgroup and a colour's rows spread over the chip.  Without it the dispatcher
 // put several on some units and none on others (13,945 rows in 9 colours, 49
-// workgroups per colour: 31 us a sweep instead of 20; 82 per colour: 112 us instead
+// workgroups per colour: 31 us a sweep instead of 20; 164 per colour: 112 us instead
 // of 110).  With more than half the units' number per colour they spread by
 // themselves, and a second workgroup per unit hides latency (four blocks of
 // 64,000 rows, 250 per colour: 505 us per V-cycle with the limit, 468 without).
 static unsigned sweep_lds(int spread) { return spread ? 84 * 1024 : 0; }
 
 // This wavefront's position of the launch (all of a workgroup call it).
-template <class T>
-__device__ __forceinline__ int sweep_position(const SweepArgs<T>& a) {
+__device__ __forceinline__ int sweep_position(uint32_t* ticket, uint32_t* ticket_next) {
     __shared__ int tick;
     if (threadIdx.x == 0) {
-        const uint32_t k = __hip_atomic_fetch_add(a.ticket, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        if (k == 0) *a.ticket_next = 0u;
+        const uint32_t k = __hip_atomic_fetch_add(ticket, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (k == 0) *ticket_next = 0u;
         tick = (int)k;
     }
     __syncthreads();
@@ -221,22 +249,29 @@ __device__ __forceinline__ void sweep_slice(const SweepArgs<T>& a, const SweepRe
     T tn = T(0);
 #pragma unroll
     for (int c = 0; c < D; ++c) tn += dv[c] * (bb[c] + acc[c]);
-    const T xn = ZX ? wgt * tn : xo + wgt * (tn - xo);
+    const T xn = ZX ? wgt * tn : damped(xo, wgt, tn);
     a.xn[at] = xn;
     if (a.t_reset) a.t_reset[at] = unwritten_value<T>();
     if (unwritten(tn)) tn = T(NAN);
     __hip_atomic_store(a.t + at, tn, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-template <class T, int D, bool ZX, bool CPL, int S>
-__global__ __launch_bounds__(SWEEP_WAVES * WAVE) void k_sweep(SweepArgs<T> a) {
-    const int pos = sweep_position(a);
-    if (pos >= a.count) return;   // whole wavefronts; no barrier follows
-    const SweepRec rec = load_rec(a.rec + a.begin + pos);
+// BOTH: positions of both blocks, block 1's coupling operand awaited; otherwise those
+// of one block, in the arguments' first places, with every operand complete.
+template <class T, int D, bool ZX, int S, bool BOTH>
+__global__ __launch_bounds__(SWEEP_WAVES * WAVE) void k_sweep(Sweep2Args<T> a) {
+    int pos = sweep_position(a.ticket, a.ticket_next);
+    const int f = BOTH && pos >= a.s[0].count ? 1 : 0;
+    if (f) pos -= a.s[0].count;
+    const SweepArgs<T>& s = a.s[f];
+    if (pos >= s.count) return;   // whole wavefronts; no barrier follows
+    const SweepRec rec = load_rec(s.rec + s.begin + pos);
     if (rec.nrow == 0) return;
     const int lane = threadIdx.x & (WAVE - 1);
-    sweep_slice<T, D, ZX, S>(a, rec, lane, [&](T (&acc)[D]) {
-        if (CPL) group_sub<T, D, 0, S>(a.cpl, rec.cpl_w, rec.cpl_c, lane, a.xg, nullptr, 0, acc);
+    sweep_slice<T, D, ZX, S>(s, rec, lane, [&](T (&acc)[D]) {
+        const SweepOperand<T>& o = a.xg[f];
+        if (BOTH && o.t) group_sub<T, D, 3, S>(a.cpl[f], rec.cpl_w, rec.cpl_c, lane, o.x, o.t, 0, acc, &o);
+        else if (o.x) group_sub<T, D, 0, S>(a.cpl[f], rec.cpl_w, rec.cpl_c, lane, o.x, nullptr, 0, acc);
     });
 }
 
@@ -288,7 +323,7 @@ __device__ __forceinline__ void group_sub_parts(const GroupPart* parts, int n, i
 // system of 4 blocks, 1266 of 2080 us per V-cycle; that cycle takes 468 us now).
 template <int D, bool ZX>
 __global__ __launch_bounds__(SWEEP_WAVES * WAVE) void k_sweep_n(SweepNArgs a) {
-    const int pos = sweep_position(a.s);
+    const int pos = sweep_position(a.ticket, a.ticket_next);
     if (pos >= a.s.count) return;   // whole wavefronts; no barrier follows
     const SweepRec rec = load_rec(a.s.rec + a.s.begin + pos);
     if (rec.nrow == 0) return;
@@ -381,25 +416,25 @@ __global__ __launch_bounds__(256) void k_resid_group(ResidGroupArgs<T> a, int pa
 }
 
 template <class T, int D, int S>
-static void sweep_dispatch_s(bool zx, bool cpl, const SweepArgs<T>& a, hipStream_t s) {
-    const unsigned grid = (unsigned)ceil_div(a.count, SWEEP_WAVES);
+static void sweep_dispatch_s(bool zx, unsigned grid, const Sweep2Args<T>& a, hipStream_t s) {
     constexpr int TPB = SWEEP_WAVES * WAVE;
-    if (zx) {
-        if (cpl) k_sweep<T, D, true, true, S><<<grid, TPB, sweep_lds(a.spread), s>>>(a);
-        else k_sweep<T, D, true, false, S><<<grid, TPB, sweep_lds(a.spread), s>>>(a);
+    const unsigned lds = sweep_lds(a.spread);
+    if (a.s[1].count > 0) {
+        if (zx) k_sweep<T, D, true, S, true><<<grid, TPB, lds, s>>>(a);
+        else k_sweep<T, D, false, S, true><<<grid, TPB, lds, s>>>(a);
     } else {
-        if (cpl) k_sweep<T, D, false, true, S><<<grid, TPB, sweep_lds(a.spread), s>>>(a);
-        else k_sweep<T, D, false, false, S><<<grid, TPB, sweep_lds(a.spread), s>>>(a);
+        if (zx) k_sweep<T, D, true, S, false><<<grid, TPB, lds, s>>>(a);
+        else k_sweep<T, D, false, S, false><<<grid, TPB, lds, s>>>(a);
     }
 }
 
 template <class T, int D>
-static void sweep_dispatch(bool zx, bool cpl, const SweepArgs<T>& a, hipStream_t s) {
+static void sweep_dispatch(bool zx, unsigned grid, const Sweep2Args<T>& a, hipStream_t s) {
     if constexpr (D > 1) {
-        if (a.shape == SHAPE_SCALED) return sweep_dispatch_s<T, D, SHAPE_SCALED>(zx, cpl, a, s);
-        if (a.shape == SHAPE_SYMMETRIC) return sweep_dispatch_s<T, D, SHAPE_SYMMETRIC>(zx, cpl, a, s);
+        if (a.shape == SHAPE_SCALED) return sweep_dispatch_s<T, D, SHAPE_SCALED>(zx, grid, a, s);
+        if (a.shape == SHAPE_SYMMETRIC) return sweep_dispatch_s<T, D, SHAPE_SYMMETRIC>(zx, grid, a, s);
     }
-    sweep_dispatch_s<T, D, SHAPE_FULL>(zx, cpl, a, s);
+    sweep_dispatch_s<T, D, SHAPE_FULL>(zx, grid, a, s);
 }
 
 template <class T, int D>
@@ -418,33 +453,40 @@ static void resid_group_dispatch(unsigned grid, const ResidGroupArgs<T>& a, hipS
     k_resid_group<T, D, SHAPE_FULL><<<grid, 256, 0, s>>>(a, pb);
 }
 
+// a block's positions come in whole workgroups, so no workgroup takes two blocks'
+static void check_sweep_block(int count, int lg) {
+    MB_CHECK(count >= 0 && count % SWEEP_WAVES == 0, MBAMG_E_INVALID, "whole workgroups per block");
+    MB_CHECK(count == 0 || (lg >= 2 && lg <= 6), MBAMG_E_INVALID, "4 to 64 lanes per row");
+}
+
 template <class T>
-void launch_sweep(int d, bool zero_x, bool has_cpl, const SweepArgs<T>& a, hipStream_t s) {
-    if (a.count <= 0) return;
-    MB_CHECK(a.lg >= 2 && a.lg <= 6, MBAMG_E_INVALID, "4 to 64 lanes per row");
+void launch_sweep(int d, bool zero_x, const Sweep2Args<T>& a, hipStream_t s) {
+    for (const SweepArgs<T>& f : a.s) check_sweep_block(f.count, f.lg);
+    const unsigned grid = (unsigned)((a.s[0].count + a.s[1].count) / SWEEP_WAVES);
+    if (grid == 0) return;
     switch (d) {
-        case 1: sweep_dispatch<T, 1>(zero_x, has_cpl, a, s); break;
-        case 2: sweep_dispatch<T, 2>(zero_x, has_cpl, a, s); break;
-        case 3: sweep_dispatch<T, 3>(zero_x, has_cpl, a, s); break;
-        case 4: sweep_dispatch<T, 4>(zero_x, has_cpl, a, s); break;
+        case 1: sweep_dispatch<T, 1>(zero_x, grid, a, s); break;
+        case 2: sweep_dispatch<T, 2>(zero_x, grid, a, s); break;
+        case 3: sweep_dispatch<T, 3>(zero_x, grid, a, s); break;
+        case 4: sweep_dispatch<T, 4>(zero_x, grid, a, s); break;
         default: throw Error(MBAMG_E_INVALID, "dofs per node must be 1..4");
     }
     MB_LAUNCH_CHECK();
 }
-template void launch_sweep<double>(int, bool, bool, const SweepArgs<double>&, hipStream_t);
-template void launch_sweep<float>(int, bool, bool, const SweepArgs<float>&, hipStream_t);
+template void launch_sweep<double>(int, bool, const Sweep2Args<double>&, hipStream_t);
+template void launch_sweep<float>(int, bool, const Sweep2Args<float>&, hipStream_t);
 
 template <int D>
 static void sweep_n_dispatch(bool zx, const SweepNArgs& a, hipStream_t s) {
-    const unsigned grid = (unsigned)ceil_div(a.s.count, SWEEP_WAVES);
+    const unsigned grid = (unsigned)(a.s.count / SWEEP_WAVES);
     constexpr int TPB = SWEEP_WAVES * WAVE;
-    if (zx) k_sweep_n<D, true><<<grid, TPB, sweep_lds(a.s.spread), s>>>(a);
-    else k_sweep_n<D, false><<<grid, TPB, sweep_lds(a.s.spread), s>>>(a);
+    if (zx) k_sweep_n<D, true><<<grid, TPB, sweep_lds(a.spread), s>>>(a);
+    else k_sweep_n<D, false><<<grid, TPB, sweep_lds(a.spread), s>>>(a);
 }
 
 void launch_sweep_n(int d, bool zero_x, const SweepNArgs& a, hipStream_t s) {
-    if (a.s.count <= 0) return;
-    MB_CHECK(a.s.lg >= 2 && a.s.lg <= 6, MBAMG_E_INVALID, "4 to 64 lanes per row");
+    check_sweep_block(a.s.count, a.s.lg);
+    if (a.s.count == 0) return;
     MB_CHECK(a.n_cpl >= 0 && a.n_cpl < SWEEP_MAX_BLOCKS, MBAMG_E_INVALID, "at most 4 blocks");
     for (int k = 0; k < a.n_cpl; ++k)
         MB_CHECK(a.cpl[k].bc >= 1 && a.cpl[k].bc <= 4, MBAMG_E_INVALID, "row blocks of at most 4 x 4");
