@@ -125,7 +125,8 @@ void transfer_maps(int n, int nc, const int32_t* perm, const int32_t* iperm, con
 struct CoarseWork {
     int n = 0;
     DevBuf<double> M;                    // two n x n matrices (ping-pong)
-    DevBuf<int32_t> sing, rowsrc, ord;   // singular flag; a panel's row sources; row order (two copies)
+    DevBuf<double> panel;                // a panel as it is factored, and in position order
+    DevBuf<int32_t> sing, rowsrc, ord;   // singular flag; a panel's row sources and the row order (two copies)
 };
 // the same for nb x nb blocks (A: nb * nb pointers, row-major; block f has A[f*nb+f]->n_rows nodes of d[f] dofs)
 void coarse_inverse_launch_blocks(const SetupBsr* const* A, int nb, const int* d, DevBuf<double>& inv, CoarseWork& w,

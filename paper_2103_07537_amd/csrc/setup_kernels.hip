@@ -1655,199 +1655,355 @@ __global__ void k_dense_scatter(int n_rows, int br, int bc, const int32_t* rp, c
 // inversion leaves (Quintana-Orti, Quintana-Orti, van de Geijn & Remon, "A
 // note on parallel matrix inversion", SIAM J. Sci. Comput. 22, 2001).
 // ----------------------------------------------------------------------------
-constexpr int GJ_TILE = 64;
-
-// larger magnitude wins, ties to the smaller position
-__device__ __forceinline__ void gj_take(double& best, int& bi, double ob, int oi) {
-    if (ob > best || (ob == best && oi < bi)) {
-        best = ob;
-        bi = oi;
-    }
-}
+// largest of a over the wave (NL = 64) or over each 8 or 16 lanes that hold the same
+// NL values, to every lane
 template <int CTRL, int ROWS>
-__device__ __forceinline__ void gj_dpp_take(double& best, int& bi) {
-    const int lo = __double2loint(best), hi = __double2hiint(best);
-    const int olo = __builtin_amdgcn_update_dpp(lo, lo, CTRL, ROWS, 0xF, false);
-    const int ohi = __builtin_amdgcn_update_dpp(hi, hi, CTRL, ROWS, 0xF, false);
-    const int oi = __builtin_amdgcn_update_dpp(bi, bi, CTRL, ROWS, 0xF, false);
-    gj_take(best, bi, __hiloint2double(ohi, olo), oi);
+__device__ __forceinline__ int gj_dpp_max(int a) {
+    return max(a, __builtin_amdgcn_update_dpp(a, a, CTRL, ROWS, 0xF, false));
 }
-// arg-max over the wave, returned to every lane: exchanges inside quads and
-// half-rows and rows of 16 lanes, then row broadcasts carry the total to lane 63
-__device__ __forceinline__ void gj_wave_argmax(double& best, int& bi) {
-    gj_dpp_take<0xB1, 0xF>(best, bi);    // quad_perm [1,0,3,2]
-    gj_dpp_take<0x4E, 0xF>(best, bi);    // quad_perm [2,3,0,1]
-    gj_dpp_take<0x141, 0xF>(best, bi);   // row_half_mirror
-    gj_dpp_take<0x140, 0xF>(best, bi);   // row_mirror
-    gj_dpp_take<0x142, 0xA>(best, bi);   // row_bcast:15 into rows 1 and 3
-    gj_dpp_take<0x143, 0xC>(best, bi);   // row_bcast:31 into rows 2 and 3
-    const int lo = __builtin_amdgcn_readlane(__double2loint(best), 63);
-    const int hi = __builtin_amdgcn_readlane(__double2hiint(best), 63);
-    bi = __builtin_amdgcn_readlane(bi, 63);
-    best = __hiloint2double(hi, lo);
+template <int NL>
+__device__ __forceinline__ int gj_lane_max(int a) {
+    static_assert(NL == 8 || NL == 16 || NL == 64, "lanes");
+    a = gj_dpp_max<0xB1, 0xF>(a);    // quad_perm [1,0,3,2]
+    a = gj_dpp_max<0x4E, 0xF>(a);    // quad_perm [2,3,0,1]
+    a = gj_dpp_max<0x141, 0xF>(a);   // row_half_mirror
+    if (NL == 8) return __builtin_amdgcn_readfirstlane(a);
+    a = gj_dpp_max<0x140, 0xF>(a);   // row_mirror
+    if (NL == 16) return __builtin_amdgcn_readfirstlane(a);
+    a = gj_dpp_max<0x142, 0xA>(a);   // row_bcast:15 into rows 1 and 3
+    a = gj_dpp_max<0x143, 0xC>(a);   // row_bcast:31 into rows 2 and 3
+    return __builtin_amdgcn_readlane(a, 63);
+}
+// the lane with the largest (hi, lo), ties to the smaller idx; hi signed, lo unsigned
+template <int NL>
+__device__ __forceinline__ int gj_pick(int hi, uint32_t lo, int idx) {
+    const int slo = (int)(lo ^ 0x80000000u);
+    const int top = gj_lane_max<NL>(hi);
+    const bool a = hi == top;
+    const int low = gj_lane_max<NL>(a ? slo : INT_MIN);
+    const bool b = a && slo == low;
+    const int first = -gj_lane_max<NL>(b ? -idx : -INT_MAX);
+    return __builtin_ctzll(__ballot(b && idx == first));
+}
+__device__ __forceinline__ double gj_readlane(double a, int lane) {
+    return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(a), lane),
+                            __builtin_amdgcn_readlane(__double2loint(a), lane));
 }
 
-// Panel [k0, k0 + b), b <= B; thread t of T owns rows t + j * T, j < R, in
-// registers.  Rows are never moved inside the panel: lab[j] is the position
-// that the thread's j-th row holds in the row order so far, and a row
-// interchange exchanges two labels.  The columns sit in a rotating frame so
-// that the step loop indexes registers with constants: at step kk, v[j][c]
-// holds panel column (c + kk) mod B, the pivot column is v[j][0].  Global
-// memory is read and written in coalesced order and redistributed through
-// LDS one slot (T rows) at a time.  Each row ends at position lab[j];
-// rowsrc[position] = the row it came from.
+// A panel, columns [k, k + b), b <= B, of a Gauss-Jordan step.  The workgroup that
+// factors it has row j * T + t, column c at [(j * B + c) * T + t] of `raw`, and leaves
+// it the same way in `done`; rowsrc[r]: the row that position r's data came from;
+// `rows`: the factored panel in position order, row-major.
+struct GjPanel {
+    int k, b;
+    double *raw, *done, *rows;
+    int32_t* rowsrc;
+};
+
+// c += (16 x B) (B x 16) in FP64 matrix instructions of depth 4.  Lane l holds row or
+// column l mod 16 of the operands at depth 4 s + l / 16 and, in element i of c, row
+// 4 i + l / 16, column l mod 16.
+using gj_acc = __attribute__((__vector_size__(4 * sizeof(double)))) double;
+template <int B>
+struct GjOperand {
+    static constexpr int S = (B + 3) / 4;
+    double x[S];
+};
+template <int B>
+__device__ __forceinline__ gj_acc gj_mfma(const GjOperand<B>& a, const GjOperand<B>& x, gj_acc c) {
+#pragma unroll
+    for (int s = 0; s < GjOperand<B>::S; ++s) c = __builtin_amdgcn_mfma_f64_16x16x4f64(a.x[s], x.x[s], c, 0, 0, 0);
+    return c;
+}
+// n <= 16384: byte offsets fit 32 bits
+__device__ __forceinline__ double gj_at(const double* M, int n, int r, int c) {
+    return *reinterpret_cast<const double*>(reinterpret_cast<const char*>(M) +
+                                            ((uint32_t)r * (uint32_t)n + (uint32_t)c) * 8u);
+}
+// row r of G - E, the panel less its columns of the identity
+template <int B>
+__device__ __forceinline__ GjOperand<B> gj_rows(const GjPanel& p, int r) {
+    GjOperand<B> a;
+#pragma unroll
+    for (int s = 0; s < GjOperand<B>::S; ++s) {
+        const int q = 4 * s + (threadIdx.x & (WAVE - 1)) / 16;
+        const double g = p.rows[r * B + min(q, p.b - 1)] - (r == p.k + q ? 1.0 : 0.0);
+        a.x[s] = q < p.b ? g : 0.0;
+    }
+    return a;
+}
+// column c of (P In)[panel rows]
+template <int B>
+__device__ __forceinline__ GjOperand<B> gj_cols(const double* M, int n, const int* src, const GjPanel& p, int c) {
+    GjOperand<B> x;
+#pragma unroll
+    for (int s = 0; s < GjOperand<B>::S; ++s) {
+        const int q = 4 * s + (threadIdx.x & (WAVE - 1)) / 16;
+        const double m = gj_at(M, n, src[p.k + min(q, p.b - 1)], c);
+        x.x[s] = q < p.b ? m : 0.0;
+    }
+    return x;
+}
+
+// Thread t of T owns rows t + j * T, j < R, of the panel in registers.  Rows are never
+// moved: lab[j] is the position that the thread's j-th row holds in the row order so
+// far, and a row interchange exchanges two labels.  The columns sit in a rotating
+// frame so that the step loop indexes registers with constants: at step kk, v[j][c]
+// holds panel column (c + kk) mod B, the pivot column is v[j][0].  A step has one
+// barrier: before it every wave offers its best row, after it every wave picks the
+// best of these and takes it, scaled, into scalar registers (from LDS it would be read
+// anew for every row).  Rows past the end and, in the last panel, columns past it hold
+// anything: no row or column that is kept takes anything from them.
+template <int T, int B>
+struct GjPanelShared {
+    double cand[2][T / WAVE][B];   // each wave's best row
+    int4 offer[2][T / WAVE];       // the halves of its pivot's magnitude, its position
+};
+
 template <int T, int R, int B>
-__global__ __launch_bounds__(T) void k_gj_panel(double* M, int n, int k0, int b, int32_t* rowsrc, int32_t* singular) {
-    __shared__ double stage[T][B + 1];
-    __shared__ int slab[T];
-    __shared__ double wbest[T / WAVE];
-    __shared__ int widx[T / WAVE];
-    __shared__ double rowk[B];
-    const int t = threadIdx.x, lane = t & (WAVE - 1), wv = t / WAVE;
+__device__ void gj_panel(GjPanelShared<T, B>& S, int n, const GjPanel& cur, int32_t* singular) {
+    constexpr int NW = T / WAVE;
+    const int t = threadIdx.x, lane = t & (WAVE - 1), wv = __builtin_amdgcn_readfirstlane(t / WAVE);
+    const int k0 = cur.k, b = cur.b;
     double v[R][B];
     int lab[R];
-    {
-        // every load in flight at once
-        double u[R][B];
 #pragma unroll
-        for (int j = 0; j < R; ++j)
+    for (int j = 0; j < R; ++j) {
+        lab[j] = t + j * T < n ? t + j * T : -1;
 #pragma unroll
-            for (int q = 0; q < B; ++q) {
-                const int e = t + q * T, rr = e / B, c = e % B, r = j * T + rr;
-                u[j][q] = (r < n && c < b) ? M[(int64_t)r * n + k0 + c] : 0.0;
-            }
-#pragma unroll
-        for (int j = 0; j < R; ++j) {
-            lab[j] = t + j * T;
-#pragma unroll
-            for (int q = 0; q < B; ++q) {
-                const int e = t + q * T;
-                stage[e / B][e % B] = u[j][q];
-            }
-            __syncthreads();
-#pragma unroll
-            for (int c = 0; c < B; ++c) v[j][c] = stage[t][c];
-            __syncthreads();
-        }
+        for (int c = 0; c < B; ++c) v[j][c] = cur.raw[(j * B + c) * T + t];
     }
     for (int kk = 0; kk < b; ++kk) {
-        const int k = k0 + kk;
-        // pivot: largest magnitude in column k at position k or below, ties to the smaller position
-        double best = -1.0;
-        int bi = INT_MAX;
+        const int k = k0 + kk, turn = kk & 1;
+        // Pivot: largest magnitude in column k at position k or below, ties to the smaller
+        // position.  Nearly always one row has the largest upper half; the lower half, the
+        // position, infinities and NaN (never a pivot) are looked at where that is not so.
+        int top = -1, at = 0;
+        bool tie = false;
 #pragma unroll
         for (int j = 0; j < R; ++j) {
-            const double a = fabs(v[j][0]);
-            if (lab[j] >= k && lab[j] < n && (a > best || (a == best && lab[j] < bi))) {
-                best = a;
-                bi = lab[j];
-            }
+            const int hi = lab[j] >= k ? __double2hiint(v[j][0]) & 0x7FFFFFFF : -1;
+            tie = hi == top || (tie && hi < top);
+            at = hi > top ? j : at;
+            top = max(top, hi);
         }
-        gj_wave_argmax(best, bi);
-        if (lane == 0) {
-            wbest[wv] = best;
-            widx[wv] = bi;
+        const int mine = top;
+        top = gj_lane_max<WAVE>(top);
+        uint64_t own = __ballot(mine == top);   // the lane with the wave's best row, and its slot there
+        const bool ties = __ballot(mine == top && tie) != 0 || __popcll(own) > 1;
+        if (top < 0) {   // no row of the wave is left
+            top = -2;
+        } else if (ties || top >= 0x7FF00000) {
+            int h = -2, x = INT_MAX;
+            uint32_t l = 0;
+#pragma unroll
+            for (int j = 0; j < R; ++j) {
+                const int hi = __double2hiint(v[j][0]) & 0x7FFFFFFF;
+                const uint32_t lo = (uint32_t)__double2loint(v[j][0]);
+                const bool left = lab[j] >= k, ok = left && (hi < 0x7FF00000 || (hi == 0x7FF00000 && lo == 0));
+                // no finite candidate (NaN after an earlier zero pivot): position k's row, a valid one
+                const int hj = ok ? hi : lab[j] == k ? -1 : -2;
+                const uint32_t wj = ok ? lo : 0;
+                if (hj > h || (hj == h && (wj > l || (wj == l && left && lab[j] < x)))) {
+                    h = hj;
+                    l = wj;
+                    x = left ? lab[j] : INT_MAX;
+                    at = j;
+                }
+            }
+            const int best = gj_pick<WAVE>(h, l, x);
+            top = __builtin_amdgcn_readlane(h, best);
+            own = 1ull << best;
+        }
+        const int owner = __builtin_ctzll(own), slot = __builtin_amdgcn_readlane(at, owner);
+        if (top == -2) {
+            if (lane == 0) S.offer[turn][wv] = make_int4(-2, 0, INT_MAX, 0);
+        } else {
+#pragma unroll
+            for (int j = 0; j < R; ++j)
+                if (slot == j) {
+                    if (lane == owner) {
+                        S.offer[turn][wv] = make_int4(top, top < 0 ? 0 : __double2loint(v[j][0]), lab[j], 0);
+#pragma unroll
+                        for (int c = 0; c < B; ++c) S.cand[turn][wv][c] = v[j][c];
+                    }
+                }
         }
         __syncthreads();
-        best = wbest[0];
-        bi = widx[0];
+        const int4 offer = S.offer[turn][lane & (NW - 1)];
+        const int wtop = gj_lane_max<NW>(offer.x);
+        const uint64_t in = __ballot(offer.x == wtop) & ((1ull << NW) - 1);
+        int win = __builtin_ctzll(in);
+        if (__popcll(in) > 1) win = gj_pick<NW>(offer.x, (uint32_t)offer.y, offer.z) & (NW - 1);
+        const int lp = __builtin_amdgcn_readlane(offer.z, win);
+        // the new row k: lane c has entry c of it
+        double rowk[B];
+        {
+            const double raw = S.cand[turn][win][lane % B];
+            const double inv = 1.0 / gj_readlane(raw, 0);
+            const double mine = raw * inv;
+            rowk[0] = gj_readlane(inv, 0);
 #pragma unroll
-        for (int w = 1; w < T / WAVE; ++w) gj_take(best, bi, wbest[w], widx[w]);
-        // no finite candidate (NaN after an earlier zero pivot): keep a valid row
-        const int lp = bi == INT_MAX ? k : bi;
-        if (t == 0 && (!(best > 0.0) || bi == INT_MAX)) atomicAdd(singular, 1);
-        // the owner of the pivot row publishes the new row k (rotated frame)
-#pragma unroll
-        for (int j = 0; j < R; ++j) {
-            if (__any(lab[j] == lp) && lab[j] == lp) {
-                const double inv = 1.0 / v[j][0];
-                rowk[0] = inv;
-#pragma unroll
-                for (int c = 1; c < B; ++c) rowk[c] = v[j][c] * inv;
-            }
+            for (int c = 1; c < B; ++c) rowk[c] = gj_readlane(mine, c);
         }
-        __syncthreads();
+        if (wtop <= 0 && t == 0 && (wtop < 0 || S.offer[turn][win].y == 0)) atomicAdd(singular, 1);
         // eliminate column k from every row and rotate the frame by one
 #pragma unroll
         for (int j = 0; j < R; ++j) {
-            const bool piv = lab[j] == lp;
             const double f = v[j][0];
 #pragma unroll
             for (int c = 1; c < B; ++c) v[j][c - 1] = fma(-f, rowk[c], v[j][c]);
             v[j][B - 1] = -f * rowk[0];
-            // one lane of one wave holds the pivot row: the others skip its copy
-            if (__any(piv)) {
-#pragma unroll
-                for (int c = 1; c < B; ++c) v[j][c - 1] = piv ? rowk[c] : v[j][c - 1];
-                v[j][B - 1] = piv ? rowk[0] : v[j][B - 1];
-            }
-            lab[j] = piv ? k : (lab[j] == k ? lp : lab[j]);
         }
+        // the pivot row itself
+        if (wv == win) {
+#pragma unroll
+            for (int j = 0; j < R; ++j)
+                if (slot == j && lane == owner) {
+#pragma unroll
+                    for (int c = 0; c < B; ++c) v[j][c] = rowk[(c + 1) % B];
+                }
+        }
+#pragma unroll
+        for (int j = 0; j < R; ++j) lab[j] = lab[j] == lp ? k : (lab[j] == k ? lp : lab[j]);
     }
     // after b steps, frame column c holds panel column (c + b) mod B
 #pragma unroll
     for (int j = 0; j < R; ++j) {
 #pragma unroll
-        for (int c = 0; c < B; ++c) stage[t][c] = v[j][c];
-        slab[t] = lab[j];
-        __syncthreads();
-#pragma unroll
-        for (int q = 0; q < B; ++q) {
-            const int e = t + q * T, rr = e / B, c = e % B, r = j * T + rr;
-            const int pc = (c + b) % B;
-            if (r < n && pc < b) M[(int64_t)slab[rr] * n + k0 + pc] = stage[rr][c];
-        }
-        if (t + j * T < n) rowsrc[lab[j]] = t + j * T;
-        __syncthreads();
+        for (int c = 0; c < B; ++c) cur.done[(j * B + (c + b) % B) * T + t] = v[j][c];
+        if (lab[j] >= 0) cur.rowsrc[lab[j]] = t + j * T;
     }
 }
 
-// Out = P In + (G - E) (P In)[panel rows] outside the panel, Out = In inside it;
-// GJ_TILE x GJ_TILE tiles, 256 threads, each thread one column and 16 rows.
-// Column-tile 0 also carries the row order: ord_out[r] = ord_in[rowsrc[r]]
-// (ord_in null: the identity).
-template <int B>
-__global__ __launch_bounds__(256) void k_gj_update(const double* __restrict__ Min, double* __restrict__ Mout, int n,
-                                                   int k0, int b, const int32_t* __restrict__ rowsrc,
-                                                   const int32_t* __restrict__ ord_in, int32_t* __restrict__ ord_out) {
-    __shared__ double G[B][GJ_TILE];
-    __shared__ int rsrc[GJ_TILE];
-    const int t = threadIdx.x, tx = t % GJ_TILE, ty = t / GJ_TILE;
-    const int row0 = blockIdx.y * GJ_TILE;
-    const int c = blockIdx.x * GJ_TILE + tx;
-    for (int e = t; e < GJ_TILE * B; e += 256) {
-        const int rr = e / B, q = e % B;
-        const int r = row0 + rr;
-        double g = 0.0;
-        if (r < n && q < b) g = Min[(int64_t)r * n + k0 + q] - (r == k0 + q ? 1.0 : 0.0);
-        G[q][rr] = g;
+// Between two panels: the factored one (prev.b == 0: none yet) into position order, and
+// the update by it of the next one's columns (cur.b == 0: none is left).  A thread has
+// row 64 * workgroup + lane and the columns wave * C ... of both.
+template <int T, int B>
+__global__ __launch_bounds__(256) void k_gj_next(const double* __restrict__ M, int n, GjPanel prev, GjPanel cur) {
+    constexpr int C = (B + 3) / 4;   // columns of a thread
+    __shared__ double x[B][B];
+    const int lane = threadIdx.x & (WAVE - 1), c0 = threadIdx.x / WAVE * C;
+    const int r = blockIdx.x * WAVE + lane;
+    const bool in = r < n && c0 < B;
+    if (prev.b > 0 && cur.b > 0) {
+        for (int e = threadIdx.x; e < B * B; e += 256)
+            x[e / B][e % B] = M[(int64_t)prev.rowsrc[prev.k + e / B] * n + min(cur.k + e % B, n - 1)];
+        __syncthreads();
     }
-    if (t < GJ_TILE) {
-        const int r = row0 + t;
-        const int sr = r < n ? rowsrc[r] : 0;
-        rsrc[t] = sr;
-        if (blockIdx.x == 0 && r < n) ord_out[r] = ord_in ? ord_in[sr] : sr;
+    if (!in) return;
+    const int sr = prev.b > 0 ? prev.rowsrc[r] : r;
+    double out[C], g[B];
+    if (cur.b > 0)
+#pragma unroll
+        for (int c = 0; c < C; ++c) out[c] = M[(int64_t)sr * n + min(cur.k + c0 + c, n - 1)];
+    if (prev.b > 0) {
+#pragma unroll
+        for (int q = 0; q < B; ++q) g[q] = prev.done[(sr / T * B + q) * T + sr % T];
+#pragma unroll
+        for (int q = 0; q < B; ++q)
+            if (q / C * C == c0) prev.rows[r * B + q] = g[q];
+        if (cur.b > 0)
+#pragma unroll
+            for (int q = 0; q < B; ++q) {
+                const double gq = g[q] - (r == prev.k + q ? 1.0 : 0.0);
+#pragma unroll
+                for (int c = 0; c < C; ++c) out[c] = fma(gq, x[q][c0 + c], out[c]);
+            }
+    }
+    if (cur.b > 0)
+#pragma unroll
+        for (int c = 0; c < C; ++c) cur.raw[(r / T * B + c0 + c) * T + r % T] = out[c];
+}
+
+// Out = P In + (G - E) (P In)[panel rows] of panel `prev`, whose own columns are taken
+// from its factors; those of panel `cur` are left alone.  A wave takes units of 32 rows
+// and 32 columns, straight between memory and the matrix instructions' layout, the
+// next unit's loads under way while one is computed.  The first workgroup also carries
+// the row order: ord_out[r] = ord_in[rowsrc[r]] (ord_in null: the identity).
+constexpr int GJ_UNIT = 32;
+template <int T, int R, int B>
+__device__ void gj_tiles(int* src, const double* Min, double* Mout, int n, const GjPanel& prev, const GjPanel& cur,
+                         int wg, int n_wg, const int32_t* ord_in, int32_t* ord_out) {
+    const int t = threadIdx.x, lane = t & (WAVE - 1), wv = __builtin_amdgcn_readfirstlane(t / WAVE);
+    for (int r = t; r < n; r += T) {
+        const int sr = prev.rowsrc[r];
+        src[r] = sr;
+        if (wg == 0) ord_out[r] = ord_in ? ord_in[sr] : sr;
     }
     __syncthreads();
-    if (c >= n) return;
-    const bool in_panel = c >= k0 && c < k0 + b;
-    double x[B];
+    const int units_x = (n + GJ_UNIT - 1) / GJ_UNIT, units = units_x * units_x;
+    constexpr int H = GJ_UNIT / 16;
+    struct Unit {
+        gj_acc acc[H][H];
+        GjOperand<B> g[H], x[H];
+    } u[2];
+    auto load = [&](int k, Unit& w) {
+        const int r0 = k / units_x * GJ_UNIT, c0 = k % units_x * GJ_UNIT;
 #pragma unroll
-    for (int q = 0; q < B; ++q) x[q] = (q < b && !in_panel) ? Min[(int64_t)rowsrc[k0 + q] * n + c] : 0.0;
-#pragma unroll 4
-    for (int i = 0; i < GJ_TILE / 4; ++i) {
-        const int rr = ty * (GJ_TILE / 4) + i;
-        const int r = row0 + rr;
-        if (r >= n) break;
-        double out;
-        if (in_panel) {
-            out = Min[(int64_t)r * n + c];
-        } else {
-            out = Min[(int64_t)rsrc[rr] * n + c];
+        for (int m = 0; m < H; ++m) {
+            const int c = min(c0 + 16 * m + lane % 16, n - 1);
+            w.x[m] = gj_cols<B>(Min, n, src, prev, c);
+            w.g[m] = gj_rows<B>(prev, min(r0 + 16 * m + lane % 16, n - 1));
+            const bool in_panel = c >= prev.k && c < prev.k + prev.b;
 #pragma unroll
-            for (int q = 0; q < B; ++q) out = fma(G[q][rr], x[q], out);
+            for (int h = 0; h < H; ++h)
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    const int r = min(r0 + 16 * h + 4 * i + lane / 16, n - 1);
+                    w.acc[h][m][i] = in_panel ? prev.rows[r * B + c - prev.k] : gj_at(Min, n, src[r], c);
+                }
         }
-        Mout[(int64_t)r * n + c] = out;
+    };
+    auto finish = [&](int k, Unit& w) {
+        const int r0 = k / units_x * GJ_UNIT, c0 = k % units_x * GJ_UNIT;
+#pragma unroll
+        for (int m = 0; m < H; ++m) {
+            const int c = c0 + 16 * m + lane % 16;
+            const bool in_panel = c >= prev.k && c < prev.k + prev.b;
+            const bool mine = c < n && !(c >= cur.k && c < cur.k + cur.b);
+#pragma unroll
+            for (int h = 0; h < H; ++h) {
+                const gj_acc out = gj_mfma<B>(w.g[h], w.x[m], w.acc[h][m]);
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    const int r = r0 + 16 * h + 4 * i + lane / 16;
+                    if (mine && r < n) Mout[(int64_t)r * n + c] = in_panel ? w.acc[h][m][i] : out[i];
+                }
+            }
+        }
+    };
+    const int step = n_wg * (T / WAVE);
+    int k = wg * (T / WAVE) + wv;
+    if (k < units) load(k, u[0]);
+    for (; k < units; k += 2 * step) {
+        if (k + step < units) load(k + step, u[1]);
+        finish(k, u[0]);
+        if (k + step >= units) break;
+        if (k + 2 * step < units) load(k + 2 * step, u[0]);
+        finish(k + step, u[1]);
+    }
+}
+
+// One step: workgroup 0 factors panel `cur` (cur.b == 0: none is left) while the
+// others apply panel `prev` (none before the first) to the columns of neither.  The
+// chain of a panel's pivots bounds it: 44 us a panel of 16 at 2,272 rows, with k_gj_next;
+// 84 us when the panel (57 us: two barriers a pivot, the row from LDS for every row, a
+// strided load and store) and the update (27 us, bound by its operand's reads of LDS)
+// were launches one after the other.  Factoring with the update pending, in one launch
+// a step, took 73 us: one compute unit has too little bandwidth for the extra operand.
+template <int T, int R, int B>
+__global__ __launch_bounds__(T) void k_gj_step(const double* Min, double* Mout, int n, GjPanel prev, GjPanel cur,
+                                               const int32_t* ord_in, int32_t* ord_out, int32_t* singular) {
+    __shared__ union Shared {
+        GjPanelShared<T, B> panel;
+        int src[T * R];
+        __device__ Shared() {}
+    } S;
+    if (blockIdx.x == 0) {
+        if (cur.b > 0) gj_panel<T, R, B>(S.panel, n, cur, singular);
+    } else {
+        gj_tiles<T, R, B>(S.src, Min, Mout, n, prev, cur, blockIdx.x - 1, gridDim.x - 1, ord_in, ord_out);
     }
 }
 
@@ -2648,26 +2804,35 @@ void transfer_maps(int n, int nc, const int32_t* perm, const int32_t* iperm, con
 
 template <int T, int R, int B>
 static void gj_run(CoarseWork& w, int n, hipStream_t s, double** result, const int32_t** order) {
-    double* cur = w.M.p;
-    double* nxt = w.M.p + (size_t)n * n;
+    constexpr size_t FRAME = (size_t)T * R * B;
+    w.panel.alloc(2 * FRAME + (size_t)n * B);
+    double* M[2] = {w.M.p, w.M.p + (size_t)n * n};
+    int32_t* ord[2] = {w.ord.p, w.ord.p + n};
+    // one workgroup a compute unit (a panel's rows fill its registers), and no more than there are units
+    const int64_t units = ceil_div(n, GJ_UNIT) * ceil_div(n, GJ_UNIT);
+    const unsigned tiles = (unsigned)std::min<int64_t>(255, ceil_div(units, T / WAVE));
+    const unsigned rows = (unsigned)ceil_div(n, WAVE);
     const int32_t* ord_in = nullptr;
-    int which = 0;
-    for (int k0 = 0; k0 < n; k0 += B) {
-        const int b = std::min(B, n - k0);
-        k_gj_panel<T, R, B><<<1, T, 0, s>>>(cur, n, k0, b, w.rowsrc.p, w.sing.p);
-        if (b == n) {   // one panel: nothing outside it
-            ord_in = w.rowsrc.p;
-            break;
+    int turn = 0;
+    GjPanel prev{0, 0, w.panel.p, w.panel.p + FRAME, w.panel.p + 2 * FRAME, nullptr};
+    for (int k = 0, step = 0;; k += B, ++step) {
+        GjPanel cur = prev;
+        cur.k = std::min(k, n);
+        cur.b = std::min(B, n - cur.k);
+        cur.rowsrc = w.rowsrc.p + (step & 1) * n;
+        k_gj_next<T, B><<<rows, 256, 0, s>>>(M[turn], n, prev, cur);
+        if (step == 0) {
+            k_gj_step<T, R, B><<<1, T, 0, s>>>(M[0], M[0], n, prev, cur, nullptr, nullptr, w.sing.p);
+        } else {
+            k_gj_step<T, R, B><<<1 + tiles, T, 0, s>>>(M[turn], M[1 - turn], n, prev, cur, ord_in, ord[turn], w.sing.p);
+            ord_in = ord[turn];
+            turn = 1 - turn;
         }
-        int32_t* ord_out = w.ord.p + (size_t)which * n;
-        const dim3 grid((n + GJ_TILE - 1) / GJ_TILE, (n + GJ_TILE - 1) / GJ_TILE);
-        k_gj_update<B><<<grid, 256, 0, s>>>(cur, nxt, n, k0, b, w.rowsrc.p, ord_in, ord_out);
-        ord_in = ord_out;
-        which ^= 1;
-        std::swap(cur, nxt);
+        if (cur.b == 0) break;
+        prev = cur;
     }
     MB_LAUNCH_CHECK();
-    *result = cur;
+    *result = M[turn];
     *order = ord_in;
 }
 
@@ -2681,7 +2846,7 @@ void coarse_inverse_launch_blocks(const SetupBsr* const* A, int nb, const int* d
     w.n = n;
     w.M.alloc((size_t)2 * n * n);
     w.sing.alloc(1);
-    w.rowsrc.alloc(std::max(n, 1));
+    w.rowsrc.alloc((size_t)2 * std::max(n, 1));
     w.ord.alloc((size_t)2 * std::max(n, 1));
     inv.alloc((size_t)n * n);
     MB_HIP(hipMemsetAsync(w.sing.p, 0, sizeof(int32_t), s));
