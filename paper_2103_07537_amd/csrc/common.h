@@ -163,7 +163,47 @@ struct HostCopies {
         items.clear();
     }
 };
-
+// Several host vectors copied to device arrays (allocated here) with one
+// synchronisation of the stream; large ones one by one, each through its own
+// page-locked buffer.
+struct DeviceCopies {
+    struct Item {
+        void* dst;
+        const void* src;
+        size_t bytes;
+    };
+    std::vector<Item> items;
+    template <class T>
+    void add(DevBuf<T>& b, const std::vector<T>& v) {
+        if (v.size() > b.n) b.alloc(v.size());
+        if (!v.empty()) items.push_back({b.p, v.data(), v.size() * sizeof(T)});
+    }
+    void run(hipStream_t s) {
+        size_t total = 0;
+        for (const Item& it : items) {
+            if (it.bytes < PINNED_STAGING_MIN) {
+                total += (it.bytes + 15) & ~(size_t)15;
+                continue;
+            }
+            PinnedBuf<char> st(it.bytes);
+            std::memcpy(st.p, it.src, it.bytes);
+            MB_HIP(hipMemcpyAsync(it.dst, st.p, it.bytes, hipMemcpyHostToDevice, s));
+            MB_HIP(hipStreamSynchronize(s));
+        }
+        if (total) {
+            PinnedBuf<char> st(total);
+            size_t off = 0;
+            for (const Item& it : items) {
+                if (it.bytes >= PINNED_STAGING_MIN) continue;
+                std::memcpy(st.p + off, it.src, it.bytes);
+                MB_HIP(hipMemcpyAsync(it.dst, st.p + off, it.bytes, hipMemcpyHostToDevice, s));
+                off += (it.bytes + 15) & ~(size_t)15;
+            }
+            MB_HIP(hipStreamSynchronize(s));
+        }
+        items.clear();
+    }
+};
 
 inline int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
 

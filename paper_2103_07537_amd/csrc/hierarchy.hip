@@ -680,17 +680,26 @@ static void natural_slicing(BlockLevel& B, int n, hipStream_t s, const std::vect
         B.perm.resize(n);
         for (int i = 0; i < n; ++i) B.perm[i] = i;
     }
-    B.row0.upload(B.h_row0, s);
-    B.nrow.upload(B.h_nrow, s);
-    B.d_perm.upload(B.perm, s);
+    DeviceCopies up;
+    up.add(B.row0, B.h_row0);
+    up.add(B.nrow, B.h_nrow);
+    up.add(B.d_perm, B.perm);
+    up.run(s);
 }
+
+// Setup buffers kept until the caller has waited for the stream.
+struct Temporaries {
+    std::vector<DevBuf<int64_t>> src;
+    std::vector<DevBuf<int32_t>> order;
+};
 
 // Pack one part of block row f into masked slices on the device.  A: the
 // natural-order source block (unused for Dinv); val: its values, or the dense
 // per-node inverse array for Dinv; col_iperm: natural column node -> colour
 // order of the column block; shape: which entries of the (square) blocks are kept.
 static void build_part(SellPart& P, PartKind kind, const BlockLevel& B, const SetupBsr* A, const int32_t* col_iperm,
-                       const double* val, int br, int bc, bool want32, hipStream_t s, int shape = SHAPE_FULL) {
+                       const double* val, int br, int bc, bool want32, hipStream_t s, Temporaries& keep,
+                       int shape = SHAPE_FULL) {
     P.br = br;
     P.bc = bc;
     const int ns = B.n_slices;
@@ -698,15 +707,14 @@ static void build_part(SellPart& P, PartKind kind, const BlockLevel& B, const Se
     const int32_t* rp = A ? A->rp.p : nullptr;
     const int32_t* ci = A ? A->ci.p : nullptr;
     DevBuf<int32_t> coff32;
-    part_layout(B.n, ns, k, B.group, B.d_perm.p, rp, ci, B.row0.p, B.nrow.p, P.width, coff32, P.n_slots, s);
+    part_layout(B.n, ns, k, B.group, B.d_perm.p, rp, ci, B.row0.p, B.nrow.p, P.width, coff32, P.coff, P.n_slots,
+                s);
     const int64_t nsl = std::max<int64_t>(P.n_slots, 1);
     P.col.alloc(nsl * WAVE);
     DevBuf<int64_t> src(nsl * WAVE);
     DevBuf<int32_t> sblk(nsl);
     part_fill_index(ns, k, B.group, B.n, B.row0.p, B.nrow.p, k == (int)PartKind::Off ? B.cstart.p : nullptr, P.width.p, coff32.p, B.d_perm.p, rp, ci, col_iperm, P.n_slots, P.col.p,
                     src.p, sblk.p, s);
-    P.coff.alloc(std::max(ns, 1));
-    i32_to_i64(ns, coff32.p, P.coff.p, s);
     P.mask.alloc(nsl);
     DevBuf<uint32_t> slot_nz(nsl);
     MB_HIP(hipMemsetAsync(slot_nz.p, 0, sizeof(uint32_t) * nsl, s));
@@ -719,7 +727,7 @@ static void build_part(SellPart& P, PartKind kind, const BlockLevel& B, const Se
         cast_to_f32(P.v64.p, P.v32.p, P.n_groups * WAVE, s);
     }
     if (B.group > 1) {   // the byte model of a grouped level counts by rows
-        MB_HIP(hipStreamSynchronize(s));   // the temporaries are released on return
+        keep.src.push_back(std::move(src));   // the other temporaries were done with before slot_offsets' wait
         return;
     }
     // host copies for the byte model, with one synchronisation (which also keeps the
@@ -760,15 +768,14 @@ static void alloc_vecs(Vecs<T>& v, int64_t n, bool grouped, hipStream_t s) {
 }
 
 // The launch records of a grouped block row, once its parts are built.
-static void build_recs(BlockLevel& B, hipStream_t s) {
+static void build_recs(BlockLevel& B, hipStream_t s, Temporaries& keep) {
     MB_CHECK(B.off.n_slots < INT_MAX && B.cpl.n_slots < INT_MAX, MBAMG_E_INVALID, "too many slots in a grouped part");
-
-    DevBuf<int32_t> order;
+    keep.order.emplace_back();
+    DevBuf<int32_t>& order = keep.order.back();
     order.upload(B.h_order, s);
     B.recs.alloc(std::max<size_t>(B.h_order.size(), 1));
     sweep_recs((int)B.h_order.size(), order.p, B.row0.p, B.nrow.p, B.cstart.p, B.off.width.p, B.off.coff.p,
                B.cpl.width.p, B.cpl.coff.p, B.recs.p, s);   // (cpl NULL: a block among more than two)
-    MB_HIP(hipStreamSynchronize(s));   // order is released on return
 }
 
 // ----------------------------------------------------------------------------
@@ -1221,23 +1228,26 @@ static void setup_impl(mbamg_hierarchy* h, const mbamg_bsr* Ab, hipStream_t s, D
             B.n = c.nodes(f);
             B.colour.assign(c.nodes(f), 0);
             order_and_slice(B, c.nodes(f), 1);   // one colour: identity order, slices for the transfer kernels
-            B.row0.upload(B.h_row0, s);
-            B.nrow.upload(B.h_nrow, s);
-            B.d_perm.upload(B.perm, s);   // used at the interface when this is the only level
-            B.d_iperm.upload(B.iperm, s);
+            DeviceCopies up;
+            up.add(B.row0, B.h_row0);
+            up.add(B.nrow, B.h_nrow);
+            up.add(B.d_perm, B.perm);   // used at the interface when this is the only level
+            up.add(B.d_iperm, B.iperm);
+            up.run(s);
         }
         if (h->L.size() == 1) {
             // the only level: the operator apply of the Krylov solver reads its blocks in the
             // sliced form (FP64, identity order, one colour); the V-cycle is the dense solve
+            Temporaries keep;
             for (int f = 0; f < 2; ++f) {
                 BlockLevel& B = c.blk[f];
                 const int g = 1 - f;
                 build_part(B.off, PartKind::Off, B, &c.A[f][f], B.d_iperm.p, c.A[f][f].val.p, c.d[f], c.d[f], false,
-                           s);
+                           s, keep);
                 build_part(B.diag, PartKind::Diag, B, &c.A[f][f], B.d_iperm.p, c.A[f][f].val.p, c.d[f], c.d[f],
-                           false, s);
+                           false, s, keep);
                 build_part(B.cpl, PartKind::Cpl, B, &c.A[f][g], c.blk[g].d_iperm.p, c.A[f][g].val.p, c.d[f], c.d[g],
-                           false, s);
+                           false, s, keep);
             }
             c.apply_parts = true;
         }
@@ -1283,19 +1293,22 @@ static void setup_impl(mbamg_hierarchy* h, const mbamg_bsr* Ab, hipStream_t s, D
             }
             clk.mark("colouring joined", l);
         }
+        DeviceCopies up;
         for (int f = 0; f < 2 && !shared; ++f) {
             BlockLevel& B = Lv.blk[f];
-            B.row0.upload(B.h_row0, s);
-            B.nrow.upload(B.h_nrow, s);
-            B.d_perm.upload(B.perm, s);
-            B.d_iperm.upload(B.iperm, s);
-            if (B.group > 1) B.cstart.upload(B.h_cstart, s);
+            up.add(B.row0, B.h_row0);
+            up.add(B.nrow, B.h_nrow);
+            up.add(B.d_perm, B.perm);
+            up.add(B.d_iperm, B.iperm);
+            if (B.group > 1) up.add(B.cstart, B.h_cstart);
         }
+        up.run(s);
         for (int f = 0; f < 2 && !shared; ++f) {
             const int g = 1 - f;
             BlockLevel& B = Lv.blk[f];
             const int df = Lv.d[f], dg = Lv.d[g];
             const int nf = Lv.nodes(f);
+            Temporaries keep;
             DevBuf<double> dinv((size_t)nf * df * df);
             if (f == 0) clk.mark("colouring", l);
             build_dinv(Lv.A[f][f], dinv.p, s);
@@ -1303,10 +1316,10 @@ static void setup_impl(mbamg_hierarchy* h, const mbamg_bsr* Ab, hipStream_t s, D
             if (B.group > 1) {
                 B.split = 1;
                 build_part(B.off, PartKind::Off, B, &Lv.A[f][f], B.d_iperm.p, Lv.A[f][f].val.p, df, df, want32, s,
-                       Lv.shape);
+                       keep, Lv.shape);
                 build_part(B.cpl, PartKind::Cpl, B, &Lv.A[f][g], Lv.blk[g].d_iperm.p, Lv.A[f][g].val.p, df, dg,
-                           want32, s, Lv.shape);
-                build_recs(B, s);
+                           want32, s, keep, Lv.shape);
+                build_recs(B, s, keep);
                 const int64_t nd = (int64_t)nf * df * df;
                 B.gdinv64.alloc(nd);
                 gather_blocks(nf, df * df, B.d_perm.p, dinv.p, B.gdinv64.p, s);
@@ -1327,12 +1340,12 @@ static void setup_impl(mbamg_hierarchy* h, const mbamg_bsr* Ab, hipStream_t s, D
                 continue;
             }
             build_part(B.off, PartKind::Off, B, &Lv.A[f][f], B.d_iperm.p, Lv.A[f][f].val.p, df, df, want32, s,
-                       Lv.shape);
+                       keep, Lv.shape);
             build_part(B.diag, PartKind::Diag, B, &Lv.A[f][f], B.d_iperm.p, Lv.A[f][f].val.p, df, df, want32, s,
-                       Lv.shape);
+                       keep, Lv.shape);
             build_part(B.cpl, PartKind::Cpl, B, &Lv.A[f][g], Lv.blk[g].d_iperm.p, Lv.A[f][g].val.p, df, dg, want32,
-                       s, Lv.shape);
-            build_part(B.dinv, PartKind::Dinv, B, nullptr, nullptr, dinv.p, df, df, want32, s);
+                       s, keep, Lv.shape);
+            build_part(B.dinv, PartKind::Dinv, B, nullptr, nullptr, dinv.p, df, df, want32, s, keep);
             B.cstats.assign(B.n_colours, ColourStats{});
             int64_t slots = 0;
             for (int c = 0; c < B.n_colours; ++c) {
@@ -1413,9 +1426,10 @@ static void setup_impl(mbamg_hierarchy* h, const mbamg_bsr* Ab, hipStream_t s, D
             BlockLevel& B = Lv.blk[f];
             BlockLevel& C = Nx.blk[f];
             // P sliced by 64 rows in colour order, whatever the level's own slices
+            Temporaries keep;
             BlockLevel col;
             natural_slicing(col, Lv.nodes(f), s, &B.perm);
-            build_part(B.pro, PartKind::Cpl, col, &Lv.P[f], C.d_iperm.p, Lv.P[f].val.p, B.d, B.d, want32, s);
+            build_part(B.pro, PartKind::Cpl, col, &Lv.P[f], C.d_iperm.p, Lv.P[f].val.p, B.d, B.d, want32, s, keep);
             B.pro_row0 = std::move(col.row0);
             B.pro_nrow = std::move(col.nrow);
             B.pro_slices = col.n_slices;
@@ -1425,7 +1439,7 @@ static void setup_impl(mbamg_hierarchy* h, const mbamg_bsr* Ab, hipStream_t s, D
             // algorithmic bytes fetched on the finest level)
             BlockLevel nat;
             natural_slicing(nat, Nx.nodes(f), s);
-            build_part(B.res, PartKind::Cpl, nat, &Lv.PT[f], B.d_iperm.p, Lv.PT[f].val.p, B.d, B.d, want32, s);
+            build_part(B.res, PartKind::Cpl, nat, &Lv.PT[f], B.d_iperm.p, Lv.PT[f].val.p, B.d, B.d, want32, s, keep);
             B.res_row0 = std::move(nat.row0);
             B.res_nrow = std::move(nat.nrow);
             B.res_slices = nat.n_slices;
@@ -2155,10 +2169,12 @@ static void gen_setup_impl(mbamg_hierarchy* h, const mbamg_bsr* Ab, hipStream_t 
                                       : greedy_colour(Lv.n, rp.data(), ci.data(), B.colour);
                 order_and_slice(B, Lv.n, ncol, rp.data(), group_lanes(Lv.n, Lv.A[f][f].nnzb));
             }
-            B.row0.upload(B.h_row0, s);
-            B.nrow.upload(B.h_nrow, s);
-            B.d_perm.upload(B.perm, s);
-            B.d_iperm.upload(B.iperm, s);
+            DeviceCopies up;
+            up.add(B.row0, B.h_row0);
+            up.add(B.nrow, B.h_nrow);
+            up.add(B.d_perm, B.perm);
+            up.add(B.d_iperm, B.iperm);
+            up.run(s);
         }
         // the coarsest level's vectors serve the dense solve; its operator is only applied when it
         // is the only level
@@ -2166,13 +2182,14 @@ static void gen_setup_impl(mbamg_hierarchy* h, const mbamg_bsr* Ab, hipStream_t 
         for (int f = 0; f < nb && parts; ++f) {
             BlockLevel& B = Lv.blk[f];
             const int df = Lv.d[f];
+            Temporaries keep;
             B.cstart.upload(B.h_cstart, s);
-            build_part(B.off, PartKind::Off, B, &Lv.A[f][f], B.d_iperm.p, Lv.A[f][f].val.p, df, df, false, s);
+            build_part(B.off, PartKind::Off, B, &Lv.A[f][f], B.d_iperm.p, Lv.A[f][f].val.p, df, df, false, s, keep);
             for (int g = 0; g < nb; ++g)
                 if (g != f && Lv.A[f][g].nnzb > 0)
                     build_part(Lv.C[f][g], PartKind::Cpl, B, &Lv.A[f][g], Lv.blk[g].d_iperm.p, Lv.A[f][g].val.p, df,
-                               Lv.d[g], false, s);
-            build_recs(B, s);
+                               Lv.d[g], false, s, keep);
+            build_recs(B, s, keep);
             const int64_t nd = (int64_t)Lv.n * df * df;
             DevBuf<double> dinv((size_t)nd);
             B.gdiag64.alloc(nd);

@@ -106,7 +106,7 @@ const char* form_override(const char* var);
 // device construction of the sliced and grouped smoother formats (see hierarchy.hip), G lanes per row
 void part_layout(int n, int ns, int kind, int G, const int32_t* perm, const int32_t* rp, const int32_t* ci,
                  const int32_t* row0, const int32_t* nrow, DevBuf<int32_t>& width, DevBuf<int32_t>& coff32,
-                 int64_t& n_slots, hipStream_t s);
+                 DevBuf<int64_t>& coff, int64_t& n_slots, hipStream_t s);
 void part_fill_index(int ns, int kind, int G, int n_cols, const int32_t* row0, const int32_t* nrow,
                      const int32_t* cstart, const int32_t* width, const int32_t* coff32, const int32_t* perm,
                      const int32_t* rp, const int32_t* ci, const int32_t* col_iperm, int64_t n_slots, int32_t* col,
@@ -116,7 +116,6 @@ void sweep_recs(int n, const int32_t* order, const int32_t* row0, const int32_t*
                 const int32_t* ow, const int64_t* oc, const int32_t* cw, const int64_t* cc, SweepRec* out,
                 hipStream_t s);
 int64_t slot_offsets(int64_t n_slots, const uint32_t* mask, DevBuf<int64_t>& voff, hipStream_t s);
-void i32_to_i64(int64_t n, const int32_t* a, int64_t* b, hipStream_t s);
 void transfer_maps(int n, int nc, const int32_t* perm, const int32_t* iperm, const int32_t* agg,
                    const int32_t* cperm, const int32_t* ciperm, const int32_t* mptr, const int32_t* midx,
                    DevBuf<int32_t>& aggp, DevBuf<int32_t>& optr, DevBuf<int32_t>& oidx, hipStream_t s);
