@@ -279,7 +279,7 @@ struct mbamg_hierarchy {
     int coarse_n = 0;
     // Krylov workspace
     int64_t n_fine = 0;
-    DevBuf<double> V, Z64, w, xw, bw, ztmp, partial, ybuf, coef;
+    DevBuf<double> V, Z64, w, xw, bw, partial, ybuf, coef;
     DevBuf<uint32_t> kcounter;     // blocks of the running Krylov pass that are done
     DevBuf<float> mlp;             // network parameters (5122) followed by feature mean and std (12 + 12)
     double* hbuf_host = nullptr;   // pinned: two sets of Krylov results, written by the device
@@ -1499,7 +1499,6 @@ static void setup_impl(mbamg_hierarchy* h, const mbamg_bsr* Ab, hipStream_t s, D
     if (want32) {
         h->Z32.alloc((size_t)m * n);
         h->vin32.alloc(n);
-        h->ztmp.alloc(n);
     } else {
         h->Z64.alloc((size_t)m * n);
     }
@@ -1879,11 +1878,11 @@ static void smooth_block(mbamg_hierarchy* h, int l, int f, bool zero, const T* b
     }
 }
 
-template <class T>
-static void resid(mbamg_hierarchy* h, int l, const T* b, const T* x, T* r, hipStream_t s, int kind) {
+template <class T, class TX = T>   // TX: the type x is stored in
+static void resid(mbamg_hierarchy* h, int l, const T* b, const TX* x, T* r, hipStream_t s, int kind) {
     Level& Lv = *h->L[l];
     const int64_t n0 = (int64_t)Lv.n * Lv.d[0];
-    ResidArgs<T> a{};
+    ResidArgs<T, TX> a{};
     a.shape = Lv.shape;
     for (int f = 0; f < 2; ++f) {
         BlockLevel& B = Lv.blk[f];
@@ -1899,10 +1898,11 @@ static void resid(mbamg_hierarchy* h, int l, const T* b, const T* x, T* r, hipSt
         a.order[f] = Lv.resid_order[f].p;
     }
     const bool timed = h->time_launches() && kind >= 0 && (l == 0 || kind == 1);
-    double bytes = timed ? resid_bytes(Lv, (int)sizeof(T), b != nullptr) : 0.0;
+    double bytes = timed ? resid_bytes(Lv, (int)sizeof(T), b != nullptr) -
+                               (double)Lv.ndof() * (sizeof(T) - sizeof(TX)) : 0.0;
     TimerScope ts(h, s, timed, launch_kind(l, kind), bytes);
     if (Lv.blk[0].group > 1) {
-        ResidGroupArgs<T> ga{};
+        ResidGroupArgs<T, TX> ga{};
         ga.shape = Lv.shape;
         for (int f = 0; f < 2; ++f) {
             const BlockLevel& B = Lv.blk[f];
@@ -1916,10 +1916,10 @@ static void resid(mbamg_hierarchy* h, int l, const T* b, const T* x, T* r, hipSt
             ga.x[f] = a.x[f];
             ga.r[f] = a.r[f];
         }
-        launch_resid_group<T>(Lv.d[0], ga, s);
+        launch_resid_group<T, TX>(Lv.d[0], ga, s);
         return;
     }
-    launch_resid<T>(Lv.d[0], Lv.resid_split, a, s);
+    launch_resid<T, TX>(Lv.d[0], Lv.resid_split, a, s);
 }
 
 // One V-cycle on level l from a zero guess: out = MGV(0, b).
@@ -2388,7 +2388,8 @@ static void gen_vcycle_level(mbamg_hierarchy* h, int l, const double* b, double*
 }
 
 // z = M^-1 v for FP64 colour-order vectors of the finest level (either form).
-static void apply_precond(mbamg_hierarchy* h, const double* v, double* z64, float* z32, hipStream_t s) {
+static void apply_precond(mbamg_hierarchy* h, const double* v, double* z64, float* z32, hipStream_t s,
+                          bool v32_there = false) {
     if (h->nb > 2) {
         TimerScope ts(h, s, h->time_vcycles(), TK_VCYCLE, 0.0);
         gen_vcycle_level(h, 0, v, z64, s);
@@ -2396,7 +2397,7 @@ static void apply_precond(mbamg_hierarchy* h, const double* v, double* z64, floa
     }
     if (h->p.precision == 1) {
         Level& L0 = *h->L[0];
-        launch_cast64to32(h->n_fine, v, h->vin32.p, s);
+        if (!v32_there) launch_cast64to32(h->n_fine, v, h->vin32.p, s);
         {
             TimerScope ts(h, s, h->time_vcycles(), TK_VCYCLE, 0.0);
             if (L0.coarsest) {
@@ -2435,14 +2436,17 @@ static void from_colour(mbamg_hierarchy* h, const double* src, double* dst, hipS
 }
 
 // A x on the finest level (colour order), FP64
-static void apply_A(mbamg_hierarchy* h, const double* x, double* w, hipStream_t s, int kind = 2) {
-    if (h->nb > 2) {
-        gen_resid(h, 0, nullptr, x, w, s);
-        return;
+template <class TX>
+static void apply_A(mbamg_hierarchy* h, const TX* x, double* w, hipStream_t s, int kind = 2) {
+    if constexpr (std::is_same_v<TX, double>) {
+        if (h->nb > 2) {
+            gen_resid(h, 0, nullptr, x, w, s);
+            return;
+        }
     }
     Level& L0 = *h->L[0];
     if (L0.coarsest && !L0.apply_parts) throw Error(MBAMG_E_STATE, "internal: finest-level operator missing");
-    resid<double>(h, 0, nullptr, x, w, s, kind);
+    resid<double, TX>(h, 0, nullptr, x, w, s, kind);
 }
 
 // ----------------------------------------------------------------------------
@@ -2552,15 +2556,23 @@ static mbamg_status solve_impl(mbamg_hierarchy* h, const double* b, double* x, d
             auto enqueue = [&](int j) {
                 double* vj = h->V.p + (size_t)j * n;
                 double* vn = h->V.p + (size_t)(j + 1) * n;
-                double* zj64 = fp32 ? h->ztmp.p : h->Z64.p + (size_t)j * n;
-                float* zj32 = fp32 ? h->Z32.p + (size_t)j * n : nullptr;
                 const KrylovBufs kb = krylov_bufs(h, j & 1);
-                apply_precond(h, vj, zj64, zj32, s);
-                apply_A(h, zj64, h->w.p, s);
+                if (fp32) {
+                    // the candidate in FP32 comes with the update pass and the operator reads z in
+                    // FP32 (casts between them as launches of their own took 80 of 2700 us per step
+                    // at 16.8M unknowns, 8 of 210 us at 393,216)
+                    float* zj = h->Z32.p + (size_t)j * n;
+                    apply_precond(h, vj, nullptr, zj, s, j > 0);
+                    apply_A(h, zj, h->w.p, s);
+                } else {
+                    double* zj = h->Z64.p + (size_t)j * n;
+                    apply_precond(h, vj, zj, nullptr, s);
+                    apply_A(h, zj, h->w.p, s);
+                }
                 // dot pass: b = Q^T w and u_j . w; c_j on the device
                 launch_orth(n, j + 1, h->V.p, n, h->w.p, kb, s);
                 // update pass: Q_j over u_j, u_{j+1} into V_{j+1}, a_{j+1} and nu_{j+1}
-                launch_dcgs_update(n, j, h->V.p, n, vj, h->w.p, vn, kb, s);
+                launch_dcgs_update(n, j, h->V.p, n, vj, h->w.p, vn, fp32 ? h->vin32.p : nullptr, kb, s);
                 MB_HIP(hipEventRecord(h->step_done[j & 1], s));
             };
             int queued = 0;

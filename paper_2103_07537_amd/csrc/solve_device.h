@@ -67,6 +67,19 @@ __device__ __forceinline__ void load_vec<double, 2>(const double* __restrict__ p
     v[0] = a.x; v[1] = a.y;
 }
 
+// a vector stored as TX, in T
+template <class T, int D, class TX>
+__device__ __forceinline__ void load_vec_from(const TX* __restrict__ p, T (&v)[D]) {
+    if constexpr (std::is_same_v<T, TX>) {
+        load_vec<T, D>(p, v);
+    } else {
+        TX x[D];
+        load_vec<TX, D>(p, x);
+#pragma unroll
+        for (int c = 0; c < D; ++c) v[c] = (T)x[c];
+    }
+}
+
 template <class T, int D>
 __device__ __forceinline__ void store_vec(T* __restrict__ p, const T (&v)[D]) {
 #pragma unroll

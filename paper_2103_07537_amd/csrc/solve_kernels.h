@@ -185,7 +185,7 @@ struct ResidNArgs {
     double* r[SWEEP_MAX_BLOCKS];
 };
 
-template <class T>
+template <class T, class TX = T>   // TX: the type x is stored in
 struct ResidGroupArgs {
     int shape;
     const SweepRec* rec[2];
@@ -194,18 +194,18 @@ struct ResidGroupArgs {
     GroupView<T> off[2], cpl[2];
     const T* diag[2];          // d x d per row, colour order
     const T* b[2];             // NULL for a plain operator apply
-    const T* x[2];
+    const TX* x[2];
     T* r[2];
 };
 
-template <class T>
+template <class T, class TX = T>
 struct ResidArgs {
     int shape;
     int s_count[2];
     SliceView sl[2];
     SellView<T> off[2], cpl[2], diag[2];
     const T* b[2];             // NULL for a plain operator apply
-    const T* x[2];
+    const TX* x[2];
     T* r[2];
     const int32_t* order[2];   // slice of each launch position (NULL: the position itself)
 };
@@ -255,16 +255,16 @@ template <class T>
 void launch_xfer_rows(int d, const XferRowArgs<T>& a, hipStream_t s);
 template <class T>
 void launch_gs(int d, int P, bool zero_x, bool has_cpl, const GsArgs<T>& a, hipStream_t s);
-template <class T>
-void launch_resid(int d, int P, const ResidArgs<T>& a, hipStream_t s);
+template <class T, class TX>
+void launch_resid(int d, int P, const ResidArgs<T, TX>& a, hipStream_t s);
 template <class T>
 void launch_gs_fc(int d, int P, bool zero_x, const GsFcArgs<T>& a, hipStream_t s);
 // positions of a record list are taken this many at a time: every colour's are padded to a multiple
 constexpr int SWEEP_WAVES = 8;
 template <class T>
 void launch_sweep(int d, bool zero_x, const Sweep2Args<T>& a, hipStream_t s);
-template <class T>
-void launch_resid_group(int d, const ResidGroupArgs<T>& a, hipStream_t s);
+template <class T, class TX>
+void launch_resid_group(int d, const ResidGroupArgs<T, TX>& a, hipStream_t s);
 void launch_sweep_n(int d, bool zero_x, const SweepNArgs& a, hipStream_t s);
 void launch_resid_n(const ResidNArgs& a, hipStream_t s);
 
@@ -302,7 +302,7 @@ void launch_orth(int64_t n, int nq, const double* V, int64_t ldv, const double* 
                  hipStream_t s);
 // One pass of the delayed reorthogonalisation step (see the kernel)
 void launch_dcgs_update(int64_t n, int nq, const double* V, int64_t ldv, double* u, const double* w, double* out,
-                        const KrylovBufs& kb, hipStream_t s);
+                        float* out32, const KrylovBufs& kb, hipStream_t s);
 void launch_combine(int64_t n, int k, const double* Z, int64_t ldz, const double* y, double* x, hipStream_t s);
 void launch_combine32(int64_t n, int k, const float* Z, int64_t ldz, const double* y, double* x, hipStream_t s);
 void launch_axpby(int64_t n, double a, const double* x, double b, double* y, hipStream_t s);

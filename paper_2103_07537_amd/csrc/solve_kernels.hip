@@ -52,9 +52,9 @@ __device__ __forceinline__ void fetch_chunk(const SellView<T>& A, int s, int lan
 
 // SKIPD: the slot holding column `self` (the row's own node) is left out.
 // pre (split slices only): the first chunk, fetched by the caller ahead of time.
-template <class T, int D, int MODE, int P, int S = SHAPE_FULL, bool SKIPD = false>
-__device__ __forceinline__ void sell_sub(const SellView<T>& A, int s, int lane, int part, const T* __restrict__ xa,
-                                         const T* __restrict__ xb, int cstart, T (&acc)[D], int self = -1,
+template <class T, int D, int MODE, int P, int S = SHAPE_FULL, bool SKIPD = false, class TX = T>
+__device__ __forceinline__ void sell_sub(const SellView<T>& A, int s, int lane, int part, const TX* __restrict__ xa,
+                                         const std::common_type_t<TX>* __restrict__ xb, int cstart, T (&acc)[D], int self = -1,
                                          const SlotChunk<sell_chunk<T, P>()>* pre = nullptr) {
     constexpr int CH = sell_chunk<T, P>();
     constexpr bool PF = P >= 4;
@@ -105,11 +105,11 @@ __device__ __forceinline__ void sell_sub(const SellView<T>& A, int s, int lane, 
 #pragma unroll
         for (int u = 0; u < CH; ++u) {
             const int jj = jc[u];
-            const T* src = nullptr;
+            const TX* src = nullptr;
             if (MODE == 0) src = xa;
             else if (MODE == 1) src = jj < cstart ? xa : xb;
             else src = jj < cstart ? xa : nullptr;
-            if (jj >= 0 && src && !(SKIPD && jj == self)) load_vec<T, D>(src + (int64_t)jj * D, xj[u]);
+            if (jj >= 0 && src && !(SKIPD && jj == self)) load_vec_from<T, D>(src + (int64_t)jj * D, xj[u]);
             else {
 #pragma unroll
                 for (int c = 0; c < D; ++c) xj[u][c] = T(0);
@@ -437,8 +437,8 @@ template void launch_xfer_rows<double>(int, const XferRowArgs<double>&, hipStrea
 template void launch_xfer_rows<float>(int, const XferRowArgs<float>&, hipStream_t);
 
 // r = b - A x (or w = A x when b is NULL) for both block rows in one launch.
-template <class T, int D, int P, int S>
-__global__ __launch_bounds__(waves_per_block<P>() * WAVE) void k_resid(ResidArgs<T> a, int padded_blocks) {
+template <class T, class TX, int D, int P, int S>
+__global__ __launch_bounds__(waves_per_block<P>() * WAVE) void k_resid(ResidArgs<T, TX> a, int padded_blocks) {
     const int wave = wave_id();
     const int part = wave % P;
     int sidx = xcd_block(padded_blocks) * (waves_per_block<P>() / P) + wave / P;
@@ -692,8 +692,8 @@ void launch_gs_fc(int d, int P, bool zero_x, const GsFcArgs<T>& a, hipStream_t s
     MB_LAUNCH_CHECK();
 }
 
-template <class T, int D>
-static void resid_dispatch(int P, const ResidArgs<T>& a, hipStream_t s) {
+template <class T, class TX, int D>
+static void resid_dispatch(int P, const ResidArgs<T, TX>& a, hipStream_t s) {
     const int total = a.s_count[0] + a.s_count[1];
     unsigned grid = xcd_grid(total, P);
     int pb = (int)grid;
@@ -701,33 +701,33 @@ static void resid_dispatch(int P, const ResidArgs<T>& a, hipStream_t s) {
         if (a.shape != SHAPE_FULL) {
             MB_CHECK(P <= SHAPE_MAX_SPLIT, MBAMG_E_INVALID, "slot split too large for this block shape");
             if (a.shape == SHAPE_SCALED) {
-                if (P == 1) k_resid<T, D, 1, SHAPE_SCALED><<<grid, 256, 0, s>>>(a, pb);
-                else k_resid<T, D, 2, SHAPE_SCALED><<<grid, 256, 0, s>>>(a, pb);
+                if (P == 1) k_resid<T, TX, D, 1, SHAPE_SCALED><<<grid, 256, 0, s>>>(a, pb);
+                else k_resid<T, TX, D, 2, SHAPE_SCALED><<<grid, 256, 0, s>>>(a, pb);
             } else {
-                if (P == 1) k_resid<T, D, 1, SHAPE_SYMMETRIC><<<grid, 256, 0, s>>>(a, pb);
-                else k_resid<T, D, 2, SHAPE_SYMMETRIC><<<grid, 256, 0, s>>>(a, pb);
+                if (P == 1) k_resid<T, TX, D, 1, SHAPE_SYMMETRIC><<<grid, 256, 0, s>>>(a, pb);
+                else k_resid<T, TX, D, 2, SHAPE_SYMMETRIC><<<grid, 256, 0, s>>>(a, pb);
             }
             return;
         }
     }
     switch (P) {
-        case 1: k_resid<T, D, 1, SHAPE_FULL><<<grid, 256, 0, s>>>(a, pb); break;
-        case 2: k_resid<T, D, 2, SHAPE_FULL><<<grid, 256, 0, s>>>(a, pb); break;
-        case 4: k_resid<T, D, 4, SHAPE_FULL><<<grid, 256, 0, s>>>(a, pb); break;
-        case 8: k_resid<T, D, 8, SHAPE_FULL><<<grid, 512, 0, s>>>(a, pb); break;
-        case 16: k_resid<T, D, 16, SHAPE_FULL><<<grid, 1024, 0, s>>>(a, pb); break;
+        case 1: k_resid<T, TX, D, 1, SHAPE_FULL><<<grid, 256, 0, s>>>(a, pb); break;
+        case 2: k_resid<T, TX, D, 2, SHAPE_FULL><<<grid, 256, 0, s>>>(a, pb); break;
+        case 4: k_resid<T, TX, D, 4, SHAPE_FULL><<<grid, 256, 0, s>>>(a, pb); break;
+        case 8: k_resid<T, TX, D, 8, SHAPE_FULL><<<grid, 512, 0, s>>>(a, pb); break;
+        case 16: k_resid<T, TX, D, 16, SHAPE_FULL><<<grid, 1024, 0, s>>>(a, pb); break;
         default: throw Error(MBAMG_E_INVALID, "slot split must be 1, 2, 4, 8 or 16");
     }
 }
 
-template <class T>
-void launch_resid(int d, int P, const ResidArgs<T>& a, hipStream_t s) {
+template <class T, class TX>
+void launch_resid(int d, int P, const ResidArgs<T, TX>& a, hipStream_t s) {
     if (a.s_count[0] + a.s_count[1] <= 0) return;
     switch (d) {
-        case 1: resid_dispatch<T, 1>(P, a, s); break;
-        case 2: resid_dispatch<T, 2>(P, a, s); break;
-        case 3: resid_dispatch<T, 3>(P, a, s); break;
-        case 4: resid_dispatch<T, 4>(P, a, s); break;
+        case 1: resid_dispatch<T, TX, 1>(P, a, s); break;
+        case 2: resid_dispatch<T, TX, 2>(P, a, s); break;
+        case 3: resid_dispatch<T, TX, 3>(P, a, s); break;
+        case 4: resid_dispatch<T, TX, 4>(P, a, s); break;
         default: throw Error(MBAMG_E_INVALID, "dofs per node must be 1..4");
     }
     MB_LAUNCH_CHECK();
@@ -816,8 +816,9 @@ template void launch_gs<double>(int, int, bool, bool, const GsArgs<double>&, hip
 template void launch_gs_fc<double>(int, int, bool, const GsFcArgs<double>&, hipStream_t);
 template void launch_gs_fc<float>(int, int, bool, const GsFcArgs<float>&, hipStream_t);
 template void launch_gs<float>(int, int, bool, bool, const GsArgs<float>&, hipStream_t);
-template void launch_resid<double>(int, int, const ResidArgs<double>&, hipStream_t);
-template void launch_resid<float>(int, int, const ResidArgs<float>&, hipStream_t);
+template void launch_resid<double, double>(int, int, const ResidArgs<double>&, hipStream_t);
+template void launch_resid<float, float>(int, int, const ResidArgs<float>&, hipStream_t);
+template void launch_resid<double, float>(int, int, const ResidArgs<double, float>&, hipStream_t);
 template void launch_restrict<double>(int, const TransferArgs<double>&, int, hipStream_t);
 template void launch_restrict<float>(int, const TransferArgs<float>&, int, hipStream_t);
 template void launch_prolong<double>(int, const TransferArgs<double>&, hipStream_t);
@@ -965,11 +966,12 @@ __global__ __launch_bounds__(KT) __attribute__((amdgpu_waves_per_eu(4, 4))) void
 // and the dots a' = [Q q]^T un and |un|^2 for the next step.  The last block
 // writes them out (d2, nu2), the next candidate's nu' = sqrt(|un|^2 - |a'|^2) (nu;
 // 0 when the candidate lies in the basis) and the next step's coefficients a' and
-// 1/nu', so the next step needs nothing from the host.  NQ is the exact count.
+// 1/nu', so the next step needs nothing from the host.  out32 (may be null): un in
+// FP32, for a preconditioner that runs in it.  NQ is the exact count.
 template <int NQ>
 __global__ __launch_bounds__(KT) void k_dcgs_update(int64_t n, const double* __restrict__ V, int64_t ldv, double* u,
                                                     const double* __restrict__ w, double* __restrict__ out,
-                                                    KrylovBufs kb) {
+                                                    float* __restrict__ out32, KrylovBufs kb) {
     constexpr int NV = NQ > 0 ? NQ : 1;
     __shared__ double sh[KW][KMAXQ];
     __shared__ double res[KMAXQ];
@@ -1000,6 +1002,7 @@ __global__ __launch_bounds__(KT) void k_dcgs_update(int64_t n, const double* __r
         un = (un - cj * q) * inv_nu;
         u[e] = q;
         out[e] = un;
+        if (out32) out32[e] = (float)un;
 #pragma unroll
         for (int k = 0; k < NQ; ++k) acc[k] += v[k] * un;
         acc[NQ] += q * un;
@@ -1148,6 +1151,7 @@ struct DcgsArgs {
     double* u;
     const double* w;
     double* out;
+    float* out32;
     const KrylovBufs& kb;
     hipStream_t s;
 };
@@ -1155,7 +1159,7 @@ template <int Q>
 struct DcgsLaunch {
     using Args = DcgsArgs;
     static void run(const DcgsArgs& a) {
-        k_dcgs_update<Q><<<krylov_blocks(a.n), KT, 0, a.s>>>(a.n, a.V, a.ldv, a.u, a.w, a.out, a.kb);
+        k_dcgs_update<Q><<<krylov_blocks(a.n), KT, 0, a.s>>>(a.n, a.V, a.ldv, a.u, a.w, a.out, a.out32, a.kb);
     }
 };
 
@@ -1172,9 +1176,9 @@ void launch_orth(int64_t n, int nq, const double* V, int64_t ldv, const double* 
 }
 
 void launch_dcgs_update(int64_t n, int nq, const double* V, int64_t ldv, double* u, const double* w, double* out,
-                        const KrylovBufs& kb, hipStream_t s) {
+                        float* out32, const KrylovBufs& kb, hipStream_t s) {
     MB_CHECK(nq >= 0 && nq <= KMAXQ - 2 && nq <= 31, MBAMG_E_INVALID, "too many Krylov vectors");
-    by_count<DcgsLaunch>(nq, std::make_integer_sequence<int, 32>{}, DcgsArgs{n, V, ldv, u, w, out, kb, s});
+    by_count<DcgsLaunch>(nq, std::make_integer_sequence<int, 32>{}, DcgsArgs{n, V, ldv, u, w, out, out32, kb, s});
     MB_LAUNCH_CHECK();
 }
 

@@ -78,8 +78,8 @@ __device__ __forceinline__ void operand_value(const SweepOperand<T>& o, int j, c
 // columns below cstart from ta (awaited), others from xa.  MODE 2: columns below
 // cstart from ta (awaited), others contribute 0.  MODE 3: the coupling operand op,
 // every column awaited.
-template <class T, int D, int MODE, int S>
-__device__ __forceinline__ void group_sub(const GroupView<T>& A, int w, int cb, int lane, const T* __restrict__ xa,
+template <class T, int D, int MODE, int S, class TX = T>
+__device__ __forceinline__ void group_sub(const GroupView<T>& A, int w, int cb, int lane, const TX* __restrict__ xa,
                                           const T* ta, int cstart, T (&acc)[D],
                                           const SweepOperand<T>* op = nullptr) {
     constexpr int CH = 2;
@@ -109,10 +109,10 @@ __device__ __forceinline__ void group_sub(const GroupView<T>& A, int w, int cb, 
             if (MODE == 3) {
 #pragma unroll
                 for (int c = 0; c < D; ++c) xo[u][c] = T(0);
-                if (xa && j[u] >= 0) load_vec<T, D>(xa + (int64_t)j[u] * D, xo[u]);
+                if (xa && j[u] >= 0) load_vec_from<T, D>(xa + (int64_t)j[u] * D, xo[u]);
             }
             if (await[u]) load_shared_vec<T, D>(ta + (int64_t)j[u] * D, xj[u]);
-            else if (MODE < 2 && j[u] >= 0) load_vec<T, D>(xa + (int64_t)j[u] * D, xj[u]);
+            else if (MODE < 2 && j[u] >= 0) load_vec_from<T, D>(xa + (int64_t)j[u] * D, xj[u]);
         }
         if (MODE != 0) {
             for (int round = 0; round < SWEEP_MAX_ROUNDS; ++round) {
@@ -240,7 +240,7 @@ __device__ __forceinline__ void sweep_slice(const SweepArgs<T>& a, const SweepRe
     couplings(acc);
     const int cstart = a.inplace ? INT_MAX : rec.cstart;
     if (ZX) {
-        if (cstart > 0) group_sub<T, D, 2, S>(a.off, rec.off_w, rec.off_c, lane, nullptr, a.t, cstart, acc);
+        if (cstart > 0) group_sub<T, D, 2, S, T>(a.off, rec.off_w, rec.off_c, lane, nullptr, a.t, cstart, acc);
     } else {
         group_sub<T, D, 1, S>(a.off, rec.off_w, rec.off_c, lane, a.x, a.t, cstart, acc);
     }
@@ -378,8 +378,8 @@ __global__ __launch_bounds__(256) void k_resid_n(ResidNArgs a, int padded_blocks
 
 // r = b - A x (or w = A x when b is NULL) in grouped form, block 0's record
 // list, then block 1's
-template <class T, int D, int S>
-__global__ __launch_bounds__(256) void k_resid_group(ResidGroupArgs<T> a, int padded_blocks) {
+template <class T, class TX, int D, int S>
+__global__ __launch_bounds__(256) void k_resid_group(ResidGroupArgs<T, TX> a, int padded_blocks) {
     int pos = xcd_block(padded_blocks) * WPB + wave_id();
     int f = 0;
     if (pos >= a.count[0]) {
@@ -396,7 +396,7 @@ __global__ __launch_bounds__(256) void k_resid_group(ResidGroupArgs<T> a, int pa
     const int64_t at = (int64_t)row * D + (q < D ? q : 0);
     T dg[D], xr[D], bq = T(0);
     load_vec<T, D>(a.diag[f] + at * D, dg);
-    load_vec<T, D>(a.x[f] + (int64_t)row * D, xr);
+    load_vec_from<T, D>(a.x[f] + (int64_t)row * D, xr);
     if (a.b[f]) bq = a.b[f][at];
     T acc[D];
 #pragma unroll
@@ -437,20 +437,20 @@ static void sweep_dispatch(bool zx, unsigned grid, const Sweep2Args<T>& a, hipSt
     sweep_dispatch_s<T, D, SHAPE_FULL>(zx, grid, a, s);
 }
 
-template <class T, int D>
-static void resid_group_dispatch(unsigned grid, const ResidGroupArgs<T>& a, hipStream_t s) {
+template <class T, class TX, int D>
+static void resid_group_dispatch(unsigned grid, const ResidGroupArgs<T, TX>& a, hipStream_t s) {
     const int pb = (int)grid;
     if constexpr (D > 1) {
         if (a.shape == SHAPE_SCALED) {
-            k_resid_group<T, D, SHAPE_SCALED><<<grid, 256, 0, s>>>(a, pb);
+            k_resid_group<T, TX, D, SHAPE_SCALED><<<grid, 256, 0, s>>>(a, pb);
             return;
         }
         if (a.shape == SHAPE_SYMMETRIC) {
-            k_resid_group<T, D, SHAPE_SYMMETRIC><<<grid, 256, 0, s>>>(a, pb);
+            k_resid_group<T, TX, D, SHAPE_SYMMETRIC><<<grid, 256, 0, s>>>(a, pb);
             return;
         }
     }
-    k_resid_group<T, D, SHAPE_FULL><<<grid, 256, 0, s>>>(a, pb);
+    k_resid_group<T, TX, D, SHAPE_FULL><<<grid, 256, 0, s>>>(a, pb);
 }
 
 // a block's positions come in whole workgroups, so no workgroup takes two blocks'
@@ -516,22 +516,23 @@ void launch_resid_n(const ResidNArgs& a, hipStream_t s) {
     MB_LAUNCH_CHECK();
 }
 
-template <class T>
-void launch_resid_group(int d, const ResidGroupArgs<T>& a, hipStream_t s) {
+template <class T, class TX>
+void launch_resid_group(int d, const ResidGroupArgs<T, TX>& a, hipStream_t s) {
     const int total = a.count[0] + a.count[1];
     if (total <= 0) return;
     MB_CHECK(a.lg[0] >= 2 && a.lg[0] <= 6 && a.lg[1] >= 2 && a.lg[1] <= 6, MBAMG_E_INVALID, "4 to 64 lanes per row");
     const unsigned grid = xcd_grid(total, 1);
     switch (d) {
-        case 1: resid_group_dispatch<T, 1>(grid, a, s); break;
-        case 2: resid_group_dispatch<T, 2>(grid, a, s); break;
-        case 3: resid_group_dispatch<T, 3>(grid, a, s); break;
-        case 4: resid_group_dispatch<T, 4>(grid, a, s); break;
+        case 1: resid_group_dispatch<T, TX, 1>(grid, a, s); break;
+        case 2: resid_group_dispatch<T, TX, 2>(grid, a, s); break;
+        case 3: resid_group_dispatch<T, TX, 3>(grid, a, s); break;
+        case 4: resid_group_dispatch<T, TX, 4>(grid, a, s); break;
         default: throw Error(MBAMG_E_INVALID, "dofs per node must be 1..4");
     }
     MB_LAUNCH_CHECK();
 }
-template void launch_resid_group<double>(int, const ResidGroupArgs<double>&, hipStream_t);
-template void launch_resid_group<float>(int, const ResidGroupArgs<float>&, hipStream_t);
+template void launch_resid_group<double, double>(int, const ResidGroupArgs<double>&, hipStream_t);
+template void launch_resid_group<float, float>(int, const ResidGroupArgs<float>&, hipStream_t);
+template void launch_resid_group<double, float>(int, const ResidGroupArgs<double, float>&, hipStream_t);
 
 }  // namespace mbamg
