@@ -30,7 +30,9 @@ struct SellPart {
     DevBuf<int32_t> width;
     DevBuf<int64_t> coff, voff;
     DevBuf<uint32_t> mask;
-    DevBuf<int32_t> col;
+    DevBuf<int32_t> col;                // empty where the columns are held in 16 bits
+    DevBuf<uint16_t> col16;
+    DevBuf<int32_t> cbase;
     DevBuf<double> v64;
     DevBuf<float> v32;
     std::vector<int64_t> h_coff;        // per slice
@@ -53,9 +55,13 @@ struct SellPart {
 };
 
 template <>
-SellView<double> SellPart::view<double>() const { return {width.p, coff.p, voff.p, mask.p, col.p, v64.p}; }
+SellView<double> SellPart::view<double>() const {
+    return {width.p, coff.p, voff.p, mask.p, col.p, col16.p, cbase.p, v64.p};
+}
 template <>
-SellView<float> SellPart::view<float>() const { return {width.p, coff.p, voff.p, mask.p, col.p, v32.p}; }
+SellView<float> SellPart::view<float>() const {
+    return {width.p, coff.p, voff.p, mask.p, col.p, col16.p, cbase.p, v32.p};
+}
 
 // Structural values and stored blocks of one colour's rows (byte model).
 struct ColourStats {
@@ -713,8 +719,8 @@ static void build_part(SellPart& P, PartKind kind, const BlockLevel& B, const Se
     P.col.alloc(nsl * WAVE);
     DevBuf<int64_t> src(nsl * WAVE);
     DevBuf<int32_t> sblk(nsl);
-    part_fill_index(ns, k, B.group, B.n, B.row0.p, B.nrow.p, k == (int)PartKind::Off ? B.cstart.p : nullptr, P.width.p, coff32.p, B.d_perm.p, rp, ci, col_iperm, P.n_slots, P.col.p,
-                    src.p, sblk.p, s);
+    part_fill_index(ns, k, B.group, B.n, B.row0.p, B.nrow.p, k == (int)PartKind::Off ? B.cstart.p : nullptr, P.width.p,
+                    coff32.p, B.d_perm.p, rp, ci, col_iperm, P.n_slots, P.col.p, src.p, sblk.p, s);
     P.mask.alloc(nsl);
     DevBuf<uint32_t> slot_nz(nsl);
     MB_HIP(hipMemsetAsync(slot_nz.p, 0, sizeof(uint32_t) * nsl, s));
@@ -740,6 +746,46 @@ static void build_part(SellPart& P, PartKind kind, const BlockLevel& B, const Se
     hc.add(sblk, P.h_slot_blocks, (size_t)nsl);
     hc.run(s);
     P.h_coff.assign(c32.begin(), c32.end());
+}
+
+// The columns of a level's sliced smoother parts as 16-bit offsets from each slot's
+// smallest, if they all fit: on levels of COL16_MIN_ROWS rows or more, whose parts
+// (about 260 bytes per row in each block row) no longer stay in the 256 MB cache from
+// launch to launch, so that launches are bound by what they read.  There a V-cycle of
+// 2,097,152 nodes took 1970 -> 1922 us and an operator of 1,009,091 nodes 210 -> 199;
+// a V-cycle of 151,951 nodes, bound by the latency of its loads, 312 -> 323.  Only the
+// kernels of one wave per slice read them.  MBAMG_COL16 = 0 | 1 forces it, for tests.
+constexpr int COL16_MIN_ROWS = 1 << 19;
+static void shorten_columns(Level& Lv, hipStream_t s) {
+    bool want = Lv.n >= COL16_MIN_ROWS;
+    if (const char* fo = form_override("MBAMG_COL16")) want = std::atoi(fo) != 0;
+    if (!want || Lv.resid_split != 1) return;
+    SellPart* parts[6];
+    for (int f = 0; f < 2; ++f) {
+        BlockLevel& B = Lv.blk[f];
+        if (B.group > 1 || B.split != 1) return;
+        parts[3 * f] = &B.off;
+        parts[3 * f + 1] = &B.diag;
+        parts[3 * f + 2] = &B.cpl;
+    }
+    DevBuf<int32_t> wide(6);
+    for (int k = 0; k < 6; ++k) {
+        SellPart& P = *parts[k];
+        const int64_t nsl = std::max<int64_t>(P.n_slots, 1);
+        P.col16.alloc(nsl * WAVE);
+        P.cbase.alloc(nsl);
+        short_columns(P.n_slots, P.col.p, P.col16.p, P.cbase.p, wide.p + k, s);
+    }
+    bool fit = true;
+    for (int32_t w : wide.download(s)) fit = fit && w == 0;
+    for (SellPart* P : parts) {
+        if (fit) {
+            P->col.release();
+        } else {
+            P->col16.release();
+            P->cbase.release();
+        }
+    }
 }
 
 // the undamped buffers all "unwritten", the tickets zero (fill kernels: this may be captured)
@@ -925,6 +971,8 @@ static void clone_part(SellPart& d, const SellPart& p, hipStream_t s) {
     clone_buf(d.voff, p.voff, s);
     clone_buf(d.mask, p.mask, s);
     clone_buf(d.col, p.col, s);
+    clone_buf(d.col16, p.col16, s);
+    clone_buf(d.cbase, p.cbase, s);
     clone_buf(d.v64, p.v64, s);
     clone_buf(d.v32, p.v32, s);
     d.h_coff = p.h_coff;
@@ -1390,6 +1438,7 @@ static void setup_impl(mbamg_hierarchy* h, const mbamg_bsr* Ab, hipStream_t s, D
             Lv.resid_split = slot_split((double)slices, slices ? (double)slots / (double)slices : 0.0, 32768);
             if (Lv.shape != SHAPE_FULL) Lv.resid_split = std::min(Lv.resid_split, SHAPE_MAX_SPLIT);
         }
+        if (!shared && p.smoother == 0) shorten_columns(Lv, s);
         // the residual's launch order: the same eighth of every colour together, so the blocks
         // each XCD takes (contiguous launch ranges) cover one slab of the domain in all colours
         // and their neighbour gathers stay in its L2 (in colour order an XCD's range spans a

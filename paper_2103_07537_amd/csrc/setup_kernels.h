@@ -115,6 +115,7 @@ struct SweepRec;
 void sweep_recs(int n, const int32_t* order, const int32_t* row0, const int32_t* nrow, const int32_t* cstart,
                 const int32_t* ow, const int64_t* oc, const int32_t* cw, const int64_t* cc, SweepRec* out,
                 hipStream_t s);
+void short_columns(int64_t n_slots, const int32_t* col, uint16_t* col16, int32_t* cbase, int32_t* wide, hipStream_t s);
 int64_t slot_offsets(int64_t n_slots, const uint32_t* mask, DevBuf<int64_t>& voff, hipStream_t s);
 void transfer_maps(int n, int nc, const int32_t* perm, const int32_t* iperm, const int32_t* agg,
                    const int32_t* cperm, const int32_t* ciperm, const int32_t* mptr, const int32_t* midx,

@@ -132,8 +132,14 @@ int scan_exclusive(const int32_t* in, int64_t n, int32_t* out, hipStream_t s) {
 //                                                   launch for every group of pairs)
 //   MBAMG_SORT_FORM   = thread | wave              (aggregate member lists)
 //   MBAMG_SYM_FORM    = thread | wave              (product pattern)
-//   MBAMG_ROWS_FORM   = rows | sliced              (coarse-level smoother layout;
-//                                                   changes the summation order)
+//   MBAMG_ROWS_FORM   = rows | sliced              (rows: levels below the finest in
+//                                                   grouped form, all of them)
+//   MBAMG_SWEEP_GROUP = 4 | 8 | 16 | 32 | 64       (lanes per row of grouped levels)
+//   MBAMG_SLICE_SPLIT = 1 | 2 | 4 | 8 | 16         (waves per slice of sliced levels)
+//   MBAMG_BLOCK_SHAPE = 0 | 1 | 2                  (the most that is used of a level's
+//                                                   block shape)
+//   MBAMG_COL16       = 0 | 1                      (16-bit columns of sliced levels)
+// MBAMG_ROWS_FORM, _SWEEP_GROUP and _SLICE_SPLIT change the order of the sums.
 const char* form_override(const char* var) {
     const char* v = std::getenv(var);
     return (v && *v) ? v : nullptr;
@@ -2735,6 +2741,36 @@ void part_layout(int n, int ns, int kind, int G, const int32_t* perm, const int3
     coff32.alloc(ns + 1);
     coff.alloc(std::max(ns, 1));
     n_slots = scan_run<false>(width.p, ns, coff32.p, coff.p, s);
+}
+
+// A slot's 64 columns as 16-bit offsets from their smallest, one wavefront per slot;
+// `wide` is set where they do not fit.
+__global__ __launch_bounds__(256) void k_col16(int64_t n_slots, const int32_t* __restrict__ col,
+                                               uint16_t* __restrict__ col16, int32_t* __restrict__ cbase,
+                                               int32_t* wide) {
+    const int64_t slot = ((int64_t)blockIdx.x * 256 + threadIdx.x) / WAVE;
+    const int lane = threadIdx.x % WAVE;
+    if (slot >= n_slots) return;
+    const int c = col[slot * WAVE + lane];
+    int lo = c < 0 ? INT_MAX : c, hi = c;
+    for (int o = WAVE / 2; o > 0; o >>= 1) {
+        lo = min(lo, __shfl_xor(lo, o, WAVE));
+        hi = max(hi, __shfl_xor(hi, o, WAVE));
+    }
+    if (hi < 0) lo = 0;
+    if (lane == 0) {
+        cbase[slot] = lo;
+        if (hi - lo >= COL16_NONE) atomicOr(wide, 1);
+    }
+    col16[slot * WAVE + lane] = c < 0 ? (uint16_t)COL16_NONE : (uint16_t)(c - lo);
+}
+
+void short_columns(int64_t n_slots, const int32_t* col, uint16_t* col16, int32_t* cbase, int32_t* wide,
+                   hipStream_t s) {
+    MB_HIP(hipMemsetAsync(wide, 0, sizeof(int32_t), s));
+    if (n_slots <= 0) return;
+    k_col16<<<grid_for(n_slots * WAVE), 256, 0, s>>>(n_slots, col, col16, cbase, wide);
+    MB_LAUNCH_CHECK();
 }
 
 void part_fill_index(int ns, int kind, int G, int n_cols, const int32_t* row0, const int32_t* nrow,

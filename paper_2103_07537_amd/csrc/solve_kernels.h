@@ -17,13 +17,16 @@ struct SliceView {
 // col[slot*64 + lane] (-1 marks padding) and a bit mask of the block entries
 // stored for every lane of the slot.  The values of the slot's set bits follow
 // each other as groups of 64 (one per lane) starting at group voff[slot].
+constexpr int COL16_NONE = 0xFFFF;   // a padding lane's 16-bit column
 template <class T>
 struct SellView {
     const int32_t* width;
     const int64_t* coff;
     const int64_t* voff;       // per slot
     const uint32_t* mask;
-    const int32_t* col;
+    const int32_t* col;        // or, where not NULL, 16-bit columns relative to the slot's cbase (0xFFFF: none)
+    const uint16_t* col16;
+    const int32_t* cbase;
     const T* val;
 };
 

@@ -35,24 +35,50 @@ struct SlotChunk {
     int64_t vg[CH];
 };
 
-// the chunk of slots t0, t0 + P, ... of slice s (slots past the width: empty)
-template <class T, int P, int CH>
-__device__ __forceinline__ void fetch_chunk(const SellView<T>& A, int s, int lane, int t0, SlotChunk<CH>& c) {
-    const int w = A.width[s];
-    const int64_t cb = A.coff[s];
+// The chunk of slots t0, t0 + P, ... of a slice of w slots from cb (slots past the
+// width: empty); C16: columns in 16 bits.
+template <class T, int P, int CH, bool C16 = false>
+__device__ __forceinline__ void fetch_slots(const SellView<T>& A, int w, int64_t cb, int lane, int t0, int (&j)[CH],
+                                            uint32_t (&m)[CH], int64_t (&vg)[CH]) {
 #pragma unroll
     for (int u = 0; u < CH; ++u) {
         const int tt = t0 + u * P;
         const bool live = tt < w;
-        c.m[u] = live ? A.mask[cb + tt] : 0u;
-        c.vg[u] = live ? A.voff[cb + tt] : 0;
-        c.j[u] = live ? A.col[(cb + tt) * WAVE + lane] : -1;
+        m[u] = live ? A.mask[cb + tt] : 0u;
+        vg[u] = live ? A.voff[cb + tt] : 0;
     }
+    if constexpr (C16) {
+        uint16_t c[CH];
+        int base[CH];
+#pragma unroll
+        for (int u = 0; u < CH; ++u) {
+            const int tt = t0 + u * P;
+            const bool live = tt < w;
+            base[u] = live ? A.cbase[cb + tt] : 0;
+            c[u] = live ? A.col16[(cb + tt) * WAVE + lane] : (uint16_t)COL16_NONE;
+        }
+#pragma unroll
+        for (int u = 0; u < CH; ++u) j[u] = c[u] == COL16_NONE ? -1 : base[u] + c[u];
+    } else {
+#pragma unroll
+        for (int u = 0; u < CH; ++u) {
+            const int tt = t0 + u * P;
+            j[u] = tt < w ? A.col[(cb + tt) * WAVE + lane] : -1;
+        }
+    }
+}
+
+// the same of slice s
+template <class T, int P, int CH>
+__device__ __forceinline__ void fetch_chunk(const SellView<T>& A, int s, int lane, int t0, SlotChunk<CH>& c) {
+    const int w = A.width[s];
+    const int64_t cb = A.coff[s];
+    fetch_slots<T, P, CH>(A, w, cb, lane, t0, c.j, c.m, c.vg);
 }
 
 // SKIPD: the slot holding column `self` (the row's own node) is left out.
 // pre (split slices only): the first chunk, fetched by the caller ahead of time.
-template <class T, int D, int MODE, int P, int S = SHAPE_FULL, bool SKIPD = false, class TX = T>
+template <class T, int D, int MODE, int P, int S = SHAPE_FULL, bool SKIPD = false, bool C16 = false, class TX = T>
 __device__ __forceinline__ void sell_sub(const SellView<T>& A, int s, int lane, int part, const TX* __restrict__ xa,
                                          const std::common_type_t<TX>* __restrict__ xb, int cstart, T (&acc)[D], int self = -1,
                                          const SlotChunk<sell_chunk<T, P>()>* pre = nullptr) {
@@ -63,16 +89,7 @@ __device__ __forceinline__ void sell_sub(const SellView<T>& A, int s, int lane, 
     int j[CH];
     uint32_t m[CH];
     int64_t vg[CH];
-    auto fetch = [&](int t0) {
-#pragma unroll
-        for (int u = 0; u < CH; ++u) {
-            const int tt = t0 + u * P;
-            const bool live = tt < w;
-            m[u] = live ? A.mask[cb + tt] : 0u;
-            vg[u] = live ? A.voff[cb + tt] : 0;
-            j[u] = live ? A.col[(cb + tt) * WAVE + lane] : -1;
-        }
-    };
+    auto fetch = [&](int t0) { fetch_slots<T, P, CH, C16>(A, w, cb, lane, t0, j, m, vg); };
     if (PF) {
         if (pre) {
 #pragma unroll
@@ -144,7 +161,7 @@ __device__ __forceinline__ void combine_parts(T (&acc)[D], int wave, int part, i
 //   xn_i = x_i + omega (t_i - x_i)
 // where t_j is the updated value for rows of earlier colours and x_j otherwise;
 // t_i - x_i is the sub-solve's correction e_i for the residual b - A x.
-template <class T, int D, bool ZX, bool CPL, int P, int S>
+template <class T, int D, bool ZX, bool CPL, int P, int S, bool C16>
 __global__ __launch_bounds__(waves_per_block<P>() * WAVE) void k_gs(GsArgs<T> a, int padded_blocks) {
     const int wave = wave_id();
     const int part = wave % P;
@@ -179,10 +196,10 @@ __global__ __launch_bounds__(waves_per_block<P>() * WAVE) void k_gs(GsArgs<T> a,
     }
     if (valid) {
         if (!a.skip_off) {
-            if (ZX) sell_sub<T, D, 2, P, S>(a.off, s, lane, part, a.t, nullptr, a.cstart, acc);
-            else sell_sub<T, D, 1, P, S>(a.off, s, lane, part, a.t, a.x, a.cstart, acc);
+            if (ZX) sell_sub<T, D, 2, P, S, false, C16>(a.off, s, lane, part, a.t, nullptr, a.cstart, acc);
+            else sell_sub<T, D, 1, P, S, false, C16>(a.off, s, lane, part, a.t, a.x, a.cstart, acc);
         }
-        if (CPL) sell_sub<T, D, 0, P, S>(a.cpl, s, lane, part, a.xg, nullptr, 0, acc, -1, P >= 4 ? &cpre : nullptr);
+        if (CPL) sell_sub<T, D, 0, P, S, false, C16>(a.cpl, s, lane, part, a.xg, nullptr, 0, acc, -1, P >= 4 ? &cpre : nullptr);
     }
     combine_parts<T, D, P>(acc, wave, part, lane);
     if (part != 0 || !valid) return;
@@ -437,7 +454,7 @@ template void launch_xfer_rows<double>(int, const XferRowArgs<double>&, hipStrea
 template void launch_xfer_rows<float>(int, const XferRowArgs<float>&, hipStream_t);
 
 // r = b - A x (or w = A x when b is NULL) for both block rows in one launch.
-template <class T, class TX, int D, int P, int S>
+template <class T, class TX, int D, int P, int S, bool C16>
 __global__ __launch_bounds__(waves_per_block<P>() * WAVE) void k_resid(ResidArgs<T, TX> a, int padded_blocks) {
     const int wave = wave_id();
     const int part = wave % P;
@@ -465,9 +482,9 @@ __global__ __launch_bounds__(waves_per_block<P>() * WAVE) void k_resid(ResidArgs
 #pragma unroll
     for (int r = 0; r < D; ++r) acc[r] = T(0);
     if (valid) {
-        sell_sub<T, D, 0, P, S>(a.diag[f], sidx, lane, part, a.x[f], nullptr, 0, acc);
-        sell_sub<T, D, 0, P, S>(a.off[f], sidx, lane, part, a.x[f], nullptr, 0, acc);
-        sell_sub<T, D, 0, P, S>(a.cpl[f], sidx, lane, part, a.x[g], nullptr, 0, acc);
+        sell_sub<T, D, 0, P, S, false, C16>(a.diag[f], sidx, lane, part, a.x[f], nullptr, 0, acc);
+        sell_sub<T, D, 0, P, S, false, C16>(a.off[f], sidx, lane, part, a.x[f], nullptr, 0, acc);
+        sell_sub<T, D, 0, P, S, false, C16>(a.cpl[f], sidx, lane, part, a.x[g], nullptr, 0, acc);
     }
     combine_parts<T, D, P>(acc, wave, part, lane);
     if (part != 0 || !act) return;
@@ -607,18 +624,27 @@ __global__ __launch_bounds__(256) void k_coarse(int n, const double* __restrict_
 // ---------------------------------------------------------------------------
 // launchers
 // ---------------------------------------------------------------------------
-template <class T, int D, int P, int S>
-static void gs_dispatch(bool zx, bool cpl, const GsArgs<T>& a, hipStream_t s) {
+template <class T, int D, int P, int S, bool C16>
+static void gs_dispatch_c(bool zx, bool cpl, const GsArgs<T>& a, hipStream_t s) {
     unsigned grid = xcd_grid(a.s_count, P);
     int pb = (int)grid;
     constexpr int TPB = waves_per_block<P>() * WAVE;
     if (zx) {
-        if (cpl) k_gs<T, D, true, true, P, S><<<grid, TPB, 0, s>>>(a, pb);
-        else k_gs<T, D, true, false, P, S><<<grid, TPB, 0, s>>>(a, pb);
+        if (cpl) k_gs<T, D, true, true, P, S, C16><<<grid, TPB, 0, s>>>(a, pb);
+        else k_gs<T, D, true, false, P, S, C16><<<grid, TPB, 0, s>>>(a, pb);
     } else {
-        if (cpl) k_gs<T, D, false, true, P, S><<<grid, TPB, 0, s>>>(a, pb);
-        else k_gs<T, D, false, false, P, S><<<grid, TPB, 0, s>>>(a, pb);
+        if (cpl) k_gs<T, D, false, true, P, S, C16><<<grid, TPB, 0, s>>>(a, pb);
+        else k_gs<T, D, false, false, P, S, C16><<<grid, TPB, 0, s>>>(a, pb);
     }
+}
+
+template <class T, int D, int P, int S>
+static void gs_dispatch(bool zx, bool cpl, const GsArgs<T>& a, hipStream_t s) {
+    if constexpr (P == 1) {
+        if (a.off.col16) return gs_dispatch_c<T, D, P, S, true>(zx, cpl, a, s);
+    }
+    MB_CHECK(!a.off.col16, MBAMG_E_INVALID, "split slices have 32-bit columns");
+    gs_dispatch_c<T, D, P, S, false>(zx, cpl, a, s);
 }
 
 template <class T, int D>
@@ -692,30 +718,43 @@ void launch_gs_fc(int d, int P, bool zero_x, const GsFcArgs<T>& a, hipStream_t s
     MB_LAUNCH_CHECK();
 }
 
+template <class T, class TX, int D, int P, int S>
+static void resid_dispatch_p(unsigned grid, const ResidArgs<T, TX>& a, hipStream_t s) {
+    constexpr int TPB = waves_per_block<P>() * WAVE;
+    if constexpr (P == 1) {
+        if (a.off[0].col16) {
+            k_resid<T, TX, D, P, S, true><<<grid, TPB, 0, s>>>(a, (int)grid);
+            return;
+        }
+    }
+    MB_CHECK(!a.off[0].col16, MBAMG_E_INVALID, "split slices have 32-bit columns");
+    k_resid<T, TX, D, P, S, false><<<grid, TPB, 0, s>>>(a, (int)grid);
+}
+
 template <class T, class TX, int D>
 static void resid_dispatch(int P, const ResidArgs<T, TX>& a, hipStream_t s) {
     const int total = a.s_count[0] + a.s_count[1];
     unsigned grid = xcd_grid(total, P);
-    int pb = (int)grid;
+    MB_CHECK(!a.off[0].col16 == !a.off[1].col16, MBAMG_E_INVALID, "both blocks' columns in one width");
     if constexpr (D > 1) {
         if (a.shape != SHAPE_FULL) {
             MB_CHECK(P <= SHAPE_MAX_SPLIT, MBAMG_E_INVALID, "slot split too large for this block shape");
             if (a.shape == SHAPE_SCALED) {
-                if (P == 1) k_resid<T, TX, D, 1, SHAPE_SCALED><<<grid, 256, 0, s>>>(a, pb);
-                else k_resid<T, TX, D, 2, SHAPE_SCALED><<<grid, 256, 0, s>>>(a, pb);
+                if (P == 1) resid_dispatch_p<T, TX, D, 1, SHAPE_SCALED>(grid, a, s);
+                else resid_dispatch_p<T, TX, D, 2, SHAPE_SCALED>(grid, a, s);
             } else {
-                if (P == 1) k_resid<T, TX, D, 1, SHAPE_SYMMETRIC><<<grid, 256, 0, s>>>(a, pb);
-                else k_resid<T, TX, D, 2, SHAPE_SYMMETRIC><<<grid, 256, 0, s>>>(a, pb);
+                if (P == 1) resid_dispatch_p<T, TX, D, 1, SHAPE_SYMMETRIC>(grid, a, s);
+                else resid_dispatch_p<T, TX, D, 2, SHAPE_SYMMETRIC>(grid, a, s);
             }
             return;
         }
     }
     switch (P) {
-        case 1: k_resid<T, TX, D, 1, SHAPE_FULL><<<grid, 256, 0, s>>>(a, pb); break;
-        case 2: k_resid<T, TX, D, 2, SHAPE_FULL><<<grid, 256, 0, s>>>(a, pb); break;
-        case 4: k_resid<T, TX, D, 4, SHAPE_FULL><<<grid, 256, 0, s>>>(a, pb); break;
-        case 8: k_resid<T, TX, D, 8, SHAPE_FULL><<<grid, 512, 0, s>>>(a, pb); break;
-        case 16: k_resid<T, TX, D, 16, SHAPE_FULL><<<grid, 1024, 0, s>>>(a, pb); break;
+        case 1: resid_dispatch_p<T, TX, D, 1, SHAPE_FULL>(grid, a, s); break;
+        case 2: resid_dispatch_p<T, TX, D, 2, SHAPE_FULL>(grid, a, s); break;
+        case 4: resid_dispatch_p<T, TX, D, 4, SHAPE_FULL>(grid, a, s); break;
+        case 8: resid_dispatch_p<T, TX, D, 8, SHAPE_FULL>(grid, a, s); break;
+        case 16: resid_dispatch_p<T, TX, D, 16, SHAPE_FULL>(grid, a, s); break;
         default: throw Error(MBAMG_E_INVALID, "slot split must be 1, 2, 4, 8 or 16");
     }
 }
