@@ -1919,6 +1919,7 @@ static void smooth_block(mbamg_hierarchy* h, int l, int f, bool zero, const T* b
             a.omega = (T)h->p.omega;
             a.w_row = Lv.damped ? wrow<T>(B) : nullptr;
             a.skip_off = (zero && k == 0 && c == 0) ? 1 : 0;
+            a.keep_t = c + 1 < B.n_colours || k + 1 < h->p.inner_sweeps;
             double bytes = timed ? gs_bytes(B, c, zero, a.skip_off, has_cpl, (int)sizeof(T), Lv.d[g]) : 0.0;
             // kind 0: passes from a nonzero iterate with the coupling term; kind 3: the others
             TimerScope ts(h, s, timed, launch_kind(l, (!zero && has_cpl) ? 0 : 3), bytes);

@@ -58,6 +58,7 @@ struct GsArgs {
     T omega;
     const T* w_row;            // per-row damping (NULL: use omega)
     int skip_off;              // nothing processed yet and zero start: the A_ff term vanishes
+    int keep_t;                // t is read by a later launch
 };
 
 // One colour of the nodal-block Gauss-Seidel over the full node blocks (both

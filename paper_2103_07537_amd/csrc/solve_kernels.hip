@@ -225,7 +225,7 @@ __global__ __launch_bounds__(waves_per_block<P>() * WAVE) void k_gs(GsArgs<T> a,
 #pragma unroll
         for (int r = 0; r < D; ++r) xn[r] = xo[r] + w * (tn[r] - xo[r]);
     }
-    store_vec<T, D>(a.t + (int64_t)row * D, tn);
+    if (a.keep_t) store_vec<T, D>(a.t + (int64_t)row * D, tn);
     store_vec<T, D>(a.xn + (int64_t)row * D, xn);
 }
 
