@@ -320,7 +320,7 @@ __device__ __forceinline__ void group_sub_parts(const GroupPart* parts, int n, i
 // The sweep of one block among more than two: its couplings with every other
 // block are summed with the row instead of being folded into a right-hand side
 // beforehand (a launch per coupling, one thread per row: 33 us each on the 40^3
-// system of 4 blocks, 1266 of 2080 us per V-cycle; that cycle takes 468 us now).
+// system of 4 blocks, 1266 of 2080 us per V-cycle; that cycle takes 456 us now).
 template <int D, bool ZX>
 __global__ __launch_bounds__(SWEEP_WAVES * WAVE) void k_sweep_n(SweepNArgs a) {
     const int pos = sweep_position(a.ticket, a.ticket_next);
