@@ -110,7 +110,8 @@ struct BlockLevel {
     bool sell_sorted = false;
     // transfer to the next level (colour orders of both levels)
     DevBuf<int32_t> agg_p, mem_ptr, mem_idx;
-    DevBuf<double> q64;
+    DevBuf<double> q64;                        // weights of the tentative P: per component while it is built,
+                                               // one per row (colour order) for the transfers
     DevBuf<float> q32;
     DevBuf<double> qm64;                       // q in member-list order (the restriction's reads)
     DevBuf<float> qm32;
@@ -1519,16 +1520,16 @@ static void setup_impl(mbamg_hierarchy* h, const mbamg_bsr* Ab, hipStream_t s, D
             transfer_maps(nf, Nx.nodes(f), B.d_perm.p, B.d_iperm.p, Gf.agg.p, C.d_perm.p, C.d_iperm.p, Gf.mptr.p,
                           Gf.midx.p, B.agg_p, B.mem_ptr, B.mem_idx, s);
             B.res_group = restrict_group(Lv.n + Lv.n1, Nx.n + Nx.n1);
-            DevBuf<double> qp((size_t)nf * B.d);
-            launch_gather(nf, B.d, B.d_perm.p, B.q64.p, qp.p, s);
-            B.q64 = std::move(qp);
-            B.qm64.alloc((size_t)nf * B.d);
-            launch_gather(nf, B.d, B.mem_idx.p, B.q64.p, B.qm64.p, s);   // member m: fine row mem_idx[m]
+            DevBuf<double> qp((size_t)nf);
+            row_weights(nf, B.d, B.d_perm.p, B.q64.p, qp.p, s);
+            std::swap(B.q64, qp);
+            B.qm64.alloc((size_t)nf);
+            row_weights(nf, 1, B.mem_idx.p, B.q64.p, B.qm64.p, s);   // member m: fine row mem_idx[m]
             if (want32) {
-                B.q32.alloc((size_t)nf * B.d);
-                cast_to_f32(B.q64.p, B.q32.p, (int64_t)nf * B.d, s);
-                B.qm32.alloc((size_t)nf * B.d);
-                cast_to_f32(B.qm64.p, B.qm32.p, (int64_t)nf * B.d, s);
+                B.q32.alloc((size_t)nf);
+                cast_to_f32(B.q64.p, B.q32.p, nf, s);
+                B.qm32.alloc((size_t)nf);
+                cast_to_f32(B.qm64.p, B.qm32.p, nf, s);
             }
         }
         alloc_vecs(Lv.v64, Lv.ndof(), Lv.blk[0].group > 1, s);
@@ -2265,11 +2266,11 @@ static void gen_setup_impl(mbamg_hierarchy* h, const mbamg_bsr* Ab, hipStream_t 
             transfer_maps(Lv.n, Nx.n, B.d_perm.p, B.d_iperm.p, Lv.G.agg.p, C.d_perm.p, C.d_iperm.p, Lv.G.mptr.p,
                           Lv.G.midx.p, B.agg_p, B.mem_ptr, B.mem_idx, s);
             B.res_group = restrict_group(Lv.n, Nx.n);
-            DevBuf<double> qp((size_t)Lv.n * B.d);
-            launch_gather(Lv.n, B.d, B.d_perm.p, B.q64.p, qp.p, s);
-            B.q64 = std::move(qp);
-            B.qm64.alloc((size_t)Lv.n * B.d);
-            launch_gather(Lv.n, B.d, B.mem_idx.p, B.q64.p, B.qm64.p, s);
+            DevBuf<double> qp((size_t)Lv.n);
+            row_weights(Lv.n, B.d, B.d_perm.p, B.q64.p, qp.p, s);
+            std::swap(B.q64, qp);
+            B.qm64.alloc((size_t)Lv.n);
+            row_weights(Lv.n, 1, B.mem_idx.p, B.q64.p, B.qm64.p, s);
         }
         MB_HIP(hipStreamSynchronize(s));
     }

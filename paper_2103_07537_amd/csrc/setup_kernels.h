@@ -117,6 +117,7 @@ void sweep_recs(int n, const int32_t* order, const int32_t* row0, const int32_t*
                 hipStream_t s);
 void short_columns(int64_t n_slots, const int32_t* col, uint16_t* col16, int32_t* cbase, int32_t* wide, hipStream_t s);
 int64_t slot_offsets(int64_t n_slots, const uint32_t* mask, DevBuf<int64_t>& voff, hipStream_t s);
+void row_weights(int n, int d, const int32_t* perm, const double* q, double* out, hipStream_t s);
 void transfer_maps(int n, int nc, const int32_t* perm, const int32_t* iperm, const int32_t* agg,
                    const int32_t* cperm, const int32_t* ciperm, const int32_t* mptr, const int32_t* midx,
                    DevBuf<int32_t>& aggp, DevBuf<int32_t>& optr, DevBuf<int32_t>& oidx, hipStream_t s);

@@ -2822,6 +2822,18 @@ int64_t slot_offsets(int64_t n_slots, const uint32_t* mask, DevBuf<int64_t>& vof
     return scan_run<true>(reinterpret_cast<const int32_t*>(mask), n_slots, nullptr, voff.p, s);
 }
 
+// out[p] = the weight of row perm[p], which is that of all its d components
+__global__ void k_row_weights(int n, int d, const int32_t* perm, const double* q, double* out) {
+    const int p = blockIdx.x * blockDim.x + threadIdx.x;
+    if (p < n) out[p] = q[(int64_t)perm[p] * d];
+}
+
+void row_weights(int n, int d, const int32_t* perm, const double* q, double* out, hipStream_t s) {
+    if (n <= 0) return;
+    k_row_weights<<<grid_for(n), 256, 0, s>>>(n, d, perm, q, out);
+    MB_LAUNCH_CHECK();
+}
+
 void transfer_maps(int n, int nc, const int32_t* perm, const int32_t* iperm, const int32_t* agg,
                    const int32_t* cperm, const int32_t* ciperm, const int32_t* mptr, const int32_t* midx,
                    DevBuf<int32_t>& aggp, DevBuf<int32_t>& optr, DevBuf<int32_t>& oidx, hipStream_t s) {

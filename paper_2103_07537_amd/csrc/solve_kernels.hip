@@ -576,17 +576,17 @@ __global__ __launch_bounds__(256) void k_restrict(TransferArgs<T> a, int padded_
     for (int c = 0; c < D; ++c) acc[c] = T(0);
     for (int m = mp[k] + gl; m < mp[k + 1]; m += G) {
         const int64_t i = mi[m];
-        T q[D], r[D];
-        load_vec<T, D>(a.q[f] + (int64_t)m * D, q);
+        const T q = a.q[f][m];
+        T r[D];
         load_vec<T, D>(a.in[f] + i * D, r);
 #pragma unroll
-        for (int c = 0; c < D; ++c) acc[c] += q[c] * r[c];
+        for (int c = 0; c < D; ++c) acc[c] += q * r[c];
     }
     group_sum_vec<T, D, G>(acc);
     if (gl == G - 1) store_vec<T, D>(a.out[f] + (int64_t)k * D, acc);
 }
 
-// x_i += q_i .* x_c[agg(i)] (per component)
+// x_i += q_i x_c[agg(i)]
 template <class T, int D>
 __global__ void k_prolong(TransferArgs<T> a) {
     int i = blockIdx.x * blockDim.x + threadIdx.x;
@@ -597,12 +597,12 @@ __global__ void k_prolong(TransferArgs<T> a) {
         if (i >= a.n_rows[1]) return;
     }
     const int64_t k = a.map[f][i];
-    T q[D], xc[D], x[D];
-    load_vec<T, D>(a.q[f] + (int64_t)i * D, q);
+    const T q = a.q[f][i];
+    T xc[D], x[D];
     load_vec<T, D>(a.in[f] + k * D, xc);
     load_vec<T, D>(a.out[f] + (int64_t)i * D, x);
 #pragma unroll
-    for (int c = 0; c < D; ++c) x[c] += q[c] * xc[c];
+    for (int c = 0; c < D; ++c) x[c] += q * xc[c];
     store_vec<T, D>(a.out[f] + (int64_t)i * D, x);
 }
 
@@ -1079,16 +1079,6 @@ __global__ void k_axpby(int64_t n, double a, const double* __restrict__ x, doubl
         y[e] = a * x[e] + b * y[e];
 }
 
-// dst[p*d + c] = src[perm[p]*d + c]
-__global__ void k_gather(int n_rows, int d, const int32_t* __restrict__ perm, const double* __restrict__ src,
-                         double* __restrict__ dst) {
-    int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (t >= (int64_t)n_rows * d) return;
-    int64_t p = t / d;
-    int c = (int)(t - p * d);
-    dst[t] = src[(int64_t)perm[p] * d + c];
-}
-
 // Between the interface's order and the colour order, all blocks in one launch:
 // block f's rows i in natural order, iperm[i] their colour positions.  The natural
 // side is read or written straight through; the colour side is as many sequential
@@ -1240,14 +1230,6 @@ void launch_seeded(int64_t n, uint64_t seed, double* v, hipStream_t s) {
 
 void launch_axpby(int64_t n, double a, const double* x, double b, double* y, hipStream_t s) {
     k_axpby<<<stream_grid(n), 256, 0, s>>>(n, a, x, b, y);
-    MB_LAUNCH_CHECK();
-}
-
-void launch_gather(int n_rows, int d, const int32_t* perm, const double* src, double* dst, hipStream_t s) {
-    int64_t n = (int64_t)n_rows * d;
-    if (n == 0) return;
-    MB_CHECK(perm && src && dst, MBAMG_E_INVALID, "gather: NULL pointer");
-    k_gather<<<(unsigned)ceil_div(n, 256), 256, 0, s>>>(n_rows, d, perm, src, dst);
     MB_LAUNCH_CHECK();
 }
 
