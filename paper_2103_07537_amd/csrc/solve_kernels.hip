@@ -606,7 +606,10 @@ __global__ void k_prolong(TransferArgs<T> a) {
     store_vec<T, D>(a.out[f] + (int64_t)i * D, x);
 }
 
-// y = inv * x with the inverse in FP64 (one wavefront per row)
+// y = inv * x with the inverse in FP64 (one wavefront per row).  A row's loads are a
+// chain when they are waited for one by one: COARSE_CH of them go out together
+// (2,152 unknowns 19.4 -> 13.5 us, 930 unknowns 6.0 -> 3.9 us; 16 together, 15.6 and 4.1).
+constexpr int COARSE_CH = 8;
 template <class T>
 __global__ __launch_bounds__(256) void k_coarse(int n, const double* __restrict__ inv, const T* __restrict__ x,
                                                 T* __restrict__ y) {
@@ -615,7 +618,18 @@ __global__ __launch_bounds__(256) void k_coarse(int n, const double* __restrict_
     if (row >= n) return;
     const double* a = inv + (int64_t)row * n;
     double s = 0.0;
-    for (int c = lane; c < n; c += WAVE) s += a[c] * (double)x[c];
+    for (int c0 = lane; c0 < n; c0 += COARSE_CH * WAVE) {
+        double av[COARSE_CH], xv[COARSE_CH];
+#pragma unroll
+        for (int u = 0; u < COARSE_CH; ++u) {
+            const int c = min(c0 + u * WAVE, n - 1);
+            av[u] = a[c];
+            xv[u] = (double)x[c];
+        }
+#pragma unroll
+        for (int u = 0; u < COARSE_CH; ++u)
+            if (c0 + u * WAVE < n) s += av[u] * xv[u];
+    }
 #pragma unroll
     for (int off = 32; off > 0; off >>= 1) s += __shfl_xor(s, off, WAVE);
     if (lane == 0) y[row] = (T)s;
