@@ -56,10 +56,21 @@ __device__ __forceinline__ U uniform_load(const U* p) {
     return *(ConstPtr)(uintptr_t)p;
 }
 
-// A wait ends after this many rounds even if the value never comes (each round
-// is a device-scope load of half a microsecond or more): the launch then
-// finishes with NaN results instead of hanging.
-constexpr int SWEEP_MAX_ROUNDS = 1 << 20;
+// The polls of a wait must not hold up what they wait for.  Every wavefront of later
+// colours that is resident polls past the L1; with four workgroups per compute unit
+// doing so without a pause, the memory path was kept so busy that an awaited store
+// was now and then not seen for 10^4 - 10^6 rounds (139,897 rows of 3 x 3 blocks in
+// FP64: a wait ran out about once in 240 solver iterations, and the solve ended in
+// NaN).  So a wavefront pauses between its polls, longer the longer it has waited
+// (4 clocks per round past the first few), and at most two workgroups share a unit
+// (see sweep_lds): there no wait was longer than 63 rounds in 4,500 iterations.
+__device__ __forceinline__ void pause_after(int round) {
+    for (int k = 0; k < round >> 4; ++k) __builtin_amdgcn_s_sleep(1);   // 64 clocks
+}
+
+// A wait ends after this many rounds even if the value never comes, with the pauses
+// about a second: the launch then finishes with NaN results instead of hanging.
+constexpr int SWEEP_MAX_ROUNDS = 1 << 15;
 
 // The damped update of one value; written by a sweep and recomputed by the blocks
 // that follow in the same launch.
@@ -123,6 +134,7 @@ __device__ __forceinline__ void group_sub(const GroupView<T>& A, int w, int cb, 
                     more = more || await[u];
                 }
                 if (!__any(more)) break;
+                pause_after(round);
 #pragma unroll
                 for (int u = 0; u < CH; ++u)
                     if (await[u]) load_shared_vec<T, D>(ta + (int64_t)j[u] * D, xj[u]);
@@ -199,15 +211,18 @@ __device__ __forceinline__ void group_all_sum(T (&acc)[D], int lg) {
 //
 // The two undamped buffers of a level take turns: a launch writes t and sets its
 // rows of the other buffer to "unwritten" for the next launch.
-// LDS asked for by the workgroups of a sweep with few of them per colour, and not
-// used: more than half of a compute unit's 160 KiB, so that each unit takes one
-// workgroup and a colour's rows spread over the chip.  Without it the dispatcher
-// put several on some units and none on others (13,945 rows in 9 colours, 49
-// workgroups per colour: 31 us a sweep instead of 20; 164 per colour: 112 us instead
-// of 110).  With more than half the units' number per colour they spread by
-// themselves, and a second workgroup per unit hides latency (four blocks of
-// 64,000 rows, 250 per colour: 505 us per V-cycle with the limit, 468 without).
-static unsigned sweep_lds(int spread) { return spread ? 84 * 1024 : 0; }
+// LDS asked for by the workgroups of a sweep, and not used, so that a compute unit
+// (160 KiB) takes one of them, or two.
+// One, where a colour has few workgroups (spread): a colour's rows then spread over
+// the chip.  Without it the dispatcher put several on some units and none on others
+// (13,945 rows in 9 colours, 49 workgroups per colour: 31 us a sweep instead of 20;
+// 164 per colour: 112 us instead of 110).
+// Two otherwise: with more than half the units' number per colour they spread by
+// themselves, and a second workgroup per unit hides latency (four blocks of 64,000
+// rows, 250 per colour: 505 us per V-cycle with one, 468 with two); more only poll
+// (see pause_after; a 30-iteration solve on 1,000,000 2D nodes 35.3 ms with four,
+// 33.9 with three, 33.2 with two).
+static unsigned sweep_lds(int spread) { return (spread ? 84 : 56) * 1024; }
 
 // This wavefront's position of the launch (all of a workgroup call it).
 __device__ __forceinline__ int sweep_position(uint32_t* ticket, uint32_t* ticket_next) {
