@@ -1088,9 +1088,10 @@ static void setup_impl(mbamg_hierarchy* h, const mbamg_bsr* Ab, hipStream_t s, D
         Bn[f].alloc((size_t)nb);
         fill_ones(Bn[f].p, nb, s);
     }
-    // per level: what rules out the shapes with fewer stored entries
-    DevBuf<int32_t> shape_flags((size_t)p.max_levels);
-    MB_HIP(hipMemsetAsync(shape_flags.p, 0, sizeof(int32_t) * p.max_levels, s));
+    // per level: what rules out the shapes with fewer stored entries, allocated as the levels
+    // come (max_levels may be any number)
+    constexpr int FLAG_CHUNK = 64;
+    std::vector<DevBuf<int32_t>> shape_flags;
     int lvl = 0;
     while (true) {
         Level& cur = *h->L.back();
@@ -1159,9 +1160,14 @@ static void setup_impl(mbamg_hierarchy* h, const mbamg_bsr* Ab, hipStream_t s, D
             colour_jobs[lvl] = std::async(std::launch::async,
                                           [lp, lvl, pp, ev, device] { colour_level(*lp, lvl, *pp, ev, device); });
         }
+        if (lvl % FLAG_CHUNK == 0) {
+            shape_flags.emplace_back((size_t)FLAG_CHUNK);
+            MB_HIP(hipMemsetAsync(shape_flags.back().p, 0, shape_flags.back().bytes(), s));
+        }
         if (d0 > 1 && p.smoother == 0)
             for (int f = 0; f < 2; ++f)
-                for (int g = 0; g < 2; ++g) block_shape_flags(cur.A[f][g], shape_flags.p + lvl, s);
+                for (int g = 0; g < 2; ++g)
+                    block_shape_flags(cur.A[f][g], shape_flags.back().p + lvl % FLAG_CHUNK, s);
         const int nc = G.n_agg;
         DevBuf<double> q[2], Bc[2];
         for (int f = 0; f < 2; ++f) {     // block 1 reuses block 0's aggregates unless aggregated separately
@@ -1307,11 +1313,12 @@ static void setup_impl(mbamg_hierarchy* h, const mbamg_bsr* Ab, hipStream_t s, D
 
     // the shapes of the levels' blocks, read back at once
     {
-        const int nl = (int)h->L.size();
-        std::vector<int32_t> bad(nl);
-        MB_HIP(hipMemcpyAsync(bad.data(), shape_flags.p, sizeof(int32_t) * nl, hipMemcpyDeviceToHost, s));
-        MB_HIP(hipStreamSynchronize(s));
-        for (int l = 0; l + 1 < nl; ++l) h->L[l]->shape = level_shape(p, d0, bad[l]);
+        std::vector<std::vector<int32_t>> bad(shape_flags.size());
+        HostCopies down;
+        for (size_t k = 0; k < bad.size(); ++k) down.add(shape_flags[k], bad[k], FLAG_CHUNK);
+        down.run(s);
+        for (int l = 0; l + 1 < (int)h->L.size(); ++l)
+            h->L[l]->shape = level_shape(p, d0, bad[l / FLAG_CHUNK][l % FLAG_CHUNK]);
     }
 
     // smoother format on every other level, in two passes: first each level's own smoother
