@@ -698,7 +698,8 @@ static void natural_slicing(BlockLevel& B, int n, hipStream_t s, const std::vect
 // Setup buffers kept until the caller has waited for the stream.
 struct Temporaries {
     std::vector<DevBuf<int64_t>> src;
-    std::vector<DevBuf<int32_t>> order;
+    std::vector<DevBuf<int32_t>> order, blocks;   // blocks, nz: per slot of a grouped part
+    std::vector<DevBuf<uint32_t>> nz;
 };
 
 // Pack one part of block row f into masked slices on the device.  A: the
@@ -734,8 +735,10 @@ static void build_part(SellPart& P, PartKind kind, const BlockLevel& B, const Se
         P.v32.alloc(std::max<int64_t>(P.n_groups, 1) * WAVE);
         cast_to_f32(P.v64.p, P.v32.p, P.n_groups * WAVE, s);
     }
-    if (B.group > 1) {   // the byte model of a grouped level counts by rows
+    if (B.group > 1) {   // a grouped level's counts are summed on the device (see group_counts)
         keep.src.push_back(std::move(src));   // the other temporaries were done with before slot_offsets' wait
+        keep.nz.push_back(std::move(slot_nz));
+        keep.blocks.push_back(std::move(sblk));
         return;
     }
     // host copies for the byte model, with one synchronisation (which also keeps the
@@ -1351,13 +1354,18 @@ static void setup_impl(mbamg_hierarchy* h, const mbamg_bsr* Ab, hipStream_t s, D
             clk.mark("colouring joined", l);
         }
         DeviceCopies up;
+        DevBuf<int32_t> colour_slice[2], colour_row[2];
         for (int f = 0; f < 2 && !shared; ++f) {
             BlockLevel& B = Lv.blk[f];
             up.add(B.row0, B.h_row0);
             up.add(B.nrow, B.h_nrow);
             up.add(B.d_perm, B.perm);
             up.add(B.d_iperm, B.iperm);
-            if (B.group > 1) up.add(B.cstart, B.h_cstart);
+            if (B.group > 1) {
+                up.add(B.cstart, B.h_cstart);
+                up.add(colour_slice[f], B.colour_slice);
+                up.add(colour_row[f], B.colour_row);
+            }
         }
         up.run(s);
         for (int f = 0; f < 2 && !shared; ++f) {
@@ -1388,7 +1396,27 @@ static void setup_impl(mbamg_hierarchy* h, const mbamg_bsr* Ab, hipStream_t s, D
                     B.gdiag32.alloc(nd);
                     cast_to_f32(B.gdiag64.p, B.gdiag32.p, nd, s);
                 }
-                MB_HIP(hipStreamSynchronize(s));   // dinv is released at the end of this iteration
+                DevBuf<unsigned long long> counts;
+                group_counts(B.n_colours, B.n_slices, df * df, colour_slice[f].p, colour_row[f].p,
+                             {B.off.coff.p, B.off.n_slots, keep.nz[0].p, keep.blocks[0].p},
+                             {B.cpl.coff.p, B.cpl.n_slots, keep.nz[1].p, keep.blocks[1].p}, B.gdinv64.p,
+                             B.gdiag64.p, counts, s);
+                std::vector<unsigned long long> sums;
+                HostCopies down;
+                down.add(counts, sums, counts.n);
+                down.run(s);   // waits for the stream: dinv is released at the end of this iteration
+                B.cstats.assign(B.n_colours, ColourStats{});
+                B.all_bl = Lv.A[f][f].nnzb + Lv.A[f][g].nnzb;
+                for (int c = 0; c < B.n_colours; ++c) {
+                    const unsigned long long* v = &sums[(size_t)c * GROUP_COUNTS];
+                    ColourStats& cs = B.cstats[c];
+                    cs.off_nz = (int64_t)v[0];
+                    cs.off_bl = (int64_t)v[1];
+                    cs.cpl_nz = (int64_t)v[2];
+                    cs.cpl_bl = (int64_t)v[3];
+                    cs.dinv_nz = (int64_t)v[4];
+                    B.all_nz += (int64_t)(v[0] + v[2] + v[5]);
+                }
                 if (clk.on)
                     std::fprintf(stderr, "[mbamg setup] level %d block %d: %d nodes, %d colours, %d lanes per row, "
                                  "fill %.2f + %.2f, shape %d\n", l, f, nf, B.n_colours, B.group,
@@ -1587,33 +1615,6 @@ static void setup_impl(mbamg_hierarchy* h, const mbamg_bsr* Ab, hipStream_t s, D
 // ----------------------------------------------------------------------------
 // byte model (algorithmic bytes of the finest level's kernels)
 // ----------------------------------------------------------------------------
-// The counts of a grouped level's block rows (what sliced parts record as they are
-// built), from its blocks when the byte model is first asked for: only measurements
-// read them.
-static void count_grouped_levels(mbamg_hierarchy* h) {
-    for (auto& lp : h->L) {
-        Level& Lv = *lp;
-        for (int f = 0; f < 2; ++f) {
-            BlockLevel& B = Lv.blk[f];
-            if (Lv.coarsest || B.group == 1 || !B.cstats.empty()) continue;
-            const std::vector<int64_t> cs7 = row_colour_stats(Lv.nodes(f), B.d_perm.p, Lv.A[f][f], Lv.A[f][1 - f],
-                                                              B.gdinv64.p, B.colour_row, nullptr);
-            B.cstats.assign(B.n_colours, ColourStats{});
-            for (int c = 0; c < B.n_colours; ++c) {
-                ColourStats& cs = B.cstats[c];
-                const int64_t* v = &cs7[(size_t)c * 7];
-                cs.off_nz = v[0];
-                cs.off_bl = v[1];
-                cs.cpl_nz = v[2];
-                cs.cpl_bl = v[3];
-                cs.dinv_nz = v[4];
-                B.all_nz += v[0] + v[2] + v[5];
-                B.all_bl += v[1] + v[3] + v[6];
-            }
-        }
-    }
-}
-
 static double gs_bytes(const BlockLevel& B, int c, bool zero_x, bool skip_off, bool cpl, int s, int dg) {
     const ColourStats& cs = B.cstats[c];
     const int64_t rows = B.colour_row[c + 1] - B.colour_row[c];
@@ -3079,7 +3080,6 @@ mbamg_status mbamg_timing_enable(mbamg_hierarchy* h, int32_t enable) {
         }
         h->timed.clear();
         MB_CHECK(enable >= 0 && enable <= 3, MBAMG_E_INVALID, "timing mode must be 0..3");
-        if (enable) count_grouped_levels(h);
         h->timing = enable;
         return MBAMG_OK;
     });
@@ -3110,7 +3110,6 @@ mbamg_status mbamg_vcycle_bytes(const mbamg_hierarchy* h, double* bytes) {
     return guarded([&]() -> mbamg_status {
         MB_CHECK(h && bytes, MBAMG_E_INVALID, "NULL argument");
         MB_CHECK(h->nb == 2, MBAMG_E_STATE, "the byte model covers two-block hierarchies");
-        count_grouped_levels(const_cast<mbamg_hierarchy*>(h));
         double tot = 0.0;
         for (int l = 0; l < (int)h->L.size(); ++l) {
             double down = 0.0, up = 0.0;
@@ -3127,7 +3126,6 @@ mbamg_status mbamg_level_vcycle_bytes(const mbamg_hierarchy* h, int32_t level, d
         MB_CHECK(h && down && up, MBAMG_E_INVALID, "NULL argument");
         MB_CHECK(h->nb == 2, MBAMG_E_STATE, "the byte model covers two-block hierarchies");
         MB_CHECK(level >= 0 && level < (int)h->L.size(), MBAMG_E_INVALID, "bad argument");
-        count_grouped_levels(const_cast<mbamg_hierarchy*>(h));
         level_vcycle_bytes(h, level, *down, *up);
         return MBAMG_OK;
     });

@@ -87,12 +87,19 @@ void build_rows(RowPart& R, int n, const int32_t* perm, const SetupBsr& A, const
 void gather_blocks(int n, int bs, const int32_t* perm, const double* src, double* dst, hipStream_t s);
 // dst[p] = the diagonal block of row perm[p] of A
 void gather_diag(int n, const int32_t* perm, const SetupBsr& A, double* dst, hipStream_t s);
-// For each colour c (rows colour_row[c] .. colour_row[c+1] in colour order,
-// node perm[p]): 7 sums -- nonzero entries and blocks of A_ff's off-diagonal
-// blocks, of A_fg, nonzero entries of D^-1 (dinv, colour order), nonzero entries
-// and blocks of A_ff's diagonal block.
-std::vector<int64_t> row_colour_stats(int n, const int32_t* perm, const SetupBsr& Aff, const SetupBsr& Afg,
-                                      const double* dinv, const std::vector<int>& colour_row, hipStream_t s);
+// What a grouped block row's colours hold (byte model), GROUP_COUNTS sums per colour: nonzero
+// entries and blocks of A_ff's off-diagonal part, of A_fg, nonzero entries of D^-1 and of A_ff's
+// diagonal blocks (both bs values per row, colour order).
+constexpr int GROUP_COUNTS = 6;
+struct SlotCounts {
+    const int64_t* coff;       // per slice: first slot
+    int64_t n_slots;
+    const uint32_t* nz;        // per slot: nonzero entries
+    const int32_t* blocks;     // per slot: blocks
+};
+void group_counts(int n_colours, int ns, int bs, const int32_t* colour_slice, const int32_t* colour_row,
+                  const SlotCounts& off, const SlotCounts& cpl, const double* dinv, const double* diag,
+                  DevBuf<unsigned long long>& out, hipStream_t s);
 
 // true when X and Y have identical block patterns (synchronous)
 bool same_pattern(const SetupBsr& X, const SetupBsr& Y, hipStream_t s);

@@ -2413,72 +2413,45 @@ void build_rows(RowPart& R, int n, const int32_t* perm, const SetupBsr& A, const
     MB_HIP(hipStreamSynchronize(s));   // cnt is released on return
 }
 
-// Per row (colour order p, node perm[p]) of a block row: nonzero entries and
-// blocks of A_ff's off-diagonal blocks, of A_fg, of D^-1 and of A_ff's
-// diagonal block -- the counts the sliced parts would record.
-__global__ __launch_bounds__(256) void k_row_stats(int n, const int32_t* __restrict__ perm,
-                                                   const int32_t* __restrict__ frp, const int32_t* __restrict__ fci,
-                                                   const double* __restrict__ fval, int fbs,
-                                                   const int32_t* __restrict__ grp, const double* __restrict__ gval,
-                                                   int gbs, const double* __restrict__ dinv,
-                                                   int32_t* __restrict__ out) {
-    // one wavefront per row: lanes over the row's values (contiguous), counts by ballot
-    const int p = (int)(((int64_t)blockIdx.x * blockDim.x + threadIdx.x) / WAVE);
-    if (p >= n) return;   // whole wavefronts
-    const int lane = threadIdx.x & (WAVE - 1);
-    const int node = perm[p];
-    int off_nz = 0, diag_nz = 0, diag_bl = 0, cpl_nz = 0, dinv_nz = 0;
-    const int f0 = frp[node], flen = frp[node + 1] - f0;
-    for (int u0 = 0; u0 < flen * fbs; u0 += WAVE) {
-        const int u = u0 + lane;
-        bool nz = false, diag = false;
-        if (u < flen * fbs) {
-            nz = fval[(int64_t)f0 * fbs + u] != 0.0;
-            diag = fci[f0 + u / fbs] == node;
-        }
-        diag_nz += (int)__popcll(__ballot(nz && diag));
-        off_nz += (int)__popcll(__ballot(nz && !diag));
-    }
-    for (int q = lane; q < flen; q += WAVE) diag_bl += fci[f0 + q] == node;
-    for (int off = WAVE / 2; off > 0; off >>= 1) diag_bl += __shfl_xor(diag_bl, off);
-    int glen = 0;
-    if (grp) {
-        const int g0 = grp[node];
-        glen = grp[node + 1] - g0;
-        for (int u0 = 0; u0 < glen * gbs; u0 += WAVE) {
-            const int u = u0 + lane;
-            const bool nz = u < glen * gbs && gval[(int64_t)g0 * gbs + u] != 0.0;
-            cpl_nz += (int)__popcll(__ballot(nz));
+// One colour (blockIdx.y) of a grouped block row: its slots follow each other, and so
+// do its rows; integer sums, so their order does not matter.
+__global__ __launch_bounds__(256) void k_group_counts(int ns, int bs, const int32_t* __restrict__ colour_slice,
+                                                      const int32_t* __restrict__ colour_row, SlotCounts off,
+                                                      SlotCounts cpl, const double* __restrict__ dinv,
+                                                      const double* __restrict__ diag, unsigned long long* out) {
+    const int c = blockIdx.y, s0 = colour_slice[c], s1 = colour_slice[c + 1];
+    const int64_t first = (int64_t)blockIdx.x * blockDim.x + threadIdx.x, step = (int64_t)gridDim.x * blockDim.x;
+    unsigned long long v[GROUP_COUNTS] = {};
+    const SlotCounts* part[2] = {&off, &cpl};
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+        const SlotCounts& P = *part[k];
+        const int64_t b = s0 < ns ? P.coff[s0] : P.n_slots, e = s1 < ns ? P.coff[s1] : P.n_slots;
+        for (int64_t i = b + first; i < e; i += step) {
+            v[2 * k] += P.nz[i];
+            v[2 * k + 1] += (unsigned long long)P.blocks[i];
         }
     }
-    for (int u0 = 0; u0 < fbs; u0 += WAVE)
-        dinv_nz += (int)__popcll(__ballot(u0 + lane < fbs && dinv[(int64_t)p * fbs + u0 + lane] != 0.0));
-    if (lane != 0) return;
-    int32_t* o = out + (int64_t)p * 7;
-    o[0] = off_nz;
-    o[1] = flen - diag_bl;
-    o[2] = cpl_nz;
-    o[3] = glen;
-    o[4] = dinv_nz;
-    o[5] = diag_nz;
-    o[6] = diag_bl;
+    for (int64_t i = (int64_t)colour_row[c] * bs + first; i < (int64_t)colour_row[c + 1] * bs; i += step) {
+        v[4] += dinv[i] != 0.0;
+        v[5] += diag[i] != 0.0;
+    }
+#pragma unroll
+    for (int k = 0; k < GROUP_COUNTS; ++k) {
+        for (int o = WAVE / 2; o > 0; o >>= 1) v[k] += __shfl_xor(v[k], o, WAVE);
+        if ((threadIdx.x & (WAVE - 1)) == 0 && v[k] != 0) atomicAdd(out + c * GROUP_COUNTS + k, v[k]);
+    }
 }
 
-std::vector<int64_t> row_colour_stats(int n, const int32_t* perm, const SetupBsr& Aff, const SetupBsr& Afg,
-                                      const double* dinv, const std::vector<int>& colour_row, hipStream_t s) {
-    const int nc = (int)colour_row.size() - 1;
-    std::vector<int64_t> sums((size_t)std::max(nc, 0) * 7, 0);
-    if (n == 0) return sums;
-    DevBuf<int32_t> per((size_t)n * 7);
-    k_row_stats<<<grid_for((int64_t)n * WAVE), 256, 0, s>>>(n, perm, Aff.rp.p, Aff.ci.p, Aff.val.p,
-                                                            Aff.br * Aff.bc, Afg.nnzb ? Afg.rp.p : nullptr,
-                                                            Afg.val.p, Afg.br * Afg.bc, dinv, per.p);
+void group_counts(int n_colours, int ns, int bs, const int32_t* colour_slice, const int32_t* colour_row,
+                  const SlotCounts& off, const SlotCounts& cpl, const double* dinv, const double* diag,
+                  DevBuf<unsigned long long>& out, hipStream_t s) {
+    out.alloc((size_t)std::max(n_colours, 1) * GROUP_COUNTS);
+    MB_HIP(hipMemsetAsync(out.p, 0, out.bytes(), s));
+    if (n_colours <= 0) return;
+    k_group_counts<<<dim3(16, (unsigned)n_colours), 256, 0, s>>>(ns, bs, colour_slice, colour_row, off, cpl, dinv,
+                                                                 diag, out.p);
     MB_LAUNCH_CHECK();
-    const std::vector<int32_t> h = per.download(s, (size_t)n * 7);
-    for (int c = 0; c < nc; ++c)
-        for (int p = colour_row[c]; p < colour_row[c + 1]; ++p)
-            for (int k = 0; k < 7; ++k) sums[(size_t)c * 7 + k] += h[(size_t)p * 7 + k];
-    return sums;
 }
 
 // dst[p] = the diagonal block of row perm[p] of A (zero where the row has none)
