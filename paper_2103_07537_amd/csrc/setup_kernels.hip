@@ -601,6 +601,13 @@ __global__ __launch_bounds__(256) void k_sell_mask(int64_t n_slots, int bs, int 
     }
 }
 
+// what the wavefront's lanes wrote to LDS before is there for all of them after
+__device__ __forceinline__ void wave_exchange() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 // The slot's blocks are staged through LDS (read as in k_sell_mask) and
 // written entry by entry of the mask, 64 rows per entry.
 __global__ __launch_bounds__(256) void k_sell_fill(int64_t n_slots, int bs, int shape, int D,
@@ -616,9 +623,7 @@ __global__ __launch_bounds__(256) void k_sell_fill(int64_t n_slots, int bs, int 
         const int64_t sb = src[slot * WAVE + row];
         tile[w][row][k] = (sb >= 0 && k < bs) ? val[sb * bs + k] : 0.0;
     }
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    wave_exchange();
     const uint32_t m = mask[slot];
     int64_t g = slot_voff[slot];
     for (int e = 0; e < shape_count(shape, D, bs); ++e) {
@@ -1591,15 +1596,11 @@ __global__ __launch_bounds__(256) void k_group_fill_index(int ns, int G, int n_c
     const bool in_lds = len <= cap;
     if (in_lds)
         for (int q = mine; q < len; q += G) keys[q] = key_of(q);
-    __builtin_amdgcn_wave_barrier();   // one wavefront: its LDS accesses stay in order
-    int placed = 0;
+    wave_exchange();
     bool diag = false;
-    for (int q = 0; q < w; ++q) {
-        col[(base + q) * WAVE + lane] = -1;
-        src[(base + q) * WAVE + lane] = -1;
-    }
     for (int q = mine; q < len; q += G) {
         const int k = in_lds ? keys[q] : key_of(q);
+        diag = diag || k == INT_MAX;
         if (k == INT_MAX) continue;
         int rank = 0;
         for (int q2 = 0; q2 < len; ++q2) rank += (in_lds ? keys[q2] : key_of(q2)) < k;
@@ -1607,12 +1608,16 @@ __global__ __launch_bounds__(256) void k_group_fill_index(int ns, int G, int n_c
         col[at] = k < 0 ? k + n_cols : k;
         src[at] = b + q;
     }
-    for (int q = mine; q < len; q += G) diag = diag || (in_lds ? keys[q] : key_of(q)) == INT_MAX;
     // off-diagonal blocks of the row: one fewer where one of its G lanes met the diagonal
     const uint64_t ball = __ballot(diag);
     const uint64_t group = G == WAVE ? ~0ull : ((1ull << G) - 1ull) << (r * G);
     const int total = len - ((ball & group) != 0 ? 1 : 0);
-    placed = total / G + (mine < total % G ? 1 : 0);
+    for (int k = total + mine; k < w * G; k += G) {   // the row's places past its last block
+        const int64_t at = (base + k / G) * WAVE + r * G + k % G;
+        col[at] = -1;
+        src[at] = -1;
+    }
+    const int placed = total / G + (mine < total % G ? 1 : 0);
     count_slot_blocks(placed, w, base, lane, slot_blocks);
 }
 
