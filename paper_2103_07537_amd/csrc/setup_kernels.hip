@@ -1565,8 +1565,10 @@ __global__ void k_part_fill_index(int ns, int kind, int G, const int32_t* row0, 
 // slice, a row's blocks in the order of the sweep's waits: the columns of its own
 // and later colours first, then the earlier colours' ascending (cstart[slice]:
 // first row of the slice's colour).  A block's place is its rank among the row's
-// keys, which are held in LDS (rows too long for their share of it read them from
-// memory again).
+// keys in LDS, which is quadratic work: G lanes for a row that fits its share of the
+// LDS, the whole wavefront for one that takes all of it.  Longer rows (more than
+// ORDER_KEYS blocks) are linear: in the order of the matrix within the two classes,
+// as where each earlier colour comes only matters for how soon it is looked at.
 constexpr int ORDER_KEYS = 1024;   // per wavefront, shared by its 64 / G rows
 __global__ __launch_bounds__(256) void k_group_fill_index(int ns, int G, int n_cols, const int32_t* row0,
                                                           const int32_t* nrow, const int32_t* cstart,
@@ -1579,7 +1581,7 @@ __global__ __launch_bounds__(256) void k_group_fill_index(int ns, int G, int n_c
     if (sl >= ns) return;   // whole wavefronts; no barrier follows
     const int lane = threadIdx.x % WAVE;
     const int r = lane / G, mine = lane % G, cap = ORDER_KEYS / (WAVE / G);
-    int32_t* keys = keys_all[threadIdx.x / WAVE] + r * cap;
+    int32_t* const keys = keys_all[threadIdx.x / WAVE];
     const int w = width[sl];
     const int64_t base = coff[sl];
     const bool row_ok = r < nrow[sl];
@@ -1587,38 +1589,62 @@ __global__ __launch_bounds__(256) void k_group_fill_index(int ns, int G, int n_c
     const int b = row_ok ? rp[node] : 0, len = row_ok ? rp[node + 1] - b : 0;
     const int cs = cstart[sl];
     // own and later colours sort before the earlier ones; the diagonal block sorts last
-    auto key_of = [&](int q) {
-        const int j = ci[b + q];
-        if (j == node) return INT_MAX;
+    auto key_of = [&](int nd, int p) {
+        const int j = ci[p];
+        if (j == nd) return INT_MAX;
         const int jp = col_iperm[j];
         return jp < cs ? jp : jp - n_cols;
     };
-    const bool in_lds = len <= cap;
-    if (in_lds)
-        for (int q = mine; q < len; q += G) keys[q] = key_of(q);
-    wave_exchange();
-    bool diag = false;
-    for (int q = mine; q < len; q += G) {
-        const int k = in_lds ? keys[q] : key_of(q);
-        diag = diag || k == INT_MAX;
-        if (k == INT_MAX) continue;
-        int rank = 0;
-        for (int q2 = 0; q2 < len; ++q2) rank += (in_lds ? keys[q2] : key_of(q2)) < k;
-        const int64_t at = (base + rank / G) * WAVE + r * G + rank % G;
-        col[at] = k < 0 ? k + n_cols : k;
-        src[at] = b + q;
-    }
-    // off-diagonal blocks of the row: one fewer where one of its G lanes met the diagonal
-    const uint64_t ball = __ballot(diag);
+    auto place = [&](int row, int rank, int k, int p) {   // k INT_MIN: no block
+        const int64_t at = (base + rank / G) * WAVE + row * G + rank % G;
+        col[at] = k == INT_MIN ? -1 : k < 0 ? k + n_cols : k;
+        src[at] = k == INT_MIN ? -1 : p;
+    };
+    // the blocks p0 .. p0 + n of one row by `step` lanes, of which this is number `first`;
+    // true where this lane met the diagonal block
+    auto place_ranked = [&](int row, int nd, int p0, int n, int32_t* ks, int first, int step) {
+        for (int q = first; q < n; q += step) ks[q] = key_of(nd, p0 + q);
+        wave_exchange();
+        bool met = false;
+        for (int q = first; q < n; q += step) {
+            const int k = ks[q];
+            if (k == INT_MAX) {
+                met = true;
+                continue;
+            }
+            int rank = 0;
+            for (int q2 = 0; q2 < n; ++q2) rank += ks[q2] < k;
+            place(row, rank, k, p0 + q);
+        }
+        wave_exchange();   // the keys are done with
+        return met;
+    };
+    const bool fits = len <= cap;
+    const uint64_t met = __ballot(place_ranked(r, node, b, fits ? len : 0, keys + r * cap, mine, G));
     const uint64_t group = G == WAVE ? ~0ull : ((1ull << G) - 1ull) << (r * G);
-    const int total = len - ((ball & group) != 0 ? 1 : 0);
-    for (int k = total + mine; k < w * G; k += G) {   // the row's places past its last block
-        const int64_t at = (base + k / G) * WAVE + r * G + k % G;
-        col[at] = -1;
-        src[at] = -1;
+    // off-diagonal blocks of the row: one fewer where one of its G lanes met the diagonal
+    int total = fits ? len - ((met & group) != 0 ? 1 : 0) : 0;
+    for (uint64_t todo = __ballot(!fits && mine == 0); todo != 0; todo &= todo - 1) {
+        const int from = __builtin_ctzll(todo), row = from / G;
+        const int nd = __shfl(node, from, WAVE), p0 = __shfl(b, from, WAVE), n = __shfl(len, from, WAVE);
+        int count = 0;
+        if (n <= ORDER_KEYS) {
+            count = n - (__ballot(place_ranked(row, nd, p0, n, keys, lane, WAVE)) != 0 ? 1 : 0);
+        } else {
+            for (int earlier = 0; earlier < 2; ++earlier)
+                for (int q0 = 0; q0 < n; q0 += WAVE) {
+                    const int p = p0 + q0 + lane;
+                    const int k = q0 + lane < n ? key_of(nd, p) : INT_MAX;
+                    const bool on = k != INT_MAX && (k >= 0) == (earlier != 0);
+                    const uint64_t all = __ballot(on);
+                    if (on) place(row, count + (int)__popcll(all & ((1ull << lane) - 1ull)), k, p);
+                    count += (int)__popcll(all);
+                }
+        }
+        if (r == row) total = count;
     }
-    const int placed = total / G + (mine < total % G ? 1 : 0);
-    count_slot_blocks(placed, w, base, lane, slot_blocks);
+    for (int k = total + mine; k < w * G; k += G) place(r, k, INT_MIN, 0);   // the row's places past its last block
+    count_slot_blocks(total / G + (mine < total % G ? 1 : 0), w, base, lane, slot_blocks);
 }
 
 // transfer maps between colour orders: aggp[p] = ciperm[agg[perm[p]]]
