@@ -53,7 +53,7 @@ typedef enum {
     MBAMG_NOT_CONVERGED = 1,   /* solve stopped at max_iters; x holds the last iterate */
     MBAMG_E_INVALID = -1,      /* inconsistent sizes, NULL pointers, aliasing, bad params */
     MBAMG_E_NOMEM = -2,        /* device or host allocation failed */
-    MBAMG_E_HIP = -3,          /* a HIP runtime call failed */
+    MBAMG_E_HIP = -3,          /* a HIP runtime call failed, or a sweep gave up a wait on the device */
     MBAMG_E_SINGULAR = -4,     /* a nodal diagonal block or the coarsest matrix is singular */
     MBAMG_E_STATE = -5         /* the hierarchy cannot do this (e.g. wrong precision form) */
 } mbamg_status;
@@ -175,7 +175,9 @@ mbamg_status mbamg_setup(const mbamg_bsr* A_blocks, const mbamg_field_map* fm,
  * finest level, pre- and post-smoothed by Algorithm 1 (Sec. 4.3.2), coarsest
  * level solved directly.  r and z are caller-owned device vectors of
  * sum_f n_nodes*dofs[f] doubles in the blocked layout; they must not alias
- * (MBAMG_E_INVALID).  Asynchronous on the stream. */
+ * (MBAMG_E_INVALID).  Asynchronous on the stream.  A smoother sweep whose wait
+ * for another row does not end within about a second leaves NaN in z; the next
+ * V-cycle, solve or probe of the hierarchy then returns MBAMG_E_HIP. */
 mbamg_status mbamg_vcycle(mbamg_hierarchy* h, const double* r, double* z, void* hip_stream);
 
 /* w = A x with the four blocks of eq. 2x2system on the finest level (device

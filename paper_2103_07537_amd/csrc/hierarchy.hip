@@ -292,6 +292,7 @@ struct mbamg_hierarchy {
     double* hbuf_host = nullptr;   // pinned: two sets of Krylov results, written by the device
     double* coef_host = nullptr;   // pinned: 1/nu of a restart's first candidate going up
     double* y_host = nullptr;
+    SweepWait wait = {SWEEP_MAX_ROUNDS, nullptr};   // pinned: a sweep's wait ran out (see check_waits)
     hipEvent_t step_done[2] = {nullptr, nullptr};   // the Krylov step whose results a set of hbuf_host holds
     double judge_rho[2] = {0.0, 0.0};   // probe factors of the learned and the fixed hierarchy
     // a learned hierarchy the judge kept holds the fixed-weight one it was judged against: a
@@ -319,6 +320,7 @@ struct mbamg_hierarchy {
         if (hbuf_host) (void)hipHostFree(hbuf_host);
         if (coef_host) (void)hipHostFree(coef_host);
         if (y_host) (void)hipHostFree(y_host);
+        if (wait.late) (void)hipHostFree(wait.late);
         for (auto e : step_done)
             if (e) (void)hipEventDestroy(e);
     }
@@ -1039,6 +1041,12 @@ static void finish_coarse(mbamg_hierarchy* h, hipStream_t s) {
 // (aggregation, precision) running at the same time; its level-0 aggregates
 // and smoother data are copied instead of recomputed.  to: this setup
 // publishes its own level-0 aggregates and smoother data there.
+static void watch_waits(mbamg_hierarchy* h) {
+    MB_HIP(hipHostMalloc((void**)&h->wait.late, sizeof(uint32_t), hipHostMallocDefault));
+    *h->wait.late = 0;
+    if (const char* fo = form_override("MBAMG_SWEEP_ROUNDS")) h->wait.rounds = std::atoi(fo);   // tests
+}
+
 static void setup_impl(mbamg_hierarchy* h, const mbamg_bsr* Ab, hipStream_t s, DonorLink* from, DonorLink* to,
                        bool defer_coarse) {
     struct Publish {   // on every exit, whatever this setup has not published is not coming
@@ -1601,6 +1609,7 @@ static void setup_impl(mbamg_hierarchy* h, const mbamg_bsr* Ab, hipStream_t s, D
     MB_HIP(hipHostMalloc((void**)&h->hbuf_host, sizeof(double) * 2 * KB_TOTAL, hipHostMallocDefault));
     MB_HIP(hipHostMalloc((void**)&h->coef_host, sizeof(double), hipHostMallocDefault));
     MB_HIP(hipHostMalloc((void**)&h->y_host, sizeof(double) * KMAXQ, hipHostMallocDefault));
+    watch_waits(h);
     for (auto& e : h->step_done) MB_HIP(hipEventCreateWithFlags(&e, hipEventDisableTiming));
     MB_HIP(hipStreamSynchronize(s));
     auto t1 = std::chrono::steady_clock::now();
@@ -1841,6 +1850,7 @@ static void sweep_level(mbamg_hierarchy* h, int l, bool zero, const T* b, const 
                           Lv.blk[1].colour_rec.back() <= BOTH_BLOCKS_MAX;
     T* const t[2] = {V.t.p, V.t2.p};
     Sweep2Args<T> a{};
+    a.wait = h->wait;
     a.shape = Lv.shape;
     a.spread = few_per_colour(Lv.blk[0]) && few_per_colour(Lv.blk[1]);
     for (int f = 0; f < 2; ++f) {
@@ -2301,6 +2311,7 @@ static void gen_setup_impl(mbamg_hierarchy* h, const mbamg_bsr* Ab, hipStream_t 
     MB_HIP(hipHostMalloc((void**)&h->hbuf_host, sizeof(double) * 2 * KB_TOTAL, hipHostMallocDefault));
     MB_HIP(hipHostMalloc((void**)&h->coef_host, sizeof(double), hipHostMallocDefault));
     MB_HIP(hipHostMalloc((void**)&h->y_host, sizeof(double) * KMAXQ, hipHostMallocDefault));
+    watch_waits(h);
     for (auto& e : h->step_done) MB_HIP(hipEventCreateWithFlags(&e, hipEventDisableTiming));
     MB_HIP(hipStreamSynchronize(s));
     h->t_setup_ms = std::chrono::duration<double, std::milli>(std::chrono::steady_clock::now() - t0).count();
@@ -2376,6 +2387,7 @@ static void gen_vcycle_level(mbamg_hierarchy* h, int l, const double* b, double*
             BlockLevel& B = Lv.blk[f];
             double* const t[2] = {V.t.p + Lv.off[f], V.t2.p + Lv.off[f]};
             SweepNArgs a{};
+            a.wait = h->wait;
             // the couplings with the blocks before f (already relaxed in this sweep) and after it
             // (the incoming iterate)
             for (int g = 0; g < nb; ++g) {
@@ -2445,6 +2457,14 @@ static void gen_vcycle_level(mbamg_hierarchy* h, int l, const double* b, double*
     MB_CHECK(buf[cur] == out, MBAMG_E_STATE, "internal: V-cycle result not in the output buffer");
     MB_CHECK(V.turn_t == 0 && V.turn_ticket == 0, MBAMG_E_STATE, "internal: sweep buffers out of turn");
     V.busy = false;
+}
+
+// A V-cycle is asynchronous, so a wait that ran out in one is reported by the next call
+// that has waited for it: the solve and the probe it belongs to, or the next V-cycle.
+static void check_waits(mbamg_hierarchy* h) {
+    if (!h->wait.late || *(volatile uint32_t*)h->wait.late == 0) return;
+    *(volatile uint32_t*)h->wait.late = 0;
+    throw Error(MBAMG_E_HIP, "a smoother sweep gave up waiting for a value: the result of that V-cycle is not valid");
 }
 
 // z = M^-1 v for FP64 colour-order vectors of the finest level (either form).
@@ -2642,6 +2662,7 @@ static mbamg_status solve_impl(mbamg_hierarchy* h, const double* b, double* x, d
                 const int upto = ahead && j + 1 < m && its + 1 < h->p.max_iters ? j + 1 : j;
                 while (queued <= upto) enqueue(queued++);
                 MB_HIP(hipEventSynchronize(h->step_done[j & 1]));
+                check_waits(h);
                 const double* hb = h->hbuf_host + (size_t)(j & 1) * KB_TOTAL;
                 const double* bq = hb + KB_D1;
                 const double* an = hb + KB_D2;
@@ -2703,6 +2724,7 @@ static mbamg_status solve_impl(mbamg_hierarchy* h, const double* b, double* x, d
     }
     from_colour(h, h->xw.p, x, s);
     MB_HIP(hipStreamSynchronize(s));
+    check_waits(h);
     if (revert) {
         // the rest of the solve with the fixed-weight hierarchy, from the current iterate
         mbamg_hierarchy* fb = h->fallback.get();
@@ -2749,6 +2771,7 @@ static double probe_impl(mbamg_hierarchy* h, int iters, uint64_t seed, hipStream
         if (k == iters - 4) nk4 = norm2_dev(h, e, s);
         if (k == iters) nk = norm2_dev(h, e, s);
     }
+    check_waits(h);
     if (nk4 <= 0.0) return 0.0;
     return std::pow(std::sqrt(nk / nk4), 0.25);
 }
@@ -2921,6 +2944,7 @@ mbamg_status mbamg_vcycle(mbamg_hierarchy* h, const double* r, double* z, void* 
     return guarded([&]() -> mbamg_status {
         MB_CHECK(h && r && z, MBAMG_E_INVALID, "NULL argument");
         MB_CHECK(r != z, MBAMG_E_INVALID, "r and z must not alias");
+        check_waits(h);
         hipStream_t s = (hipStream_t)hip_stream;
         to_colour(h, r, h->vio.p, s);
         if (h->nb > 2) {

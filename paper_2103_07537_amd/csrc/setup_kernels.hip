@@ -135,6 +135,7 @@ int scan_exclusive(const int32_t* in, int64_t n, int32_t* out, hipStream_t s) {
 //   MBAMG_ROWS_FORM   = rows | sliced              (rows: levels below the finest in
 //                                                   grouped form, all of them)
 //   MBAMG_SWEEP_GROUP = 4 | 8 | 16 | 32 | 64       (lanes per row of grouped levels)
+//   MBAMG_SWEEP_ROUNDS = 0 ...                     (rounds after which a sweep's wait ends)
 //   MBAMG_SLICE_SPLIT = 1 | 2 | 4 | 8 | 16         (waves per slice of sliced levels)
 //   MBAMG_BLOCK_SHAPE = 0 | 1 | 2                  (the most that is used of a level's
 //                                                   block shape)

@@ -143,6 +143,15 @@ struct SweepOperand {
     T omega;
 };
 
+// A wait ends after this many rounds even if the value never comes, with the pauses
+// between them about a second.  The launch then finishes, with NaN results, and says
+// so in *late (page-locked host memory).
+constexpr int SWEEP_MAX_ROUNDS = 1 << 15;
+struct SweepWait {
+    int rounds;
+    uint32_t* late;
+};
+
 // Algorithm 1 over two blocks of one size: block 0's positions, then block 1's; or
 // one block alone, in the first places (the second count is zero then).
 template <class T>
@@ -154,6 +163,7 @@ struct Sweep2Args {
     SweepOperand<T> xg[2];     // x and t NULL: no coupling term; t: launches of both blocks only
     uint32_t* ticket;          // zero at launch
     uint32_t* ticket_next;     // set to zero for the next launch
+    SweepWait wait;
 };
 
 // More than two blocks: one coupling block A_fg (any shape up to 4 x 4) in
@@ -173,6 +183,7 @@ struct SweepNArgs {
     GroupPart cpl[SWEEP_MAX_BLOCKS - 1];
     uint32_t* ticket;
     uint32_t* ticket_next;
+    SweepWait wait;
 };
 // r_f = b_f - sum_g A_fg x_g (b NULL: w_f = sum_g A_fg x_g) for every block f
 struct ResidNArgs {

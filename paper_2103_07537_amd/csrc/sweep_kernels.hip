@@ -68,10 +68,6 @@ __device__ __forceinline__ void pause_after(int round) {
     for (int k = 0; k < round >> 4; ++k) __builtin_amdgcn_s_sleep(1);   // 64 clocks
 }
 
-// A wait ends after this many rounds even if the value never comes, with the pauses
-// about a second: the launch then finishes with NaN results instead of hanging.
-constexpr int SWEEP_MAX_ROUNDS = 1 << 15;
-
 // The damped update of one value; written by a sweep and recomputed by the blocks
 // that follow in the same launch.
 template <class T>
@@ -92,7 +88,7 @@ __device__ __forceinline__ void operand_value(const SweepOperand<T>& o, int j, c
 template <class T, int D, int MODE, int S, class TX = T>
 __device__ __forceinline__ void group_sub(const GroupView<T>& A, int w, int cb, int lane, const TX* __restrict__ xa,
                                           const T* ta, int cstart, T (&acc)[D],
-                                          const SweepOperand<T>* op = nullptr) {
+                                          SweepWait wait = {}, const SweepOperand<T>* op = nullptr) {
     constexpr int CH = 2;
     for (int t0 = 0; t0 < w; t0 += CH) {
         int j[CH];
@@ -126,7 +122,7 @@ __device__ __forceinline__ void group_sub(const GroupView<T>& A, int w, int cb, 
             else if (MODE < 2 && j[u] >= 0) load_vec_from<T, D>(xa + (int64_t)j[u] * D, xj[u]);
         }
         if (MODE != 0) {
-            for (int round = 0; round < SWEEP_MAX_ROUNDS; ++round) {
+            for (int round = 0;; ++round) {
                 bool more = false;
 #pragma unroll
                 for (int u = 0; u < CH; ++u) {
@@ -134,6 +130,10 @@ __device__ __forceinline__ void group_sub(const GroupView<T>& A, int w, int cb, 
                     more = more || await[u];
                 }
                 if (!__any(more)) break;
+                if (round >= wait.rounds) {
+                    __hip_atomic_store(wait.late, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+                    break;
+                }
                 pause_after(round);
 #pragma unroll
                 for (int u = 0; u < CH; ++u)
@@ -238,7 +238,8 @@ __device__ __forceinline__ int sweep_position(uint32_t* ticket, uint32_t* ticket
 
 // One slice of a sweep; couplings(acc) subtracts the coupling terms.
 template <class T, int D, bool ZX, int S, class Cpl>
-__device__ __forceinline__ void sweep_slice(const SweepArgs<T>& a, const SweepRec& rec, int lane, Cpl&& couplings) {
+__device__ __forceinline__ void sweep_slice(const SweepArgs<T>& a, const SweepWait& wait, const SweepRec& rec, int lane,
+                                            Cpl&& couplings) {
     const int q = lane & ((1 << a.lg) - 1), rr = lane >> a.lg;
     const bool act = rr < rec.nrow && q < D;   // lane q of a row's group finishes component q
     const int row = rec.row0 + (rr < rec.nrow ? rr : 0);
@@ -255,9 +256,9 @@ __device__ __forceinline__ void sweep_slice(const SweepArgs<T>& a, const SweepRe
     couplings(acc);
     const int cstart = a.inplace ? INT_MAX : rec.cstart;
     if (ZX) {
-        if (cstart > 0) group_sub<T, D, 2, S, T>(a.off, rec.off_w, rec.off_c, lane, nullptr, a.t, cstart, acc);
+        if (cstart > 0) group_sub<T, D, 2, S, T>(a.off, rec.off_w, rec.off_c, lane, nullptr, a.t, cstart, acc, wait);
     } else {
-        group_sub<T, D, 1, S>(a.off, rec.off_w, rec.off_c, lane, a.x, a.t, cstart, acc);
+        group_sub<T, D, 1, S>(a.off, rec.off_w, rec.off_c, lane, a.x, a.t, cstart, acc, wait);
     }
     group_all_sum<T, D>(acc, a.lg);
     if (!act) return;
@@ -283,9 +284,9 @@ __global__ __launch_bounds__(SWEEP_WAVES * WAVE) void k_sweep(Sweep2Args<T> a) {
     const SweepRec rec = load_rec(s.rec + s.begin + pos);
     if (rec.nrow == 0) return;
     const int lane = threadIdx.x & (WAVE - 1);
-    sweep_slice<T, D, ZX, S>(s, rec, lane, [&](T (&acc)[D]) {
+    sweep_slice<T, D, ZX, S>(s, a.wait, rec, lane, [&](T (&acc)[D]) {
         const SweepOperand<T>& o = a.xg[f];
-        if (BOTH && o.t) group_sub<T, D, 3, S>(a.cpl[f], rec.cpl_w, rec.cpl_c, lane, o.x, o.t, 0, acc, &o);
+        if (BOTH && o.t) group_sub<T, D, 3, S>(a.cpl[f], rec.cpl_w, rec.cpl_c, lane, o.x, o.t, 0, acc, a.wait, &o);
         else if (o.x) group_sub<T, D, 0, S>(a.cpl[f], rec.cpl_w, rec.cpl_c, lane, o.x, nullptr, 0, acc);
     });
 }
@@ -343,7 +344,7 @@ __global__ __launch_bounds__(SWEEP_WAVES * WAVE) void k_sweep_n(SweepNArgs a) {
     const SweepRec rec = load_rec(a.s.rec + a.s.begin + pos);
     if (rec.nrow == 0) return;
     const int lane = threadIdx.x & (WAVE - 1);
-    sweep_slice<double, D, ZX, SHAPE_FULL>(a.s, rec, lane,
+    sweep_slice<double, D, ZX, SHAPE_FULL>(a.s, a.wait, rec, lane,
                                [&](double (&acc)[D]) { group_sub_parts<D>(a.cpl, a.n_cpl, rec.slice, lane, acc); });
 }
 
@@ -477,6 +478,7 @@ static void check_sweep_block(int count, int lg) {
 template <class T>
 void launch_sweep(int d, bool zero_x, const Sweep2Args<T>& a, hipStream_t s) {
     for (const SweepArgs<T>& f : a.s) check_sweep_block(f.count, f.lg);
+    MB_CHECK(a.wait.late, MBAMG_E_INVALID, "a place for late waits");
     const unsigned grid = (unsigned)((a.s[0].count + a.s[1].count) / SWEEP_WAVES);
     if (grid == 0) return;
     switch (d) {
@@ -501,6 +503,7 @@ static void sweep_n_dispatch(bool zx, const SweepNArgs& a, hipStream_t s) {
 
 void launch_sweep_n(int d, bool zero_x, const SweepNArgs& a, hipStream_t s) {
     check_sweep_block(a.s.count, a.s.lg);
+    MB_CHECK(a.wait.late, MBAMG_E_INVALID, "a place for late waits");
     if (a.s.count == 0) return;
     MB_CHECK(a.n_cpl >= 0 && a.n_cpl < SWEEP_MAX_BLOCKS, MBAMG_E_INVALID, "at most 4 blocks");
     for (int k = 0; k < a.n_cpl; ++k)
