@@ -40,9 +40,15 @@ std::vector<Block>& orphans() {
     static auto* v = new std::vector<Block>;   // guarded by pool().m
     return *v;
 }
+// A thread's other per-thread data may be released after its pending list (buffers
+// kept for the thread's life are constructed before the first block is freed):
+// from then on its blocks go to the orphans at once.  Without a destructor, so it
+// can be read until the thread is gone.
+thread_local bool t_pending_ended = false;
 struct Pending {
     std::vector<Block> v;
     ~Pending() {
+        t_pending_ended = true;
         if (v.empty()) return;
         std::lock_guard<std::mutex> g(pool().m);
         orphans().insert(orphans().end(), v.begin(), v.end());
@@ -107,7 +113,13 @@ void* dev_alloc(size_t bytes) {
 
 void dev_free(void* p, size_t bytes) {
     if (!p) return;
-    t_pending.v.push_back({current_device(), size_class(bytes), p});
+    const Block b{current_device(), size_class(bytes), p};
+    if (t_pending_ended) {
+        std::lock_guard<std::mutex> g(pool().m);
+        orphans().push_back(b);
+    } else {
+        t_pending.v.push_back(b);
+    }
 }
 
 // the current device has been synchronised: its pending blocks are idle
@@ -180,7 +192,7 @@ void pool_device_idle() {
         }
         list.resize(keep);
     };
-    promote(t_pending.v);
+    if (!t_pending_ended) promote(t_pending.v);
     promote(orphans());
 }
 
