@@ -258,12 +258,11 @@ mbamg_status mbamg_mlp_loss_grad(const float* params, const float* x, const floa
 /* For callers that cannot allocate device memory (code under HIP graph
  * capture, training loops that must not call hipMalloc): the same loss and
  * gradient as mbamg_mlp_loss_grad, bit for bit (same grid, same summation
- * order), with the per-workgroup partial sums kept in a static device buffer
- * of 5.0 MiB (256 workgroups x 5123 floats) instead of
- * library-allocated memory.  It calls no allocator: each GPU holds its own
+ * order), with the partial sums kept in a static device buffer of 5.0 MiB (at
+ * most 256 of them x 5123 floats) instead of library-allocated memory.  It calls no allocator: each GPU holds its own
  * copy of the buffer, reserved when the library's code is loaded on it and
  * held until the process ends; its device address is looked up on the first
- * call on each device.  The need does not grow with n (at most 256 workgroups
+ * call on each device.  The need does not grow with n (at most 256 partial sums
  * for any batch), so every n > 0 fits; a grid that would need more than the
  * buffer holds is rejected with MBAMG_E_INVALID.  The buffer keeps the last
  * call's contents; every call overwrites all the entries it reads, so nothing

@@ -31,6 +31,9 @@ constexpr float OMEGA_P_MAX = 5.0f / 6.0f;
 constexpr float OMEGA_S_MIN = 0.3f, OMEGA_S_SPAN = 1.0f;
 constexpr int MLP_WAVES = 4;                  // 256 threads, 16 rows per wave, 64 rows per block step
 constexpr int MLP_MAX_BLOCKS = 256;
+// grids of at most this many blocks leave a partial per wave (see k_mlp_grad)
+constexpr int GRAD_PER_WAVE_BLOCKS = 64;
+static_assert(GRAD_PER_WAVE_BLOCKS * MLP_WAVES <= MLP_MAX_BLOCKS, "no more partials than the largest grid leaves");
 
 // float -> bfloat16, round to nearest even
 __device__ __forceinline__ short f2bf(float f) {
@@ -198,13 +201,19 @@ __global__ __launch_bounds__(256) void k_mlp_forward(const float* __restrict__ t
     }
 }
 
-// Forward and backward of the mean squared error over n rows.  The four waves'
-// gradients (5122 values) and losses are added up in LDS, in wave order, over
-// the tile buffers the loop no longer needs, and the block writes one partial
-// to partial[block * 5123 + ...]; k_mlp_grad_reduce sums them in a fixed order.
-// A batch of 8192 rows is 128 blocks of one tile per wave, so the kernel is a
-// chain of latencies (parameters, the tile's products, the partial's stores):
-// 8192 rows 25 -> 23 us on its own, and a quarter of the partials to reduce.
+// Forward and backward of the mean squared error over n rows.  Each wave has a
+// gradient (5122 values) and a loss; k_mlp_grad_reduce sums what is left of them
+// in a fixed order.
+// PER_WAVE: the wave writes them out itself, to partial[(block * 4 + wave) * 5123].
+// Otherwise the block's four are added up in LDS, in wave order, over the tile
+// buffers the loop no longer needs, and it writes one partial to
+// partial[block * 5123 + ...].  A batch of 8192 rows is 128 blocks of one tile per
+// wave, so the kernel is a chain of latencies (parameters, the tile's products, the
+// partial's stores): 25 -> 23 us on its own, and a quarter of the partials to reduce.
+// The four turns through LDS cost more than the partials they save where those are
+// few: loss and gradient of 1 row 23.1 us and per wave 16.4, 1,000 rows 23.4 and
+// 17.3, 4,096 rows (64 blocks, as many partials as the largest grid leaves) 24.0 and 21.1.
+template <bool PER_WAVE>
 __global__ __launch_bounds__(256) void k_mlp_grad(const float* __restrict__ th, const float* __restrict__ x,
                                                   const float* __restrict__ tgt, int64_t n,
                                                   float* __restrict__ partial) {
@@ -306,35 +315,41 @@ __global__ __launch_bounds__(256) void k_mlp_grad(const float* __restrict__ th, 
     gb3 += __shfl_xor(gb3, 32, 64);
 #pragma unroll
     for (int off = 32; off > 0; off >>= 1) loss += __shfl_xor(loss, off, 64);
+    // this wave's values, by parameter.  Result lane layout: rows g4 + v, column j.
+    auto each = [&](auto&& put) {
+#pragma unroll
+        for (int a = 0; a < 4; ++a)
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                const int o = 16 * a + g4 + v;
+                if (j < 12) put(OFF_W1 + o * 12 + j, gW1[a][v]);
+#pragma unroll
+                for (int t = 0; t < 4; ++t) put(OFF_W2 + o * 64 + 16 * t + j, gW2[a][t][v]);
+            }
+#pragma unroll
+        for (int t = 0; t < 4; ++t)
+#pragma unroll
+            for (int v = 0; v < 4; ++v)
+                if (g4 + v < 2) put(OFF_W3 + (g4 + v) * 64 + 16 * t + j, gW3[t][v]);
+        if (lane < 16)
+#pragma unroll
+            for (int t = 0; t < 4; ++t) {
+                put(OFF_B1 + 16 * t + j, gb1[t]);
+                put(OFF_B2 + 16 * t + j, gb2[t]);
+            }
+        if (lane < 2) put(OFF_B3 + lane, gb3);
+        if (lane == 0) put(N_MLP_PARAMS, loss * inv_n);
+    };
+    if constexpr (PER_WAVE) {
+        float* out = partial + ((int64_t)blockIdx.x * MLP_WAVES + w) * (N_MLP_PARAMS + 1);
+        each([&](int k, float v) { out[k] = v; });
+        return;
+    }
     // the block's sum over its waves, in wave order; the loop ended with a barrier, so the
-    // tile buffers are free.  Result lane layout: rows g4 + v, column j.
+    // tile buffers are free
     float* P = reinterpret_cast<float*>(&S.X[0][0]);
     for (int ww = 0; ww < MLP_WAVES; ++ww) {
-        if (w == ww) {
-            auto put = [&](int k, float v) { P[k] = ww == 0 ? v : P[k] + v; };
-#pragma unroll
-            for (int a = 0; a < 4; ++a)
-#pragma unroll
-                for (int v = 0; v < 4; ++v) {
-                    const int o = 16 * a + g4 + v;
-                    if (j < 12) put(OFF_W1 + o * 12 + j, gW1[a][v]);
-#pragma unroll
-                    for (int t = 0; t < 4; ++t) put(OFF_W2 + o * 64 + 16 * t + j, gW2[a][t][v]);
-                }
-#pragma unroll
-            for (int t = 0; t < 4; ++t)
-#pragma unroll
-                for (int v = 0; v < 4; ++v)
-                    if (g4 + v < 2) put(OFF_W3 + (g4 + v) * 64 + 16 * t + j, gW3[t][v]);
-            if (lane < 16)
-#pragma unroll
-                for (int t = 0; t < 4; ++t) {
-                    put(OFF_B1 + 16 * t + j, gb1[t]);
-                    put(OFF_B2 + 16 * t + j, gb2[t]);
-                }
-            if (lane < 2) put(OFF_B3 + lane, gb3);
-            if (lane == 0) put(N_MLP_PARAMS, loss * inv_n);
-        }
+        if (w == ww) each([&](int k, float v) { P[k] = ww == 0 ? v : P[k] + v; });
         __syncthreads();
     }
     float* out = partial + (int64_t)blockIdx.x * (N_MLP_PARAMS + 1);
@@ -722,22 +737,36 @@ void mlp_forward(const float* th, const float* x, int64_t n, float* out, hipStre
     MB_LAUNCH_CHECK();
 }
 
-void mlp_loss_grad(const float* th, const float* x, const float* t, int64_t n, float* grad, float* loss,
-                   DevBuf<float>& partial, hipStream_t s) {
-    MB_CHECK(n > 0, MBAMG_E_INVALID, "empty batch");
-    int blocks = (int)std::min<int64_t>(MLP_MAX_BLOCKS, ceil_div(n, 64));
-    const int64_t need = (int64_t)blocks * (N_MLP_PARAMS + 1);
-    if ((int64_t)partial.n < need) partial.alloc(need);
-    k_mlp_grad<<<blocks, 256, 0, s>>>(th, x, t, n, partial.p);
+// The gradient's grid for n rows, and the partials it leaves: one per wave on small
+// grids, one per block otherwise (see k_mlp_grad); the same for both entry points.
+struct GradGrid {
+    int blocks, parts;
+    int64_t floats() const { return (int64_t)parts * (N_MLP_PARAMS + 1); }
+};
+static GradGrid grad_grid(int64_t n) {
+    const int blocks = (int)std::min<int64_t>(MLP_MAX_BLOCKS, ceil_div(n, 64));
+    return {blocks, blocks <= GRAD_PER_WAVE_BLOCKS ? blocks * MLP_WAVES : blocks};
+}
+static void grad_launch(const GradGrid& g, const float* th, const float* x, const float* t, int64_t n, float* grad,
+                        float* loss, float* partial, hipStream_t s) {
+    if (g.parts > g.blocks) k_mlp_grad<true><<<g.blocks, 256, 0, s>>>(th, x, t, n, partial);
+    else k_mlp_grad<false><<<g.blocks, 256, 0, s>>>(th, x, t, n, partial);
     MB_LAUNCH_CHECK();
-    k_mlp_grad_reduce<<<gridn(N_MLP_PARAMS + 1, WAVE), GRAD_RED_WAVES * WAVE, 0, s>>>(partial.p, blocks, grad, loss);
+    k_mlp_grad_reduce<<<gridn(N_MLP_PARAMS + 1, WAVE), GRAD_RED_WAVES * WAVE, 0, s>>>(partial, g.parts, grad, loss);
     MB_LAUNCH_CHECK();
 }
 
-// Scratch of the allocation-free gradient: the per-workgroup partial sums of
-// k_mlp_grad for the largest grid mlp_loss_grad launches (MLP_MAX_BLOCKS
-// workgroups, N_MLP_PARAMS + 1 floats each: 1,311,488 floats = 5.0 MiB).  Each GPU the library runs on holds its own
-// copy until the process ends.  In host code `scratch` names a host-side
+void mlp_loss_grad(const float* th, const float* x, const float* t, int64_t n, float* grad, float* loss,
+                   DevBuf<float>& partial, hipStream_t s) {
+    MB_CHECK(n > 0, MBAMG_E_INVALID, "empty batch");
+    const GradGrid g = grad_grid(n);
+    if ((int64_t)partial.n < g.floats()) partial.alloc(g.floats());
+    grad_launch(g, th, x, t, n, grad, loss, partial.p, s);
+}
+
+// Scratch of the allocation-free gradient: the most partial sums k_mlp_grad
+// leaves (MLP_MAX_BLOCKS of them, N_MLP_PARAMS + 1 floats each: 1,311,488 floats
+// = 5.0 MiB).  Each GPU the library runs on holds its own copy until the process ends.  In host code `scratch` names a host-side
 // stand-in; the device address comes from hipGetSymbolAddress, once per
 // device, and only that address is ever passed to a kernel.
 constexpr int64_t NOALLOC_SCRATCH_FLOATS = (int64_t)MLP_MAX_BLOCKS * (N_MLP_PARAMS + 1);
@@ -767,17 +796,12 @@ void mlp_loss_grad_noalloc(const float* th, const float* x, const float* t, int6
                            hipStream_t s) {
     MB_CHECK(n > 0, MBAMG_E_INVALID, "empty batch");
     // the same grid as mlp_loss_grad, so the partial sums and their reduction order are the same
-    const int blocks = (int)std::min<int64_t>(MLP_MAX_BLOCKS, ceil_div(n, 64));
-    const int64_t need = (int64_t)blocks * (N_MLP_PARAMS + 1);
-    MB_CHECK(need <= NOALLOC_SCRATCH_FLOATS, MBAMG_E_INVALID,
+    const GradGrid g = grad_grid(n);
+    MB_CHECK(g.floats() <= NOALLOC_SCRATCH_FLOATS, MBAMG_E_INVALID,
              "gradient scratch: the grid needs more than the 5 MiB static buffer holds");
-    float* partial = scratch_address();
-    // every workgroup of the grid writes all N_MLP_PARAMS + 1 of its entries and the
-    // reduction reads only those: nothing needs clearing, stale entries are never read
-    k_mlp_grad<<<blocks, 256, 0, s>>>(th, x, t, n, partial);
-    MB_LAUNCH_CHECK();
-    k_mlp_grad_reduce<<<gridn(N_MLP_PARAMS + 1, WAVE), GRAD_RED_WAVES * WAVE, 0, s>>>(partial, blocks, grad, loss);
-    MB_LAUNCH_CHECK();
+    // every partial of the grid is written whole and the reduction reads only those:
+    // nothing needs clearing, stale entries are never read
+    grad_launch(g, th, x, t, n, grad, loss, scratch_address(), s);
 }
 
 void mlp_adam(float* th, const float* g, float* m, float* v, int64_t step, float lr, float b1, float b2, float eps,
