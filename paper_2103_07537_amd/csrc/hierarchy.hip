@@ -292,7 +292,7 @@ struct mbamg_hierarchy {
     double* hbuf_host = nullptr;   // pinned: two sets of Krylov results, written by the device
     double* coef_host = nullptr;   // pinned: 1/nu of a restart's first candidate going up
     double* y_host = nullptr;
-    SweepWait wait = {SWEEP_MAX_ROUNDS, nullptr};   // pinned: a sweep's wait ran out (see check_waits)
+    SweepWait wait = {SWEEP_MAX_ROUNDS, nullptr};   // late: behind hbuf_host's results (see check_waits)
     hipEvent_t step_done[2] = {nullptr, nullptr};   // the Krylov step whose results a set of hbuf_host holds
     double judge_rho[2] = {0.0, 0.0};   // probe factors of the learned and the fixed hierarchy
     // a learned hierarchy the judge kept holds the fixed-weight one it was judged against: a
@@ -320,7 +320,6 @@ struct mbamg_hierarchy {
         if (hbuf_host) (void)hipHostFree(hbuf_host);
         if (coef_host) (void)hipHostFree(coef_host);
         if (y_host) (void)hipHostFree(y_host);
-        if (wait.late) (void)hipHostFree(wait.late);
         for (auto e : step_done)
             if (e) (void)hipEventDestroy(e);
     }
@@ -1046,7 +1045,7 @@ static void finish_coarse(mbamg_hierarchy* h, hipStream_t s) {
 // and smoother data are copied instead of recomputed.  to: this setup
 // publishes its own level-0 aggregates and smoother data there.
 static void watch_waits(mbamg_hierarchy* h) {
-    MB_HIP(hipHostMalloc((void**)&h->wait.late, sizeof(uint32_t), hipHostMallocDefault));
+    h->wait.late = reinterpret_cast<uint32_t*>(h->hbuf_host + 2 * KB_TOTAL);
     *h->wait.late = 0;
     if (const char* fo = form_override("MBAMG_SWEEP_ROUNDS")) h->wait.rounds = std::atoi(fo);   // tests
 }
@@ -1341,6 +1340,31 @@ static void setup_impl(mbamg_hierarchy* h, const mbamg_bsr* Ab, hipStream_t s, D
     // level's order.  A build that lends its level 0 does that level first and publishes
     // it at once; a build that borrows it does it last.
     const int n_fine_levels = (int)h->L.size() - 1;
+    struct Counts {   // of a grouped block row's colours, copied to the host when all are there
+        BlockLevel* block;
+        DevBuf<unsigned long long> dev;
+        std::vector<unsigned long long> host;
+    };
+    std::vector<Counts> counts;
+    auto keep_counts = [&] {
+        HostCopies down;
+        for (Counts& q : counts) down.add(q.dev, q.host, q.dev.n);
+        down.run(s);
+        for (Counts& q : counts) {
+            q.block->cstats.assign(q.block->n_colours, ColourStats{});
+            for (int c = 0; c < q.block->n_colours; ++c) {
+                const unsigned long long* v = &q.host[(size_t)c * GROUP_COUNTS];
+                ColourStats& cs = q.block->cstats[c];
+                cs.off_nz = (int64_t)v[0];
+                cs.off_bl = (int64_t)v[1];
+                cs.cpl_nz = (int64_t)v[2];
+                cs.cpl_bl = (int64_t)v[3];
+                cs.dinv_nz = (int64_t)v[4];
+                q.block->all_nz += (int64_t)(v[0] + v[2] + v[5]);
+            }
+        }
+        counts.clear();
+    };
     for (int k = 0; k < n_fine_levels; ++k) {
         const int l = to ? k : n_fine_levels - 1 - k;
         Level& Lv = *h->L[l];
@@ -1366,18 +1390,13 @@ static void setup_impl(mbamg_hierarchy* h, const mbamg_bsr* Ab, hipStream_t s, D
             clk.mark("colouring joined", l);
         }
         DeviceCopies up;
-        DevBuf<int32_t> colour_slice[2], colour_row[2];
         for (int f = 0; f < 2 && !shared; ++f) {
             BlockLevel& B = Lv.blk[f];
             up.add(B.row0, B.h_row0);
             up.add(B.nrow, B.h_nrow);
             up.add(B.d_perm, B.perm);
             up.add(B.d_iperm, B.iperm);
-            if (B.group > 1) {
-                up.add(B.cstart, B.h_cstart);
-                up.add(colour_slice[f], B.colour_slice);
-                up.add(colour_row[f], B.colour_row);
-            }
+            if (B.group > 1) up.add(B.cstart, B.h_cstart);
         }
         up.run(s);
         for (int f = 0; f < 2 && !shared; ++f) {
@@ -1408,27 +1427,14 @@ static void setup_impl(mbamg_hierarchy* h, const mbamg_bsr* Ab, hipStream_t s, D
                     B.gdiag32.alloc(nd);
                     cast_to_f32(B.gdiag64.p, B.gdiag32.p, nd, s);
                 }
-                DevBuf<unsigned long long> counts;
-                group_counts(B.n_colours, B.n_slices, df * df, colour_slice[f].p, colour_row[f].p,
+                counts.emplace_back();
+                counts.back().block = &B;
+                group_counts(B.n_colours, B.colour_slice.data(), B.colour_row.data(), B.n_slices, df * df,
                              {B.off.coff.p, B.off.n_slots, keep.nz[0].p, keep.blocks[0].p},
                              {B.cpl.coff.p, B.cpl.n_slots, keep.nz[1].p, keep.blocks[1].p}, B.gdinv64.p,
-                             B.gdiag64.p, counts, s);
-                std::vector<unsigned long long> sums;
-                HostCopies down;
-                down.add(counts, sums, counts.n);
-                down.run(s);   // waits for the stream: dinv is released at the end of this iteration
-                B.cstats.assign(B.n_colours, ColourStats{});
+                             B.gdiag64.p, counts.back().dev, s);
                 B.all_bl = Lv.A[f][f].nnzb + Lv.A[f][g].nnzb;
-                for (int c = 0; c < B.n_colours; ++c) {
-                    const unsigned long long* v = &sums[(size_t)c * GROUP_COUNTS];
-                    ColourStats& cs = B.cstats[c];
-                    cs.off_nz = (int64_t)v[0];
-                    cs.off_bl = (int64_t)v[1];
-                    cs.cpl_nz = (int64_t)v[2];
-                    cs.cpl_bl = (int64_t)v[3];
-                    cs.dinv_nz = (int64_t)v[4];
-                    B.all_nz += (int64_t)(v[0] + v[2] + v[5]);
-                }
+                MB_HIP(hipStreamSynchronize(s));   // dinv is released at the end of this iteration
                 if (clk.on)
                     std::fprintf(stderr, "[mbamg setup] level %d block %d: %d nodes, %d colours, %d lanes per row, "
                                  "fill %.2f + %.2f, shape %d\n", l, f, nf, B.n_colours, B.group,
@@ -1511,11 +1517,13 @@ static void setup_impl(mbamg_hierarchy* h, const mbamg_bsr* Ab, hipStream_t s, D
             clk.mark("full node inverses", l);
         }
         if (l == 0 && to && to->agg_set) {   // level 0's smoother blocks are complete on s
+            keep_counts();
             MB_HIP(hipEventRecord(to->smooth_ev, s));
             to->publish_smooth(true);
         }
         MB_HIP(hipStreamSynchronize(s));
     }
+    keep_counts();
     for (int l = n_fine_levels - 1; l >= 0; --l) {
         Level& Lv = *h->L[l];
         Level& Nx = *h->L[l + 1];
@@ -1610,7 +1618,7 @@ static void setup_impl(mbamg_hierarchy* h, const mbamg_bsr* Ab, hipStream_t s, D
     fill_words(h->kcounter.p, KCOUNTER_WORDS, 0u, s);
     h->ybuf.alloc(KMAXQ);
     h->coef.alloc(KC_TOTAL);
-    MB_HIP(hipHostMalloc((void**)&h->hbuf_host, sizeof(double) * 2 * KB_TOTAL, hipHostMallocDefault));
+    MB_HIP(hipHostMalloc((void**)&h->hbuf_host, sizeof(double) * (2 * KB_TOTAL + 1), hipHostMallocDefault));
     MB_HIP(hipHostMalloc((void**)&h->coef_host, sizeof(double), hipHostMallocDefault));
     MB_HIP(hipHostMalloc((void**)&h->y_host, sizeof(double) * KMAXQ, hipHostMallocDefault));
     watch_waits(h);
@@ -2318,7 +2326,7 @@ static void gen_setup_impl(mbamg_hierarchy* h, const mbamg_bsr* Ab, hipStream_t 
     fill_words(h->kcounter.p, KCOUNTER_WORDS, 0u, s);
     h->ybuf.alloc(KMAXQ);
     h->coef.alloc(KC_TOTAL);
-    MB_HIP(hipHostMalloc((void**)&h->hbuf_host, sizeof(double) * 2 * KB_TOTAL, hipHostMallocDefault));
+    MB_HIP(hipHostMalloc((void**)&h->hbuf_host, sizeof(double) * (2 * KB_TOTAL + 1), hipHostMallocDefault));
     MB_HIP(hipHostMalloc((void**)&h->coef_host, sizeof(double), hipHostMallocDefault));
     MB_HIP(hipHostMalloc((void**)&h->y_host, sizeof(double) * KMAXQ, hipHostMallocDefault));
     watch_waits(h);

@@ -89,7 +89,7 @@ void gather_blocks(int n, int bs, const int32_t* perm, const double* src, double
 void gather_diag(int n, const int32_t* perm, const SetupBsr& A, double* dst, hipStream_t s);
 // What a grouped block row's colours hold (byte model), GROUP_COUNTS sums per colour: nonzero
 // entries and blocks of A_ff's off-diagonal part, of A_fg, nonzero entries of D^-1 and of A_ff's
-// diagonal blocks (both bs values per row, colour order).
+// diagonal blocks (both bs values per row, colour order); colour_slice, colour_row: on the host.
 constexpr int GROUP_COUNTS = 6;
 struct SlotCounts {
     const int64_t* coff;       // per slice: first slot
@@ -97,7 +97,7 @@ struct SlotCounts {
     const uint32_t* nz;        // per slot: nonzero entries
     const int32_t* blocks;     // per slot: blocks
 };
-void group_counts(int n_colours, int ns, int bs, const int32_t* colour_slice, const int32_t* colour_row,
+void group_counts(int n_colours, const int* colour_slice, const int* colour_row, int ns, int bs,
                   const SlotCounts& off, const SlotCounts& cpl, const double* dinv, const double* diag,
                   DevBuf<unsigned long long>& out, hipStream_t s);
 

@@ -2447,11 +2447,14 @@ void build_rows(RowPart& R, int n, const int32_t* perm, const SetupBsr& A, const
 
 // One colour (blockIdx.y) of a grouped block row: its slots follow each other, and so
 // do its rows; integer sums, so their order does not matter.
-__global__ __launch_bounds__(256) void k_group_counts(int ns, int bs, const int32_t* __restrict__ colour_slice,
-                                                      const int32_t* __restrict__ colour_row, SlotCounts off,
+constexpr int COUNT_COLOURS = 32;   // per launch
+struct ColourRanges {
+    int slice[COUNT_COLOURS + 1], row[COUNT_COLOURS + 1];
+};
+__global__ __launch_bounds__(256) void k_group_counts(int ns, int bs, ColourRanges colours, SlotCounts off,
                                                       SlotCounts cpl, const double* __restrict__ dinv,
                                                       const double* __restrict__ diag, unsigned long long* out) {
-    const int c = blockIdx.y, s0 = colour_slice[c], s1 = colour_slice[c + 1];
+    const int c = blockIdx.y, s0 = colours.slice[c], s1 = colours.slice[c + 1];
     const int64_t first = (int64_t)blockIdx.x * blockDim.x + threadIdx.x, step = (int64_t)gridDim.x * blockDim.x;
     unsigned long long v[GROUP_COUNTS] = {};
     const SlotCounts* part[2] = {&off, &cpl};
@@ -2464,7 +2467,7 @@ __global__ __launch_bounds__(256) void k_group_counts(int ns, int bs, const int3
             v[2 * k + 1] += (unsigned long long)P.blocks[i];
         }
     }
-    for (int64_t i = (int64_t)colour_row[c] * bs + first; i < (int64_t)colour_row[c + 1] * bs; i += step) {
+    for (int64_t i = (int64_t)colours.row[c] * bs + first; i < (int64_t)colours.row[c + 1] * bs; i += step) {
         v[4] += dinv[i] != 0.0;
         v[5] += diag[i] != 0.0;
     }
@@ -2475,14 +2478,19 @@ __global__ __launch_bounds__(256) void k_group_counts(int ns, int bs, const int3
     }
 }
 
-void group_counts(int n_colours, int ns, int bs, const int32_t* colour_slice, const int32_t* colour_row,
+void group_counts(int n_colours, const int* colour_slice, const int* colour_row, int ns, int bs,
                   const SlotCounts& off, const SlotCounts& cpl, const double* dinv, const double* diag,
                   DevBuf<unsigned long long>& out, hipStream_t s) {
     out.alloc((size_t)std::max(n_colours, 1) * GROUP_COUNTS);
     MB_HIP(hipMemsetAsync(out.p, 0, out.bytes(), s));
-    if (n_colours <= 0) return;
-    k_group_counts<<<dim3(16, (unsigned)n_colours), 256, 0, s>>>(ns, bs, colour_slice, colour_row, off, cpl, dinv,
-                                                                 diag, out.p);
+    for (int c0 = 0; c0 < n_colours; c0 += COUNT_COLOURS) {
+        const int n = std::min(COUNT_COLOURS, n_colours - c0);
+        ColourRanges colours{};
+        std::copy(colour_slice + c0, colour_slice + c0 + n + 1, colours.slice);
+        std::copy(colour_row + c0, colour_row + c0 + n + 1, colours.row);
+        k_group_counts<<<dim3(16, (unsigned)n), 256, 0, s>>>(ns, bs, colours, off, cpl, dinv, diag,
+                                                             out.p + (size_t)c0 * GROUP_COUNTS);
+    }
     MB_LAUNCH_CHECK();
 }
 
