@@ -585,17 +585,17 @@ enum class PartKind { Off = 0, Cpl = 1, Diag = 2, Dinv = 3 };
 // Lanes per row of a block row (see BlockLevel::group) of n rows and `blocks`
 // blocks in A_ff, on a level whose larger block row has n_level rows.
 //
-// Which levels: all coarse ones, and finest levels of up to GROUP_FINEST_MAX
-// nodes, whose colour passes are short launches.  Measured per FP64 V-cycle,
-// all sweeps of a level, one launch per colour (sliced, or one wavefront per
-// row) against this form: 583 nodes in 10 colours 210 -> 67 us, 13,945 in 9
-// colours 222 -> 85 us, 188,588 in 9 colours 602 -> 453 us, 976 in 5 colours
-// (3 x 3 blocks) 85 -> 33 us; a finest level of 65,536 nodes (two colours)
-// 61 -> 54 us, but one of 151,951 nodes 87 -> 150 us: there a colour pass
-// already runs at the bandwidth its loads get, and the sliced form moves fewer
-// lanes.  (With every block entry stored; with block shapes the 188,588-row level's
-// sweeps take 399 us.)
-//
+// Which levels: all coarse ones, and finest levels whose colour passes are short
+// launches.  Coarse levels, all FP64 sweeps of a level per V-cycle, one launch per
+// colour (sliced, or one wavefront per row) against this form: 583 nodes in 10 colours
+// 210 -> 67 us, 13,945 in 9 colours 222 -> 85 us, 188,588 in 9 colours 602 -> 399 us,
+// 976 in 5 colours (3 x 3 blocks) 85 -> 33 us.
+// Finest levels, sliced against this form, a V-cycle and an operator apply together
+// (FP64; FP32 cycles cross over at the same sizes): two colours of rows that take two
+// slots of 4 lanes (3D, 6 off-diagonal blocks) 28^3 nodes 172 -> 160 us, 32^3 179 -> 180,
+// 36^3 189 -> 204, 40^3 198 -> 232; with full blocks 24^3 162 -> 152, 28^3 176 -> 180,
+// 32^3 194 -> 195, 36^3 209 -> 233.  Rows that fit one slot waste fewer lanes (2D,
+// 4 off-diagonal blocks): 160^2 146 -> 132, 210^2 192 -> 181, 256^2 203 -> 202.
 // How many lanes: the first power of two that covers an average row's
 // off-diagonal blocks, so that most rows are at most two slots, one round of
 // loads (10 colours of 583 rows, 13 off-diagonal blocks on average: 26 us a
@@ -603,7 +603,7 @@ enum class PartKind { Off = 0, Cpl = 1, Diag = 2, Dinv = 3 };
 // few times over, as fewer lanes waste less on short rows (188,588 rows: 4 lanes
 // 453 us, 8 lanes 495 us, 16 lanes 597 us per cycle; 65,536 rows of 4 blocks: 4 lanes
 // 54 us, 8 lanes 76 us).
-constexpr int GROUP_FINEST_MAX = 65536;
+constexpr int GROUP_FINEST_MAX = 32768, GROUP_FINEST_ONE_SLOT_MAX = 65536;
 constexpr int64_t GROUP_WAVES_MAX = 16384;
 static int group_lanes(int n, int64_t blocks) {
     const double len = n ? (double)blocks / n : 1.0;
@@ -618,9 +618,10 @@ static int group_lanes(int n, int64_t blocks) {
     return g;
 }
 
-static int choose_group(const mbamg_params& p, int lvl, int n_level, int n, int64_t blocks) {
+// one_slot: the off-diagonal blocks of the level's rows fit 4 lanes, on average, in both block rows
+static int choose_group(const mbamg_params& p, int lvl, int n_level, bool one_slot, int n, int64_t blocks) {
     if (p.smoother == 1) return 1;   // the full-node kernel reads the sliced parts
-    bool grouped = lvl > 0 || n_level <= GROUP_FINEST_MAX;
+    bool grouped = lvl > 0 || n_level <= (one_slot ? GROUP_FINEST_ONE_SLOT_MAX : GROUP_FINEST_MAX);
     // MBAMG_ROWS_FORM (tests): "rows" forces the grouped form on every coarse level, anything
     // else the sliced one on every level; MBAMG_SLICE_SPLIT the sliced one on the finest level
     if (const char* fo = form_override("MBAMG_ROWS_FORM")) grouped = lvl > 0 && std::strcmp(fo, "rows") == 0;
@@ -946,6 +947,9 @@ static void colour_level(Level& Lv, int lvl, const mbamg_params& p, hipEvent_t r
                          "colour %.2f ms\n", n, ms(t0, t1), ms(t1, t2), ms(t2, t3));
         }
     } report{verbose, Lv.n, t0, t1, t2};
+    bool one_slot = true;
+    for (int f = 0; f < (same ? 1 : 2); ++f)
+        one_slot = one_slot && rp[f][Lv.nodes(f)] <= 5 * (int64_t)Lv.nodes(f);
     for (int f = 0; f < 2; ++f) {
         BlockLevel& B = Lv.blk[f];
         B.d = Lv.d[f];
@@ -960,7 +964,8 @@ static void colour_level(Level& Lv, int lvl, const mbamg_params& p, hipEvent_t r
             int ncol = asym ? greedy_colour(nf, rp[f], ci[f], B.colour, trp.data(), tci.data())
                             : greedy_colour(nf, rp[f], ci[f], B.colour);
             // one form for the whole level (its size: the larger block's)
-            order_and_slice(B, nf, ncol, rp[f], choose_group(p, lvl, std::max(Lv.n, Lv.n1), nf, rp[f][nf]));
+            order_and_slice(B, nf, ncol, rp[f],
+                            choose_group(p, lvl, std::max(Lv.n, Lv.n1), one_slot, nf, rp[f][nf]));
         }
     }
 }
