@@ -497,7 +497,8 @@ static double slice_fill(const std::vector<int32_t>& order, const std::vector<in
 // The launch order of a grouped block row: every colour's slices, padded to a
 // multiple of SWEEP_WAVES positions (-1: nothing to do).  Workgroups take their
 // tickets about in turn over the 8 XCDs, so every eighth ticket of a colour gets
-// neighbouring slices: an XCD's gathers then stay in one region of the colour.
+// neighbouring slices: an XCD's gathers then stay in one region of the colour.  (A
+// colour may start on any XCD: which region an XCD has changes from colour to colour.)
 static void launch_order(BlockLevel& B) {
     B.h_order.clear();
     B.h_cstart.assign((size_t)std::max(B.n_slices, 1), 0);
