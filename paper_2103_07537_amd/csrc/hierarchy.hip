@@ -288,6 +288,8 @@ struct mbamg_hierarchy {
     int64_t n_fine = 0;
     DevBuf<double> V, Z64, w, xw, bw, partial, ybuf, coef;
     DevBuf<uint32_t> kcounter;     // blocks of the running Krylov pass that are done
+    int partial_turn = 0;          // the set of partial sums the next pass uses
+    int partial_used = 0;          // sums the last pass left in the other set
     DevBuf<float> mlp;             // network parameters (5122) followed by feature mean and std (12 + 12)
     double* hbuf_host = nullptr;   // pinned: two sets of Krylov results, written by the device
     double* coef_host = nullptr;   // pinned: 1/nu of a restart's first candidate going up
@@ -1619,7 +1621,8 @@ static void setup_impl(mbamg_hierarchy* h, const mbamg_bsr* Ab, hipStream_t s, D
     h->bw.alloc(n);
     h->vio.alloc(n);
     h->vio2.alloc(n);
-    h->partial.alloc((size_t)KBLOCKS * KMAXQ);
+    h->partial.alloc((size_t)2 * KBLOCKS * KMAXQ);
+    fill_words(reinterpret_cast<uint32_t*>(h->partial.p), (int64_t)(h->partial.bytes() / 4), 0xFFFFFFFFu, s);
     h->kcounter.alloc(KCOUNTER_WORDS);
     fill_words(h->kcounter.p, KCOUNTER_WORDS, 0u, s);
     h->ybuf.alloc(KMAXQ);
@@ -2327,7 +2330,8 @@ static void gen_setup_impl(mbamg_hierarchy* h, const mbamg_bsr* Ab, hipStream_t 
     h->bw.alloc(n);
     h->vio.alloc(n);
     h->vio2.alloc(n);
-    h->partial.alloc((size_t)KBLOCKS * KMAXQ);
+    h->partial.alloc((size_t)2 * KBLOCKS * KMAXQ);
+    fill_words(reinterpret_cast<uint32_t*>(h->partial.p), (int64_t)(h->partial.bytes() / 4), 0xFFFFFFFFu, s);
     h->kcounter.alloc(KCOUNTER_WORDS);
     fill_words(h->kcounter.p, KCOUNTER_WORDS, 0u, s);
     h->ybuf.alloc(KMAXQ);
@@ -2556,14 +2560,21 @@ static void apply_A(mbamg_hierarchy* h, const TX* x, double* w, hipStream_t s, i
 // ----------------------------------------------------------------------------
 // GMRES (right preconditioned) / FGMRES, restarted
 // ----------------------------------------------------------------------------
-static KrylovBufs krylov_bufs(mbamg_hierarchy* h, int set = 0) {
+// The buffers of the next Krylov pass, of `sums` sums, which `launch` launches: the sets of
+// partials have changed places once it is on its way.
+template <class Fn>
+static void krylov_pass(mbamg_hierarchy* h, int set, int sums, Fn&& launch) {
     double* r = h->hbuf_host + (size_t)set * KB_TOTAL;
-    return {h->partial.p, h->kcounter.p, h->coef.p, r + KB_D1, r + KB_D2, r + KB_NU, r + KB_NU2};
+    double* p[2] = {h->partial.p, h->partial.p + (size_t)KBLOCKS * KMAXQ};
+    launch(KrylovBufs{p[h->partial_turn], p[1 - h->partial_turn], h->partial_used, h->kcounter.p, h->coef.p,
+                      r + KB_D1, r + KB_D2, r + KB_NU, r + KB_NU2, h->wait});
+    h->partial_turn = 1 - h->partial_turn;
+    h->partial_used = sums;
 }
 
 // ||v||^2 through the deterministic reduction (synchronous)
 static double norm2_dev(mbamg_hierarchy* h, const double* v, hipStream_t s) {
-    launch_norm2(h->n_fine, v, krylov_bufs(h), s);
+    krylov_pass(h, 0, 1, [&](const KrylovBufs& kb) { launch_norm2(h->n_fine, v, kb, s); });
     MB_HIP(hipStreamSynchronize(s));
     return h->hbuf_host[KB_NU2];
 }
@@ -2660,7 +2671,6 @@ static mbamg_status solve_impl(mbamg_hierarchy* h, const double* b, double* x, d
             auto enqueue = [&](int j) {
                 double* vj = h->V.p + (size_t)j * n;
                 double* vn = h->V.p + (size_t)(j + 1) * n;
-                const KrylovBufs kb = krylov_bufs(h, j & 1);
                 if (fp32) {
                     // the candidate in FP32 comes with the update pass and the operator reads z in
                     // FP32 (casts between them as launches of their own took 80 of 2700 us per step
@@ -2674,9 +2684,12 @@ static mbamg_status solve_impl(mbamg_hierarchy* h, const double* b, double* x, d
                     apply_A(h, zj, h->w.p, s);
                 }
                 // dot pass: b = Q^T w and u_j . w; c_j on the device
-                launch_orth(n, j + 1, h->V.p, n, h->w.p, kb, s);
+                krylov_pass(h, j & 1, j + 1,
+                            [&](const KrylovBufs& kb) { launch_orth(n, j + 1, h->V.p, n, h->w.p, kb, s); });
                 // update pass: Q_j over u_j, u_{j+1} into V_{j+1}, a_{j+1} and nu_{j+1}
-                launch_dcgs_update(n, j, h->V.p, n, vj, h->w.p, vn, fp32 ? h->vin32.p : nullptr, kb, s);
+                krylov_pass(h, j & 1, j + 2, [&](const KrylovBufs& kb) {
+                    launch_dcgs_update(n, j, h->V.p, n, vj, h->w.p, vn, fp32 ? h->vin32.p : nullptr, kb, s);
+                });
                 MB_HIP(hipEventRecord(h->step_done[j & 1], s));
             };
             int queued = 0;

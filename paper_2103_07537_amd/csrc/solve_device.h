@@ -5,6 +5,29 @@
 
 namespace mbamg {
 
+// "not yet written" where other workgroups of the running launch wait for a value:
+// all bits set, a NaN that is never stored as a value.  Each value is its own signal,
+// so no order between different addresses is needed.
+__device__ __forceinline__ bool unwritten(double v) { return __double_as_longlong(v) == -1ll; }
+__device__ __forceinline__ bool unwritten(float v) { return __float_as_uint(v) == 0xFFFFFFFFu; }
+template <class T>
+__device__ __forceinline__ T unwritten_value() {
+    if constexpr (sizeof(T) == 8) return __longlong_as_double(-1ll);
+    else return __uint_as_float(0xFFFFFFFFu);
+}
+
+// The polls of a wait must not hold up what they wait for.  Every wavefront of later
+// colours that is resident polls past the L1; with four workgroups per compute unit
+// doing so without a pause, the memory path was kept so busy that an awaited store
+// was now and then not seen for 10^4 - 10^6 rounds (139,897 rows of 3 x 3 blocks in
+// FP64: a wait ran out about once in 240 solver iterations, and the solve ended in
+// NaN).  So a wavefront pauses between its polls, longer the longer it has waited
+// (4 clocks per round past the first few), and at most two workgroups share a unit
+// (see sweep_lds): there no wait was longer than 63 rounds in 4,500 iterations.
+__device__ __forceinline__ void pause_after(int round) {
+    for (int k = 0; k < round >> 4; ++k) __builtin_amdgcn_s_sleep(1);   // 64 clocks
+}
+
 constexpr int WPB = 4;          // waves per block when a slice has at most 4 waves
 
 // P waves share each slice; a block holds max(P, WPB) waves

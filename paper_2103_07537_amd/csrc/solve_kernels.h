@@ -297,7 +297,7 @@ void launch_coarse(int n, const double* inv, const T* x, T* y, hipStream_t s);
 
 // Krylov helpers (FP64).  Reductions are deterministic: per-block partial sums
 // stored slot-major (partial[q * KBLOCKS + block]), summed in a fixed order by the
-// block that finishes last.
+// block that finishes last.  Every launch uses the same number of blocks.
 constexpr int KMAXQ = 33;        // basis vectors + 2 slots (a dot with the candidate, a norm)
 constexpr int KBLOCKS = 1024;
 // layout of the coefficient buffer of the delayed-reorthogonalisation update:
@@ -307,7 +307,9 @@ constexpr int KC_A = 0, KC_B = KMAXQ, KC_INV_NU = 2 * KMAXQ, KC_CJ = 2 * KMAXQ +
 // counters of finished blocks, each in a cache line of its own
 constexpr int KCOUNTERS = 16, KCOUNTER_STRIDE = 32, KCOUNTER_WORDS = (1 + KCOUNTERS) * KCOUNTER_STRIDE;
 struct KrylovBufs {
-    double* partial;             // KBLOCKS * KMAXQ
+    double* partial;             // KBLOCKS * KMAXQ, "unwritten" at launch
+    double* partial_next;        // the other set, made so for the next launch:
+    int n_next;                  // the sums it holds (at most KMAXQ)
     uint32_t* counter;           // KCOUNTER_WORDS, zero between launches
     double* coef;                // KC_TOTAL, device
     // results (page-locked host memory the device writes, read after the stream is waited for)
@@ -315,6 +317,7 @@ struct KrylovBufs {
     double* d2;                  // update pass: the next candidate's a'
     double* nu;                  // update pass: its nu'
     double* nu2;                 // norm: w . w
+    SweepWait wait;
 };
 void launch_norm2(int64_t n, const double* w, const KrylovBufs& kb, hipStream_t s);
 void launch_orth(int64_t n, int nq, const double* V, int64_t ldv, const double* w, const KrylovBufs& kb,

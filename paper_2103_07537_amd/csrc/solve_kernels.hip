@@ -907,32 +907,36 @@ __device__ __forceinline__ double block_sums(double (&v)[N], double (*sh)[KMAXQ]
 
 // Publishes this block's N sums (thread q < N holds sum q) and tells whether it is
 // the last block to do so; that block gets the totals in res (all threads, after
-// the return) and leaves the counters at zero for the next launch.  The partials go
-// through device-scope stores and loads: a store has reached the point all compute
-// units see when its wait ends, so the counter's increment follows the block's
-// partials without flushing the cache (a release at device scope writes back the
-// XCD's whole L2, once per block).
+// the return) and leaves the counters at zero for the next launch.  The counters say
+// who is last, not that the others' partials can be seen yet: a partial is its own
+// signal ("unwritten" before) and is loaded until it is there, which it nearly always
+// is.  (A release at device scope before the increment would write back the XCD's
+// whole L2, once per block.)  The two sets of partials take turns: a launch sets what
+// the one before it used of the other set to "unwritten".
 template <int N>
-__device__ __forceinline__ bool last_block_totals(double mine, double* partial, uint32_t* counter, double* res) {
+__device__ __forceinline__ bool last_block_totals(double mine, const KrylovBufs& kb, double* res) {
     __shared__ int last;
     const int t = threadIdx.x, nb = gridDim.x;
+    static_assert(KMAXQ <= KT, "a thread per partial");
+    if (t < kb.n_next)
+        __hip_atomic_store(kb.partial_next + (int64_t)t * KBLOCKS + blockIdx.x, unwritten_value<double>(),
+                           __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     if (t < N)
-        __hip_atomic_store(partial + (int64_t)t * KBLOCKS + blockIdx.x, mine, __ATOMIC_RELAXED,
-                           __HIP_MEMORY_SCOPE_AGENT);
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        __hip_atomic_store(kb.partial + (int64_t)t * KBLOCKS + blockIdx.x, unwritten(mine) ? (double)NAN : mine,
+                           __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     __syncthreads();
     // increments of one address take 11 ns each (1024 blocks: 12 us at the end of a short
     // pass), so the blocks count in KCOUNTERS groups, and the groups' last ones in one more
     if (t == 0) {
         const int k = blockIdx.x % KCOUNTERS, members = (nb - k + KCOUNTERS - 1) / KCOUNTERS;
-        uint32_t* sub = counter + (1 + k) * KCOUNTER_STRIDE;
+        uint32_t* sub = kb.counter + (1 + k) * KCOUNTER_STRIDE;
         last = 0;
         if (__hip_atomic_fetch_add(sub, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == (uint32_t)members - 1u) {
             __hip_atomic_store(sub, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             const int groups = nb < KCOUNTERS ? nb : KCOUNTERS;
-            last = __hip_atomic_fetch_add(counter, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) ==
+            last = __hip_atomic_fetch_add(kb.counter, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) ==
                    (uint32_t)groups - 1u;
-            if (last) __hip_atomic_store(counter, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            if (last) __hip_atomic_store(kb.counter, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         }
     }
     __syncthreads();
@@ -942,15 +946,29 @@ __device__ __forceinline__ bool last_block_totals(double mine, double* partial, 
     constexpr int G = 8, U = 16;
     static_assert(N <= 2 * (KT / G), "two sums per group at most");
     const int l = t % G;
+    auto partial_at = [&](int q, int b) {
+        return __hip_atomic_load(kb.partial + (int64_t)q * KBLOCKS + b, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    };
     for (int q = t / G; q < N; q += KT / G) {
         double v = 0.0;
         for (int b0 = l; b0 < nb; b0 += U * G) {
             double x[U];
 #pragma unroll
-            for (int u = 0; u < U; ++u)
-                x[u] = b0 + u * G < nb ? __hip_atomic_load(partial + (int64_t)q * KBLOCKS + b0 + u * G,
-                                                           __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)
-                                       : 0.0;
+            for (int u = 0; u < U; ++u) x[u] = b0 + u * G < nb ? partial_at(q, b0 + u * G) : 0.0;
+            for (int round = 0;; ++round) {
+                bool more = false;
+#pragma unroll
+                for (int u = 0; u < U; ++u) more = more || unwritten(x[u]);
+                if (!__any(more)) break;
+                if (round >= kb.wait.rounds) {
+                    __hip_atomic_store(kb.wait.late, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+                    break;
+                }
+                pause_after(round);
+#pragma unroll
+                for (int u = 0; u < U; ++u)
+                    if (unwritten(x[u])) x[u] = partial_at(q, b0 + u * G);
+            }
 #pragma unroll
             for (int u = 0; u < U; ++u) v += x[u];
         }
@@ -993,7 +1011,7 @@ __global__ __launch_bounds__(KT) __attribute__((amdgpu_waves_per_eu(4, 4))) void
         }
     }
     const double mine = block_sums<N>(acc, sh);
-    if (!last_block_totals<N>(mine, kb.partial, kb.counter, res)) return;
+    if (!last_block_totals<N>(mine, kb, res)) return;
     const int t = threadIdx.x;
     if constexpr (NORM) {
         if (t == 0) *kb.nu2 = res[0];
@@ -1062,9 +1080,9 @@ __global__ __launch_bounds__(KT) void k_dcgs_update(int64_t n, const double* __r
         acc[NQ + 1] += un * un;
     }
     const double mine = block_sums<NQ + 2>(acc, sh);
-    if (!last_block_totals<NQ + 2>(mine, kb.partial, kb.counter, res)) return;
+    if (!last_block_totals<NQ + 2>(mine, kb, res)) return;
     const int t = threadIdx.x;
-    // every block has read its coefficients before it published its sums
+    // every block has read its coefficients: its sums, which have arrived, depend on them
     if (t <= NQ) {
         kb.d2[t] = res[t];
         kb.coef[KC_A + t] = res[t];

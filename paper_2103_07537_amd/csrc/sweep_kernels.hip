@@ -12,20 +12,9 @@
 namespace mbamg {
 
 
-// "not yet written" in an undamped buffer: all bits set, a NaN that no store
-// below ever writes
-__device__ __forceinline__ bool unwritten(double v) { return __double_as_longlong(v) == -1ll; }
-__device__ __forceinline__ bool unwritten(float v) { return __float_as_uint(v) == 0xFFFFFFFFu; }
-template <class T>
-__device__ __forceinline__ T unwritten_value() {
-    if constexpr (sizeof(T) == 8) return __longlong_as_double(-1ll);
-    else return __uint_as_float(0xFFFFFFFFu);
-}
-
 // A row's D values as other workgroups of the running launch may be writing
 // them: relaxed loads at device scope (past the L1, coherent across the XCDs),
-// 8 bytes at a time where rows are 8-byte aligned.  Each value is its own
-// signal, so no order between different addresses is needed.
+// 8 bytes at a time where rows are 8-byte aligned.
 template <class T, int D>
 __device__ __forceinline__ void load_shared_vec(const T* p, T (&v)[D]) {
     if constexpr (sizeof(T) == 4 && D % 2 == 0) {
@@ -54,18 +43,6 @@ template <class U>
 __device__ __forceinline__ U uniform_load(const U* p) {
     typedef const U __attribute__((address_space(4))) * ConstPtr;
     return *(ConstPtr)(uintptr_t)p;
-}
-
-// The polls of a wait must not hold up what they wait for.  Every wavefront of later
-// colours that is resident polls past the L1; with four workgroups per compute unit
-// doing so without a pause, the memory path was kept so busy that an awaited store
-// was now and then not seen for 10^4 - 10^6 rounds (139,897 rows of 3 x 3 blocks in
-// FP64: a wait ran out about once in 240 solver iterations, and the solve ended in
-// NaN).  So a wavefront pauses between its polls, longer the longer it has waited
-// (4 clocks per round past the first few), and at most two workgroups share a unit
-// (see sweep_lds): there no wait was longer than 63 rounds in 4,500 iterations.
-__device__ __forceinline__ void pause_after(int round) {
-    for (int k = 0; k < round >> 4; ++k) __builtin_amdgcn_s_sleep(1);   // 64 clocks
 }
 
 // The damped update of one value; written by a sweep and recomputed by the blocks
