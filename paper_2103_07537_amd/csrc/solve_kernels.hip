@@ -941,40 +941,46 @@ __device__ __forceinline__ bool last_block_totals(double mine, const KrylovBufs&
     }
     __syncthreads();
     if (!last) return false;
-    // 8 lanes per sum, all sums at once: lane l adds the blocks l, l + 8, ... in turn (16
-    // loads in flight), then the group (a wavefront per sum took the sums one after the other)
-    constexpr int G = 8, U = 16;
+    // 8 lanes per sum, all sums at once: lane l adds the blocks l, l + 8, ... in turn (32
+    // loads in flight, 16 where that covers the blocks), then the group (a wavefront per sum
+    // took the sums one after the other)
+    constexpr int G = 8;
     static_assert(N <= 2 * (KT / G), "two sums per group at most");
     const int l = t % G;
     auto partial_at = [&](int q, int b) {
         return __hip_atomic_load(kb.partial + (int64_t)q * KBLOCKS + b, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     };
-    for (int q = t / G; q < N; q += KT / G) {
-        double v = 0.0;
-        for (int b0 = l; b0 < nb; b0 += U * G) {
-            double x[U];
+    auto add_all = [&](auto in_flight) {
+        constexpr int U = decltype(in_flight)::value;
+        for (int q = t / G; q < N; q += KT / G) {
+            double v = 0.0;
+            for (int b0 = l; b0 < nb; b0 += U * G) {
+                double x[U];
 #pragma unroll
-            for (int u = 0; u < U; ++u) x[u] = b0 + u * G < nb ? partial_at(q, b0 + u * G) : 0.0;
-            for (int round = 0;; ++round) {
-                bool more = false;
+                for (int u = 0; u < U; ++u) x[u] = b0 + u * G < nb ? partial_at(q, b0 + u * G) : 0.0;
+                for (int round = 0;; ++round) {
+                    bool more = false;
 #pragma unroll
-                for (int u = 0; u < U; ++u) more = more || unwritten(x[u]);
-                if (!__any(more)) break;
-                if (round >= kb.wait.rounds) {
-                    __hip_atomic_store(kb.wait.late, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
-                    break;
+                    for (int u = 0; u < U; ++u) more = more || unwritten(x[u]);
+                    if (!__any(more)) break;
+                    if (round >= kb.wait.rounds) {
+                        __hip_atomic_store(kb.wait.late, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+                        break;
+                    }
+                    pause_after(round);
+#pragma unroll
+                    for (int u = 0; u < U; ++u)
+                        if (unwritten(x[u])) x[u] = partial_at(q, b0 + u * G);
                 }
-                pause_after(round);
 #pragma unroll
-                for (int u = 0; u < U; ++u)
-                    if (unwritten(x[u])) x[u] = partial_at(q, b0 + u * G);
+                for (int u = 0; u < U; ++u) v += x[u];
             }
-#pragma unroll
-            for (int u = 0; u < U; ++u) v += x[u];
+            v = group_sum<G>(v);
+            if (l == G - 1) res[q] = v;
         }
-        v = group_sum<G>(v);
-        if (l == G - 1) res[q] = v;
-    }
+    };
+    if (nb <= 16 * G) add_all(std::integral_constant<int, 16>{});
+    else add_all(std::integral_constant<int, 32>{});
     __syncthreads();
     return true;
 }
