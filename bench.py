@@ -54,8 +54,8 @@ def parse():
     ap.add_argument("--no-cpu-baseline", action="store_true")
     ap.add_argument("--cpu-sample-n", type=int, default=0, help="grid size of the oracle sample (0: automatic)")
     ap.add_argument("--counter-run", action="store_true",
-                    help="for hardware-counter profiling: one FP64 setup, a 1 GiB calibration copy, "
-                         "then a few V-cycles and operator applies (no solve)")
+                    help="for hardware-counter profiling: one setup of the first of --forms, a 1 GiB calibration "
+                         "copy, then a few V-cycles and operator applies (no solve)")
     return ap.parse_args()
 
 
@@ -69,7 +69,12 @@ def counter_run(args):
     system = workload(args.workload, seed=args.seed)
     blocks = mbamg.to_device(system)
     b = torch.from_numpy(system.b).cuda()
-    h = mbamg.Hierarchy(blocks, system.dofs, system.n_vec, precision=0)
+    precision, use_mlp = FORMS[args.forms.split(",")[0]]
+    mlp = None
+    if use_mlp:
+        from paper_2103_07537_amd import learned
+        mlp = learned.load(args.weights or learned.DEFAULT_WEIGHTS)
+    h = mbamg.Hierarchy(blocks, system.dofs, system.n_vec, precision=precision, mlp=mlp)
     log("[counters] setup done")
     src = torch.ones(1 << 27, dtype=torch.float64, device="cuda")      # 1 GiB
     dst = torch.empty_like(src)
@@ -295,13 +300,28 @@ def cpu_baseline(args, form, gpu_iters, mlp):
     }
 
 
-def measured_traffic(workload_name, kind):
-    """HBM bytes per launch of the reported kernel from the committed counter
-    summaries, or None when none matches this workload and kernel source."""
-    import glob
+# what a launch moves is decided here: the solve's kernels, and the layouts and launches around them
+TRAFFIC_SOURCES = ("solve_kernels.hip", "solve_kernels.h", "solve_device.h", "sweep_kernels.hip", "dpp.h",
+                   "setup_kernels.hip", "hierarchy.hip")
+
+
+def traffic_source_hash():
+    """SHA-256 over those of TRAFFIC_SOURCES that are there, in order."""
     import hashlib
-    src = os.path.join(ROOT, "paper_2103_07537_amd", "csrc", "solve_kernels.hip")
-    sha = hashlib.sha256(open(src, "rb").read()).hexdigest()
+    sha = hashlib.sha256()
+    for name in TRAFFIC_SOURCES:
+        path = os.path.join(ROOT, "paper_2103_07537_amd", "csrc", name)
+        if os.path.exists(path):
+            sha.update(open(path, "rb").read())
+    return sha.hexdigest()
+
+
+def measured_traffic(workload_name, kind, form="fp64"):
+    """HBM bytes per launch of a kind of launch, and of the form's whole
+    V-cycle, from the committed counter summaries, or None where none matches
+    this workload, form and source."""
+    import glob
+    sha = traffic_source_hash()
     for path in sorted(glob.glob(os.path.join(ROOT, "profiles", "traffic_*.txt"))):
         kv = {}
         for line in open(path):
@@ -309,7 +329,7 @@ def measured_traffic(workload_name, kind):
                 k, v = line.strip().split("=", 1)
                 kv[k] = v
         if (kv.get("workload") == workload_name and kv.get("kind") == str(kind)
-                and kv.get("source_sha256") == sha):
+                and kv.get("form", "fp64") == form and kv.get("source_sha256") == sha):
             vc = float(kv["vcycle_traffic_bytes"]) if "vcycle_traffic_bytes" in kv else None
             return float(kv["traffic_bytes_per_launch"]), os.path.relpath(path, ROOT), vc
     return None, None, None
@@ -377,6 +397,7 @@ def main():
         h.close()
         prof = profile_steps(blocks, system, b, form, args.rtol, mlp)
         vin = prof["vcycle_in_solve_ms"]
+        vc_traffic = measured_traffic(args.workload, 0, form)[2]
         results[form] = {
             "ms_per_step": ms_step,
             "t_setup_ms": float(np.median([i["t_setup_ms"] for i in infos])),
@@ -391,11 +412,15 @@ def main():
             # the V-cycle as GMRES applies it (colour-order vectors; HIP events around each one
             # in an untimed profiling step)
             "vcycle_ms": vin,
+            # the matrix's structural bytes (the byte model's) over that time: a measure of the method, not
+            # of the memory, which moves less (blocks are stored by what determines them)
             "vcycle_alg_GBps": vc_bytes / (vin * 1e-3) / 1e9,
-            "vcycle_hbm_frac": vc_bytes / (vin * 1e-3) / 1e9 / HBM_PEAK_GBS,
-            # the same through mbamg_vcycle: adds the natural <-> colour reordering of r and z
+            # counted HBM bytes of a V-cycle over that time, and against the peak
+            "vcycle_measured_bytes": vc_traffic,
+            "vcycle_measured_GBps": vc_traffic / (vin * 1e-3) / 1e9 if vc_traffic else None,
+            "vcycle_hbm_frac": vc_traffic / (vin * 1e-3) / 1e9 / HBM_PEAK_GBS if vc_traffic else None,
+            # the V-cycle through mbamg_vcycle: adds the natural <-> colour reordering of r and z
             "vcycle_abi_ms": vc_ms,
-            "vcycle_abi_hbm_frac": vc_bytes / (vc_ms * 1e-3) / 1e9 / HBM_PEAK_GBS,
             "per_level": prof["levels"],
             "per_launch_kind": prof["launch_stats"],
             "kernel_stats": prof.get("kernel_stats"),
@@ -406,7 +431,9 @@ def main():
 
     chosen = next((f for f in ("learned", "fp32") if f in results), forms[0])
     # roofline of the dominant finest-level kernel in the FP64 form (HIP events around every launch of
-    # the finest level's kernels during an untimed profiling step: the timed steps carry no events)
+    # the finest level's kernels during an untimed profiling step: the timed steps carry no events): the
+    # HBM bytes counted for a launch over its time.  Without a counter summary for this workload and
+    # source the rate is not known: the byte model's structural bytes are more than a launch moves.
     roof = None
     st = results.get("fp64", {}).get("kernel_stats")
     if st:
@@ -417,17 +444,12 @@ def main():
         s = st[kind]
         per_launch_bytes = s["bytes"] / max(s["launches"], 1)
         avg_ms = s["total_ms"] / max(s["launches"], 1)
-        achieved = per_launch_bytes / (avg_ms * 1e-3) / 1e9
-        traffic, tsrc, vc_traffic = measured_traffic(args.workload, kind)
-        if vc_traffic:
-            # the whole FP64 V-cycle's counted HBM bytes (same counter runs) over its in-solver time
-            f64 = results["fp64"]
-            f64["vcycle_measured_bytes"] = vc_traffic
-            f64["vcycle_measured_GBps"] = vc_traffic / (f64["vcycle_ms"] * 1e-3) / 1e9
-            f64["vcycle_measured_frac"] = f64["vcycle_measured_GBps"] / HBM_PEAK_GBS
+        traffic, tsrc, _ = measured_traffic(args.workload, kind)
+        achieved = traffic / (avg_ms * 1e-3) / 1e9 if traffic else None
         roof = {"bound": "hbm", "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s",
-                "frac": achieved / HBM_PEAK_GBS, "traffic": traffic, "kernel": names[kind],
+                "frac": achieved / HBM_PEAK_GBS if traffic else None, "traffic": traffic, "kernel": names[kind],
                 "launches": s["launches"], "avg_us": avg_ms * 1e3, "alg_bytes_per_launch": per_launch_bytes,
+                "alg_GBps": per_launch_bytes / (avg_ms * 1e-3) / 1e9,
                 "traffic_source": tsrc, "stream_copy_GBps": stream_copy_rate()}
     cpu = None
     if not args.no_cpu_baseline:
