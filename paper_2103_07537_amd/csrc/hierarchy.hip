@@ -1502,6 +1502,9 @@ static void setup_impl(mbamg_hierarchy* h, const mbamg_bsr* Ab, hipStream_t s, D
             if (Lv.shape != SHAPE_FULL) Lv.resid_split = std::min(Lv.resid_split, SHAPE_MAX_SPLIT);
         }
         if (!shared && p.smoother == 0) shorten_columns(Lv, s);
+        if (clk.on && !shared && Lv.blk[0].group == 1)
+            std::fprintf(stderr, "[mbamg setup] level %d: sliced, shape %d, %d-bit columns\n", l, Lv.shape,
+                         Lv.blk[0].off.col16.p ? 16 : 32);
         // the residual's launch order: the same eighth of every colour together, so the blocks
         // each XCD takes (contiguous launch ranges) cover one slab of the domain in all colours
         // and their neighbour gathers stay in its L2 (in colour order an XCD's range spans a
