@@ -779,12 +779,14 @@ static void build_part(SellPart& P, PartKind kind, const BlockLevel& B, const Se
 }
 
 // The columns of a level's sliced smoother parts as 16-bit offsets from each slot's
-// smallest, if they all fit: on levels of COL16_MIN_ROWS rows or more, whose parts
-// (about 260 bytes per row in each block row) no longer stay in the 256 MB cache from
-// launch to launch, so that launches are bound by what they read.  There a V-cycle of
-// 2,097,152 nodes took 1970 -> 1922 us and an operator of 1,009,091 nodes 210 -> 199;
-// a V-cycle of 151,951 nodes, bound by the latency of its loads, 312 -> 323.  Only the
-// kernels of one wave per slice read them.  MBAMG_COL16 = 0 | 1 forces it, for tests.
+// smallest, if they all fit: on levels of COL16_MIN_ROWS rows or more, whose launches
+// are bound by what they read.  A V-cycle of 2,097,152 nodes took 1970 -> 1922 us and an
+// operator of 1,009,091 nodes 210 -> 199.  Around the line, 1 to 4 dofs per node, 2D and
+// 3D, FP64 and FP32: 343,000 and 360,000 rows cycles 2 % slower to 2.5 % faster (FP64 0.5
+// to 1 % slower), 551,368 and 562,500 rows 1 % slower to 2 % faster, 1,000,000 rows 0 to
+// 3 % faster; operators 0 to 16 % faster throughout.  A V-cycle of 151,951 nodes, bound by
+// the latency of its loads, 312 -> 323.  Only the kernels of one wave per slice read them.
+// MBAMG_COL16 = 0 | 1 forces it, for tests.
 constexpr int COL16_MIN_ROWS = 1 << 19;
 static void shorten_columns(Level& Lv, hipStream_t s) {
     bool want = Lv.n >= COL16_MIN_ROWS;

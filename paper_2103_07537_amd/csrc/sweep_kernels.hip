@@ -188,6 +188,7 @@ __device__ __forceinline__ void group_all_sum(T (&acc)[D], int lg) {
 //
 // The two undamped buffers of a level take turns: a launch writes t and sets its
 // rows of the other buffer to "unwritten" for the next launch.
+
 // LDS asked for by the workgroups of a sweep, and not used, so that a compute unit
 // (160 KiB) takes one of them, or two.
 // One, where a colour has few workgroups (spread): a colour's rows then spread over
