@@ -47,8 +47,11 @@ constexpr int WAVE = 64;
 // off the driver's map/unmap path.
 void* dev_alloc(size_t bytes);
 void dev_free(void* p, size_t bytes);
-// Call right after hipDeviceSynchronize(): this thread's pending blocks become reusable.
-void pool_device_idle();
+// Call right after hipDeviceSynchronize(): this thread's pending blocks become reusable, and
+// ended threads' that were handed over before `mark`, taken by pool_mark() before the wait.
+// (Without a mark, all of them: only where no other thread can end meanwhile.)
+uint64_t pool_mark();
+void pool_device_idle(uint64_t mark = UINT64_MAX);
 
 // Page-locked host memory from a process-wide pool (memory.hip): a copy to or
 // from pageable memory is staged by the runtime and ran at 1.6-2.6 GB/s here.

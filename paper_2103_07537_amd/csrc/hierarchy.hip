@@ -2912,8 +2912,9 @@ mbamg_status mbamg_setup(const mbamg_bsr* A_blocks, const mbamg_field_map* fm, c
             return h;
         };
         auto settle = [] {   // the build's temporaries are idle now and can serve the next allocations
+            const uint64_t mark = pool_mark();
             MB_HIP(hipDeviceSynchronize());
-            pool_device_idle();
+            pool_device_idle(mark);
         };
         std::unique_ptr<mbamg_hierarchy> h;
         if (fm->n_blocks > 2) {
@@ -2972,8 +2973,7 @@ mbamg_status mbamg_setup(const mbamg_bsr* A_blocks, const mbamg_field_map* fm, c
             settle();
             h->info.used_learned = p->learned != 0;
         }
-        MB_HIP(hipDeviceSynchronize());
-        pool_device_idle();
+        settle();
         auto t1 = std::chrono::steady_clock::now();
         h->t_setup_ms = std::chrono::duration<double, std::milli>(t1 - t0).count();
         h->info.t_setup_ms = h->t_setup_ms;
@@ -3033,8 +3033,10 @@ mbamg_status mbamg_get_info(const mbamg_hierarchy* h, mbamg_info* info) {
 }
 
 void mbamg_destroy(mbamg_hierarchy* h) {
+    if (!h) return;
+    const uint64_t mark = pool_mark();
     delete h;   // the destructor synchronises the device before its buffers are released
-    pool_device_idle();
+    pool_device_idle(mark);
 }
 
 mbamg_status mbamg_num_levels(const mbamg_hierarchy* h, int32_t* n_levels) {

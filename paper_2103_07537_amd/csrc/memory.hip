@@ -6,9 +6,10 @@
 // block is idle once the device has been synchronised, so pending blocks are
 // moved to the free lists by pool_device_idle(), which the library calls right
 // after hipDeviceSynchronize().  A thread that ends hands its pending blocks
-// to a shared list that the next pool_device_idle() promotes as well.  When
-// hipMalloc fails, the cached free blocks are released and the allocation is
-// retried once.
+// to a shared list.  Threads may end while another one waits for the device, so
+// pool_device_idle() promotes of that list only what was in it before the wait
+// (pool_mark()).  When hipMalloc fails, the cached free blocks are released and
+// the allocation is retried once.
 #include <map>
 #include <mutex>
 #include <unordered_map>
@@ -23,6 +24,7 @@ struct Block {
     int dev;
     size_t bytes;
     void* p;
+    uint64_t turn = 0;   // orphans: how many came before it
 };
 
 struct Pool {
@@ -35,10 +37,15 @@ Pool& pool() {
     return *p;
 }
 
-// blocks freed by threads that have ended, promoted by the next idle point
+// blocks freed by threads that have ended; guarded by pool().m
 std::vector<Block>& orphans() {
-    static auto* v = new std::vector<Block>;   // guarded by pool().m
+    static auto* v = new std::vector<Block>;
     return *v;
+}
+uint64_t n_orphans = 0;   // ever added; guarded by pool().m
+void add_orphan(Block b) {
+    b.turn = n_orphans++;
+    orphans().push_back(b);
 }
 // A thread's other per-thread data may be released after its pending list (buffers
 // kept for the thread's life are constructed before the first block is freed):
@@ -51,7 +58,7 @@ struct Pending {
         t_pending_ended = true;
         if (v.empty()) return;
         std::lock_guard<std::mutex> g(pool().m);
-        orphans().insert(orphans().end(), v.begin(), v.end());
+        for (const Block& b : v) add_orphan(b);
     }
 };
 thread_local Pending t_pending;
@@ -116,13 +123,12 @@ void dev_free(void* p, size_t bytes) {
     const Block b{current_device(), size_class(bytes), p};
     if (t_pending_ended) {
         std::lock_guard<std::mutex> g(pool().m);
-        orphans().push_back(b);
+        add_orphan(b);
     } else {
         t_pending.v.push_back(b);
     }
 }
 
-// the current device has been synchronised: its pending blocks are idle
 namespace {
 struct PinnedPool {
     std::mutex m;
@@ -181,19 +187,26 @@ void pinned_give(void* p) {
     P.taken.erase(it);
 }
 
-void pool_device_idle() {
+uint64_t pool_mark() {
+    std::lock_guard<std::mutex> g(pool().m);
+    return n_orphans;
+}
+
+// the current device has been synchronised: this thread's pending blocks are idle, and
+// of the ended threads' those that were handed over before the wait began
+void pool_device_idle(uint64_t mark) {
     const int dev = current_device();
     std::lock_guard<std::mutex> g(pool().m);
-    auto promote = [dev](std::vector<Block>& list) {
+    auto promote = [dev](std::vector<Block>& list, uint64_t before) {
         size_t keep = 0;
         for (const Block& b : list) {
-            if (b.dev == dev) pool().free_lists[dev].emplace(b.bytes, b.p);
+            if (b.dev == dev && b.turn < before) pool().free_lists[dev].emplace(b.bytes, b.p);
             else list[keep++] = b;
         }
         list.resize(keep);
     };
-    if (!t_pending_ended) promote(t_pending.v);
-    promote(orphans());
+    if (!t_pending_ended) promote(t_pending.v, UINT64_MAX);
+    promote(orphans(), mark);
 }
 
 }  // namespace mbamg
